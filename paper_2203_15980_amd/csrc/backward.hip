@@ -478,39 +478,73 @@ __global__ __launch_bounds__(512) void wgrad_reduce_kernel(const float *partial,
     }
 }
 
-// fp32 layers (the small correctness configuration): plain fp32 multiply-adds.  One workgroup per
-// 16 x 16 tile of (k, c) and tap; thread (kk, cc) walks every position in order, 64 at a time through
-// LDS, so there are no partial sums, no workspace and one fixed order of summation.
+// fp32 layers (config 1's size and its like): one workgroup per tap and tile of 16 T x 16 T (k, c), its 16 wavefronts
+// sharing the positions, on the fp32 MFMA (16x16x4: exact fp32 products, fp32 sums).  A workgroup holds all
+// of a tile's sums, so there is no partial buffer and no workspace: wavefront v takes the v-th run of
+// positions and the 16 sums are added in the order of v through LDS (a fixed function of the inputs).  Both operands are
+// position-major with the channels contiguous, which is what this MFMA reads (lane l: position l / 16, channel
+// T * (l % 16) + i), so they go from memory straight to registers, eight steps of four positions in flight.
+// What bounds it is that latency: a thread per (k, c) pair with all positions in one serial chain of
+// multiply-adds through LDS took 94-110 us for each of config 1's layers (2048 positions), this 5-6.
 // g: [N,H,W,K] (dL/d(pre-activation) at the input's resolution), x: [N,H,W,C], gw: [K][R][R][C].
-__global__ __launch_bounds__(256) void wgrad_f32_kernel(const float *x, const float *g, const float *scale, float *gw,
-                                                        int N, int H, int W, int C, int K, int R, int pad) {
-    __shared__ float gs[64][17], xs[64][17];
-    const int t = threadIdx.x, kk = t >> 4, cc = t & 15;
-    const int k0 = blockIdx.x * 16, c0 = blockIdx.y * 16, tap = blockIdx.z;
-    const int r = tap / R, s = tap % R;
-    const long long M = (long long)N * H * W;
-    float acc = 0.f;
-    for (long long m0 = 0; m0 < M; m0 += 64) {
-        for (int i = t; i < 1024; i += 256) {
-            const int p = i >> 4, ch = i & 15;
-            const long long m = m0 + p;
-            float gv = 0.f, xv = 0.f;
-            if (m < M) {
-                gv = g[(size_t)m * K + k0 + ch];
-                const int w_ = (int)(m % W), h_ = (int)((m / W) % H);
-                const long long n = m / ((long long)W * H);
-                const int ih = h_ + r - pad, iw = w_ + s - pad;
-                if (ih >= 0 && ih < H && iw >= 0 && iw < W) xv = x[((size_t)(n * H + ih) * W + iw) * C + c0 + ch];
+template <int T>
+__global__ __launch_bounds__(1024) void wgrad_f32_kernel(const float *x, const float *g, const float *scale, float *gw,
+                                                         int H, int W, int C, int K, int R, int pad, long long M) {
+    typedef float vec __attribute__((ext_vector_type(T)));
+    constexpr int kWaves = 16, kSteps = 8;                       // positions in flight: 4 per step
+    __shared__ float part[kWaves][T * T * 256];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l16 = lane & 15, quad = lane >> 4;
+    const int k0 = blockIdx.x * (16 * T), c0 = blockIdx.y * (16 * T), tap = blockIdx.z;
+    const int dr = tap / R - pad, ds = tap % R - pad;
+    const long long per = ((M + kWaves - 1) / kWaves + 3) / 4 * 4;
+    long long m = (long long)wv * per + quad;                    // this lane's position
+    const long long end = (long long)(wv + 1) * per < M ? (long long)(wv + 1) * per : M;
+    const long long rounds = (per + 4 * kSteps - 1) / (4 * kSteps);
+    int w = (int)(m % W), h = (int)((m / W) % H);
+    const float *gp = g + m * K + k0 + T * l16, *xp = x + (m + (long long)dr * W + ds) * C + c0 + T * l16;
+    f32x4 acc[T][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (long long t = 0; t < rounds; ++t) {
+        vec gv[kSteps], xv[kSteps];
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            // outside: the tensor's first element is read and dropped (no branch around a load)
+            const bool live = m < end, in = live && (unsigned)(h + dr) < (unsigned)H && (unsigned)(w + ds) < (unsigned)W;
+            const vec gr = *reinterpret_cast<const vec *>(live ? gp : g), xr = *reinterpret_cast<const vec *>(in ? xp : x);
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                gv[u][i] = live ? gr[i] : 0.f;
+                xv[u][i] = in ? xr[i] : 0.f;
             }
-            gs[p][ch] = gv;
-            xs[p][ch] = xv;
+            m += 4; gp += 4 * (long long)K; xp += 4 * (long long)C;
+            w += 4;
+            while (w >= W) { w -= W; h = h + 1 == H ? 0 : h + 1; }
         }
-        __syncthreads();
-#pragma unroll 16
-        for (int p = 0; p < 64; ++p) acc += gs[p][kk] * xs[p][cc];
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(gv[u][i], xv[u][j], acc[i][j], 0, 0, 0);
     }
-    gw[((size_t)(k0 + kk) * R * R + tap) * C + c0 + cc] = acc * scale[k0 + kk];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[wv][((i * T + j) * 4 + e) * 64 + lane] = acc[i][j][e];
+    __syncthreads();
+    if (tid >= T * T * 256) return;
+    float sum = part[0][tid];
+#pragma unroll
+    for (int v = 1; v < kWaves; ++v) sum += part[v][tid];
+    // lane of this sum: column (c) l % 16, row (k) 4 (l / 16) + e of the tile's (i, j) interleave
+    const int k = k0 + T * (4 * quad + (wv & 3)) + (tid >> 8) / T, c = c0 + T * l16 + (tid >> 8) % T;
+    gw[((size_t)k * R * R + tap) * C + c] = sum * scale[k];
 }
 
 }  // namespace bwd
@@ -842,9 +876,16 @@ hipError_t launch_wgrad(const ConvArgs &a, const void *g, float *gw, void *works
     const int taps = a.R * a.S;
     if (!a.bf16) {                                               // no workspace
         if (wgrad_f32_check(a) || !a.x || !a.scale || !g || !gw) return hipErrorInvalidValue;
-        bwd::wgrad_f32_kernel<<<dim3(a.Cout / 16, a.Cin / 16, taps), dim3(256), 0, stream>>>(
-            static_cast<const float *>(a.x), static_cast<const float *>(g), a.scale, gw, a.N, a.H, a.W, a.Cin, a.Cout, a.R,
-            a.pad);
+        // 32 x 32 tiles where they fill the chip by themselves: half the loads per product
+        const bool wide = a.Cout % 32 == 0 && a.Cin % 32 == 0 && (long long)(a.Cout / 32) * (a.Cin / 32) * taps >= 256;
+        const long long M = (long long)a.N * a.H * a.W;
+        const float *x = static_cast<const float *>(a.x), *gf = static_cast<const float *>(g);
+        if (wide)
+            bwd::wgrad_f32_kernel<2><<<dim3(a.Cout / 32, a.Cin / 32, taps), dim3(1024), 0, stream>>>(x, gf, a.scale, gw, a.H, a.W,
+                                                                                                     a.Cin, a.Cout, a.R, a.pad, M);
+        else
+            bwd::wgrad_f32_kernel<1><<<dim3(a.Cout / 16, a.Cin / 16, taps), dim3(1024), 0, stream>>>(x, gf, a.scale, gw, a.H, a.W,
+                                                                                                     a.Cin, a.Cout, a.R, a.pad, M);
         return hipGetLastError();
     }
     return run_wgrad(a, g, gw, workspace, workspace_bytes, 0, taps == 9 ? kAllTaps : 0ull, taps, taps == 9 ? kAllTaps : 0ull,

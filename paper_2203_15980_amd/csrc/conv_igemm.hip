@@ -87,18 +87,6 @@ __device__ __forceinline__ void wave_lds_fence() {
 // offset that lies outside every buffer descriptor used here (their sizes stay below 2 GiB)
 static constexpr int kOutOfRange = (int)0x80000000;
 
-// GELU in its erf form, v/2 (1 + erf(v / sqrt 2)).  1 + erf(x) = erfc(-x): for x < 0 it is
-// erfc(|x|), for x >= 0 it is 2 - erfc(x), and erfc(|x|) = poly(t) exp(-x^2), t = 1/(1 + p |x|)
-// (Abramowitz & Stegun 7.1.26, absolute error 1.5e-7) - no cancellation in the negative tail, one
-// exp and one reciprocal per element instead of the library erff's branches.
-__device__ __forceinline__ float gelu_erf(float v) {
-    const float x = fabsf(v) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * x);
-    const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-    const float c = poly * __builtin_amdgcn_exp2f(-x * x * 1.4426950408889634f);   // erfc(|x|)
-    return 0.5f * v * (v < 0.f ? c : 2.0f - c);
-}
-
 // SCATTER: the scattered form described at ConvArgs (strided output pixels, a strided subset of the
 // weight tensor's taps, residual read in the epilogue); HAS_RES is then false.
 template <bool BF16, int BM, int BN, int WM, int WN, bool HAS_RES, bool SCATTER = false>
@@ -437,9 +425,15 @@ static int conv_tile_n(const ConvArgs &a) {
     return a.Cout > 64 ? 128 : 64;
 }
 
+// The streaming kernel's layers with 128 input channels when they are few tiles (128 -> 512 at M = 784: 8.9 -> 6.3 us).  Those with
+// 64, and 256 -> 64, stay with it at any size: the block kernel regenerates their tensors too, with its bits.
+static bool splitk_before_stream(const ConvArgs &a) { return a.Cin == 128 && conv_splitk_applies(a); }
+
 const char *conv_kernel_name(const ConvArgs &a) {
+    if (splitk_before_stream(a)) return conv_splitk_kernel_name(a);
     if (conv1x1_stream_applies(a)) return "conv1x1_stream bf16";
     if (conv3x3_c64_applies(a)) return "conv3x3_c64 bf16 (persistent, nine taps resident in LDS)";
+    if (conv_splitk_applies(a)) return conv_splitk_kernel_name(a);
     if (conv3x3_halo_applies(a)) return "conv3x3_halo bf16 256x64 (4x1 waves)";
     if (gemm_nt_applies(a)) return gemm_nt_kernel_name(a);
     const int bn = conv_tile_n(a);
@@ -510,6 +504,7 @@ const char *conv_scatter_check(const ConvArgs &a) {
 
 hipError_t launch_conv_scatter(const ConvArgs &a, hipStream_t stream) {
     if (conv_scatter_check(a)) return hipErrorInvalidValue;
+    if (conv_splitk_applies(a)) return launch_conv_splitk(a, stream);
     const int bn = conv_tile_n(a);
     if (a.bf16) {
         if (bn == 128) return launch<true, 128, 128, 2, 2>(a, stream);
@@ -521,8 +516,10 @@ hipError_t launch_conv_scatter(const ConvArgs &a, hipStream_t stream) {
 
 hipError_t launch_conv(const ConvArgs &a, hipStream_t stream) {
     if (conv_check(a) || a.oy_s) return hipErrorInvalidValue;
+    if (splitk_before_stream(a)) return launch_conv_splitk(a, stream);
     if (conv1x1_stream_applies(a)) return launch_conv1x1_stream(a, stream);
     if (conv3x3_c64_applies(a)) return launch_conv3x3_c64(a, stream);
+    if (conv_splitk_applies(a)) return launch_conv_splitk(a, stream);
     if (conv3x3_halo_applies(a)) return launch_conv3x3_halo(a, stream);
     if (gemm_nt_applies(a)) return launch_gemm_nt(a, stream);
     const int bn = conv_tile_n(a);

@@ -80,14 +80,6 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ float gelu_erf(float v) {     // v/2 (1 + erf(v / sqrt 2)); see conv_igemm.hip
-    const float x = fabsf(v) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * x);
-    const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-    const float c = poly * __builtin_amdgcn_exp2f(-x * x * 1.4426950408889634f);
-    return 0.5f * v * (v < 0.f ? c : 2.0f - c);
-}
-
 // BM: rows of x per workgroup, 256 or 128 (BM / 64 wavefront rows); BN: rows of w (output channels)
 // per workgroup, 256, 192 or 128 (BN / 64 wavefront columns).
 // S: LDS buffers of one K slice each (2 or 4); S - 1 slices are in flight while one is multiplied.

@@ -38,12 +38,28 @@ __device__ __forceinline__ uint32_t keep_where_positive_f32(uint32_t v, uint32_t
     return __uint_as_float(m) > 0.f ? v : 0u;
 }
 
+// GELU in its erf form, v/2 (1 + erf(v / sqrt 2)).  1 + erf(x) = erfc(-x): for x < 0 it is
+// erfc(|x|), for x >= 0 it is 2 - erfc(x), and erfc(|x|) = poly(t) exp(-x^2), t = 1/(1 + p |x|)
+// (Abramowitz & Stegun 7.1.26, absolute error 1.5e-7) - no cancellation in the negative tail, one
+// exp and one reciprocal per element instead of the library erff's branches.
+__device__ __forceinline__ float gelu_erf(float v) {
+    const float x = fabsf(v) * 0.70710678118654752f;
+    const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * x);
+    const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
+    const float c = poly * __builtin_amdgcn_exp2f(-x * x * 1.4426950408889634f);   // erfc(|x|)
+    return 0.5f * v * (v < 0.f ? c : 2.0f - c);
+}
+
 // nullptr when the kernel supports the shape, else the reason.
 const char *conv_check(const ConvArgs &a);
 const char *conv_kernel_name(const ConvArgs &a);
 hipError_t launch_conv(const ConvArgs &a, hipStream_t stream);
 const char *conv_scatter_check(const ConvArgs &a);
 hipError_t launch_conv_scatter(const ConvArgs &a, hipStream_t stream);
+// conv_splitk.hip: layers with too little output to fill the chip, the reduction split over a workgroup's wavefronts
+bool conv_splitk_applies(const ConvArgs &a);
+const char *conv_splitk_kernel_name(const ConvArgs &a);
+hipError_t launch_conv_splitk(const ConvArgs &a, hipStream_t stream);
 // conv1x1.hip: streaming kernel for bf16 1x1 convolutions whose weights fit LDS
 bool conv1x1_stream_applies(const ConvArgs &a);
 hipError_t launch_conv1x1_stream(const ConvArgs &a, hipStream_t stream);
