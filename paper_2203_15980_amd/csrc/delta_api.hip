@@ -1339,6 +1339,14 @@ uint64_t staging_bytes(const delta_layer_desc &L, const delta::ConvArgs &fa) {
     return (b + 255) / 256 * 256;
 }
 uint64_t partials_bytes(const delta::ConvArgs &fa) { return ((uint64_t)delta::wgrad_workspace_bytes(fa) + 255) / 256 * 256; }
+// Whether a weight gradient is worth a stream of its own.  Its two events and two waits cost the host
+// about 18 us and the GPU a pair of barrier packets; what they buy is that it runs beside the data gradients.
+// Below the line it is over in less than that (`fa` after as_stride_1).
+const uint64_t kAsideFlops = 1000000000ull;
+bool wgrad_aside(const delta_layer_desc &L, const delta::ConvArgs &fa) {
+    const uint64_t rows = L.stride == 2 && L.R == 3 ? (uint64_t)fa.M / 4 : (uint64_t)fa.M;
+    return 2ull * rows * fa.R * fa.S * fa.Cin * fa.Cout >= kAsideFlops;
+}
 // `fa` after as_stride_1
 uint64_t backward_workspace_bytes(const delta_layer_desc &L, const delta::ConvArgs &fa) {
     uint64_t need = partials_bytes(fa) + staging_bytes(L, fa);
@@ -1668,9 +1676,10 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
         }
         const unsigned char *gp = c->arena + c->tensors[D.gpre].offset;
         Ev ready;
+        const bool aside = D.gw && wgrad_aside(L, fa);
         if (D.gw && !direct) {
             if ((r = compute_uses(c, c->tensors[L.x])) != DELTA_OK) return r;
-            if ((r = new_event(c, s, &ready)) != DELTA_OK) return r;
+            if (aside && (r = new_event(c, s, &ready)) != DELTA_OK) return r;
         }
         if (D.gx != DELTA_NO_TENSOR) {
             Tensor &tgx = c->tensors[D.gx];
@@ -1712,35 +1721,39 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
             // gpre and x are complete once the compute stream reaches `ready` (for a strided 1x1 layer:
             // and the data gradient has left the staging area); from there the weight gradient runs on
             // its own stream, and both tensors remember that reader.
-            if (direct && (r = new_event(c, s, &ready)) != DELTA_OK) return r;
-            HIP_TRY(c, hipStreamWaitEvent(c->stream[S_AUX], ready.e, 0));
+            // A small one stays on the compute stream, after whatever still uses the workspace on the other.
+            const bool by_class = class_wgrad(D, fo);
+            const uint64_t need = by_class ? delta::wgrad_s2_workspace_bytes(fo) : partials_bytes(fa);
+            hipStream_t gs = s;
+            if (aside) {
+                gs = c->stream[S_AUX];
+                if (direct && (r = new_event(c, s, &ready)) != DELTA_OK) return r;
+                HIP_TRY(c, hipStreamWaitEvent(gs, ready.e, 0));
+            } else if (aux_holds(c, D.workspace, need) && (r = join_aux(c)) != DELTA_OK) {
+                return r;
+            }
             if (direct) {
-                HIP_TRY(c, delta::launch_subsample(fa.x, staging, L.N, L.H, L.W, outP, outQ, L.Cin, L.stride, fa.bf16,
-                                                   c->stream[S_AUX]));
+                HIP_TRY(c, delta::launch_subsample(fa.x, staging, L.N, L.H, L.W, outP, outQ, L.Cin, L.stride, fa.bf16, gs));
                 fa.x = staging;
             }
-            if (class_wgrad(D, fo)) {
+            if (by_class) {
                 // by parity class, from gy itself (it needs no mask of this layer's) and x
                 fo.x = fa.x;
-                const uint64_t need = delta::wgrad_s2_workspace_bytes(fo);
-                HIP_TRY(c, delta::launch_wgrad_s2(fo, c->arena + tgy.offset, static_cast<float *>(D.gw), D.workspace, need,
-                                                  c->stream[S_AUX]));
-                aux_claims(c, D.workspace, need);
-                if ((r = new_event(c, c->stream[S_AUX], &c->aux_tail)) != DELTA_OK) return r;
-                tx.aux_done = tgy.aux_done = c->aux_tail;
+                HIP_TRY(c, delta::launch_wgrad_s2(fo, c->arena + tgy.offset, static_cast<float *>(D.gw), D.workspace, need, gs));
                 c->st.recompute_flops += 2ull * (uint64_t)fo.M * 9 * fo.Cin * fo.Cout;
             } else {
-                HIP_TRY(c, delta::launch_wgrad(fa, gp, static_cast<float *>(D.gw), D.workspace, partials_bytes(fa),
-                                               c->stream[S_AUX]));
-                aux_claims(c, D.workspace, partials_bytes(fa));
-                if ((r = new_event(c, c->stream[S_AUX], &c->aux_tail)) != DELTA_OK) return r;
-                tx.aux_done = c->tensors[D.gpre].aux_done = c->aux_tail;
+                HIP_TRY(c, delta::launch_wgrad(fa, gp, static_cast<float *>(D.gw), D.workspace, need, gs));
+                c->st.recompute_flops += 2ull * (uint64_t)fa.M * fa.R * fa.S * fa.Cin * fa.Cout;
+            }
+            if (aside) {
+                aux_claims(c, D.workspace, need);
+                if ((r = new_event(c, gs, &c->aux_tail)) != DELTA_OK) return r;
+                tx.aux_done = (by_class ? tgy : c->tensors[D.gpre]).aux_done = c->aux_tail;
                 if (direct) {                                   // the staging range is tracked on its own
                     c->stg_tail = c->aux_tail;
                     c->stg_lo = (uintptr_t)staging;
                     c->stg_hi = c->stg_lo + stg_bytes;
                 }
-                c->st.recompute_flops += 2ull * (uint64_t)fa.M * fa.R * fa.S * fa.Cin * fa.Cout;
             }
         }
         c->st.recompute_launches += 1;
