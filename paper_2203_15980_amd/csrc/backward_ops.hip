@@ -18,6 +18,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float lo16(uint32_t p) { return __uint_as_float(p << 16); }
 __device__ __forceinline__ float hi16(uint32_t p) { return __uint_as_float(p & 0xFFFF0000u); }
@@ -202,8 +203,58 @@ __global__ __launch_bounds__(256) void avgpool_bwd_kernel(const void *gy, void *
 }
 
 // ---------------------------------------------------------------- cross-entropy
-// dL/dz[i,k] = (softmax(z_i)[k] - [k == label_i]) / N.  One wavefront per image, lanes stride over
-// the classes; fixed reduction trees.
+// dL/dz[i,k] = (softmax(z_i)[k] - [k == label_i]) / N.  One wavefront per image; fixed reduction trees.
+// HELD: the image's logits in registers, PER_LANE 16-byte pieces of 8 classes per lane, read once and written once
+// (classes a multiple of 8, at most PER_LANE * 512); else three passes over the row, a class per lane and step.
+// 128 images of 1000 classes, latency-bound: 12 us with three passes of 2-byte loads, 4 held (kernel trace).
+template <int PER_LANE>
+__global__ __launch_bounds__(256) void softmax_ce_bwd_held_kernel(const uint16_t *logits, const long long *labels, int N,
+                                                                  int classes, uint16_t *gz) {
+    const int lane = threadIdx.x & 63;
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= N) return;
+    const int pieces = classes / 8;
+    const u32x4 *z = reinterpret_cast<const u32x4 *>(logits + (size_t)i * classes);
+    const long long lab = labels[i];
+    float v[PER_LANE][8], mx = -INFINITY;
+#pragma unroll
+    for (int p = 0; p < PER_LANE; ++p) {
+        const bool in = lane + 64 * p < pieces;
+        unpack8(z[in ? lane + 64 * p : 0], v[p]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[p][e] = in ? v[p][e] : -INFINITY;
+            mx = fmaxf(mx, v[p][e]);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    float se = 0.f;
+#pragma unroll
+    for (int p = 0; p < PER_LANE; ++p)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const bool in = lane + 64 * p < pieces;              // past the row: no term, whatever the maximum is
+            v[p][e] = __expf(v[p][e] - mx);
+            se += in ? v[p][e] : 0.f;
+        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
+    const float inv = 1.0f / se, invn = 1.0f / (float)N;
+    const bool bad = lab < 0 || lab >= classes;                  // a bad label cannot pass unnoticed
+#pragma unroll
+    for (int p = 0; p < PER_LANE; ++p) {
+        if (lane + 64 * p >= pieces) continue;
+        float g[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            g[e] = v[p][e] * inv - ((lane + 64 * p) * 8 + e == lab ? 1.0f : 0.0f);
+            g[e] = bad ? __builtin_nanf("") : g[e] * invn;
+        }
+        reinterpret_cast<u32x4 *>(gz + (size_t)i * classes)[lane + 64 * p] = pack8(g);
+    }
+}
+
 __global__ __launch_bounds__(256) void softmax_ce_bwd_kernel(const uint16_t *logits, const long long *labels, int N,
                                                              int classes, uint16_t *gz) {
     const int lane = threadIdx.x & 63;
@@ -229,66 +280,108 @@ __global__ __launch_bounds__(256) void softmax_ce_bwd_kernel(const uint16_t *log
 }
 
 // ---------------------------------------------------------------- classifier z = x w^T + bias
-// gx[n][c] = sum_k gy[n][k] * scale_k * w[k][c].  A workgroup: one image, 32 x 8 input channels; its
-// 8 wavefront-halves split the classes (group g takes k = g, g + 8, ...), then the 8 partial sums
-// are added in group order.
-__global__ __launch_bounds__(256) void dense_bwd_data_kernel(const uint16_t *gy, const void *w, const float *scale,
-                                                             void *gx, int N, int Cin, int Cout) {
-    __shared__ float part[8][32][8];
-    const int chunks = Cin / 8, cblocks = (chunks + 31) / 32;
-    const int n = blockIdx.x / cblocks, cb = blockIdx.x % cblocks;
-    const int lane = threadIdx.x & 31, grp = threadIdx.x >> 5;
-    const int ck = cb * 32 + lane;
-    float acc[8];
+// Both gradients are small products (0.5 GFLOP for 128 images, 2048 -> 1000) whose operands all sit in the L2; they run on the
+// fp32 MFMA (16x16x4), so that gy * scale and every sum keep 32 bits, and read each operand once per tile.
+//
+// gx[n][c] = sum_k gy[n][k] * scale_k * w[k][c].  A workgroup owns 16 images x 64 channels; its 8 wavefronts split the
+// classes (wavefront v takes steps v, v + 8, ... of 16) and their sums are added in the order of v.  In a step, MFMA
+// e takes classes 4 * (lane / 16) + e of the 16, so that a lane reads 8 contiguous bytes of gy; a lane's four
+// channels are contiguous, and four accumulators take one each.  31 -> 11 us (kernel trace): a workgroup per image read all of w.
+__global__ __launch_bounds__(512) void dense_bwd_data_kernel(const uint16_t *gy, const uint16_t *w, const float *scale, uint16_t *gx,
+                                                             int N, int Cin, int Cout) {
+    constexpr int kWaves = 8;
+    __shared__ float part[kWaves][16][64];
+    const int cblocks = (Cin + 63) / 64;
+    const int n0 = (int)(blockIdx.x / cblocks) * 16, c0 = (int)(blockIdx.x % cblocks) * 64;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l16 = lane & 15, quad = lane >> 4;
+    const bool nin = n0 + l16 < N, cin = c0 + 4 * l16 < Cin;     // Cin and Cout are multiples of 8
+    const uint16_t *gp = gy + (size_t)(nin ? n0 + l16 : 0) * Cout;
+    const uint16_t *wp = w + (cin ? c0 + 4 * l16 : 0);
+    f32x4 acc[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    const unsigned char *wg = static_cast<const unsigned char *>(w);
-    if (ck < chunks) {
-#pragma unroll 4
-        for (int k = grp; k < Cout; k += 8) {
-            const float g = __uint_as_float((uint32_t)gy[(size_t)n * Cout + k] << 16) * scale[k];
-            float v[8];
-            unpack8(*reinterpret_cast<const u32x4 *>(wg + ((size_t)k * chunks + ck) * 16), v);
+    for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int k0 = 16 * wv; k0 < Cout; k0 += 16 * kWaves) {
+        const int k = k0 + 4 * quad;
+        const bool kin = k < Cout;                               // this lane's four classes, together
+        const int kc = kin ? k : 0;
+        const u32x2 g = *reinterpret_cast<const u32x2 *>(gp + kc);
+        const f32x4 sc = *reinterpret_cast<const f32x4 *>(scale + kc);
+        u32x2 wv4[4];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] += g * v[e];
+        for (int e = 0; e < 4; ++e) wv4[e] = *reinterpret_cast<const u32x2 *>(wp + (size_t)(kc + e) * Cin);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float gf = (e & 1) ? hi16(g[e >> 1]) : lo16(g[e >> 1]);
+            const float ga = nin && kin ? gf * sc[e] : 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float wf = (j & 1) ? hi16(wv4[e][j >> 1]) : lo16(wv4[e][j >> 1]);
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga, cin && kin ? wf : 0.f, acc[j], 0, 0, 0);
+            }
         }
     }
+    // acc[j]: image 4 * quad + e, channel 4 * l16 + j
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part[grp][lane][e] = acc[e];
+    for (int e = 0; e < 4; ++e)
+        *reinterpret_cast<f32x4 *>(&part[wv][4 * quad + e][4 * l16]) = f32x4{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
     __syncthreads();
-    if (grp != 0 || ck >= chunks) return;
+    const int n = threadIdx.x >> 4, c = 4 * (threadIdx.x & 15);
+    if (threadIdx.x >= 256 || n0 + n >= N || c0 + c >= Cin) return;
+    f32x4 v = *reinterpret_cast<const f32x4 *>(&part[0][n][c]);
 #pragma unroll
-    for (int g = 1; g < 8; ++g)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += part[g][lane][e];
-    *reinterpret_cast<u32x4 *>(static_cast<unsigned char *>(gx) + ((size_t)n * chunks + ck) * 16) = pack8(acc);
+    for (int g = 1; g < kWaves; ++g) v += *reinterpret_cast<const f32x4 *>(&part[g][n][c]);
+    *reinterpret_cast<u32x2 *>(gx + (size_t)(n0 + n) * Cin + c0 + c) = u32x2{pack2(v.x, v.y), pack2(v.z, v.w)};
 }
 
-// gw[k][c] = scale_k * sum_n gy[n][k] * x[n][c] (fp32): one thread per (k, 8 input channels); n ascending.
-// Threads with ck == 0 also write the bias gradient sum_n gy[n][k] behind the weights.
-__global__ __launch_bounds__(256) void dense_bwd_weight_kernel(const uint16_t *gy, const void *x, const float *scale,
-                                                               float *gw, int N, int Cin, int Cout) {
-    const int chunks = Cin / 8;
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long long)Cout * chunks) return;
-    const int ck = (int)(idx % chunks), k = (int)(idx / chunks);
-    float acc[8], gsum = 0.f;
+// gw[k][c] = scale_k * sum_n gy[n][k] * x[n][c] (fp32).  A wavefront owns 16 classes x 64 channels and all images (four per MFMA);
+// the workgroup's four take neighbouring channels.  The wavefronts of channel 0 also write the bias gradient
+// sum_n gy[n][k] behind the weights.  52 -> 12 us (kernel trace): a thread per (k, 8 channels) read gy one value per image and step.
+__global__ __launch_bounds__(256) void dense_bwd_weight_kernel(const uint16_t *gy, const uint16_t *x, const float *scale, float *gw,
+                                                               int N, int Cin, int Cout) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l16 = lane & 15, quad = lane >> 4;
+    const int cblocks = (Cin + 255) / 256;
+    const int k0 = (int)(blockIdx.x / cblocks) * 16, c0 = ((int)(blockIdx.x % cblocks) * 4 + wv) * 64;
+    const bool kin = k0 + l16 < Cout, cin = c0 + 4 * l16 < Cin;
+    const uint16_t *gp = gy + (kin ? k0 + l16 : 0), *xp = x + (cin ? c0 + 4 * l16 : 0);
+    f32x4 acc[4];
+    float gsum = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    const unsigned char *xg = static_cast<const unsigned char *>(x);
-#pragma unroll 8
-    for (int n = 0; n < N; ++n) {
-        const float g = __uint_as_float((uint32_t)gy[(size_t)n * Cout + k] << 16);
-        gsum += g;
-        float v[8];
-        unpack8(*reinterpret_cast<const u32x4 *>(xg + ((size_t)n * chunks + ck) * 16), v);
+    for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int kSteps = 8;                                    // of four images, in flight together
+    for (int n0 = 0; n0 < N; n0 += 4 * kSteps) {
+        uint32_t g[kSteps];
+        u32x2 xv[kSteps];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += g * v[e];
+        for (int u = 0; u < kSteps; ++u) {
+            const int n = n0 + 4 * u + quad;
+            const size_t row = n < N ? n : 0;
+            g[u] = gp[row * Cout];
+            xv[u] = *reinterpret_cast<const u32x2 *>(xp + row * Cin);
+        }
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const bool nin = n0 + 4 * u + quad < N;
+            const float ga = nin && kin ? __uint_as_float(g[u] << 16) : 0.f;
+            gsum += ga;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float xf = (j & 1) ? hi16(xv[u][j >> 1]) : lo16(xv[u][j >> 1]);
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga, nin && cin ? xf : 0.f, acc[j], 0, 0, 0);
+            }
+        }
     }
-    const float sc = scale[k];
+    // acc[j]: class 4 * quad + e, channel 4 * l16 + j
 #pragma unroll
-    for (int e = 0; e < 8; ++e) gw[(size_t)k * Cin + ck * 8 + e] = acc[e] * sc;
-    if (ck == 0) gw[(size_t)Cout * Cin + k] = gsum;
+    for (int e = 0; e < 4; ++e) {
+        const int k = k0 + 4 * quad + e;
+        if (k >= Cout || !cin) continue;
+        const float sc = scale[k];
+        *reinterpret_cast<f32x4 *>(gw + (size_t)k * Cin + c0 + 4 * l16) = f32x4{acc[0][e] * sc, acc[1][e] * sc, acc[2][e] * sc, acc[3][e] * sc};
+    }
+    gsum += __shfl_xor(gsum, 16);
+    gsum += __shfl_xor(gsum, 32);
+    if (c0 == 0 && quad == 0 && kin) gw[(size_t)Cout * Cin + k0 + l16] = gsum;
 }
 
 }  // namespace bops
@@ -320,29 +413,37 @@ hipError_t launch_avgpool_bwd(const PoolArgs &a, const void *gy, void *gx, hipSt
 
 hipError_t launch_softmax_ce_bwd(const void *logits, const void *labels, int N, int classes, void *gz, hipStream_t stream) {
     if (!logits || !labels || !gz || N <= 0 || classes <= 0) return hipErrorInvalidValue;
-    bops::softmax_ce_bwd_kernel<<<dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream>>>(
-        static_cast<const uint16_t *>(logits), static_cast<const long long *>(labels), N, classes,
-        static_cast<uint16_t *>(gz));
+    const dim3 grid((unsigned)((N + 3) / 4)), block(256);
+    const auto *z = static_cast<const uint16_t *>(logits);
+    const auto *lab = static_cast<const long long *>(labels);
+    auto *out = static_cast<uint16_t *>(gz);
+    const bool pieces = classes % 8 == 0 && !(((uintptr_t)logits | (uintptr_t)gz) & 15);
+    if (pieces && classes <= 512) bops::softmax_ce_bwd_held_kernel<1><<<grid, block, 0, stream>>>(z, lab, N, classes, out);
+    else if (pieces && classes <= 1024) bops::softmax_ce_bwd_held_kernel<2><<<grid, block, 0, stream>>>(z, lab, N, classes, out);
+    else bops::softmax_ce_bwd_kernel<<<grid, block, 0, stream>>>(z, lab, N, classes, out);
     return hipGetLastError();
 }
 
 // Classifier: x [N][Cin], w [Cout][Cin] bf16, gy [N][Cout] bf16; gx [N][Cin] bf16 (or null),
-// gw fp32 [Cout*Cin + Cout] (weights, then bias; or null).  Cin a multiple of 8.
+// gw fp32 [Cout*Cin + Cout] (weights, then bias; or null).  Cin and Cout multiples of 8, pointers 16-byte aligned.
 hipError_t launch_dense_bwd(const void *x, const void *w, const float *scale, const void *gy, void *gx, float *gw,
                             int N, int Cin, int Cout, hipStream_t stream) {
-    if (!w || !scale || !gy || N <= 0 || Cin <= 0 || Cout <= 0 || Cin % 8) return hipErrorInvalidValue;
+    if (!w || !scale || !gy || N <= 0 || Cin <= 0 || Cout <= 0 || Cin % 8 || Cout % 8) return hipErrorInvalidValue;
+    if (((uintptr_t)x | (uintptr_t)w | (uintptr_t)scale | (uintptr_t)gy | (uintptr_t)gx | (uintptr_t)gw) & 15) return hipErrorInvalidValue;
     if (gx) {
-        const long long t = (long long)N * ((Cin / 8 + 31) / 32);
-        bops::dense_bwd_data_kernel<<<dim3((unsigned)t), dim3(256), 0, stream>>>(
-            static_cast<const uint16_t *>(gy), w, scale, gx, N, Cin, Cout);
+        const long long t = ((long long)N + 15) / 16 * ((Cin + 63) / 64);
+        if (t > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+        bops::dense_bwd_data_kernel<<<dim3((unsigned)t), dim3(512), 0, stream>>>(
+            static_cast<const uint16_t *>(gy), static_cast<const uint16_t *>(w), scale, static_cast<uint16_t *>(gx), N, Cin, Cout);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (gw) {
         if (!x) return hipErrorInvalidValue;
-        const long long t = (long long)Cout * (Cin / 8);
-        bops::dense_bwd_weight_kernel<<<dim3((unsigned)((t + 255) / 256)), dim3(256), 0, stream>>>(
-            static_cast<const uint16_t *>(gy), x, scale, gw, N, Cin, Cout);
+        const long long t = ((long long)Cout + 15) / 16 * ((Cin + 255) / 256);
+        if (t > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+        bops::dense_bwd_weight_kernel<<<dim3((unsigned)t), dim3(256), 0, stream>>>(
+            static_cast<const uint16_t *>(gy), static_cast<const uint16_t *>(x), scale, gw, N, Cin, Cout);
         return hipGetLastError();
     }
     return hipSuccess;

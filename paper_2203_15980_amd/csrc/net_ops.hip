@@ -336,30 +336,43 @@ __global__ __launch_bounds__(256) void maxpool_kernel(PoolArgs a, long long tota
     *reinterpret_cast<u32x4_s *>(static_cast<unsigned char *>(a.y) + (size_t)idx * 16) = o;
 }
 
-// Global average: one thread per (image, 16 bytes of channels), fp32 accumulation in pixel order.
-template <bool BF16>
-__global__ __launch_bounds__(256) void avgpool_kernel(PoolArgs a, long long total) {
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
+// Global average.  A workgroup takes 64 (image, 16 bytes of channels) pairs, one per lane; its G wavefronts split the
+// pixels (wavefront g takes pixels g, g + G, ...), four of a wavefront's loads are in flight, and the G fp32 sums are
+// added in the order of g through LDS.  HBM-bound: 128 x 7 x 7 x 2048 is 25.7 MB; with one thread per pair walking all
+// pixels the launch was 512 wavefronts and 17 us, with eight per pair 6.6.
+template <bool BF16, int G>
+__global__ __launch_bounds__(G * 64) void avgpool_kernel(PoolArgs a, long long total) {
     constexpr int CPT = BF16 ? 8 : 4;
-    const int chunks = a.C / CPT;
-    const int ck = (int)(idx % chunks);
-    const int n = (int)(idx / chunks);
+    __shared__ float part[G][64][CPT + 1];
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const long long idx = (long long)blockIdx.x * 64 + lane;
+    const int chunks = a.C / CPT, hw = a.H * a.W;
     float s[CPT];
 #pragma unroll
     for (int e = 0; e < CPT; ++e) s[e] = 0.f;
-    const unsigned char *xg = static_cast<const unsigned char *>(a.x);
-    const int hw = a.H * a.W;
-    for (int i = 0; i < hw; ++i) {
-        const u32x4_s v = *reinterpret_cast<const u32x4_s *>(xg + (((size_t)n * hw + i) * chunks + ck) * 16);
-        if constexpr (BF16) {
-            s[0] += blo(v.x); s[1] += bhi(v.x); s[2] += blo(v.y); s[3] += bhi(v.y);
-            s[4] += blo(v.z); s[5] += bhi(v.z); s[6] += blo(v.w); s[7] += bhi(v.w);
-        } else {
-            s[0] += __uint_as_float(v.x); s[1] += __uint_as_float(v.y);
-            s[2] += __uint_as_float(v.z); s[3] += __uint_as_float(v.w);
+    if (idx < total) {
+        const int ck = (int)(idx % chunks), n = (int)(idx / chunks);
+        const u32x4_s *xg = static_cast<const u32x4_s *>(a.x) + (size_t)n * hw * chunks + ck;
+#pragma unroll 4
+        for (int i = g; i < hw; i += G) {
+            const u32x4_s v = xg[(size_t)i * chunks];
+            if constexpr (BF16) {
+                s[0] += blo(v.x); s[1] += bhi(v.x); s[2] += blo(v.y); s[3] += bhi(v.y);
+                s[4] += blo(v.z); s[5] += bhi(v.z); s[6] += blo(v.w); s[7] += bhi(v.w);
+            } else {
+                s[0] += __uint_as_float(v.x); s[1] += __uint_as_float(v.y);
+                s[2] += __uint_as_float(v.z); s[3] += __uint_as_float(v.w);
+            }
         }
     }
+#pragma unroll
+    for (int e = 0; e < CPT; ++e) part[g][lane][e] = s[e];
+    __syncthreads();
+    if (g != 0 || idx >= total) return;
+#pragma unroll
+    for (int k = 1; k < G; ++k)
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) s[e] += part[k][lane][e];
     const float inv = 1.0f / (float)hw;
     u32x4_s o;
     if constexpr (BF16) {
@@ -401,18 +414,19 @@ hipError_t launch_maxpool(const PoolArgs &a, hipStream_t stream) {
 hipError_t launch_avgpool(const PoolArgs &a, hipStream_t stream) {
     if (pool_check(a, true)) return hipErrorInvalidValue;
     const long long total = (long long)a.N * (a.C / (a.bf16 ? 8 : 4));
-    const long long blocks = (total + 255) / 256;
-    if (a.bf16) avgpool_kernel<true><<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(a, total);
-    else avgpool_kernel<false><<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(a, total);
+    const long long blocks = (total + 63) / 64;
+    if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+    if (a.bf16) avgpool_kernel<true, 8><<<dim3((unsigned)blocks), dim3(512), 0, stream>>>(a, total);
+    else avgpool_kernel<false, 8><<<dim3((unsigned)blocks), dim3(512), 0, stream>>>(a, total);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------ loss
-// Mean over images of logsumexp(z_i) - z_i[label_i].  One workgroup of 16 wavefronts (the
-// result is one float, so there is nothing to spread over the chip; what matters is that the
-// loads of a wavefront are all in flight together).  A wavefront takes two images per round;
-// a lane owns classes lane, lane + 64, ... and holds up to 16 of them per image in registers,
-// so each logit is read once; more than 1024 classes fall back to re-reading loops.  Fixed
+// Mean over images of logsumexp(z_i) - z_i[label_i].  One workgroup of 16 wavefronts: the result is one float,
+// and what the launch costs is the latency of its loads and reductions.  Where a row is whole 16-byte pieces (bf16,
+// classes a multiple of 8, at most 1024) a wavefront holds FOUR images at once, two 16-byte pieces per lane and image:
+// eight loads in flight, and the four images' reduction trees interleave (128 images of 1000 classes: 45 -> 14 us;
+// it was two images in 2-byte loads).  Otherwise a lane owns classes lane, lane + 64, ... and re-reads them.  Fixed
 // reduction trees and a fixed image -> wavefront map: the result does not depend on timing.
 // A label outside [0, classes) makes the result NaN, so that it cannot pass unnoticed.
 template <bool BF16>
@@ -421,46 +435,58 @@ __device__ __forceinline__ float logit_at(const void *logits, size_t idx) {
                 : static_cast<const float *>(logits)[idx];
 }
 
-template <bool BF16>
+template <bool BF16, bool HELD>
 __global__ __launch_bounds__(1024) void softmax_ce_kernel(const void *logits, const long long *labels, int N,
                                                           int classes, float *out) {
-    constexpr int WAVES = 16, IMGS = 2, KMAX = 16;
+    constexpr int WAVES = 16, IMGS = 4;
     __shared__ float part[WAVES];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     float total = 0.f;
-    if (classes <= 64 * KMAX) {
+    auto logit_of_label = [&](int i) {
+        const long long lab = labels[i];
+        return lab >= 0 && lab < classes ? logit_at<BF16>(logits, (size_t)i * classes + lab) : __builtin_nanf("");
+    };
+    if constexpr (HELD) {
+        const int pieces = classes / 8;
         for (int i0 = wv * IMGS; i0 < N; i0 += WAVES * IMGS) {
-            float z[IMGS][KMAX], zl[IMGS];
+            u32x4_s v[IMGS][2];
+            float zl[IMGS], mx[IMGS], se[IMGS];
 #pragma unroll
             for (int u = 0; u < IMGS; ++u) {
-                const int i = i0 + u;
+                const int i = i0 + u < N ? i0 + u : N - 1;        // past the last image: read again, not counted
+                const u32x4_s *z = reinterpret_cast<const u32x4_s *>(static_cast<const uint16_t *>(logits) + (size_t)i * classes);
 #pragma unroll
-                for (int k = 0; k < KMAX; ++k) {
-                    const int c = lane + 64 * k;
-                    z[u][k] = (i < N && c < classes) ? logit_at<BF16>(logits, (size_t)i * classes + c) : -INFINITY;
-                }
-                zl[u] = __builtin_nanf("");
-                if (i < N) {
-                    const long long lab = labels[i];
-                    if (lab >= 0 && lab < classes) zl[u] = logit_at<BF16>(logits, (size_t)i * classes + lab);
-                }
+                for (int p = 0; p < 2; ++p) v[u][p] = z[lane + 64 * p < pieces ? lane + 64 * p : 0];
+                zl[u] = logit_of_label(i);
             }
+            auto at = [&](int u, int k) {                        // value k of the lane's 16, -inf past the row
+                const u32x4_s q = v[u][k >> 3];
+                const uint32_t w = q[(k & 7) >> 1];
+                return lane + 64 * (k >> 3) < pieces ? ((k & 1) ? bhi(w) : blo(w)) : -INFINITY;
+            };
 #pragma unroll
             for (int u = 0; u < IMGS; ++u) {
-                if (i0 + u >= N) break;                       // uniform over the wavefront
-                float mx = -INFINITY;
+                mx[u] = -INFINITY;
 #pragma unroll
-                for (int k = 0; k < KMAX; ++k) mx = fmaxf(mx, z[u][k]);
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-                float se = 0.f;
-#pragma unroll
-                for (int k = 0; k < KMAX; ++k)
-                    if (lane + 64 * k < classes) se += __expf(z[u][k] - mx);
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
-                total += (mx + __logf(se)) - zl[u];
+                for (int k = 0; k < 16; ++k) mx[u] = fmaxf(mx[u], at(u, k));
             }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+                for (int u = 0; u < IMGS; ++u) mx[u] = fmaxf(mx[u], __shfl_xor(mx[u], o));
+#pragma unroll
+            for (int u = 0; u < IMGS; ++u) {
+                se[u] = 0.f;
+#pragma unroll
+                for (int k = 0; k < 16; ++k) se[u] += lane + 64 * (k >> 3) < pieces ? __expf(at(u, k) - mx[u]) : 0.f;
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+                for (int u = 0; u < IMGS; ++u) se[u] += __shfl_xor(se[u], o);
+#pragma unroll
+            for (int u = 0; u < IMGS; ++u)
+                if (i0 + u < N) total += (mx[u] + __logf(se[u])) - zl[u];
         }
     } else {
         for (int i = wv; i < N; i += WAVES) {
@@ -472,10 +498,7 @@ __global__ __launch_bounds__(1024) void softmax_ce_kernel(const void *logits, co
             for (int c = lane; c < classes; c += 64) se += __expf(logit_at<BF16>(logits, (size_t)i * classes + c) - mx);
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
-            const long long lab = labels[i];
-            float zl = __builtin_nanf("");
-            if (lab >= 0 && lab < classes) zl = logit_at<BF16>(logits, (size_t)i * classes + lab);
-            total += (mx + __logf(se)) - zl;
+            total += (mx + __logf(se)) - logit_of_label(i);
         }
     }
     if (lane == 0) part[wv] = total;
@@ -491,8 +514,11 @@ __global__ __launch_bounds__(1024) void softmax_ce_kernel(const void *logits, co
 hipError_t launch_softmax_ce(const void *logits, const void *labels, int N, int classes, int bf16, float *out,
                              hipStream_t stream) {
     if (!logits || !labels || !out || N <= 0 || classes <= 0) return hipErrorInvalidValue;
-    if (bf16) softmax_ce_kernel<true><<<dim3(1), dim3(1024), 0, stream>>>(logits, static_cast<const long long *>(labels), N, classes, out);
-    else softmax_ce_kernel<false><<<dim3(1), dim3(1024), 0, stream>>>(logits, static_cast<const long long *>(labels), N, classes, out);
+    const auto *lab = static_cast<const long long *>(labels);
+    if (bf16 && classes % 8 == 0 && classes <= 1024 && !((uintptr_t)logits & 15))
+        softmax_ce_kernel<true, true><<<dim3(1), dim3(1024), 0, stream>>>(logits, lab, N, classes, out);
+    else if (bf16) softmax_ce_kernel<true, false><<<dim3(1), dim3(1024), 0, stream>>>(logits, lab, N, classes, out);
+    else softmax_ce_kernel<false, false><<<dim3(1), dim3(1024), 0, stream>>>(logits, lab, N, classes, out);
     return hipGetLastError();
 }
 
