@@ -68,16 +68,13 @@ __device__ __forceinline__ void mma(const u32x4 w, const u32x4 x, f32x16 &acc) {
     }
 }
 
-// Division by a launch constant d as a multiplication: ceil(2^32 / d), so that floor(n * that / 2^32) == n / d while
-// n * d < 2^32 (the launcher checks the ranges); 0 stands for d = 1, which 32 bits cannot express.
-struct Reciprocals { unsigned pq, q, cs, s; };
-__device__ __forceinline__ int divide(int n, unsigned inv) { return inv ? (int)__umulhi((unsigned)n, inv) : n; }
+struct Divisors { Divisor pq, q, cs, s; };
 
 // wR, wS, w_r0, w_s0, w_step of `a` are filled by the launcher for every form (see ConvArgs).
 // AHEAD: steps in flight per wavefront.
 template <bool BF16, int KW, int AHEAD>
 __global__ __launch_bounds__(KW * 64) void conv_splitk_kernel(ConvArgs a, int tiles_m, int tiles_n, int pixels_first,
-                                                              Reciprocals inv) {
+                                                              Divisors inv) {
     constexpr int ES = BF16 ? 2 : 4;
     __shared__ __align__(16) unsigned char smem[KW * kWaveLds];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -247,15 +244,13 @@ __global__ __launch_bounds__(KW * 64) void conv_splitk_kernel(ConvArgs a, int ti
     }
 }
 
-unsigned reciprocal(unsigned d) { return d == 1 ? 0u : (unsigned)((0x100000000ull + d - 1) / d); }
-
 template <bool BF16, int KW, int AHEAD>
 hipError_t launch(const ConvArgs &a, hipStream_t stream) {
     const int tiles_m = (a.M + kTile - 1) / kTile, tiles_n = (a.Cout + kTile - 1) / kTile;
     const long long xbytes = (long long)a.N * a.H * a.W * a.Cin, wbytes = (long long)a.Cout * a.R * a.S * a.Cin;
     conv_splitk_kernel<BF16, KW, AHEAD><<<dim3((unsigned)tiles_m * (unsigned)tiles_n), dim3(KW * 64), 0, stream>>>(
         a, tiles_m, tiles_n, wbytes > xbytes,
-        Reciprocals{reciprocal(a.P * a.Q), reciprocal(a.Q), reciprocal(a.Cin * (BF16 ? 2 : 4) / kStepBytes), reciprocal(a.S)});
+        Divisors{make_divisor(a.P * a.Q), make_divisor(a.Q), make_divisor(a.Cin * (BF16 ? 2 : 4) / kStepBytes), make_divisor(a.S)});
     return hipGetLastError();
 }
 
@@ -271,9 +266,7 @@ bool conv_splitk_applies(const ConvArgs &a) {
     if (a.bf16 && a.R == 3 && a.Cin == 64 && a.Cout == 64) return false;   // the block kernel's middle layer: its bits
     // 32-bit offsets from the tensors' own starts
     if ((long long)a.N * a.H * a.W * a.Cin * es > 0x7FFFFFFFLL) return false;
-    const long long per_tap = (long long)a.Cin * es / splitk::kStepBytes, steps = (long long)a.R * a.S * per_tap;
-    // the kernel's divisions by multiplication
-    if ((steps + 256) * per_tap > 0xFFFFFFFFLL || ((long long)a.M + splitk::kTile) * a.P * a.Q > 0xFFFFFFFFLL) return false;
+    const long long steps = (long long)a.R * a.S * a.Cin * es / splitk::kStepBytes;
     // Where the line lies.  A tiled kernel that does not fill the chip takes about 4.5 + 0.55 us per 128-byte step of
     // the reduction however small the output; this one about 4.5 us + (3 + 0.37 steps) ns per tile.  Measured (us, tiled
     // kernel | this one; the number of 32 x 32 tiles in brackets):

@@ -110,8 +110,6 @@ struct delta_ctx {
     hipStream_t stream[N_STREAMS] = {nullptr, nullptr, nullptr, nullptr};
     Ev aux_tail;                                   // last launch on S_AUX the compute stream has not joined
     uintptr_t aux_lo = 0, aux_hi = 0;              // caller memory (workspace) those launches use: [aux_lo, aux_hi)
-    Ev stg_tail;                                   // last launch on S_AUX that used a staging range, and that range
-    uintptr_t stg_lo = 0, stg_hi = 0;
     std::map<uint64_t, Block> free_blocks;         // offset -> block, coalesced
     std::deque<Resting> cooling;                   // freed blocks the weight-gradient stream may still read, oldest first
     std::deque<Resting> copying;                   // freed blocks a copy may still touch, oldest first
@@ -213,8 +211,8 @@ void retire_events(delta_ctx *c) {
         c->tensors[i].d2h_done = c->tensors[i].h2d_done = c->tensors[i].aux_done = Ev();
         c->tensors[i].d2h_piece.clear();
     }
-    c->aux_tail = c->stg_tail = Ev();              // every stream is idle: nothing in flight uses the caller's workspace
-    c->aux_lo = c->aux_hi = c->stg_lo = c->stg_hi = 0;
+    c->aux_tail = Ev();                            // every stream is idle: nothing in flight uses the caller's workspace
+    c->aux_lo = c->aux_hi = 0;
     c->ev_pool.insert(c->ev_pool.end(), c->ev_live.begin(), c->ev_live.end());
     c->ev_live.clear();
 }
@@ -1281,7 +1279,7 @@ delta_status prepare_backward_other(delta_ctx *c, const delta_bwd_desc &D, uint3
 // Validates one backward descriptor; fills the forward geometry (fa) and, if gx is asked for, the
 // convolution that computes the data gradient (da).  Pointers in fa/da are placeholders.
 // A 1x1 layer with stride > 1 touches only the input pixels (stride p, stride q): its gradients are
-// computed at the output's resolution (input pixels gathered, data gradient spread back out).
+// computed at the output's resolution (the weight gradient picks those pixels, the data gradient is spread back out).
 bool strided_1x1(const delta_layer_desc &L) { return L.stride > 1 && L.R == 1 && L.S == 1 && L.pad == 0; }
 
 // A 3x3 stride-2 pad-1 layer whose incoming gradient needs no mask of its own: input pixel (2i+a, 2j+b)
@@ -1322,17 +1320,17 @@ void class_args(const delta_layer_desc &L, int bf16, int a, int b, delta::ConvAr
     ca.wR = 3; ca.wS = 3; ca.w_r0 = a ? 0 : 1; ca.w_s0 = b ? 0 : 1; ca.w_step = 2;
 }
 
-// `fa` (the forward layer's arguments) as the weight gradient sees the layer: stride 1.
+// `fa` (the forward layer's arguments) as the weight gradient sees the layer: a 1x1 layer as it is, any other at
+// stride 1 (its gradient is spread to the input's resolution).
 void as_stride_1(const delta_layer_desc &L, delta::ConvArgs &fa) {
-    if (strided_1x1(L)) { fa.H = fa.P; fa.W = fa.Q; }
-    else { fa.P = L.H; fa.Q = L.W; }
+    if (strided_1x1(L)) return;
+    fa.P = L.H; fa.Q = L.W;
     fa.stride = 1;
     fa.M = L.N * fa.P * fa.Q;
 }
 
-// Bytes of the staging tensor of a strided 1x1 layer (the gathered input pixels, and before that
-// the data gradient at the output's resolution): N*P*Q*Cin elements, after the weight gradient's
-// partial sums in the workspace.
+// Bytes of the staging tensor of a strided 1x1 layer, its data gradient at the output's resolution: N*P*Q*Cin elements,
+// after the weight gradient's partial sums in the workspace.
 uint64_t staging_bytes(const delta_layer_desc &L, const delta::ConvArgs &fa) {
     if (!strided_1x1(L)) return 0;
     const uint64_t b = (uint64_t)L.N * fa.P * fa.Q * L.Cin * (fa.bf16 ? 2 : 4);
@@ -1422,7 +1420,7 @@ delta_status prepare_backward(delta_ctx *c, const delta_bwd_desc &D, uint32_t i,
         return fail(c, DELTA_ERR_INVALID, "backward %u: gx_add without gx", i);
     }
     // the weight gradient sees the layer at stride 1 (gpre is at the input's resolution; a strided
-    // 1x1 layer at the output's, on the gathered input pixels)
+    // 1x1 layer at the output's)
     as_stride_1(L, fa);
     if (D.gw) {
         const char *why = class_wgrad(D, fo) ? nullptr : delta::wgrad_check(fa);
@@ -1459,8 +1457,6 @@ delta_status join_aux(delta_ctx *c) {
         c->aux_tail = Ev();
     }
     c->aux_lo = c->aux_hi = 0;
-    c->stg_tail = Ev();
-    c->stg_lo = c->stg_hi = 0;
     return DELTA_OK;
 }
 
@@ -1645,22 +1641,13 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
         const bool own_mask = L.relu && !D.gy_masked;
         const bool direct = strided_1x1(L);
         const int outP = (L.H + 2 * L.pad - L.R) / L.stride + 1, outQ = (L.W + 2 * L.pad - L.S) / L.stride + 1;
-        // A strided 1x1 layer stages both of its gradients at the END of the workspace; weight gradients
+        // A strided 1x1 layer stages its data gradient at the END of the workspace; weight gradients
         // still running on the other stream use its beginning.  Only if the two ranges meet (a
         // workspace no larger than this layer needs) does the compute stream wait for them.
         const uint64_t stg_bytes = direct ? staging_bytes(L, fa) : 0;
         unsigned char *staging =
             direct ? static_cast<unsigned char *>(D.workspace) + ((D.workspace_bytes - stg_bytes) & ~(uint64_t)255) : nullptr;
-        if (direct) {
-            const uintptr_t lo = (uintptr_t)staging, hi = lo + stg_bytes;
-            if (aux_holds(c, staging, stg_bytes)) {
-                if ((r = join_aux(c)) != DELTA_OK) return r;
-            } else if (c->stg_tail && lo < c->stg_hi && c->stg_lo < hi) {
-                // only an earlier strided 1x1 layer's weight gradient used these bytes: wait for that one launch
-                HIP_TRY(c, hipStreamWaitEvent(s, c->stg_tail.e, 0));
-                c->stg_tail = Ev();
-            }
-        }
+        if (direct && aux_holds(c, staging, stg_bytes) && (r = join_aux(c)) != DELTA_OK) return r;
         delta::ConvArgs fo = fa;                             // the forward layer's own geometry (fa is its stride-1 view)
         fo.stride = L.stride; fo.P = outP; fo.Q = outQ; fo.M = L.N * outP * outQ;
         const bool no_spread = D.gpre == D.gy && class_only(D, fo);
@@ -1683,7 +1670,7 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
         const unsigned char *gp = c->arena + c->tensors[D.gpre].offset;
         Ev ready;
         const bool aside = D.gw && wgrad_aside(L, fa);
-        if (D.gw && !direct) {
+        if (D.gw) {
             if ((r = compute_uses(c, c->tensors[L.x])) != DELTA_OK) return r;
             if (aside && (r = new_event(c, s, &ready)) != DELTA_OK) return r;
         }
@@ -1724,8 +1711,7 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
             Tensor &tx = c->tensors[L.x];
             if ((r = compute_uses(c, tx)) != DELTA_OK) return r;
             fa.x = c->arena + tx.offset;
-            // gpre and x are complete once the compute stream reaches `ready` (for a strided 1x1 layer:
-            // and the data gradient has left the staging area); from there the weight gradient runs on
+            // gpre and x are complete once the compute stream reaches `ready`; from there the weight gradient runs on
             // its own stream, and both tensors remember that reader.
             // A small one stays on the compute stream, after whatever still uses the workspace on the other.
             const bool by_class = class_wgrad(D, fo);
@@ -1733,17 +1719,12 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
             hipStream_t gs = s;
             if (aside) {
                 gs = c->stream[S_AUX];
-                if (direct && (r = new_event(c, s, &ready)) != DELTA_OK) return r;
                 HIP_TRY(c, hipStreamWaitEvent(gs, ready.e, 0));
             } else if (aux_holds(c, D.workspace, need) && (r = join_aux(c)) != DELTA_OK) {
                 return r;
             }
-            if (direct) {
-                HIP_TRY(c, delta::launch_subsample(fa.x, staging, L.N, L.H, L.W, outP, outQ, L.Cin, L.stride, fa.bf16, gs));
-                fa.x = staging;
-            }
             if (by_class) {
-                // by parity class, from gy itself (it needs no mask of this layer's) and x
+                // from gy itself (it needs no mask of this layer's) and x
                 fo.x = fa.x;
                 HIP_TRY(c, delta::launch_wgrad_s2(fo, c->arena + tgy.offset, static_cast<float *>(D.gw), D.workspace, need, gs));
                 c->st.recompute_flops += 2ull * (uint64_t)fo.M * 9 * fo.Cin * fo.Cout;
@@ -1755,11 +1736,6 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
                 aux_claims(c, D.workspace, need);
                 if ((r = new_event(c, gs, &c->aux_tail)) != DELTA_OK) return r;
                 tx.aux_done = (by_class ? tgy : c->tensors[D.gpre]).aux_done = c->aux_tail;
-                if (direct) {                                   // the staging range is tracked on its own
-                    c->stg_tail = c->aux_tail;
-                    c->stg_lo = (uintptr_t)staging;
-                    c->stg_hi = c->stg_lo + stg_bytes;
-                }
             }
         }
         c->st.recompute_launches += 1;

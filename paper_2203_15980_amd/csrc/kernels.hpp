@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
+#include <stdint.h>
 
 namespace delta {
 
@@ -24,6 +25,17 @@ struct ConvArgs {
     int oy_s = 0, oy_a = 0, oy_b = 0, OH = 0, OW = 0;
     int wR = 0, wS = 0, w_r0 = 0, w_s0 = 0, w_step = 1;
 };
+
+// Division by a launch constant as a multiplication, exact for 0 <= n < 2^31: with 2^(s-1) < d <= 2^s and mul = ceil(2^(31+s) / d),
+// floor(n mul / 2^(31+s)) == floor(n / d), because mul d exceeds 2^(31+s) by less than d <= 2^s.  mul 0 stands for d = 1.
+struct Divisor { uint32_t mul, shift; };
+inline Divisor make_divisor(uint32_t d) {
+    if (d <= 1) return Divisor{0u, 0u};
+    uint32_t s = 1;
+    while (s < 32 && (1ull << s) < d) ++s;
+    return Divisor{(uint32_t)(((1ull << (31 + s)) + d - 1) / d), s - 1};
+}
+__device__ __forceinline__ int divide(int n, Divisor d) { return d.mul ? (int)(__umulhi((uint32_t)n, d.mul) >> d.shift) : n; }
 
 // The test behind every ReLU mask of the backward pass.  bf16: greater than zero <=> sign bit clear,
 // not zero and not NaN.  Returns the bits of `v` (two bf16 values) with the halves cleared whose
@@ -134,22 +146,29 @@ hipError_t launch_softmax_ce(const void *logits, const void *labels, int N, int 
 hipError_t launch_relu_mask(const void *y, const void *gy, void *out, size_t bytes, int bf16, hipStream_t stream);
 hipError_t launch_relu_mask_dilate(const void *y, const void *gy, void *out, int N, int H, int W, int P, int Q, int K,
                                    int stride, int bf16, hipStream_t stream);
-hipError_t launch_subsample(const void *x, void *xs, int N, int H, int W, int P, int Q, int C, int stride, int bf16,
-                            hipStream_t stream, int oa = 0, int ob = 0);
 hipError_t launch_spread_add(const void *t, const void *add, const void *mask, void *out, int N, int H, int W, int P,
                              int Q, int C, int stride, int bf16, hipStream_t stream);
 hipError_t launch_bwd_weights(const void *w, const float *scale, void *wt, int K, int R, int S, int C, int bf16,
                               hipStream_t stream);
-const char *wgrad_check(const ConvArgs &a);            // nullptr when the weight-gradient kernel applies
+const char *wgrad_check(const ConvArgs &a);            // nullptr when a weight-gradient kernel applies
 size_t wgrad_workspace_bytes(const ConvArgs &a);
-// 3x3 stride-2 pad-1 layers by parity class, from the gradient at the output's resolution (a.x = x at the
-// input's resolution, a.H, a.W, a.P, a.Q the layer's own)
+// 3x3 stride-2 pad-1 layers, from the gradient at the output's resolution (a.x = x at the input's resolution, a.H, a.W,
+// a.P, a.Q the layer's own)
 bool wgrad_s2_applies(const ConvArgs &a);
 size_t wgrad_s2_workspace_bytes(const ConvArgs &a);
 hipError_t launch_wgrad_s2(const ConvArgs &a, const void *g, float *gw, void *workspace, size_t workspace_bytes,
                            hipStream_t stream);
 hipError_t launch_wgrad(const ConvArgs &a, const void *g, float *gw, void *workspace, size_t workspace_bytes,
                         hipStream_t stream);
+
+// wgrad1x1.hip, wgrad3x3.hip: the bf16 weight gradients (the layer's own geometry; g at the output's resolution)
+int wgrad_splits(long long pixels, int tiles, double pixel_ns, double sums_ns);
+const char *wgrad1x1_check(const ConvArgs &a);
+size_t wgrad1x1_workspace_bytes(const ConvArgs &a);
+hipError_t launch_wgrad1x1(const ConvArgs &a, const void *g, float *gw, void *workspace, size_t workspace_bytes, hipStream_t stream);
+const char *wgrad3x3_check(const ConvArgs &a);
+size_t wgrad3x3_workspace_bytes(const ConvArgs &a);
+hipError_t launch_wgrad3x3(const ConvArgs &a, const void *g, float *gw, void *workspace, size_t workspace_bytes, hipStream_t stream);
 
 // backward_ops.hip: backward of pooling, the classifier and the loss (bf16)
 // mask_x: gx is also multiplied by [x > 0] (the ReLU mask of the layer that produced the pool's input)

@@ -1,0 +1,70 @@
+"""The bf16 weight gradients alone, against float64 on the stored operands, at the edges of their tiles and chunks.
+
+Tolerance: products of two bf16 values are exact in fp32; the sums have at most 6000 terms, split over wavefronts and
+workgroups: 1e-5 of the largest entry (about sqrt(6000) * 2^-24, with a margin of two)."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import numeric as on
+from test_gpu_backward import _bits, _dev, _small_ctx, torch_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N  H   W   Cin  Cout R stride
+    (1, 1, 1, 64, 64, 1, 1),          # one pixel; one 64 x 64 tile, eight wavefronts on it
+    (1, 9, 15, 128, 64, 1, 1),        # 135 pixels: a full slice of 128 and one of 7
+    (2, 8, 8, 256, 64, 1, 1),         # four tiles along the input channels; whole slices
+    (1, 5, 13, 64, 128, 1, 1),
+    (3, 7, 31, 64, 512, 1, 1),        # four tiles along the output channels, two of those; 651 pixels
+    (2, 11, 13, 192, 320, 1, 1),      # neither count a multiple of 128
+    (2, 9, 7, 128, 256, 1, 2),        # strided, odd sizes
+    (1, 8, 6, 64, 64, 1, 3),
+    (1, 1, 1, 64, 64, 3, 1),          # only the centre tap has anything
+    (5, 3, 1, 64, 128, 3, 1),         # images one pixel wide: two list pixels to a row
+    (3, 7, 7, 128, 64, 3, 1),         # several images to a chunk
+    (1, 3, 116, 64, 64, 3, 1),        # the widest row a chunk takes
+    (2, 30, 17, 64, 64, 3, 1),        # chunks that end inside an image, a short last one
+    (2, 6, 5, 128, 128, 3, 2),        # even height, odd width
+    (3, 7, 8, 128, 256, 3, 2),
+    (1, 1, 3, 128, 128, 3, 2),        # no odd rows at all
+    (1, 9, 79, 128, 128, 3, 2),       # 40 output columns
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%dx%dx%d_%d_%d_r%d_s%d" % c)
+def test_weight_gradient_matches_float64(torch_mod, case):  # noqa: F811
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    N, H, W, Cin, Cout, R, stride = case
+    print("case", case, flush=True)
+    P, Q, pad = (H - 1) // stride + 1, (W - 1) // stride + 1, R // 2
+    x, gy = _bits(94, 1, (N, H, W, Cin)), _bits(94, 2, (N, P, Q, Cout))
+    scale = (synth.normal(94, 3, Cout) * 0.3 + 1.0).astype(np.float32)
+    d, put, get = _small_ctx(torch, [x.nbytes, gy.nbytes, gy.nbytes])
+    put(0, x)
+    put(2, gy)
+    w, sc, sh = torch.zeros(Cout * R * R * Cin, dtype=torch.bfloat16, device="cuda:0"), _dev(torch, scale), torch.zeros(Cout, device="cuda:0")
+    fwd = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=sc.data_ptr(), shift=sh.data_ptr(), N=N, H=H, W=W,
+                       Cin=Cin, Cout=Cout, R=R, S=R, stride=stride, pad=pad, relu=0)
+    ws = torch.full((max(d.backward_workspace(fwd), 256),), 255, dtype=torch.uint8, device="cuda:0")     # NaN wherever nothing is written
+    got = []
+    for _ in range(2):
+        gw = torch.full((Cout, R, R, Cin), float("nan"), device="cuda:0")
+        d.backward_segment([dl.BwdDesc(fwd=fwd, gy=2, gpre=2, gx=dl.NO_TENSOR, gx_add=dl.NO_TENSOR, gw=gw.data_ptr(), workspace=ws.data_ptr(),
+                                       workspace_bytes=ws.numel())])
+        d.backward_join()
+        d.sync()
+        got.append(gw.cpu().numpy())
+    xf, gf = on.to_f64(x, "bf16"), on.to_f64(gy, "bf16")
+    xp = np.pad(xf, ((0, 0), (pad, pad), (pad, pad), (0, 0)))
+    ref = np.empty((Cout, R, R, Cin))
+    for r in range(R):
+        for s in range(R):
+            ref[:, r, s] = np.tensordot(gf, xp[:, r:r + stride * (P - 1) + 1:stride, s:s + stride * (Q - 1) + 1:stride], ((0, 1, 2), (0, 1, 2)))
+    ref *= scale.astype(np.float64)[:, None, None, None]
+    err = float(np.max(np.abs(got[0] - ref)) / np.max(np.abs(ref)))
+    print("  err %.2e" % err, flush=True)
+    assert err <= 1e-5 and np.array_equal(got[0], got[1])
+    d.close()
