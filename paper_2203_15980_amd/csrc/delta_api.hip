@@ -1691,12 +1691,16 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
             da.scale = c->ones; da.shift = c->zeros;
             if (direct) { da.res = nullptr; da.mask = nullptr; da.y = staging; }
             if (class_dgrad(D)) {
-                for (int cls = 0; cls < 4; ++cls) {
+                for (int cls = 3; cls >= 0; --cls) {
                     delta::ConvArgs ca;
                     class_args(L, fa.bf16, cls >> 1, cls & 1, ca);
-                    if (ca.P <= 0 || ca.Q <= 0) continue;
                     ca.x = c->arena + tgy.offset; ca.w = D.wt; ca.res = addp; ca.mask = maskp; ca.y = c->arena + tgx.offset;
                     ca.scale = c->ones; ca.shift = c->zeros;
+                    if (delta::dgrad_s2_applies(ca)) {           // all four in one launch
+                        HIP_TRY(c, delta::launch_dgrad_s2(ca, s));
+                        break;
+                    }
+                    if (ca.P <= 0 || ca.Q <= 0) continue;
                     HIP_TRY(c, delta::launch_conv_scatter(ca, s));
                 }
             } else

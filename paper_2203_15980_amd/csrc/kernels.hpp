@@ -68,6 +68,8 @@ const char *conv_kernel_name(const ConvArgs &a);
 hipError_t launch_conv(const ConvArgs &a, hipStream_t stream);
 const char *conv_scatter_check(const ConvArgs &a);
 hipError_t launch_conv_scatter(const ConvArgs &a, hipStream_t stream);
+bool dgrad_s2_applies(const ConvArgs &a);
+hipError_t launch_dgrad_s2(const ConvArgs &a, hipStream_t stream);
 // conv_splitk.hip: layers with too little output to fill the chip, the reduction split over a workgroup's wavefronts
 bool conv_splitk_applies(const ConvArgs &a);
 const char *conv_splitk_kernel_name(const ConvArgs &a);
