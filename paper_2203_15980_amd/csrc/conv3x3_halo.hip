@@ -10,9 +10,12 @@
 //
 // Layout: output channels on the MFMA row axis, pixels on the column axis, lane half h owns bytes
 // [64h, 64h+64) of every 128-byte row for both operands (as in conv_igemm.hip).  A workgroup is
-// (BM/64) x (BN/64) wavefronts of 64 pixels x 64 channels; 256 x 64 measured best on MI355X for
-// every ResNet-50 shape (two workgroups share a CU).
-// Pipeline: one step = one tap of one channel block = 16 MFMAs per wavefront and one barrier.
+// (BM/32) x (BN/64) wavefronts of 32 pixels x 64 channels, 256 x 64 in all where that fills the chip and 128 x 64 where it does not.
+// What bounds it is the chain of a step - barrier, weights to LDS, operand reads, MFMAs - so a SIMD needs wavefronts to
+// switch between: with 64 x 64 per wavefront (four to a workgroup, a quarter fewer operand reads) it had one or two, here two
+// to four in 128 registers.  Batch 128, us (TFLOP/s) before -> now: 28 x 28 x 128 38.5 -> 34.2 (865), 14 x 14 x 256
+// 34.2 -> 31.6 (938), 7 x 7 x 512 46.2 -> 41.2 (719: 200 workgroups); batch 64: 21.1 -> 18.9, 25.5 -> 22.1, 45.2 -> 34.9.
+// Pipeline: one step = one tap of one channel block = 8 MFMAs per wavefront and one barrier.
 // Weight tiles are requested D = 4 steps ahead into a register ring and move to one of two LDS
 // buffers a step before use; the halo of the next channel block is requested at tap 0 and stored
 // after tap 8.  The operand pieces of a 16-wide step are read into one of two register sets while
@@ -51,8 +54,8 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 template <int BM, int BN, int HL>
-__global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void conv3x3_halo_kernel(ConvArgs a, int HR) {
-    constexpr int TP = 2;                         // 32-pixel tiles per wavefront (and 2 channel tiles)
+__global__ __launch_bounds__((BM / 32) * (BN / 64) * 64, BM == 256 ? 4 : 1) void conv3x3_halo_kernel(ConvArgs a, int HR) {
+    constexpr int TP = 1;                         // 32-pixel tiles per wavefront (and 2 channel tiles)
     constexpr int KB = 128;                       // bytes of input channels per step (64 bf16)
     constexpr int WM = BM / (32 * TP), WN = BN / 64, NW = WM * WN, NT = NW * 64;
     constexpr int SEGS = KB / 16;                 // 16-byte segments per row (KB bytes of channels per step)
@@ -194,9 +197,9 @@ __global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void conv3x3_halo_kerne
     };
     auto interleave = [&]() {                     // one LDS read, one MFMA, ... (2-3 % on 28x28 and 7x7 images, 1 % slower on 14x14)
 #pragma unroll
-        for (int k = 0; k < 2 + TP; ++k) {
+        for (int k = 0; k < 2 * TP; ++k) {
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, (2 * TP) / (2 + TP), 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         }
     };
 
@@ -337,32 +340,39 @@ __global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void conv3x3_halo_kerne
     }
 }
 
-static constexpr int kBM = 256, kBN = 64;       // 4 wavefronts of 64 pixels x 64 channels
-static constexpr int kNT = (kBM / 64) * (kBN / 64) * 64;
-static constexpr int kMaxW = 127;                // halo rows per thread stay within 16 loads
+static constexpr int kBN = 64;
+static constexpr int kMaxW = 127;                // halo rows per thread stay within 12 loads
 static constexpr size_t kMaxLds = 160 * 1024;
 
-static int halo_rows(const ConvArgs &a) { return kBM + 2 * a.W + 2; }
-
-static size_t smem_bytes(int HR) {
+static size_t smem_bytes(int BM, int HR) {
     const size_t tiles = 2 * (size_t)kBN * 144 + (size_t)(HR + 1) * 144;
-    const size_t stg = (size_t)(kNT / 64) * 32 * kStgPitch;
+    const size_t stg = (size_t)(BM / 32) * 32 * kStgPitch;
     return tiles > stg ? tiles : stg;
 }
 
-template <int HL>
-static hipError_t launch_one(const ConvArgs &a, int HR, hipStream_t stream) {
-    const size_t smem = smem_bytes(HR);
+// 256 pixels per workgroup, or 128 where that leaves half of the CUs without one: 98 workgroups against 196, us:
+// 12.9 -> 11.4 (28 x 28 x 128, batch 16), 21.3 -> 18.4 (14 x 14 x 256, batch 32), 40.1 -> 34.9 (7 x 7 x 512, batch 64);
+// 147 against 294 are 17.6 -> 18.2 already.  128 also for rows of 64 pixels and more, whose halo of 256 would not
+// fit the 128 registers that let two workgroups share a CU: 112 x 112 x 128, batch 8: 47 us against 51 at one workgroup to a CU.
+static int tile_pixels(const ConvArgs &a) {
+    return a.W > 63 || (((long long)a.M + 255) / 256) * (a.Cout / kBN) < 128 ? 128 : 256;
+}
+
+template <int BM, int HL>
+static hipError_t launch_one(const ConvArgs &a, hipStream_t stream) {
+    constexpr int NT = (BM / 32) * (kBN / 64) * 64;
+    const int HR = BM + 2 * a.W + 2;
+    const size_t smem = smem_bytes(BM, HR);
     static bool raised = false;                   // per instantiation
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv3x3_halo_kernel<kBM, kBN, HL>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv3x3_halo_kernel<BM, kBN, HL>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    const long long blocks = (((long long)a.M + kBM - 1) / kBM) * (a.Cout / kBN);
-    if (blocks <= 0 || blocks > 0x7FFFFFFFLL || smem > kMaxLds) return hipErrorInvalidValue;
-    conv3x3_halo_kernel<kBM, kBN, HL><<<dim3((unsigned)blocks), dim3(kNT), smem, stream>>>(a, HR);
+    const long long blocks = (((long long)a.M + BM - 1) / BM) * (a.Cout / kBN);
+    if (blocks <= 0 || blocks > 0x7FFFFFFFLL || smem > kMaxLds || HR * 8 > HL * NT) return hipErrorInvalidValue;
+    conv3x3_halo_kernel<BM, kBN, HL><<<dim3((unsigned)blocks), dim3(NT), smem, stream>>>(a, HR);
     return hipGetLastError();
 }
 
@@ -376,16 +386,23 @@ bool conv3x3_halo_applies(const ConvArgs &a) {
     if (a.P != a.H || a.Q != a.W) return false;
     if ((unsigned long long)a.M * a.Cin * 2ull >= 0xFFFFFFFFull) return false;        // x offsets
     if ((unsigned long long)a.Cout * 9ull * a.Cin * 2ull >= 0xFFFFFFFFull) return false;  // w offsets
-    return halo::smem_bytes(halo::halo_rows(a)) <= halo::kMaxLds;
+    return true;
+}
+
+const char *conv3x3_halo_kernel_name(const ConvArgs &a) {
+    return halo::tile_pixels(a) == 128 ? "conv3x3_halo bf16 128x64 (4x1 waves)" : "conv3x3_halo bf16 256x64 (8x1 waves)";
 }
 
 hipError_t launch_conv3x3_halo(const ConvArgs &a, hipStream_t stream) {
     if (conv_check(a) || !conv3x3_halo_applies(a)) return hipErrorInvalidValue;
-    const int HR = halo::halo_rows(a);
-    const int hl = (HR * 8 + halo::kNT - 1) / halo::kNT;      // 16-byte halo loads per thread
-    if (hl <= 12) return halo::launch_one<12>(a, HR, stream);
-    if (hl <= 16) return halo::launch_one<16>(a, HR, stream);
-    return hipErrorInvalidValue;
+    // 16-byte halo loads per thread: (BM + 2 W + 2) 8 / threads
+    if (halo::tile_pixels(a) == 128) {
+        if (a.W <= 31) return halo::launch_one<128, 6>(a, stream);
+        if (a.W <= 63) return halo::launch_one<128, 8>(a, stream);
+        return halo::launch_one<128, 12>(a, stream);
+    }
+    if (a.W <= 31) return halo::launch_one<256, 5>(a, stream);
+    return halo::launch_one<256, 6>(a, stream);
 }
 
 }  // namespace delta

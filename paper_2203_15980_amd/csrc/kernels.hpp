@@ -83,6 +83,7 @@ const char *gemm_nt_kernel_name(const ConvArgs &a);   // with the tile the launc
 hipError_t launch_gemm_nt(const ConvArgs &a, hipStream_t stream);
 // conv3x3_halo.hip: bf16 3x3 stride-1 kernel that keeps the input halo of a pixel tile in LDS
 bool conv3x3_halo_applies(const ConvArgs &a);
+const char *conv3x3_halo_kernel_name(const ConvArgs &a);
 hipError_t launch_conv3x3_halo(const ConvArgs &a, hipStream_t stream);
 // conv3x3_c64.hip: bf16 3x3 stride-1 64 -> 64 channels, persistent workgroups with all nine taps resident in LDS
 bool conv3x3_c64_applies(const ConvArgs &a);
