@@ -4,7 +4,7 @@
 //
 // The reduction index is the output pixel and both operands are stored pixel-major, so tiles are staged in LDS
 // as they lie in memory (pixel rows x 64 channels) and turned into MFMA operands by gfx950's transposing LDS read
-// (ds_read_b64_tr_b16; see backward.hip's 1x1 kernel for the lane layout).
+// (ds_read_b64_tr_b16; see wgrad1x1.hip for the lane layout).
 //
 // One list of padded pixels.  The images of the batch are stacked into one list of rows with ONE zero row
 // after each image, and every row gets ONE zero pixel at its end: the zero at the end of row p is also the pixel left
