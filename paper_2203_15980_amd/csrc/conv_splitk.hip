@@ -274,10 +274,14 @@ bool conv_splitk_applies(const ConvArgs &a) {
     //   2048 -> 512 (32 steps)     M = 784 [400] 20.5 | 10    1568 [784] 20.7 | 17   3136 [1568] 21.0 | 26
     //   3072 -> 768 (48 steps)     M = 196 [168] 27.9 | 8.4   784 [600] 28.4 | 18    1568 [1176] 28.6 | 30
     //   768 -> 768 (12 steps)      M = 196 [168] 10.9 | 6.0   784 [600] 11.1 | 10.6  1568 [1176] 11.2 | 15
-    //   256 -> 1024 (4 steps)      M = 196 [224] 8.6 | 4.9    784 [800] 8.7 | 7.8    1568 [1568] 8.9 | 11
+    //   256 -> 1024 (4 steps)      M = 196 [224] 8.6 | 4.9    656 [656] 8.6 | 6.6    1000 [1000] 8.7 | 7.6    1568 [1568] 8.9 | 11
+    //   448 -> 512 (7 steps)       M = 640 [320] 11 | 5.7     1280 [640] 11 | 6.8
+    //   512 -> 512 (8 steps)       M = 960 [480] 9.7 | 7.5    1040 [528] 9.8 | 9.9 (eight wavefronts to a tile: a second round)
     //   fp32 3x3 64 -> 64 (18)     M = 3136 [196] 27 | 8.0    6272 [392] 27 | 14     12544 [784] 27 | 23
     //   fp32 256 -> 64 (8)         M = 3136 [196] 15 | 7.0    6272 [392] 15 | 10     12544 [784] 15 | 18
-    return splitk::tiles_of(a) <= (steps >= 24 ? 1024 : 640);
+    // bf16 layers of three to seven steps have the tiled convolution kernel on the other side; from eight on the GEMM.
+    const long long line = steps >= 24 || (a.bf16 && steps >= 3 && steps < 8) ? 1024 : a.bf16 && steps == 8 ? 512 : 640;
+    return splitk::tiles_of(a) <= line;
 }
 
 // The 1x1 bf16 layers with a long reduction are GEMMs that gemm_nt.hip's tiles would take otherwise: same family name.
