@@ -75,8 +75,7 @@ __global__ __launch_bounds__(256, 2) void dgrad3x3_s2_kernel(Args a) {
         const uint32_t dst = lds0 + (uint32_t)(kRing + (chunk & 1) * gbytes + (32 * i + 8 * wv) * 128);
         row = row < last ? row : last;                           // past the last pixel: that pixel, never looked at
         const uint32_t off = (uint32_t)row * pitch + (uint32_t)chunk * 128u + seg;
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-                     :: "v"(off), "s"(g0), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory", "m0");
+        load_lds_b128(g0, off, dst);
     };
     const uint32_t wbase = (uint32_t)(ct * 128 + wv * 32 + (lane >> 3)) * 9u * pitch + seg;
     auto fetch_taps = [&](int chunk, int tap, int slot) {        // this wavefront's 32 channels of one tap
@@ -84,8 +83,7 @@ __global__ __launch_bounds__(256, 2) void dgrad3x3_s2_kernel(Args a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint32_t off = wbase + (uint32_t)(i * 72 + tap) * pitch + (uint32_t)chunk * 128u;
-            asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-                         :: "v"(off), "s"(a.w), "s"(__builtin_amdgcn_readfirstlane(dst + i * 1024)) : "memory", "m0");
+            load_lds_b128(a.w, off, dst + i * 1024);
         }
     };
     // direct loads complete in order: all but the newest `newer` are done

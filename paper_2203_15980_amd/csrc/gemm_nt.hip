@@ -135,21 +135,16 @@ __global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(Con
         wsrc[q] = wg + (size_t)wr * krow + piece * 16;
         wdst[q] = (uint32_t)kXBytes + (uint32_t)g * 1024u;
     }
-    // The direct loads and the waits for them are written as inline assembly: the compiler does not
-    // track what a direct load writes, the explicit waits below do.
+    // The waits for the direct loads are inline assembly as they are: the compiler does not track what a direct load writes.
     typedef __attribute__((address_space(3))) unsigned char *lptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
     const int nslices = K / kBK;
     auto fetch = [&](int t, int buf) {
         const uint32_t sb = lds0 + (uint32_t)buf * kStageBytes;
 #pragma unroll
-        for (int q = 0; q < XI; ++q)
-            asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
-                         :: "v"(xsrc[q] + (size_t)t * 128), "s"(__builtin_amdgcn_readfirstlane(sb + xdst[q])) : "memory", "m0");
+        for (int q = 0; q < XI; ++q) load_lds_b128(xsrc[q] + (size_t)t * 128, sb + xdst[q]);
 #pragma unroll
-        for (int q = 0; q < WI; ++q)
-            asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
-                         :: "v"(wsrc[q] + (size_t)t * 128), "s"(__builtin_amdgcn_readfirstlane(sb + wdst[q])) : "memory", "m0");
+        for (int q = 0; q < WI; ++q) load_lds_b128(wsrc[q] + (size_t)t * 128, sb + wdst[q]);
     };
     f32x16 acc[kTM][kTN];
 #pragma unroll

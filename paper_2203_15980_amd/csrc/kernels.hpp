@@ -37,6 +37,20 @@ inline Divisor make_divisor(uint32_t d) {
 }
 __device__ __forceinline__ int divide(int n, Divisor d) { return d.mul ? (int)(__umulhi((uint32_t)n, d.mul) >> d.shift) : n; }
 
+// 16 bytes per lane from memory straight into LDS: lane l's land at byte `lds` + 16 l, `lds` the same for the whole wavefront.  Inline
+// assembly, because the compiler does not track what a direct load writes; whoever uses it waits with s_waitcnt vmcnt
+// (direct loads complete in order).  The load reads M0, and the hardware needs one wait state between the scalar write of
+// M0 and such a load; the compiler inserts none inside an asm block, hence the s_nop.
+__device__ __forceinline__ void load_lds_b128(const unsigned char *at, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :: "v"(at), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
+}
+// The same from `off` bytes past a base that is the same for the whole wavefront.
+__device__ __forceinline__ void load_lds_b128(const unsigned char *base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
+}
+
 // The test behind every ReLU mask of the backward pass.  bf16: greater than zero <=> sign bit clear,
 // not zero and not NaN.  Returns the bits of `v` (two bf16 values) with the halves cleared whose
 // half of `m` fails it.

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(512) void wgrad1x1_kernel(Args a) {
     }
     typedef __attribute__((address_space(3))) unsigned char *lptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
-    // The loads and the waits for them are inline assembly: the compiler does not track what a direct load writes.
+    // The waits for these loads are inline assembly as they are: the compiler does not track what a direct load writes.
     auto fetch = [&](int slice, int buf) {
         const int m0 = slice * T::kPixels, last = a.M - 1 - m0;  // rows past the last pixel: that pixel
         const uint32_t sb = lds0 + (uint32_t)(buf * T::kSlice + wv * T::kGL * 1024);
@@ -94,8 +94,7 @@ __global__ __launch_bounds__(512) void wgrad1x1_kernel(Args a) {
         for (int i = 0; i < T::kGL; ++i) {
             const int row = grow[i] < last ? grow[i] : last;
             const uint32_t off = (uint32_t)(m0 + row) * (uint32_t)a.K * 2u + gseg[i];
-            asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-                         :: "v"(off), "s"(a.g), "s"(__builtin_amdgcn_readfirstlane(sb + i * 1024)) : "memory", "m0");
+            load_lds_b128(a.g, off, sb + i * 1024);
         }
         const uint32_t sx = lds0 + (uint32_t)(buf * T::kSlice + T::kG + wv * T::kXL * 1024);
 #pragma unroll
@@ -104,13 +103,9 @@ __global__ __launch_bounds__(512) void wgrad1x1_kernel(Args a) {
             if constexpr (STRIDED) {
                 const int n = divide(m, a.pq), pq = m - n * (a.P * a.Q), p = divide(pq, a.q), q = pq - p * a.Q;
                 m = (n * a.H + p * a.stride) * a.W + q * a.stride;
-                const unsigned char *at = a.x + (size_t)m * a.C * 2 + xseg[i];           // x may be 2 GiB or more
-                asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
-                             :: "v"(at), "s"(__builtin_amdgcn_readfirstlane(sx + i * 1024)) : "memory", "m0");
+                load_lds_b128(a.x + (size_t)m * a.C * 2 + xseg[i], sx + i * 1024);       // x may be 2 GiB or more
             } else {
-                const uint32_t off = (uint32_t)m * (uint32_t)a.C * 2u + xseg[i];
-                asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-                             :: "v"(off), "s"(a.x), "s"(__builtin_amdgcn_readfirstlane(sx + i * 1024)) : "memory", "m0");
+                load_lds_b128(a.x, (uint32_t)m * (uint32_t)a.C * 2u + xseg[i], sx + i * 1024);
             }
         }
     };
