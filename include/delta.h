@@ -343,7 +343,7 @@ typedef struct delta_bwd_desc {
                                   or gy_masked) and stride == 1 or a 1x1 layer.  May equal gy with no mask
                                   to apply on a 3x3 stride-2 pad-1 layer whose gradients both run at the
                                   output's resolution (bf16; if gw is set, channel counts multiples of
-                                  128): gy is then not spread out and gpre not written */
+                                  128 and at most 51 output columns): gy is then not spread out and gpre not written */
     uint32_t gx;               /* tensor id that receives dL/dx (bytes of x), or DELTA_NO_TENSOR */
     uint32_t gx_add;           /* resident tensor (bytes of x) added to dL/dx before it is stored: the
                                   contribution of another consumer of x; or DELTA_NO_TENSOR */

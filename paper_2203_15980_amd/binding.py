@@ -15,6 +15,7 @@ DTYPE_F32, DTYPE_BF16 = 0, 1
 SYNC_D2H, SYNC_H2D, SYNC_COMPUTE, SYNC_ALL = 1, 2, 4, 7
 DIR_D2H, DIR_H2D, DIR_BOTH = 0, 1, 2
 NO_TENSOR = 0xFFFFFFFF
+WGRAD_S2_MAX_Q = 51     # output columns up to which a 3x3 stride-2 layer's weight gradient runs at the output's resolution
 OP_CONV, OP_MAXPOOL, OP_AVGPOOL, OP_SOFTMAX_CE, OP_ATTENTION, OP_LAYERNORM = 0, 1, 2, 3, 4, 5
 OP_BATCHNORM, OP_RELU, OP_ADD = 6, 7, 8
 ACT_NONE, ACT_RELU, ACT_GELU = 0, 1, 2

@@ -471,10 +471,11 @@ hipError_t launch_wgrad(const ConvArgs &a, const void *g, float *gw, void *works
     return hipGetLastError();
 }
 
-// The weight gradient of a 3x3 stride-2 pad-1 bf16 layer from dL/d(pre-activation) at the OUTPUT's resolution.
+// The weight gradient of a 3x3 stride-2 pad-1 bf16 layer from dL/d(pre-activation) at the OUTPUT's resolution: where the one-launch
+// kernel has a plan, that is up to 51 output columns.  Wider layers spread the gradient out and take the stride-1 kernel.
 bool wgrad_s2_applies(const ConvArgs &a) {
     return a.bf16 && a.R == 3 && a.S == 3 && a.stride == 2 && a.pad == 1 && a.Cin % 128 == 0 && a.Cout % 128 == 0 &&
-           a.P == (a.H - 1) / 2 + 1 && a.Q == (a.W - 1) / 2 + 1;
+           a.P == (a.H - 1) / 2 + 1 && a.Q == (a.W - 1) / 2 + 1 && !wgrad3x3_check(a);
 }
 
 size_t wgrad_s2_workspace_bytes(const ConvArgs &a) {

@@ -1293,7 +1293,7 @@ bool class_dgrad(const delta_bwd_desc &D) {
 }
 
 // The same layers' weight gradient by parity class (delta::launch_wgrad_s2): bf16, channel counts that
-// are multiples of 128.  `fo`: the forward layer's own arguments.
+// are multiples of 128, at most 51 output columns.  `fo`: the forward layer's own arguments.
 bool class_layer(const delta_bwd_desc &D) {
     const delta_layer_desc &L = D.fwd;
     return L.stride == 2 && L.R == 3 && L.S == 3 && L.pad == 1 && (!L.relu || D.gy_masked);

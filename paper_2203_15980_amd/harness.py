@@ -220,10 +220,10 @@ class Net:
 
     def _by_class(self, l):
         """A 3x3 stride-2 layer whose incoming gradient needs no mask of its own and whose channel
-        counts the class-wise weight gradient takes: both gradients run at the output's resolution
+        counts and width the class-wise weight gradient takes: both gradients run at the output's resolution
         (by parity class of the input pixels), so no zero-filled copy of dL/dy is needed."""
         return (l.kind == "conv" and l.stride == 2 and l.R == 3 and l.S == 3 and l.pad == 1 and self.dtype == "bf16" and
-                l.Cin % 128 == 0 and l.Cout % 128 == 0 and (not l.relu or self._gy_masked(l)))
+                l.Cin % 128 == 0 and l.Cout % 128 == 0 and l.Q <= B.WGRAD_S2_MAX_Q and (not l.relu or self._gy_masked(l)))
 
     def _own_gpre(self, l):
         if l.kind != "conv":
@@ -693,7 +693,8 @@ class OpNet:
     def _dilated(self, name):
         """A strided convolution wider than 1x1 (the stem aside, which has no data gradient)."""
         l = self.op_layer[name]
-        by_class = l.stride == 2 and l.R == 3 and l.S == 3 and l.pad == 1 and l.Cin % 128 == 0 and l.Cout % 128 == 0
+        by_class = (l.stride == 2 and l.R == 3 and l.S == 3 and l.pad == 1 and l.Cin % 128 == 0 and l.Cout % 128 == 0 and
+                    l.Q <= B.WGRAD_S2_MAX_Q)
         return self._kind(name) == "conv" and l.stride > 1 and l.R > 1 and self.op_inputs[name][0] != "x0" and not by_class
 
     def enable_backward(self):

@@ -68,3 +68,79 @@ def test_weight_gradient_matches_float64(torch_mod, case):  # noqa: F811
     print("  err %.2e" % err, flush=True)
     assert err <= 1e-5 and np.array_equal(got[0], got[1])
     d.close()
+
+
+@pytest.mark.parametrize("W", [102, 103, 112, 125, 126])
+def test_strided_rows_wider_than_a_chunk(torch_mod, W):  # noqa: F811
+    """A 3x3 stride-2 layer's rows of more than 51 output columns (width 103 and up) do not fit the one-launch kernel's chunk: gpre = gy is
+    then refused before anything is launched, and a separate gpre at the input's resolution takes the stride-1 kernel up to
+    its own width, 125.  Same bound as above."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    from paper_2203_15980_amd import binding
+    N, H, C = 2, 5, 128
+    P, Q = (H - 1) // 2 + 1, (W - 1) // 2 + 1
+    print("W", W, "Q", Q, flush=True)
+    x, gy = _bits(94, 4, (N, H, W, C)), _bits(94, 5, (N, P, Q, C))
+    wide = N * H * W * C * 2
+    d, put, get = _small_ctx(torch, [x.nbytes, gy.nbytes, gy.nbytes, wide])
+    put(0, x)
+    put(2, gy)
+    w, one = torch.zeros(C * 9 * C, dtype=torch.bfloat16, device="cuda:0"), torch.ones(C, device="cuda:0")
+    fwd = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=one.data_ptr(), shift=one.data_ptr(), N=N, H=H,
+                       W=W, Cin=C, Cout=C, R=3, S=3, stride=2, pad=1, relu=0)
+    ws = torch.full((max(d.backward_workspace(fwd), 256),), 255, dtype=torch.uint8, device="cuda:0")
+    xf, gf = on.to_f64(x, "bf16"), on.to_f64(gy, "bf16")
+    xp = np.pad(xf, ((0, 0), (1, 1), (1, 1), (0, 0)))
+    ref = np.empty((C, 3, 3, C))
+    for r in range(3):
+        for s in range(3):
+            ref[:, r, s] = np.tensordot(gf, xp[:, r:r + 2 * (P - 1) + 1:2, s:s + 2 * (Q - 1) + 1:2], ((0, 1, 2), (0, 1, 2)))
+    for gpre, takes in ((2, Q <= binding.WGRAD_S2_MAX_Q), (3, W <= 125)):
+        gw = torch.full((C, 3, 3, C), float("nan"), device="cuda:0")
+        desc = dl.BwdDesc(fwd=fwd, gy=2, gpre=gpre, gx=dl.NO_TENSOR, gx_add=dl.NO_TENSOR, gw=gw.data_ptr(), workspace=ws.data_ptr(),
+                          workspace_bytes=ws.numel())
+        if not takes:
+            with pytest.raises(dl.DeltaError) as e:
+                d.backward_segment([desc])
+            assert e.value.status == dl.ERR_INVALID
+            continue
+        d.backward_segment([desc])
+        d.backward_join()
+        d.sync()
+        err = float(np.max(np.abs(gw.cpu().numpy() - ref)) / np.max(np.abs(ref)))
+        print("  gpre %d err %.2e" % (gpre, err), flush=True)
+        assert err <= 1e-5
+    d.close()
+
+
+@pytest.mark.parametrize("W", [102, 112])
+def test_network_takes_the_route_its_width_allows(torch_mod, W):  # noqa: F811
+    """A strided 3x3 layer between two 1x1 layers: 51 output columns run at the output's resolution, 56 are spread out."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    from paper_2203_15980_amd.harness import Net
+    layers = [synth.LayerSpec("a", "conv", "x0", None, "a", 1, 4, W, 128, 128, index=1),
+              synth.LayerSpec("b", "conv", "a", None, "b", 1, 4, W, 128, 128, 3, 3, 2, 1, index=2),
+              synth.LayerSpec("c", "conv", "b", None, "c", 1, 2, W // 2, 128, 128, index=3)]
+    g = synth.fused_graph(layers, "bf16")
+    d = dl.Delta(torch.empty(32 << 20, dtype=torch.uint8, device="cuda:0"), torch.cuda.current_stream().cuda_stream)
+    d.bind([t["bytes"] for t in g.tensors])
+    net = Net(d, layers, "bf16", synth.master_seed(2))
+    net.enable_backward(input_gradient=True)
+    net.forward()
+    net.backward(keep=True)
+    d.sync()
+    trace = {t[0]: t for t in net.bwd_trace}
+    _, gy_name, gpre_name, gx_name, _, masks_gx = trace["b"]
+    assert (gpre_name == gy_name) == (W == 102)
+    l, p = layers[1], net.params_np["b"]
+    xa = net.read("a")
+    ref_gx, ref_gw, _ = on.conv_bn_act_bwd(xa, p["w"], p, net.read("b"), net.read(gy_name), stride=2, pad=1, relu=True, dtype="bf16")
+    if masks_gx:
+        ref_gx = np.where(on.to_f64(xa, "bf16") > 0, ref_gx, 0.0)
+    ex = float(np.max(np.abs(on.to_f64(net.read(gx_name), "bf16") - ref_gx)) / np.max(np.abs(ref_gx)))
+    ew = float(np.max(np.abs(net.gw["b"].cpu().numpy().reshape(ref_gw.shape) - ref_gw)) / np.max(np.abs(ref_gw)))
+    print("  gx %.2e gw %.2e" % (ex, ew), flush=True)
+    assert ex <= 2e-2 and ew <= 2e-4             # the bounds of the layer-by-layer comparisons (weights rounded once more)
+    d.close()
