@@ -423,10 +423,12 @@ hipError_t launch_avgpool(const PoolArgs &a, hipStream_t stream) {
 
 // ------------------------------------------------------------------------------ loss
 // Mean over images of logsumexp(z_i) - z_i[label_i].  One workgroup of 16 wavefronts: the result is one float,
-// and what the launch costs is the latency of its loads and reductions.  Where a row is whole 16-byte pieces (bf16,
-// classes a multiple of 8, at most 1024) a wavefront holds FOUR images at once, two 16-byte pieces per lane and image:
-// eight loads in flight, and the four images' reduction trees interleave (128 images of 1000 classes: 45 -> 14 us;
-// it was two images in 2-byte loads).  Otherwise a lane owns classes lane, lane + 64, ... and re-reads them.  Fixed
+// and what the launch costs is the latency of its loads and reductions.  PIECES (bf16 rows of whole 16-byte pieces, up to 1024
+// classes): a wavefront holds four images at once, two pieces per lane and image, so that each logit is read once and the
+// images' reduction trees interleave.  ELEMENTS (other rows of 257 to 1024 classes): a lane holds classes lane, lane + 64, ...
+// of two images (four spill).  REREAD (up to 256 classes, or more than 1024): an image at a time, the row read twice.  128 images,
+// us, REREAD | ELEMENTS: fp32 127 classes 9.9 | 13, 250 12.8 | 12.9, 310 14.5 | 13.0, 1000 34 | 13; bf16 127 10.2 | 14.1,
+// 250 13.6 | 14.0, 310 15.4 | 14.0, 1001 35 | 14; bf16 1000 in pieces 12.5.  Fixed
 // reduction trees and a fixed image -> wavefront map: the result does not depend on timing.
 // A label outside [0, classes) makes the result NaN, so that it cannot pass unnoticed.
 template <bool BF16>
@@ -435,10 +437,12 @@ __device__ __forceinline__ float logit_at(const void *logits, size_t idx) {
                 : static_cast<const float *>(logits)[idx];
 }
 
-template <bool BF16, bool HELD>
+enum LossForm { REREAD, ELEMENTS, PIECES };
+
+template <bool BF16, LossForm FORM>
 __global__ __launch_bounds__(1024) void softmax_ce_kernel(const void *logits, const long long *labels, int N,
                                                           int classes, float *out) {
-    constexpr int WAVES = 16, IMGS = 4;
+    constexpr int WAVES = 16, IMGS = FORM == PIECES ? 4 : 2;
     __shared__ float part[WAVES];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     float total = 0.f;
@@ -446,23 +450,34 @@ __global__ __launch_bounds__(1024) void softmax_ce_kernel(const void *logits, co
         const long long lab = labels[i];
         return lab >= 0 && lab < classes ? logit_at<BF16>(logits, (size_t)i * classes + lab) : __builtin_nanf("");
     };
-    if constexpr (HELD) {
+    if constexpr (FORM != REREAD) {
         const int pieces = classes / 8;
+        auto live = [&](int k) { return FORM == PIECES ? lane + 64 * (k >> 3) < pieces : lane + 64 * k < classes; };
         for (int i0 = wv * IMGS; i0 < N; i0 += WAVES * IMGS) {
             u32x4_s v[IMGS][2];
+            float held[IMGS][16];
             float zl[IMGS], mx[IMGS], se[IMGS];
 #pragma unroll
             for (int u = 0; u < IMGS; ++u) {
                 const int i = i0 + u < N ? i0 + u : N - 1;        // past the last image: read again, not counted
-                const u32x4_s *z = reinterpret_cast<const u32x4_s *>(static_cast<const uint16_t *>(logits) + (size_t)i * classes);
+                if constexpr (FORM == PIECES) {
+                    const u32x4_s *z = reinterpret_cast<const u32x4_s *>(static_cast<const uint16_t *>(logits) + (size_t)i * classes);
 #pragma unroll
-                for (int p = 0; p < 2; ++p) v[u][p] = z[lane + 64 * p < pieces ? lane + 64 * p : 0];
+                    for (int p = 0; p < 2; ++p) v[u][p] = z[lane + 64 * p < pieces ? lane + 64 * p : 0];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) held[u][k] = logit_at<BF16>(logits, (size_t)i * classes + (live(k) ? lane + 64 * k : 0));
+                }
                 zl[u] = logit_of_label(i);
             }
             auto at = [&](int u, int k) {                        // value k of the lane's 16, -inf past the row
-                const u32x4_s q = v[u][k >> 3];
-                const uint32_t w = q[(k & 7) >> 1];
-                return lane + 64 * (k >> 3) < pieces ? ((k & 1) ? bhi(w) : blo(w)) : -INFINITY;
+                if constexpr (FORM == PIECES) {
+                    const u32x4_s q = v[u][k >> 3];
+                    const uint32_t w = q[(k & 7) >> 1];
+                    return live(k) ? ((k & 1) ? bhi(w) : blo(w)) : -INFINITY;
+                } else {
+                    return live(k) ? held[u][k] : -INFINITY;
+                }
             };
 #pragma unroll
             for (int u = 0; u < IMGS; ++u) {
@@ -478,7 +493,7 @@ __global__ __launch_bounds__(1024) void softmax_ce_kernel(const void *logits, co
             for (int u = 0; u < IMGS; ++u) {
                 se[u] = 0.f;
 #pragma unroll
-                for (int k = 0; k < 16; ++k) se[u] += lane + 64 * (k >> 3) < pieces ? __expf(at(u, k) - mx[u]) : 0.f;
+                for (int k = 0; k < 16; ++k) se[u] += live(k) ? __expf(at(u, k) - mx[u]) : 0.f;
             }
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1)
@@ -515,10 +530,11 @@ hipError_t launch_softmax_ce(const void *logits, const void *labels, int N, int 
                              hipStream_t stream) {
     if (!logits || !labels || !out || N <= 0 || classes <= 0) return hipErrorInvalidValue;
     const auto *lab = static_cast<const long long *>(labels);
-    if (bf16 && classes % 8 == 0 && classes <= 1024 && !((uintptr_t)logits & 15))
-        softmax_ce_kernel<true, true><<<dim3(1), dim3(1024), 0, stream>>>(logits, lab, N, classes, out);
-    else if (bf16) softmax_ce_kernel<true, false><<<dim3(1), dim3(1024), 0, stream>>>(logits, lab, N, classes, out);
-    else softmax_ce_kernel<false, false><<<dim3(1), dim3(1024), 0, stream>>>(logits, lab, N, classes, out);
+    auto run = [&](auto kernel) { kernel<<<dim3(1), dim3(1024), 0, stream>>>(logits, lab, N, classes, out); };
+    const bool held = classes > 256 && classes <= 1024;
+    if (bf16 && classes % 8 == 0 && classes <= 1024 && !((uintptr_t)logits & 15)) run(softmax_ce_kernel<true, PIECES>);
+    else if (bf16) held ? run(softmax_ce_kernel<true, ELEMENTS>) : run(softmax_ce_kernel<true, REREAD>);
+    else held ? run(softmax_ce_kernel<false, ELEMENTS>) : run(softmax_ce_kernel<false, REREAD>);
     return hipGetLastError();
 }
 

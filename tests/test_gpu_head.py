@@ -60,6 +60,38 @@ def test_classifier_gradients_and_loss_at_tile_edges(torch_mod, N, Cin, Cout):  
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,classes", [(1, 1), (33, 256), (33, 257), (1, 1000), (31, 1001), (65, 1024), (3, 1025), (34, 520)])
+def test_loss_forms_match_float64(torch_mod, dtype, N, classes):  # noqa: F811
+    """Every form of the loss: class counts on both sides of the lines at 256 and 1024, whole 16-byte rows and not, image counts
+    that leave wavefronts and their last rounds partly empty.  A label out of range makes the result NaN."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    z = synth.normal(10, 1, N * classes).astype(np.float32).reshape(N, classes) * 3
+    z = z if dtype == "f32" else synth.f32_to_bf16_bits(z).reshape(N, classes)
+    labels = synth.make_labels(10, N, classes)
+    d, put, get = _small_ctx(torch, [z.nbytes, N * 8, 4])
+    put(0, z)
+    put(1, labels)
+    loss = dl.LayerDesc(x=0, res=1, y=2, dtype=dl.DTYPE_F32 if dtype == "f32" else dl.DTYPE_BF16, N=N, H=1, W=1, Cin=classes, Cout=1, R=1,
+                        S=1, stride=1, pad=0, relu=0, op=dl.OP_SOFTMAX_CE)
+    d.recompute_segment([loss])
+    d.sync()
+    got = float(get(2, (1,), np.float32)[0])
+    zf = on.to_f64(z, dtype)
+    top = zf.max(1)
+    ref = float(np.mean(top + np.log(np.exp(zf - top[:, None]).sum(1)) - zf[np.arange(N), labels]))
+    print("%s N %d classes %d: %.8g %.8g" % (dtype, N, classes, got, ref), flush=True)
+    assert abs(got - ref) <= 1e-5 * max(abs(ref), 1.0)
+    bad = labels.copy()
+    bad[N // 2] = classes
+    d.arena[d.tensor_ptr(1) - d.arena.data_ptr():][:N * 8].copy_(_dev(torch, bad.view(np.uint8)))
+    d.recompute_segment([loss])
+    d.sync()
+    assert np.isnan(get(2, (1,), np.float32)[0])
+    d.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,H,W,C", [(1, 1, 1, 8), (3, 1, 7, 40), (5, 7, 7, 264), (2, 9, 3, 2048)])
 def test_average_pool_at_tile_edges(torch_mod, dtype, N, H, W, C):  # noqa: F811
     torch = torch_mod
