@@ -336,16 +336,18 @@ __global__ __launch_bounds__(256) void maxpool_kernel(PoolArgs a, long long tota
     *reinterpret_cast<u32x4_s *>(static_cast<unsigned char *>(a.y) + (size_t)idx * 16) = o;
 }
 
-// Global average.  A workgroup takes 64 (image, 16 bytes of channels) pairs, one per lane; its G wavefronts split the
-// pixels (wavefront g takes pixels g, g + G, ...), four of a wavefront's loads are in flight, and the G fp32 sums are
+// Global average.  G wavefronts of a workgroup's eight share 64 (image, 16 bytes of channels) pairs, one per lane: wavefront g
+// takes pixels g, g + G, ..., four of its loads are in flight, and the G fp32 sums are
 // added in the order of g through LDS.  HBM-bound: 128 x 7 x 7 x 2048 is 25.7 MB; with one thread per pair walking all
-// pixels the launch was 512 wavefronts and 17 us, with eight per pair 6.6.
+// pixels the launch was 512 wavefronts and 17 us, with eight per pair 6.6.  Up to 16 pixels a wavefront has too little to do for
+// that: one per pair.  bf16, us, one | eight wavefronts: 2^20 pairs of 1 pixel 6.1 | 17.4, 4 pixels 14.0 | 22.0, 9 pixels
+// 25.6 | 29.7, 16 pixels 42.8 | 45.8, 25 pixels 80 | 75, 49 pixels 151 | 141; 2^16 pairs of 9 pixels 5.0 | 4.6 (both the launch), 25
+// pixels 6.0 | 5.0.
 template <bool BF16, int G>
-__global__ __launch_bounds__(G * 64) void avgpool_kernel(PoolArgs a, long long total) {
+__global__ __launch_bounds__(512) void avgpool_kernel(PoolArgs a, long long total) {
     constexpr int CPT = BF16 ? 8 : 4;
-    __shared__ float part[G][64][CPT + 1];
-    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const long long idx = (long long)blockIdx.x * 64 + lane;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = wv % G;
+    const long long idx = ((long long)blockIdx.x * (8 / G) + wv / G) * 64 + lane;
     const int chunks = a.C / CPT, hw = a.H * a.W;
     float s[CPT];
 #pragma unroll
@@ -365,14 +367,18 @@ __global__ __launch_bounds__(G * 64) void avgpool_kernel(PoolArgs a, long long t
             }
         }
     }
+    if constexpr (G > 1) {
+        __shared__ float part[8][64][CPT + 1];
 #pragma unroll
-    for (int e = 0; e < CPT; ++e) part[g][lane][e] = s[e];
-    __syncthreads();
-    if (g != 0 || idx >= total) return;
+        for (int e = 0; e < CPT; ++e) part[wv][lane][e] = s[e];
+        __syncthreads();
+        if (g != 0) return;
 #pragma unroll
-    for (int k = 1; k < G; ++k)
+        for (int k = 1; k < G; ++k)
 #pragma unroll
-        for (int e = 0; e < CPT; ++e) s[e] += part[k][lane][e];
+            for (int e = 0; e < CPT; ++e) s[e] += part[wv + k][lane][e];
+    }
+    if (idx >= total) return;
     const float inv = 1.0f / (float)hw;
     u32x4_s o;
     if constexpr (BF16) {
@@ -414,11 +420,14 @@ hipError_t launch_maxpool(const PoolArgs &a, hipStream_t stream) {
 hipError_t launch_avgpool(const PoolArgs &a, hipStream_t stream) {
     if (pool_check(a, true)) return hipErrorInvalidValue;
     const long long total = (long long)a.N * (a.C / (a.bf16 ? 8 : 4));
-    const long long blocks = (total + 63) / 64;
-    if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    if (a.bf16) avgpool_kernel<true, 8><<<dim3((unsigned)blocks), dim3(512), 0, stream>>>(a, total);
-    else avgpool_kernel<false, 8><<<dim3((unsigned)blocks), dim3(512), 0, stream>>>(a, total);
-    return hipGetLastError();
+    auto run = [&](auto kernel, int G) {
+        const long long pairs = 64 * (8 / G), blocks = (total + pairs - 1) / pairs;
+        if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+        kernel<<<dim3((unsigned)blocks), dim3(512), 0, stream>>>(a, total);
+        return hipGetLastError();
+    };
+    if ((long long)a.H * a.W <= 16) return a.bf16 ? run(avgpool_kernel<true, 1>, 1) : run(avgpool_kernel<false, 1>, 1);
+    return a.bf16 ? run(avgpool_kernel<true, 8>, 8) : run(avgpool_kernel<false, 8>, 8);
 }
 
 // ------------------------------------------------------------------------------ loss

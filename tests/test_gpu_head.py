@@ -92,7 +92,7 @@ def test_loss_forms_match_float64(torch_mod, dtype, N, classes):  # noqa: F811
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("N,H,W,C", [(1, 1, 1, 8), (3, 1, 7, 40), (5, 7, 7, 264), (2, 9, 3, 2048)])
+@pytest.mark.parametrize("N,H,W,C", [(1, 1, 1, 8), (3, 1, 7, 40), (5, 7, 7, 264), (2, 9, 3, 2048), (513, 1, 1, 8), (130, 4, 4, 40), (19, 1, 17, 264)])
 def test_average_pool_at_tile_edges(torch_mod, dtype, N, H, W, C):  # noqa: F811
     torch = torch_mod
     import paper_2203_15980_amd as dl
