@@ -284,10 +284,7 @@ bool conv_splitk_applies(const ConvArgs &a) {
     return splitk::tiles_of(a) <= line;
 }
 
-// The 1x1 bf16 layers with a long reduction are GEMMs that gemm_nt.hip's tiles would take otherwise: same family name.
 const char *conv_splitk_kernel_name(const ConvArgs &a) {
-    if (a.bf16 && a.R == 1 && a.S == 1 && a.Cin >= 512 && a.Cout >= 128)
-        return "gemm_nt bf16 32x32 (conv_splitk: reduction split over the workgroup's wavefronts)";
     return a.bf16 ? "conv_splitk bf16 32x32 (reduction split over the workgroup's wavefronts)"
                   : "conv_splitk f32 32x32 (reduction split over the workgroup's wavefronts)";
 }

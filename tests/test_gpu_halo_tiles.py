@@ -1,6 +1,5 @@
 """The 3x3 layers that keep their input halo in LDS, at both tile heights and every width at which the rule or the number
-of halo loads changes, against the CPU oracle with the bound derived beside the helper
-("past": beyond the sizes that the split-reduction kernel takes, which the helper asserts)."""
+of halo loads changes, against the CPU oracle with the bound derived beside the helper, which also asserts the kernel."""
 import pytest
 
 import test_gpu_small_problems as layers
@@ -8,16 +7,17 @@ from test_gpu_parity import torch_mod  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
+HIGH, LOW = {"bf16": "conv3x3_halo bf16 256x64"}, {"bf16": "conv3x3_halo bf16 128x64"}
 CASES = [
     # name           N  H    W   Cin Cout R st relu  res
-    ("past_256_w31",      1, 133, 31,  64, 512, 3, 1, True, False),      # 17 x 8 workgroups of 256 pixels, the last with 27
-    ("past_256_w32",      2, 64,  32, 128, 512, 3, 1, False, True),      # 16 x 8: the first that takes 256; two channel blocks
-    ("past_256_w63",      1, 66,  63,  64, 512, 3, 1, True, True),
-    ("past_128_w31",      1, 83,  31,  64, 256, 3, 1, True, True),       # 21 x 4 workgroups of 128 pixels
-    ("past_128_w32",      9, 9,   32, 128, 256, 3, 1, True, False),
-    ("past_128_w63",      1, 41,  63,  64, 256, 3, 1, False, False),
-    ("past_wide_w64",     1, 65,  64,  64, 512, 3, 1, True, False),      # enough pixels for 256, rows too long for it
-    ("past_wide_w127",    1, 33, 127,  64, 512, 3, 1, True, True),       # the longest halo
+    ("past_256_w31",      1, 133, 31,  64, 512, 3, 1, True, False, HIGH),      # 17 x 8 workgroups of 256 pixels, the last with 27
+    ("past_256_w32",      2, 64,  32, 128, 512, 3, 1, False, True, HIGH),      # 16 x 8: the first that takes 256; two channel blocks
+    ("past_256_w63",      1, 66,  63,  64, 512, 3, 1, True, True, HIGH),
+    ("past_128_w31",      1, 83,  31,  64, 256, 3, 1, True, True, LOW),       # 21 x 4 workgroups of 128 pixels
+    ("past_128_w32",      9, 9,   32, 128, 256, 3, 1, True, False, LOW),
+    ("past_128_w63",      1, 41,  63,  64, 256, 3, 1, False, False, LOW),
+    ("past_wide_w64",     1, 65,  64,  64, 512, 3, 1, True, False, LOW),      # enough pixels for 256, rows too long for it
+    ("past_wide_w127",    1, 33, 127,  64, 512, 3, 1, True, True, LOW),       # the longest halo
 ]
 
 

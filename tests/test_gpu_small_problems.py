@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-5, "bf16": 4e-3}
 
 CASES = [
-    # name              N   H   W  Cin Cout R st relu  res
+    # name              N   H   W  Cin Cout R st relu  res  (kernel, where it is not the split-reduction one: by type)
     ("one_tile",        1,  4,  8, 128,  32, 1, 1, True, False),     # exactly 32 pixels x 32 channels, one or two steps
     ("ragged_tile",     1,  3, 11, 192,  40, 1, 1, True, True),      # 33 pixels, 40 channels
     ("one_pixel",       1,  1,  1, 256,   8, 3, 1, False, False),    # only the centre tap; 8 channels
@@ -26,8 +26,8 @@ CASES = [
     ("long",            1,  7,  9, 256,  64, 3, 1, True, True),
     ("5x5",             1,  6,  5,  64,  72, 5, 1, True, False),
     ("at_the_line",     1, 64, 80, 128, 128, 1, 1, True, False),     # 160 x 4 tiles: the last of the short reductions
-    ("past_the_line",   1, 64, 81, 128, 128, 1, 1, True, False),     # 162 x 4: the kernel for larger layers
-    ("halo_past_the_line", 3, 75, 73, 192, 64, 3, 1, True, True),    # 514 x 2 tiles of 27 steps, ragged, odd width
+    ("past_the_line",   1, 64, 81, 128, 128, 1, 1, True, False, {"f32": "conv_igemm f32", "bf16": "conv1x1_stream"}),    # 162 x 4: the kernel for larger layers
+    ("halo_past_the_line", 3, 75, 73, 192, 64, 3, 1, True, True, {"f32": "conv_igemm f32", "bf16": "conv3x3_halo bf16 128x64"}),    # 514 x 2 tiles of 27 steps, ragged, odd width
 ]
 
 
@@ -36,7 +36,8 @@ CASES = [
 def test_few_tile_layers_match_oracle(torch_mod, dtype, case):  # noqa: F811
     torch = torch_mod
     import paper_2203_15980_amd as dl
-    name, N, H, W, Cin, Cout, R, stride, relu, res = case
+    name, N, H, W, Cin, Cout, R, stride, relu, res = case[:10]
+    kernel = case[10][dtype] if len(case) > 10 else "conv_splitk"
     print("case", name, dtype, flush=True)
     l = single(name, N, H, W, Cin, Cout, R, stride, R // 2, relu, res)
     es, master = (4 if dtype == "f32" else 2), 79
@@ -63,7 +64,7 @@ def test_few_tile_layers_match_oracle(torch_mod, dtype, case):  # noqa: F811
     desc = dl.LayerDesc(x=0, res=1 if res else dl.NO_TENSOR, y=2, dtype=dl.DTYPE_F32 if dtype == "f32" else dl.DTYPE_BF16,
                         w=w.data_ptr(), scale=scale.data_ptr(), shift=shift.data_ptr(), N=N, H=H, W=W, Cin=Cin, Cout=Cout, R=R,
                         S=R, stride=stride, pad=R // 2, relu=1 if relu else 0)
-    assert ("32x32" in d.layer_kernel(desc)) == ("past" not in name), d.layer_kernel(desc)
+    assert kernel in d.layer_kernel(desc), d.layer_kernel(desc)
     got = []
     for _ in range(2):                                                          # the same bits both times
         d.recompute_segment([desc])

@@ -113,11 +113,16 @@ def test_layernorm_matches_oracle(torch_mod, rows, C):
 
 @pytest.mark.parametrize("case", [("gelu", 2, 70, 128, 192, "gelu", False), ("res", 1, 45, 768, 64, None, True),
                                   ("plain", 3, 33, 64, 256, None, False),
-                                  # few tiles and a long reduction: the GEMM kernel's 128 x 128 tile with four slice
-                                  # buffers (8, 16 and 20 slices; one tile, ragged rows, ragged channels)
-                                  ("gemm4_ffn2", 1, 40, 512, 128, None, True),
-                                  ("gemm4_ragged", 3, 211, 1024, 200, "gelu", True),
-                                  ("gemm4_short_tail", 1, 300, 1280, 136, "relu", False),
+                                  # few tiles and a long reduction: the split-reduction kernel (8, 16 and 20 steps of 64;
+                                  # ragged rows, ragged channels)
+                                  ("split_ffn2", 1, 40, 512, 128, None, True),
+                                  ("split_ragged", 3, 211, 1024, 200, "gelu", True),
+                                  ("split_short_tail", 1, 300, 1280, 136, "relu", False),
+                                  # the same beyond its range: the GEMM kernel's 128 x 128 tile with four slice buffers
+                                  # (33, 48 and 66 tiles; ragged rows, ragged channels)
+                                  ("gemm4_ffn2", 1, 4130, 512, 128, None, True),
+                                  ("gemm4_ragged", 3, 1003, 1024, 200, "gelu", True),
+                                  ("gemm4_short_tail", 1, 4101, 1280, 136, "relu", False),
                                   # large enough for the 256 x 256-tiled GEMM kernel; ragged rows and channels
                                   ("gemm_gelu", 1, 8465, 256, 1024, "gelu", False),
                                   ("gemm_res_ragged_n", 1, 8300, 768, 776, None, True),
@@ -141,7 +146,9 @@ def test_linear_layers_match_oracle(torch_mod, case):
     desc = dl.LayerDesc(x=0, res=1 if has_res else dl.NO_TENSOR, y=2, dtype=dl.DTYPE_BF16, w=wd.data_ptr(),
                         scale=ones.data_ptr(), shift=bd.data_ptr(), N=N, H=S, W=1, Cin=Cin, Cout=Cout, R=1, S=1,
                         stride=1, pad=0, relu={"gelu": dl.ACT_GELU, "relu": dl.ACT_RELU, None: dl.ACT_NONE}[act], op=dl.OP_CONV)
-    assert ("gemm_nt" in d.layer_kernel(desc)) == name.startswith("gemm"), d.layer_kernel(desc)
+    kernel = d.layer_kernel(desc)
+    assert ("gemm_nt" in kernel) == name.startswith("gemm") and ("four slice buffers" in kernel) == name.startswith("gemm4"), kernel
+    assert "conv_splitk" in kernel or not name.startswith("split"), kernel
     d.recompute_segment([desc])
     d.sync()
     got = ot.to_f64(get(2, (M, Cout)), "bf16")
