@@ -307,8 +307,8 @@ delta_status delta_set_skip_copies(delta_ctx *ctx, int32_t skip);
  *     gx   = conv^T(gpre * scale, w) (+ gx_add)           - dL/dx
  *     gw[k,r,s,c] = scale_k * sum_m gpre[m,k] * x[m+(r,s),c]   - dL/dw, fp32
  * Supported: DELTA_OP_CONV with 2*pad == R-1 == S-1; gx for bf16 and fp32; gw with R in {1,3}: bf16
- * with channel counts that are multiples of 64 (MFMA kernel), fp32 with any channel counts the
- * forward accepts (a plain fp32 kernel, one fixed summation order, no workspace bytes).  A layer with stride > 1 (no residual allowed)
+ * with channel counts that are multiples of 64 (MFMA kernel), fp32 with channel counts that
+ * are multiples of 16 (fp32 products and sums, one fixed summation order, no workspace bytes).  A layer with stride > 1 (no residual allowed)
  * and a window larger than 1x1 gets gpre at the INPUT's resolution: gpre[n, stride*p, stride*q, :] =
  * gy[n,p,q,:] * [y > 0], zero elsewhere, so that both gradients are stride-1 operations on it
  * (stride^2 times the arithmetic).  A 1x1 layer with stride > 1 only reads the input pixels
@@ -374,8 +374,8 @@ delta_status delta_backward_workspace(delta_ctx *ctx, const delta_layer_desc *la
 /* Runs the descriptors in order on the compute stream.  Everything is validated before the first
  * launch.  Output tensors are allocated from the arena when not resident (DELTA_ERR_OOM_ARENA);
  * a non-resident input is DELTA_ERR_STATE.
- * Weight gradients of convolutions and of the classifier (gw) are the exception to "on the compute stream": nothing later
- * in the backward pass reads them, so they run on a stream of the library's own, beside the
+ * Weight gradients of convolutions and of the classifier (gw) of 1 GFLOP and more are the exception to "on the compute
+ * stream": nothing later in the backward pass reads them, so they run on a stream of the library's own, beside the
  * data-gradient chain, each after the launches that produce its inputs.  The arena accounts for
  * these readers when a tensor is released or rewritten.  The gw buffers and the workspace are the
  * caller's: their contents are ordered for later work on the compute stream only after
@@ -391,6 +391,9 @@ delta_status delta_backward_join(delta_ctx *ctx);
  * the descriptor exactly as delta_recompute_segment does; launches nothing.  Needs a context
  * with an arena and the tensors bound (delta_bind), since the descriptor names tensor ids. */
 delta_status delta_layer_kernel(delta_ctx *ctx, const delta_layer_desc *layer, char *out, uint64_t cap);
+/* The same for the backward of a layer: "gx: <data gradient>; gw: <weight gradient>, <its stream>", as far as the
+ * descriptor asks for them.  Validates as delta_backward_segment does, except for residency. */
+delta_status delta_backward_kernel(delta_ctx *ctx, const delta_bwd_desc *desc, char *out, uint64_t cap);
 
 /* Measurement probes (rooflines the hot path is reported against). */
 /* Pinned host <-> device hipMemcpyAsync throughput for `bytes` per copy, `iters` copies,

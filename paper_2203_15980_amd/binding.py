@@ -25,7 +25,7 @@ EXPORTS = ["delta_create", "delta_destroy", "delta_last_error", "delta_plan", "d
            "delta_alloc", "delta_tensor_ptr", "delta_release", "delta_swap_out", "delta_prefetch",
            "delta_recompute_segment", "delta_sync", "delta_bn_fold", "delta_stats",
            "delta_stats_reset", "delta_set_skip_copies", "delta_probe_hostlink",
-           "delta_probe_hbm", "delta_probe_mfma", "delta_layer_kernel", "delta_bwd_weights",
+           "delta_probe_hbm", "delta_probe_mfma", "delta_layer_kernel", "delta_backward_kernel", "delta_bwd_weights",
            "delta_backward_workspace", "delta_backward_segment", "delta_backward_join",
            "delta_batchnorm_static", "delta_reserve_pinned"]
 
@@ -130,6 +130,7 @@ def load_library():
         "delta_probe_hbm": (i32, [vp, u64, u32, C.POINTER(C.c_double)]),
         "delta_probe_mfma": (i32, [vp, u32, C.POINTER(C.c_double)]),
         "delta_layer_kernel": (i32, [vp, C.POINTER(LayerDesc), C.c_char_p, u64]),
+        "delta_backward_kernel": (i32, [vp, C.POINTER(BwdDesc), C.c_char_p, u64]),
         "delta_bwd_weights": (i32, [vp, C.POINTER(LayerDesc), vp]),
         "delta_backward_workspace": (i32, [vp, C.POINTER(LayerDesc), C.POINTER(u64)]),
         "delta_backward_segment": (i32, [vp, C.POINTER(BwdDesc), u32]),
@@ -321,6 +322,12 @@ class Delta:
         arr = layer_array([desc])
         buf = C.create_string_buffer(128)
         self._check(self.lib.delta_layer_kernel(self.ctx, arr, buf, 128))
+        return buf.value.decode()
+
+    def backward_kernel(self, desc):
+        """Names of the kernel variants a backward descriptor dispatches to."""
+        buf = C.create_string_buffer(256)
+        self._check(self.lib.delta_backward_kernel(self.ctx, C.byref(desc), buf, 256))
         return buf.value.decode()
 
     def probe_mfma(self, iters):

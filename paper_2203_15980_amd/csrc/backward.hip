@@ -435,6 +435,21 @@ const char *wgrad_check(const ConvArgs &a) {
     return a.R == 1 ? wgrad1x1_check(a) : wgrad3x3_check(a);
 }
 
+// fp32: 32 x 32 tiles where they fill the chip by themselves (half the loads per product), else 16 x 16; 32-bit offsets where stride and
+// sizes allow.
+static bool wgrad_f32_wide(const ConvArgs &a) {
+    return a.Cout % 32 == 0 && a.Cin % 32 == 0 && (long long)(a.Cout / 32) * (a.Cin / 32) * a.R * a.S >= 256;
+}
+static bool wgrad_f32_flat(const ConvArgs &a) {
+    return a.stride == 1 && (long long)a.N * a.P * a.Q * (a.Cin > a.Cout ? a.Cin : a.Cout) * 4 <= 0x7FFFFFFFLL;
+}
+
+const char *wgrad_kernel_name(const ConvArgs &a) {
+    if (a.bf16) return a.R == 1 ? "wgrad1x1 bf16" : "wgrad3x3 bf16";
+    if (wgrad_f32_flat(a)) return wgrad_f32_wide(a) ? "wgrad_f32 32x32, 32-bit offsets" : "wgrad_f32 16x16, 32-bit offsets";
+    return wgrad_f32_wide(a) ? "wgrad_f32 32x32, 64-bit addresses" : "wgrad_f32 16x16, 64-bit addresses";
+}
+
 size_t wgrad_workspace_bytes(const ConvArgs &a) {
     if (!a.bf16 || wgrad_check(a)) return 0;
     return a.R == 1 ? wgrad1x1_workspace_bytes(a) : wgrad3x3_workspace_bytes(a);
@@ -449,12 +464,11 @@ hipError_t launch_wgrad(const ConvArgs &a, const void *g, float *gw, void *works
         return a.R == 1 ? launch_wgrad1x1(a, g, gw, workspace, workspace_bytes, stream)
                         : launch_wgrad3x3(a, g, gw, workspace, workspace_bytes, stream);
     const int taps = a.R * a.S;
-    // 32 x 32 tiles where they fill the chip by themselves: half the loads per product
-    const bool wide = a.Cout % 32 == 0 && a.Cin % 32 == 0 && (long long)(a.Cout / 32) * (a.Cin / 32) * taps >= 256;
+    const bool wide = wgrad_f32_wide(a);
     const long long M = (long long)a.N * a.P * a.Q;
     const float *x = static_cast<const float *>(a.x), *gf = static_cast<const float *>(g);
     const dim3 grid = wide ? dim3(a.Cout / 32, a.Cin / 32, taps) : dim3(a.Cout / 16, a.Cin / 16, taps);
-    if (a.stride == 1 && M * (a.Cin > a.Cout ? a.Cin : a.Cout) * 4 <= 0x7FFFFFFFLL) {
+    if (wgrad_f32_flat(a)) {
         auto run = [&](auto kernel) {
             kernel<<<grid, dim3(1024), 0, stream>>>(x, gf, a.scale, gw, a.P, a.Q, a.Cin, a.Cout, a.R, a.pad, (int)M, make_divisor(a.P * a.Q),
                                                     make_divisor(a.Q));

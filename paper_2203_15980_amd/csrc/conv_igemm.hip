@@ -502,6 +502,11 @@ const char *conv_scatter_check(const ConvArgs &a) {
     return nullptr;
 }
 
+const char *conv_scatter_kernel_name(const ConvArgs &a) {
+    if (conv_splitk_applies(a)) return conv_splitk_kernel_name(a);
+    return a.bf16 ? "conv_igemm bf16" : "conv_igemm f32";
+}
+
 hipError_t launch_conv_scatter(const ConvArgs &a, hipStream_t stream) {
     if (conv_scatter_check(a)) return hipErrorInvalidValue;
     if (conv_splitk_applies(a)) return launch_conv_splitk(a, stream);

@@ -1779,6 +1779,56 @@ delta_status delta_layer_kernel(delta_ctx *c, const delta_layer_desc *layer, cha
     return DELTA_OK;
 }
 
+delta_status delta_backward_kernel(delta_ctx *c, const delta_bwd_desc *desc, char *out, uint64_t cap) {
+    delta_status r = need_gpu(c);
+    if (r != DELTA_OK) return r;
+    if (!desc || !out || cap == 0) return fail(c, DELTA_ERR_INVALID, "null argument");
+    const delta_bwd_desc &D = *desc;
+    const delta_layer_desc &L = D.fwd;
+    delta::ConvArgs fa, da;
+    delta::PoolArgs pa;
+    const BwdKind kind = bwd_kind(L);
+    if (kind == BK_STEM) {
+        if ((r = prepare_backward_stem(c, D, 0, fa)) != DELTA_OK) return r;
+        snprintf(out, (size_t)cap, "gw: stem_wgrad");
+        return DELTA_OK;
+    }
+    if (kind != BK_CONV) {
+        if ((r = prepare_backward_other(c, D, 0, kind, fa, pa)) != DELTA_OK) return r;
+        const char *name = kind == BK_MAXPOOL ? "maxpool" : kind == BK_AVGPOOL ? "avgpool" : kind == BK_LOSS ? "softmax_ce"
+                           : kind == BK_BATCHNORM ? "batchnorm" : kind == BK_RELU ? "relu" : "dense";
+        snprintf(out, (size_t)cap, "%s%s", D.gx != DELTA_NO_TENSOR ? "gx: " : "gw: ", name);
+        return DELTA_OK;
+    }
+    if ((r = prepare_backward(c, D, 0, fa, da)) != DELTA_OK) return r;
+    std::string text;
+    if (D.gx != DELTA_NO_TENSOR) {
+        text = "gx: ";
+        if (class_dgrad(D)) {
+            delta::ConvArgs ca;
+            class_args(L, fa.bf16, 1, 1, ca);
+            if (delta::dgrad_s2_applies(ca)) {
+                text += "dgrad3x3_s2 bf16";
+            } else {
+                class_args(L, fa.bf16, 0, 0, ca);
+                text += std::string("four classes, ") + delta::conv_scatter_kernel_name(ca);
+            }
+        } else {
+            text += std::string(delta::conv_kernel_name(da)) + (strided_1x1(L) ? " + spread_add" : "");
+        }
+    }
+    if (D.gw) {
+        delta::ConvArgs fo = fa;
+        fo.stride = L.stride; fo.P = (L.H + 2 * L.pad - L.R) / L.stride + 1; fo.Q = (L.W + 2 * L.pad - L.S) / L.stride + 1;
+        fo.M = L.N * fo.P * fo.Q;
+        text += text.empty() ? "gw: " : "; gw: ";
+        text += class_wgrad(D, fo) ? "wgrad3x3 stride 2 bf16" : delta::wgrad_kernel_name(fa);
+        text += wgrad_aside(L, fa) ? ", second stream" : ", compute stream";
+    }
+    snprintf(out, (size_t)cap, "%s", text.c_str());
+    return DELTA_OK;
+}
+
 delta_status delta_probe_mfma(delta_ctx *c, uint32_t iters, double *out) {
     delta_status r = need_gpu(c);
     if (r != DELTA_OK) return r;

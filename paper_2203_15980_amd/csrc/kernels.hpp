@@ -81,6 +81,7 @@ const char *conv_check(const ConvArgs &a);
 const char *conv_kernel_name(const ConvArgs &a);
 hipError_t launch_conv(const ConvArgs &a, hipStream_t stream);
 const char *conv_scatter_check(const ConvArgs &a);
+const char *conv_scatter_kernel_name(const ConvArgs &a);
 hipError_t launch_conv_scatter(const ConvArgs &a, hipStream_t stream);
 bool dgrad_s2_applies(const ConvArgs &a);
 hipError_t launch_dgrad_s2(const ConvArgs &a, hipStream_t stream);
@@ -168,6 +169,7 @@ hipError_t launch_spread_add(const void *t, const void *add, const void *mask, v
 hipError_t launch_bwd_weights(const void *w, const float *scale, void *wt, int K, int R, int S, int C, int bf16,
                               hipStream_t stream);
 const char *wgrad_check(const ConvArgs &a);            // nullptr when a weight-gradient kernel applies
+const char *wgrad_kernel_name(const ConvArgs &a);
 size_t wgrad_workspace_bytes(const ConvArgs &a);
 // 3x3 stride-2 pad-1 layers, from the gradient at the output's resolution (a.x = x at the input's resolution, a.H, a.W,
 // a.P, a.Q the layer's own)

@@ -24,7 +24,7 @@ CASES = [
     (1, 1, 1, 64, 64, 3, 1),          # only the centre tap has anything
     (5, 3, 1, 64, 128, 3, 1),         # images one pixel wide: two list pixels to a row
     (3, 7, 7, 128, 64, 3, 1),         # several images to a chunk
-    (1, 3, 116, 64, 64, 3, 1),        # the widest row a chunk takes
+    (1, 3, 125, 64, 64, 3, 1),        # the widest row a chunk takes
     (2, 30, 17, 64, 64, 3, 1),        # chunks that end inside an image, a short last one
     (2, 6, 5, 128, 128, 3, 2),        # even height, odd width
     (3, 7, 8, 128, 256, 3, 2),
@@ -52,8 +52,10 @@ def test_weight_gradient_matches_float64(torch_mod, case):  # noqa: F811
     got = []
     for _ in range(2):
         gw = torch.full((Cout, R, R, Cin), float("nan"), device="cuda:0")
-        d.backward_segment([dl.BwdDesc(fwd=fwd, gy=2, gpre=2, gx=dl.NO_TENSOR, gx_add=dl.NO_TENSOR, gw=gw.data_ptr(), workspace=ws.data_ptr(),
-                                       workspace_bytes=ws.numel())])
+        desc = dl.BwdDesc(fwd=fwd, gy=2, gpre=2, gx=dl.NO_TENSOR, gx_add=dl.NO_TENSOR, gw=gw.data_ptr(), workspace=ws.data_ptr(),
+                          workspace_bytes=ws.numel())
+        assert d.backward_kernel(desc).startswith("gw: wgrad%dx%d %sbf16" % (R, R, "stride 2 " if R == 3 and stride == 2 else ""))
+        d.backward_segment([desc])
         d.backward_join()
         d.sync()
         got.append(gw.cpu().numpy())
@@ -143,4 +145,68 @@ def test_network_takes_the_route_its_width_allows(torch_mod, W):  # noqa: F811
     ew = float(np.max(np.abs(net.gw["b"].cpu().numpy().reshape(ref_gw.shape) - ref_gw)) / np.max(np.abs(ref_gw)))
     print("  gx %.2e gw %.2e" % (ex, ew), flush=True)
     assert ex <= 2e-2 and ew <= 2e-4             # the bounds of the layer-by-layer comparisons (weights rounded once more)
+    d.close()
+
+
+def test_a_row_wider_than_a_chunk_is_refused(torch_mod):  # noqa: F811
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    nbytes = 3 * 126 * 64 * 2
+    d, put, get = _small_ctx(torch, [nbytes, nbytes, nbytes])
+    for t in (0, 2):
+        d.alloc(t)
+    w, one, gw = torch.zeros(64 * 9 * 64, device="cuda:0"), torch.ones(64, device="cuda:0"), torch.empty(64 * 9 * 64, device="cuda:0")
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda:0")
+    fwd = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=one.data_ptr(), shift=one.data_ptr(), N=1, H=3,
+                       W=126, Cin=64, Cout=64, R=3, S=3, stride=1, pad=1, relu=0)
+    with pytest.raises(dl.DeltaError) as e:
+        d.backward_segment([dl.BwdDesc(fwd=fwd, gy=2, gpre=2, gx=dl.NO_TENSOR, gx_add=dl.NO_TENSOR, gw=gw.data_ptr(), workspace=ws.data_ptr(),
+                                       workspace_bytes=ws.numel())])
+    assert e.value.status == dl.ERR_INVALID
+    d.close()
+
+
+def test_large_and_small_weight_gradients_share_a_workspace(torch_mod):  # noqa: F811
+    """A weight gradient of 1 GFLOP runs on the second stream, a smaller one on the compute stream, and all use one workspace:
+    the small one that follows has to wait for the large one's sums, the large one that follows for the small one's.  In one segment the
+    bits are those of runs with a synchronisation between."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    shapes = [(8, 32, 32, 256, 256, 1, "second"), (1, 9, 7, 128, 256, 1, "compute"), (32, 14, 14, 128, 128, 3, "second"),
+              (2, 7, 7, 128, 64, 3, "compute"), (8, 32, 32, 256, 256, 1, "second")]
+    sizes, data = [], []
+    for i, (N, H, W, Ci, Co, R, _) in enumerate(shapes):
+        data.append((_bits(95, 2 * i, (N, H, W, Ci)), _bits(95, 2 * i + 1, (N, H, W, Co))))
+        sizes += [data[i][0].nbytes, data[i][1].nbytes, data[i][1].nbytes]
+    d, put, get = _small_ctx(torch, sizes, mb=96)
+    w, one = torch.zeros(256 * 256 * 9, device="cuda:0"), torch.ones(256, device="cuda:0")
+    fwds, need = [], 0
+    for i, (N, H, W, Ci, Co, R, _) in enumerate(shapes):
+        put(3 * i, data[i][0])
+        put(3 * i + 2, data[i][1])
+        fwds.append(dl.LayerDesc(x=3 * i, res=dl.NO_TENSOR, y=3 * i + 1, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=one.data_ptr(),
+                                 shift=one.data_ptr(), N=N, H=H, W=W, Cin=Ci, Cout=Co, R=R, S=R, stride=1, pad=R // 2, relu=0))
+        need = max(need, d.backward_workspace(fwds[i]))
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+
+    def run(apart):
+        gws, descs = [], []
+        for i, (N, H, W, Ci, Co, R, stream) in enumerate(shapes):
+            gws.append(torch.full((Co * R * R * Ci,), float("nan"), device="cuda:0"))
+            descs.append(dl.BwdDesc(fwd=fwds[i], gy=3 * i + 2, gpre=3 * i + 2, gx=dl.NO_TENSOR, gx_add=dl.NO_TENSOR, gw=gws[i].data_ptr(),
+                                    workspace=ws.data_ptr(), workspace_bytes=need))
+            assert stream + " stream" in d.backward_kernel(descs[i]), d.backward_kernel(descs[i])
+        torch.cuda.synchronize()
+        for part in ([[x] for x in descs] if apart else [descs]):
+            d.backward_segment(part)
+            if apart:
+                d.backward_join()
+                d.sync()
+        d.backward_join()
+        d.sync()
+        return [g.cpu().numpy() for g in gws]
+    ref = run(True)
+    assert all(np.all(np.isfinite(r)) for r in ref)
+    for _ in range(4):
+        assert all(np.array_equal(a, b) for a, b in zip(run(False), ref))
     d.close()
