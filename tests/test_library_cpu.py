@@ -354,6 +354,20 @@ def test_executed_encoder_plan_matches_oracle():
         assert st["peak"] == want[1] <= p["budget_bytes"]
 
 
+def test_bench_line_stays_short_and_keeps_the_result():
+    import importlib.util
+    import json
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    record = {k: k for k in bench.LINE_FIELDS}
+    record.update(summary={"a": "s" * 1500}, roofline={"b": "r" * 900}, legs={"c": "l" * 40000}, resnet50_step_50pct={"runs": ["x" * 3000]})
+    line = bench.result_line(record)
+    got = json.loads(line)
+    assert "\n" not in line and len(line) <= 6000
+    assert set(got) == set(bench.LINE_FIELDS) | {"summary", "roofline"}
+
+
 def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run(["python", os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0 and "one GPU" in r.stderr and r.stdout.strip() == ""
