@@ -13,8 +13,9 @@
 // (BM/32) x (BN/64) wavefronts of 32 pixels x 64 channels, 256 x 64 in all where that fills the chip and 128 x 64 where it does not.
 // What bounds it is the chain of a step - barrier, weights to LDS, operand reads, MFMAs - so a SIMD needs wavefronts to
 // switch between: with 64 x 64 per wavefront (four to a workgroup, a quarter fewer operand reads) it had one or two, here two
-// to four in 128 registers.  Batch 128, us (TFLOP/s) before -> now: 28 x 28 x 128 38.5 -> 34.2 (865), 14 x 14 x 256
-// 34.2 -> 31.6 (938), 7 x 7 x 512 46.2 -> 41.2 (719: 200 workgroups); batch 64: 21.1 -> 18.9, 25.5 -> 22.1, 45.2 -> 34.9.
+// to four in 128 registers.  Back to back on N(0, 1) values, batch 128, us (TFLOP/s) before -> now: 28 x 28 x 128 46.0 -> 44.5 (665), 14 x 14 x 256
+// 39.5 -> 37.8 (783), 7 x 7 x 512 48.7 -> 44.7 (662: 200 workgroups); batch 64: 22.9 -> 21.2, 26.5 -> 23.6, 46.1 -> 35.8.  On a network's own
+// values, half of them zeros behind a ReLU, the chip clocks higher: 40, 35 and 42 us at batch 128.
 // Pipeline: one step = one tap of one channel block = 8 MFMAs per wavefront and one barrier.
 // Weight tiles are requested D = 4 steps ahead into a register ring and move to one of two LDS
 // buffers a step before use; the halo of the next channel block is requested at tap 0 and stored
@@ -354,6 +355,8 @@ static size_t smem_bytes(int BM, int HR) {
 // 12.9 -> 11.4 (28 x 28 x 128, batch 16), 21.3 -> 18.4 (14 x 14 x 256, batch 32), 40.1 -> 34.9 (7 x 7 x 512, batch 64);
 // 147 against 294 are 17.6 -> 18.2 already.  128 also for rows of 64 pixels and more, whose halo of 256 would not
 // fit the 128 registers that let two workgroups share a CU: 112 x 112 x 128, batch 8: 47 us against 51 at one workgroup to a CU.
+// There the kernel with 256 pixels and 64 x 64 per wavefront took 62.6; 64 x 64 x 128, batch 16: 33 -> 29; 100 x 100, 128 -> 64, batch 32:
+// 81 -> 67; 96 x 96 x 512, batch 1: 95 -> 76; 127 x 127 x 256, batch 2: 53 -> 49.
 static int tile_pixels(const ConvArgs &a) {
     return a.W > 63 || (((long long)a.M + 255) / 256) * (a.Cout / kBN) < 128 ? 128 : 256;
 }

@@ -229,6 +229,9 @@ __global__ __launch_bounds__(256, 2) void dgrad3x3_s2_kernel(Args a) {
 // their reductions split cost 21 to 25 us then, whatever K is, and lose from 40 tiles on.  56 x 56 x 128, 28 x 28 x 256 and 14 x 14 x 512, us for four
 // launches -> one:  batch 1: 21 -> 13, 23 -> 18, 25 -> 28;  8: 44 -> 14, 29 -> 19, 26 -> 29 (28 tiles);
 // 16: 45 -> 15, 56 -> 19, 33 -> 29 (52 tiles);  32: 52 -> 20, 59 -> 21, 73 -> 30;  128: 124 -> 62 (3.7 TB/s), 87 -> 53, 90 -> 46.
+// From 32 output columns on the staged rows leave one workgroup to a CU, which is still the better side.  gx of 128 channels, gradient of 128 | 512
+// with gx of 512: batch 1 of 64 x 64 44 -> 14 | 87 -> 30, of 318 x 318 53 -> 29 | 215 -> 193; batch 8 of 160 x 160 68 -> 52 | 396 -> 382;
+// batch 64 of 64 x 64 76 -> 55 | 468 -> 475, batch 32 of 112 x 112 122 -> 87 | 716 -> 731 (even).
 bool dgrad_s2_applies(const ConvArgs &a) {
     if (!a.bf16 || a.Cout % 128 || a.Cin % 64 || a.W > dg3::kMaxQ) return false;
     const long long tiles = ((long long)a.N * a.H * a.W + dg3::kTile - 1) / dg3::kTile * (a.Cout / 128);
