@@ -1801,31 +1801,32 @@ delta_status delta_backward_kernel(delta_ctx *c, const delta_bwd_desc *desc, cha
         return DELTA_OK;
     }
     if ((r = prepare_backward(c, D, 0, fa, da)) != DELTA_OK) return r;
-    std::string text;
+    char gx[160] = "", gw[80] = "";                       // a C entry: nothing here throws
     if (D.gx != DELTA_NO_TENSOR) {
-        text = "gx: ";
+        const char *name = nullptr, *before = "", *after = strided_1x1(L) ? " + spread_add" : "";
         if (class_dgrad(D)) {
             delta::ConvArgs ca;
             class_args(L, fa.bf16, 1, 1, ca);
             if (delta::dgrad_s2_applies(ca)) {
-                text += "dgrad3x3_s2 bf16";
+                name = "dgrad3x3_s2 bf16";
             } else {
                 class_args(L, fa.bf16, 0, 0, ca);
-                text += std::string("four classes, ") + delta::conv_scatter_kernel_name(ca);
+                before = "four classes, ";
+                name = delta::conv_scatter_kernel_name(ca);
             }
         } else {
-            text += std::string(delta::conv_kernel_name(da)) + (strided_1x1(L) ? " + spread_add" : "");
+            name = delta::conv_kernel_name(da);
         }
+        snprintf(gx, sizeof gx, "gx: %s%s%s", before, name, after);
     }
     if (D.gw) {
         delta::ConvArgs fo = fa;
         fo.stride = L.stride; fo.P = (L.H + 2 * L.pad - L.R) / L.stride + 1; fo.Q = (L.W + 2 * L.pad - L.S) / L.stride + 1;
         fo.M = L.N * fo.P * fo.Q;
-        text += text.empty() ? "gw: " : "; gw: ";
-        text += class_wgrad(D, fo) ? "wgrad3x3 stride 2 bf16" : delta::wgrad_kernel_name(fa);
-        text += wgrad_aside(L, fa) ? ", second stream" : ", compute stream";
+        snprintf(gw, sizeof gw, "%sgw: %s%s", gx[0] ? "; " : "", class_wgrad(D, fo) ? "wgrad3x3 stride 2 bf16" : delta::wgrad_kernel_name(fa),
+                 wgrad_aside(L, fa) ? ", second stream" : ", compute stream");
     }
-    snprintf(out, (size_t)cap, "%s", text.c_str());
+    snprintf(out, (size_t)cap, "%s%s", gx, gw);
     return DELTA_OK;
 }
 
