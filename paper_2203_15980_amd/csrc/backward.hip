@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include "kernels.hpp"
+#include "wgrad_f32_tile.hpp"
 
 namespace delta {
 namespace bwd {
@@ -251,86 +252,13 @@ __global__ __launch_bounds__(1024) void wgrad_f32_kernel(const float *x, const f
     gw[((size_t)k * R * R + tap) * C + c] = sum * scale[k];
 }
 
-// The form for stride 1 and tensors below 2 GiB: 32-bit offsets, and buffer loads that return zero for an offset outside the
-// tensor, which is where positions past a wavefront's run and taps outside the image point: 8 instructions per MFMA for a 1x1
-// layer, about 20 with taps.  Sixteen steps in flight for T = 1 without taps (a run of 128 positions is two round trips; with
-// taps eight are better, 9.6 us against 11.3: the address arithmetic of a round runs before its first product).
-// 2 x 32 x 32 positions, us by the form above -> this one: 64 -> 256 10.0 -> 7.0, 256 -> 64 10.0 -> 9.1, 64 -> 64 10.0 -> 6.5, 3x3
-// 64 -> 64 10.0 -> 9.6.
+// The form for stride 1 and tensors below 2 GiB (wgrad_f32_tile.hpp).
 template <int T, bool TAPS>
 __global__ __launch_bounds__(1024) void wgrad_f32_flat_kernel(const float *x, const float *g, const float *scale, float *gw, int H, int W, int C,
                                                               int K, int R, int pad, int M, Divisor dhw, Divisor dw) {
-    typedef uint32_t uvec __attribute__((ext_vector_type(T)));
-    constexpr int kWaves = 16, kSteps = T == 1 && !TAPS ? 16 : 8;
-    __shared__ float part[kWaves][T * T * 256];
-    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int k0 = blockIdx.x * (16 * T), c0 = blockIdx.y * (16 * T), tap = blockIdx.z;
-    const int dr = TAPS ? tap / R - pad : 0, ds = TAPS ? tap % R - pad : 0;
-    const int per = ((M + kWaves - 1) / kWaves + 3) / 4 * 4;
-    const int first = wv * per, end = first + per < M ? first + per : M;
-    const __amdgpu_buffer_rsrc_t grsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(g), 0, (int)((size_t)M * K * 4), 0x00020000);
-    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(x), 0, (int)((size_t)M * C * 4), 0x00020000);
-    auto fetch = [&](__amdgpu_buffer_rsrc_t r, uint32_t off) {
-        if constexpr (T == 1) return uvec{__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0)};
-        else return __builtin_bit_cast(uvec, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-    };
-    int m = first + quad, h = 0, w = 0;                          // this lane's position
-    if constexpr (TAPS) {
-        const int rest = m - divide(m, dhw) * (H * W);
-        h = divide(rest, dw);
-        w = rest - h * W;
-    }
-    const int hstep = 4 / W % H, wstep = 4 % W;                  // four positions on: at most one carry each
-    uint32_t goff = ((uint32_t)m * (uint32_t)K + (uint32_t)(k0 + T * l16)) * 4u;
-    uint32_t xoff = ((uint32_t)(m + dr * W + ds) * (uint32_t)C + (uint32_t)(c0 + T * l16)) * 4u;
-    f32x4 acc[T][T];
-#pragma unroll
-    for (int i = 0; i < T; ++i)
-#pragma unroll
-        for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int m0 = first; m0 < end; m0 += 4 * kSteps) {
-        uvec gv[kSteps], xv[kSteps];
-#pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
-            const bool live = m < end;
-            bool in = live;
-            if constexpr (TAPS) in = live & ((unsigned)(h + dr) < (unsigned)H) & ((unsigned)(w + ds) < (unsigned)W);
-            gv[u] = fetch(grsrc, live ? goff : (uint32_t)kOutOfRange);
-            xv[u] = fetch(xrsrc, in ? xoff : (uint32_t)kOutOfRange);
-            m += 4;
-            goff += (uint32_t)K * 16u;
-            xoff += (uint32_t)C * 16u;
-            if constexpr (TAPS) {
-                w += wstep;
-                const bool carry = w >= W;
-                w -= carry ? W : 0;
-                h += hstep + (carry ? 1 : 0);
-                h -= h >= H ? H : 0;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kSteps; ++u)
-#pragma unroll
-            for (int i = 0; i < T; ++i)
-#pragma unroll
-                for (int j = 0; j < T; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(gv[u][i]), __uint_as_float(xv[u][j]), acc[i][j], 0, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < T; ++i)
-#pragma unroll
-        for (int j = 0; j < T; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) part[wv][((i * T + j) * 4 + e) * 64 + lane] = acc[i][j][e];
-    __syncthreads();
-    if (tid >= T * T * 256) return;
-    float sum = part[0][tid];
-#pragma unroll
-    for (int v = 1; v < kWaves; ++v) sum += part[v][tid];
-    // lane of this sum: column (c) l % 16, row (k) 4 (l / 16) + e of the tile's (i, j) interleave
-    const int k = k0 + T * (4 * quad + (wv & 3)) + (tid >> 8) / T, c = c0 + T * l16 + (tid >> 8) % T;
-    gw[((size_t)k * R * R + tap) * C + c] = sum * scale[k];
+    __shared__ float part[16 * T * T * 256];
+    wgrad_f32_tile<T, TAPS, 16>(x, g, scale, gw, H, W, C, K, R, pad, M, dhw, dw, blockIdx.x * (16 * T), blockIdx.y * (16 * T), blockIdx.z, threadIdx.x,
+                                part);
 }
 
 }  // namespace bwd

@@ -1345,6 +1345,19 @@ bool wgrad_aside(const delta_layer_desc &L, const delta::ConvArgs &fa) {
     const uint64_t rows = L.stride == 2 && L.R == 3 ? (uint64_t)fa.M / 4 : (uint64_t)fa.M;
     return 2ull * rows * fa.R * fa.S * fa.Cin * fa.Cout >= kAsideFlops;
 }
+// How a layer that was asked for both gradients gets them where they are small (delta::launch_small_backward):
+// OL_LAYER - one launch for both; OL_CLASS - a strided 3x3 layer whose data gradient goes by parity class: the weight gradient in the
+// launch of class (1, 1); OL_WEIGHT - such a layer where one launch makes all four classes: the weight gradient in a launch of its own, without
+// partial sums.  `fo`: the layer's own geometry, `fa` after as_stride_1, `da` the data gradient's convolution.
+enum OneLaunch { OL_NONE, OL_LAYER, OL_CLASS, OL_WEIGHT };
+OneLaunch one_launch(const delta_bwd_desc &D, const delta::ConvArgs &fo, const delta::ConvArgs &fa, const delta::ConvArgs &da) {
+    if (!D.gw || D.gx == DELTA_NO_TENSOR) return OL_NONE;
+    if (!class_dgrad(D)) return delta::small_backward_applies(&da, fa) ? OL_LAYER : OL_NONE;
+    delta::ConvArgs ca;
+    class_args(D.fwd, fa.bf16, 1, 1, ca);
+    if (delta::dgrad_s2_applies(ca)) return delta::small_backward_applies(nullptr, fo) ? OL_WEIGHT : OL_NONE;
+    return ca.P > 0 && ca.Q > 0 && delta::small_backward_applies(&ca, fo) ? OL_CLASS : OL_NONE;
+}
 // `fa` after as_stride_1
 uint64_t backward_workspace_bytes(const delta_layer_desc &L, const delta::ConvArgs &fa) {
     uint64_t need = partials_bytes(fa) + staging_bytes(L, fa);
@@ -1669,9 +1682,11 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
         }
         const unsigned char *gp = c->arena + c->tensors[D.gpre].offset;
         Ev ready;
-        const bool aside = D.gw && wgrad_aside(L, fa);
+        const OneLaunch one = one_launch(D, fo, fa, da);
+        const bool aside = D.gw && one == OL_NONE && wgrad_aside(L, fa);
         if (D.gw) {
             if ((r = compute_uses(c, c->tensors[L.x])) != DELTA_OK) return r;
+            fa.x = fo.x = c->arena + c->tensors[L.x].offset;
             if (aside && (r = new_event(c, s, &ready)) != DELTA_OK) return r;
         }
         if (D.gx != DELTA_NO_TENSOR) {
@@ -1701,20 +1716,28 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
                         break;
                     }
                     if (ca.P <= 0 || ca.Q <= 0) continue;
-                    HIP_TRY(c, delta::launch_conv_scatter(ca, s));
+                    if (one == OL_CLASS && cls == 3)
+                        HIP_TRY(c, delta::launch_small_backward(&ca, fo, c->arena + tgy.offset, static_cast<float *>(D.gw), s));
+                    else
+                        HIP_TRY(c, delta::launch_conv_scatter(ca, s));
                 }
-            } else
-            HIP_TRY(c, delta::launch_conv(da, s));
+            } else if (one == OL_LAYER) {
+                HIP_TRY(c, delta::launch_small_backward(&da, fa, gp, static_cast<float *>(D.gw), s));
+            } else {
+                HIP_TRY(c, delta::launch_conv(da, s));
+            }
             if (direct)
                 HIP_TRY(c, delta::launch_spread_add(staging, addp, maskp, c->arena + tgx.offset, L.N, L.H, L.W, outP, outQ,
                                                     L.Cin, L.stride, fa.bf16, s));
             c->st.recompute_flops += class_dgrad(D) ? 2ull * (uint64_t)L.N * outP * outQ * 9 * L.Cin * L.Cout
                                                     : 2ull * (uint64_t)da.M * da.R * da.S * da.Cin * da.Cout;
         }
-        if (D.gw) {
+        if (one != OL_NONE) {
+            if (one == OL_WEIGHT) HIP_TRY(c, delta::launch_small_backward(nullptr, fo, c->arena + tgy.offset, static_cast<float *>(D.gw), s));
+            c->st.recompute_flops += 2ull * (uint64_t)fo.M * fo.R * fo.S * fo.Cin * fo.Cout;
+        } else if (D.gw) {
             Tensor &tx = c->tensors[L.x];
             if ((r = compute_uses(c, tx)) != DELTA_OK) return r;
-            fa.x = c->arena + tx.offset;
             // gpre and x are complete once the compute stream reaches `ready`; from there the weight gradient runs on
             // its own stream, and both tensors remember that reader.
             // A small one stays on the compute stream, after whatever still uses the workspace on the other.
@@ -1729,7 +1752,6 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
             }
             if (by_class) {
                 // from gy itself (it needs no mask of this layer's) and x
-                fo.x = fa.x;
                 HIP_TRY(c, delta::launch_wgrad_s2(fo, c->arena + tgy.offset, static_cast<float *>(D.gw), D.workspace, need, gs));
                 c->st.recompute_flops += 2ull * (uint64_t)fo.M * 9 * fo.Cin * fo.Cout;
             } else {
@@ -1823,8 +1845,14 @@ delta_status delta_backward_kernel(delta_ctx *c, const delta_bwd_desc *desc, cha
         delta::ConvArgs fo = fa;
         fo.stride = L.stride; fo.P = (L.H + 2 * L.pad - L.R) / L.stride + 1; fo.Q = (L.W + 2 * L.pad - L.S) / L.stride + 1;
         fo.M = L.N * fo.P * fo.Q;
-        snprintf(gw, sizeof gw, "%sgw: %s%s", gx[0] ? "; " : "", class_wgrad(D, fo) ? "wgrad3x3 stride 2 bf16" : delta::wgrad_kernel_name(fa),
-                 wgrad_aside(L, fa) ? ", second stream" : ", compute stream");
+        const OneLaunch one = one_launch(D, fo, fa, da);
+        if (one == OL_LAYER) snprintf(gx, sizeof gx, "gx: %s%s", delta::small_backward_name(fa), strided_1x1(L) ? " + spread_add" : "");
+        if (one != OL_NONE)
+            snprintf(gw, sizeof gw, "; gw: %s%s", delta::small_backward_name(fa),
+                     one == OL_LAYER ? ", the same launch" : one == OL_CLASS ? ", the launch of one class" : ", compute stream");
+        else
+            snprintf(gw, sizeof gw, "%sgw: %s%s", gx[0] ? "; " : "", class_wgrad(D, fo) ? "wgrad3x3 stride 2 bf16" : delta::wgrad_kernel_name(fa),
+                     wgrad_aside(L, fa) ? ", second stream" : ", compute stream");
     }
     snprintf(out, (size_t)cap, "%s%s", gx, gw);
     return DELTA_OK;

@@ -189,6 +189,13 @@ const char *wgrad3x3_check(const ConvArgs &a);
 size_t wgrad3x3_workspace_bytes(const ConvArgs &a);
 hipError_t launch_wgrad3x3(const ConvArgs &a, const void *g, float *gw, void *workspace, size_t workspace_bytes, hipStream_t stream);
 
+// small_backward.hip: both gradients of a layer that cannot fill the chip in one launch (da: the data gradient's convolution
+// or null for the weight gradient alone, fa: the layer as
+// launch_wgrad or launch_wgrad_s2 takes it)
+bool small_backward_applies(const ConvArgs *da, const ConvArgs &fa);
+const char *small_backward_name(const ConvArgs &fa);
+hipError_t launch_small_backward(const ConvArgs *da, const ConvArgs &fa, const void *g, float *gw, hipStream_t stream);
+
 // backward_ops.hip: backward of pooling, the classifier and the loss (bf16)
 // mask_x: gx is also multiplied by [x > 0] (the ReLU mask of the layer that produced the pool's input)
 hipError_t launch_maxpool_bwd(const PoolArgs &a, const void *gy, void *gx, int mask_x, hipStream_t stream);
