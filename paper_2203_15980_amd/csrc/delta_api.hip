@@ -918,6 +918,28 @@ static delta_status claim_output(delta_ctx *c, Tensor &ty) {
     return DELTA_OK;
 }
 
+// How many of the layers from `i` on are one pass over the elements: a batch normalisation, the add of its result, the ReLU of that, each
+// of which reads what the one before it leaves; or an add and its ReLU.  1: the layer goes by itself.
+static uint32_t elementwise_run(const delta_layer_desc *layers, uint32_t n_layers, uint32_t i) {
+    uint32_t n = 1;
+    const uint32_t x = layers[i].x;
+    auto goes_on = [&](uint32_t op) {
+        if (i + n >= n_layers || layers[i + n].op != op) return false;
+        const delta_layer_desc &next = layers[i + n];
+        if (next.x != layers[i + n - 1].y || next.res == next.x || next.y == x) return false;
+        for (uint32_t j = 0; j < n; ++j)                         // nothing that the run writes is written or read elsewhere in it
+            if (next.y == layers[i + j].y || next.y == layers[i + j].res || next.res == layers[i + j].y) return false;
+        return true;
+    };
+    if (layers[i].op == DELTA_OP_BATCHNORM) {
+        if (goes_on(DELTA_OP_ADD)) ++n;
+        if (goes_on(DELTA_OP_RELU)) ++n;
+    } else if (layers[i].op == DELTA_OP_ADD) {
+        if (goes_on(DELTA_OP_RELU)) ++n;
+    }
+    return n;
+}
+
 delta_status delta_recompute_segment(delta_ctx *c, const delta_layer_desc *layers, uint32_t n_layers) {
     delta_status r = need_gpu(c);
     if (r != DELTA_OK) return r;
@@ -985,6 +1007,23 @@ delta_status delta_recompute_segment(delta_ctx *c, const delta_layer_desc *layer
         if ((r = claim_output(c, ty)) != DELTA_OK) return r;
         unsigned char *xp = c->arena + tx.offset, *yp = c->arena + ty.offset;
         unsigned char *rp = L.res != DELTA_NO_TENSOR ? c->arena + c->tensors[L.res].offset : nullptr;
+        // the run's other outputs; one that finds no room ends the run, which is launched as far as it got
+        const uint32_t run = elementwise_run(layers, n_layers, i);
+        delta::ElementwiseTail tail;
+        delta_status tail_status = DELTA_OK;
+        uint32_t done = 1;
+        for (; done < run; ++done) {
+            const delta_layer_desc &next = layers[i + done];
+            if (next.res != DELTA_NO_TENSOR && (r = compute_uses(c, c->tensors[next.res])) != DELTA_OK) return r;
+            if ((tail_status = claim_output(c, c->tensors[next.y])) != DELTA_OK) break;
+            void *at = c->arena + c->tensors[next.y].offset;
+            if (next.op == DELTA_OP_RELU) {
+                tail.y_relu = at;
+            } else {
+                tail.y_add = at;
+                tail.r = c->arena + c->tensors[next.res].offset;
+            }
+        }
         switch (L.op) {
         case DELTA_OP_CONV:
             a.x = xp; a.y = yp; a.res = rp;
@@ -1004,14 +1043,20 @@ delta_status delta_recompute_segment(delta_ctx *c, const delta_layer_desc *layer
             break;
         case DELTA_OP_BATCHNORM:
             if (!c->bn_scratch) HIP_TRY(c, hipMalloc(&c->bn_scratch, delta::bn_train_scratch_bytes()));
-            HIP_TRY(c, delta::launch_bn_train(xp, yp, L.scale, L.shift, (long long)L.N * L.H * L.W, L.Cin, L.eps, 1,
+            HIP_TRY(c, delta::launch_bn_train(xp, yp, L.scale, L.shift, (long long)L.N * L.H * L.W, L.Cin, L.eps, 1, tail,
                                               c->bn_scratch, delta::bn_train_scratch_bytes(), c->stream[S_COMPUTE]));
             break;
         case DELTA_OP_RELU:
             HIP_TRY(c, delta::launch_relu(xp, yp, ty.bytes, 1, c->stream[S_COMPUTE]));
             break;
         case DELTA_OP_ADD:
-            HIP_TRY(c, delta::launch_add(xp, rp, yp, ty.bytes, 1, c->stream[S_COMPUTE]));
+            if (tail.y_relu) {
+                tail.r = rp;
+                tail.y_add = yp;
+                HIP_TRY(c, delta::launch_add_relu(xp, tail, ty.bytes, 1, c->stream[S_COMPUTE]));
+            } else {
+                HIP_TRY(c, delta::launch_add(xp, rp, yp, ty.bytes, 1, c->stream[S_COMPUTE]));
+            }
             break;
         case DELTA_OP_LAYERNORM:
             HIP_TRY(c, delta::launch_layernorm(xp, yp, L.scale, L.shift, (long long)L.N * L.H * L.W, L.Cin, L.eps,
@@ -1022,8 +1067,10 @@ delta_status delta_recompute_segment(delta_ctx *c, const delta_layer_desc *layer
                                                 reinterpret_cast<float *>(yp), c->stream[S_COMPUTE]));
             break;
         }
-        c->st.recompute_launches += 1;
+        c->st.recompute_launches += done;
         c->st.recompute_flops += flops;
+        if (tail_status != DELTA_OK) return tail_status;
+        i += done - 1;
     }
     return DELTA_OK;
 }
@@ -1051,7 +1098,8 @@ delta_status delta_batchnorm_static(delta_ctx *c, const void *x, void *y, const 
     }
     // Nothing in the scratch has to start at zero: every partial sum and factor the later kernels of
     // this call read is written by an earlier kernel of this call.
-    HIP_TRY(c, delta::launch_bn_train(x, y, gamma, beta, (long long)rows, (int)channels, eps, 1, c->static_scratch,
+    HIP_TRY(c, delta::launch_bn_train(x, y, gamma, beta, (long long)rows, (int)channels, eps, 1, delta::ElementwiseTail(),
+                                      c->static_scratch,
                                       kStaticScratchBytes, c->stream[S_COMPUTE]));
     return DELTA_OK;
 }
@@ -1618,11 +1666,32 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
             case BK_BATCHNORM:
                 if (!c->bn_scratch) HIP_TRY(c, hipMalloc(&c->bn_scratch, delta::bn_train_scratch_bytes()));
                 HIP_TRY(c, delta::launch_bn_train_bwd(xp, gyp, gxp, L.scale, static_cast<float *>(D.gw),
-                                                      (long long)L.N * L.H * L.W, L.Cin, L.eps, 1, c->bn_scratch, s));
+                                                      (long long)L.N * L.H * L.W, L.Cin, L.eps, 1, nullptr, nullptr,
+                                                      c->bn_scratch, s));
                 break;
             case BK_RELU: {
                 Tensor &ty = c->tensors[L.y];
                 if ((r = compute_uses(c, ty)) != DELTA_OK) return r;
+                // a batch normalisation that takes this gradient next applies the mask in its own first pass, unless its output finds no room
+                const bool on = i + 1 < n && bwd_kind(descs[i + 1].fwd) == BK_BATCHNORM && descs[i + 1].gy == D.gx &&
+                                descs[i + 1].fwd.x != D.gx && descs[i + 1].gx != D.gx && descs[i + 1].gx != L.y && descs[i + 1].gx != D.gy;
+                if (on) {
+                    const delta_bwd_desc &B = descs[i + 1];
+                    Tensor &tx = c->tensors[B.fwd.x], &tgx = c->tensors[B.gx];
+                    if ((r = compute_uses(c, tx)) != DELTA_OK) return r;
+                    if (!c->bn_scratch) HIP_TRY(c, hipMalloc(&c->bn_scratch, delta::bn_train_scratch_bytes()));
+                    const delta_status room = compute_writes(c, tgx);
+                    if (room == DELTA_OK) {
+                        HIP_TRY(c, delta::launch_bn_train_bwd(c->arena + tx.offset, gyp, c->arena + tgx.offset, B.fwd.scale,
+                                                              static_cast<float *>(B.gw), (long long)B.fwd.N * B.fwd.H * B.fwd.W, B.fwd.Cin,
+                                                              B.fwd.eps, 1, c->arena + ty.offset, gxp, c->bn_scratch, s));
+                        c->st.recompute_launches += 1;
+                        ++i;
+                        break;
+                    }
+                    HIP_TRY(c, delta::launch_relu_mask(c->arena + ty.offset, gyp, gxp, c->tensors[D.gy].bytes, 1, s));
+                    return room;
+                }
                 HIP_TRY(c, delta::launch_relu_mask(c->arena + ty.offset, gyp, gxp, c->tensors[D.gy].bytes, 1, s));
                 break;
             }

@@ -132,10 +132,17 @@ const char *bn_train_check(const void *x, const void *y, const float *gamma, con
                            int bf16);
 size_t bn_train_scratch_bytes();
 size_t bn_train_fwd_scratch_bytes();      // what the forward alone needs of it (any C up to 8192)
+// What a segment does next with the result, element by element: y_add = result + r, y_relu = ReLU of that (or of the result).  Null: not there.
+struct ElementwiseTail {
+    const void *r = nullptr;
+    void *y_add = nullptr, *y_relu = nullptr;
+    bool bad() const { return !r != !y_add || (((uintptr_t)r | (uintptr_t)y_add | (uintptr_t)y_relu) & 15); }
+};
 hipError_t launch_bn_train(const void *x, void *y, const float *gamma, const float *beta, long long M, int C, float eps,
-                           int bf16, void *scratch, size_t scratch_bytes, hipStream_t stream);
+                           int bf16, const ElementwiseTail &tail, void *scratch, size_t scratch_bytes, hipStream_t stream);
 hipError_t launch_bn_train_bwd(const void *x, const void *gy, void *gx, const float *gamma, float *gw, long long M, int C,
-                               float eps, int bf16, void *scratch, hipStream_t stream);
+                               float eps, int bf16, const void *relu_y, void *gm, void *scratch, hipStream_t stream);
+hipError_t launch_add_relu(const void *x, const ElementwiseTail &tail, size_t bytes, int bf16, hipStream_t stream);
 hipError_t launch_relu(const void *x, void *y, size_t bytes, int bf16, hipStream_t stream);
 hipError_t launch_add(const void *x, const void *r, void *y, size_t bytes, int bf16, hipStream_t stream);
 // net_ops.hip: ResNet stem (7x7, stride 2, pad 3, 3 -> 64 channels, bf16), pooling, loss

@@ -12,14 +12,16 @@
 //                       scratch buffer
 //   bn_finalize_kernel  one thread per channel adds the partials in block order (double), forms
 //                       mean, biased variance and a = gamma / sqrt(var + eps)
-//   bn_apply_kernel     y = a_c (x - mean_c) + beta_c   (centred first: no cancellation of two large products)
+//   bn_tail_kernel      y = a_c (x - mean_c) + beta_c   (centred first: no cancellation of two large products); where the
+//                       segment goes on with the residual add and / or the ReLU of that result, those too, in the same pass
 // No atomics: the result is a fixed function of the input (recomputation is bit-identical).
 // Backward of the batch normalisation (chain rule through the three lines above, collapsed):
 //   gx = a_c (gy - mean(gy)_c - (x - mu_c) S_c / ((var_c + eps) M)),   S_c = sum gy (x - mu_c)
 //   dgamma_c = S_c / sqrt(var_c + eps),   dbeta_c = sum gy
 // reads x and gy twice and writes gx once, the floor without stored statistics (x has to be read
 // for S_c in any case):
-//   bn_bwd_stats_kernel     sums of (x - K_c), (x - K_c)^2, gy, gy (x - K_c) per channel and workgroup
+//   bn_bwd_stats_kernel     sums of (x - K_c), (x - K_c)^2, gy, gy (x - K_c) per channel and workgroup; where gy is the
+//                           gradient that the ReLU before it in the segment leaves, its mask is applied and stored here
 //   bn_bwd_finalize_kernel  adds the partials (double), forms a, mu, mean(gy), S/((var + eps) M) and
 //                           the two parameter gradients
 //   bn_bwd_apply_kernel     gx from x, gy and the four per-channel factors
@@ -45,6 +47,14 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
 __device__ __forceinline__ void unpack8(const u32x4 v, float (&f)[8]) {
     f[0] = lo16(v.x); f[1] = hi16(v.x); f[2] = lo16(v.y); f[3] = hi16(v.y);
     f[4] = lo16(v.z); f[5] = hi16(v.z); f[6] = lo16(v.w); f[7] = hi16(v.w);
+}
+
+// g where m > 0, else 0
+__device__ __forceinline__ u32x4 keep8(const u32x4 g, const u32x4 m) {
+    u32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = keep_where_positive_bf16(g[e], m[e]);
+    return o;
 }
 
 // NT = blockDim.x threads (256 or 1024): CH = min(chunks, NT) chunk columns per pass, RS = NT / CH rows
@@ -169,31 +179,78 @@ __global__ __launch_bounds__(1024) void bn_finalize_kernel(const unsigned char *
     (void)beta;
 }
 
-__global__ __launch_bounds__(256) void bn_apply_kernel(const u32x4 *__restrict__ x, u32x4 *__restrict__ y,
-                                                       const float *__restrict__ ab, const float *__restrict__ beta, int C,
-                                                       size_t n16) {
-    const size_t step = (size_t)gridDim.x * blockDim.x;          // a multiple of C / 8: a thread stays with its channels (11.0 -> 9.8 us at 25088 x 512)
-    const int ck = (int)((blockIdx.x * blockDim.x + threadIdx.x) % (unsigned)(C / 8));
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += step) {
-        float v[8];
-        unpack8(x[i], v);
-        const f32x4 a0 = *reinterpret_cast<const f32x4 *>(ab + ck * 8), a1 = *reinterpret_cast<const f32x4 *>(ab + ck * 8 + 4);
-        const f32x4 m0 = *reinterpret_cast<const f32x4 *>(ab + C + ck * 8), m1 = *reinterpret_cast<const f32x4 *>(ab + C + ck * 8 + 4);
-        const f32x4 b0 = *reinterpret_cast<const f32x4 *>(beta + ck * 8), b1 = *reinterpret_cast<const f32x4 *>(beta + ck * 8 + 4);
-        u32x4 o;
-        o.x = pack2((v[0] - m0.x) * a0.x + b0.x, (v[1] - m0.y) * a0.y + b0.y);
-        o.y = pack2((v[2] - m0.z) * a0.z + b0.z, (v[3] - m0.w) * a0.w + b0.w);
-        o.z = pack2((v[4] - m1.x) * a1.x + b1.x, (v[5] - m1.y) * a1.y + b1.y);
-        o.w = pack2((v[6] - m1.z) * a1.z + b1.z, (v[7] - m1.w) * a1.w + b1.w);
-        y[i] = o;
+// max(v, 0): a negative bf16 has its sign bit set (NaN passes through, as in the fused epilogue)
+__device__ __forceinline__ u32x4 relu8(u32x4 v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t lo = v[e] & 0xFFFFu, hi = v[e] >> 16;
+        const bool nlo = (lo & 0x8000u) && (lo & 0x7FFFu) <= 0x7F80u;    // negative, not NaN
+        const bool nhi = (hi & 0x8000u) && (hi & 0x7FFFu) <= 0x7F80u;
+        v[e] = (nlo ? 0u : lo) | ((nhi ? 0u : hi) << 16);
+    }
+    return v;
+}
+
+__device__ __forceinline__ u32x4 add8(const u32x4 a, const u32x4 b) {
+    u32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = pack2(lo16(a[e]) + lo16(b[e]), hi16(a[e]) + hi16(b[e]));
+    return o;
+}
+
+// Element by element, from x: [the normalisation], [+ r], [ReLU], each result rounded to bf16, stored and read on as it is
+// stored, so the bits are those of separate passes.  Two pieces in flight per thread.  Bound by memory: 25088 x 512 with all three, five
+// tensor passes in 20 us where three launches took 31.6 for seven.  What the run itself has read already leaves past the caches (the
+// case of the backward pass too 78.3 -> 76.4 us, 100352 x 512 266 -> 255): only its last result is read next.
+template <bool BN, bool ADD, bool RELU>
+__global__ __launch_bounds__(256) void bn_tail_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ r, u32x4 *__restrict__ y,
+                                                      u32x4 *__restrict__ ya, u32x4 *__restrict__ yr, const float *__restrict__ ab,
+                                                      const float *__restrict__ beta, int C, size_t n16) {
+    const size_t step = (size_t)gridDim.x * blockDim.x;          // BN: a multiple of C / 8, a thread stays with its channels (11.0 -> 9.8 us at 25088 x 512)
+    const size_t first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    f32x4 a0, a1, m0, m1, b0, b1;
+    if constexpr (BN) {
+        const int ck = (int)(first % (unsigned)(C / 8));
+        a0 = *reinterpret_cast<const f32x4 *>(ab + ck * 8); a1 = *reinterpret_cast<const f32x4 *>(ab + ck * 8 + 4);
+        m0 = *reinterpret_cast<const f32x4 *>(ab + C + ck * 8); m1 = *reinterpret_cast<const f32x4 *>(ab + C + ck * 8 + 4);
+        b0 = *reinterpret_cast<const f32x4 *>(beta + ck * 8); b1 = *reinterpret_cast<const f32x4 *>(beta + ck * 8 + 4);
+    }
+    auto finish = [&](size_t i, u32x4 v, const u32x4 rv) {
+        if constexpr (BN) {
+            float f[8];
+            unpack8(v, f);
+            v.x = pack2((f[0] - m0.x) * a0.x + b0.x, (f[1] - m0.y) * a0.y + b0.y);
+            v.y = pack2((f[2] - m0.z) * a0.z + b0.z, (f[3] - m0.w) * a0.w + b0.w);
+            v.z = pack2((f[4] - m1.x) * a1.x + b1.x, (f[5] - m1.y) * a1.y + b1.y);
+            v.w = pack2((f[6] - m1.z) * a1.z + b1.z, (f[7] - m1.w) * a1.w + b1.w);
+            if constexpr (ADD || RELU) __builtin_nontemporal_store(v, y + i);
+            else y[i] = v;
+        }
+        if constexpr (ADD) {
+            v = add8(v, rv);
+            if constexpr (RELU) __builtin_nontemporal_store(v, ya + i);
+            else ya[i] = v;
+        }
+        if constexpr (RELU) yr[i] = relu8(v);
+    };
+    for (size_t i = first; i < n16; i += 2 * step) {
+        const size_t j = i + step;
+        const bool two = j < n16;
+        const u32x4 v0 = x[i], v1 = two ? x[j] : v0;
+        u32x4 r0 = {0u, 0u, 0u, 0u}, r1 = r0;
+        if constexpr (ADD) { r0 = r[i]; r1 = two ? r[j] : r0; }
+        finish(i, v0, r0);
+        if (two) finish(j, v1, r1);
     }
 }
 
-
 // Backward statistics.  Same decomposition as bn_stats_kernel; partial: [gridDim.x][4][C] floats
 // (sum d, sum d^2, sum g, sum g d with d = x - K_c).  red: [RS][CH][32].
-__global__ __launch_bounds__(1024) void bn_bwd_stats_kernel(const unsigned char *x, const unsigned char *g, float *partial,
-                                                           long long M, int C, long long rows_per_block, int CH, int RS) {
+// MASK: g is first set to zero where mask is not > 0, and stored (gm): four tensor passes instead of the five of two launches.
+template <bool MASK>
+__global__ __launch_bounds__(1024) void bn_bwd_stats_kernel(const unsigned char *x, const unsigned char *g, const unsigned char *mask,
+                                                           unsigned char *gm, float *partial, long long M, int C,
+                                                           long long rows_per_block, int CH, int RS) {
     extern __shared__ __align__(16) float red[];
     const int chunks = C / 8;
     const int t = threadIdx.x;
@@ -210,16 +267,25 @@ __global__ __launch_bounds__(1024) void bn_bwd_stats_kernel(const unsigned char 
         if (live) {
             unpack8(*reinterpret_cast<const u32x4 *>(x + (size_t)ck * 16), k);
             long long r = r0 + rsub;
-            for (; r + 3LL * RS < r1; r += 4LL * RS) {            // four rows of both tensors in flight per lane
-                u32x4 rx[4], rg[4];
+            constexpr int kRows = MASK ? 2 : 4;                   // rows of every tensor in flight per lane (128 registers)
+            for (; r + (kRows - 1) * (long long)RS < r1; r += kRows * (long long)RS) {
+                u32x4 rx[kRows], rg[kRows], rm[kRows];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kRows; ++u) {
                     const size_t at = ((size_t)(r + (long long)u * RS) * chunks + ck) * 16;
                     rx[u] = *reinterpret_cast<const u32x4 *>(x + at);
                     rg[u] = *reinterpret_cast<const u32x4 *>(g + at);
+                    if constexpr (MASK) rm[u] = *reinterpret_cast<const u32x4 *>(mask + at);
+                }
+                if constexpr (MASK) {
+#pragma unroll
+                    for (int u = 0; u < kRows; ++u) {
+                        rg[u] = keep8(rg[u], rm[u]);
+                        *reinterpret_cast<u32x4 *>(gm + ((size_t)(r + (long long)u * RS) * chunks + ck) * 16) = rg[u];
+                    }
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kRows; ++u) {
                     float v[8], w[8];
                     unpack8(rx[u], v);
                     unpack8(rg[u], w);
@@ -237,7 +303,12 @@ __global__ __launch_bounds__(1024) void bn_bwd_stats_kernel(const unsigned char 
                 const size_t at = ((size_t)r * chunks + ck) * 16;
                 float v[8], w[8];
                 unpack8(*reinterpret_cast<const u32x4 *>(x + at), v);
-                unpack8(*reinterpret_cast<const u32x4 *>(g + at), w);
+                u32x4 rg = *reinterpret_cast<const u32x4 *>(g + at);
+                if constexpr (MASK) {
+                    rg = keep8(rg, *reinterpret_cast<const u32x4 *>(mask + at));
+                    *reinterpret_cast<u32x4 *>(gm + at) = rg;
+                }
+                unpack8(rg, w);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float d = v[e] - k[e];
@@ -328,7 +399,7 @@ __global__ __launch_bounds__(1024) void bn_bwd_finalize_kernel(const unsigned ch
 __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ g,
                                                            u32x4 *__restrict__ gx, const float *__restrict__ coef, int C,
                                                            size_t n16) {
-    const size_t step = (size_t)gridDim.x * blockDim.x;          // as in bn_apply_kernel
+    const size_t step = (size_t)gridDim.x * blockDim.x;          // as in bn_tail_kernel
     const int ck = (int)((blockIdx.x * blockDim.x + threadIdx.x) % (unsigned)(C / 8));
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += step) {
         float v[8], w[8], o[8];
@@ -349,32 +420,15 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const u32x4 *__restri
     }
 }
 
-// y = max(x, 0): a negative bf16 has its sign bit set (NaN passes through, as in the fused epilogue)
 __global__ __launch_bounds__(256) void relu_kernel(const u32x4 *__restrict__ x, u32x4 *__restrict__ y, size_t n16) {
     const size_t step = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += step) {
-        u32x4 v = x[i];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t lo = v[e] & 0xFFFFu, hi = v[e] >> 16;
-            const bool nlo = (lo & 0x8000u) && (lo & 0x7FFFu) <= 0x7F80u;    // negative, not NaN
-            const bool nhi = (hi & 0x8000u) && (hi & 0x7FFFu) <= 0x7F80u;
-            v[e] = (nlo ? 0u : lo) | ((nhi ? 0u : hi) << 16);
-        }
-        y[i] = v;
-    }
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += step) y[i] = relu8(x[i]);
 }
 
 __global__ __launch_bounds__(256) void add_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ r,
                                                   u32x4 *__restrict__ y, size_t n16) {
     const size_t step = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += step) {
-        const u32x4 a = x[i], b = r[i];
-        u32x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = pack2(lo16(a[e]) + lo16(b[e]), hi16(a[e]) + hi16(b[e]));
-        y[i] = o;
-    }
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += step) y[i] = add8(x[i], r[i]);
 }
 
 static unsigned stream_blocks(size_t n16) {
@@ -386,6 +440,23 @@ static unsigned row_blocks(size_t n16, int chunks) {
     int q = chunks;
     for (int twos = 256; twos > 1 && q % 2 == 0; twos /= 2) q /= 2;
     return (stream_blocks(n16) + q - 1) / q * q;
+}
+
+// The last pass over the elements: whatever of normalisation, add and ReLU there is.
+static hipError_t launch_tail(const void *x, const ElementwiseTail &t, void *y, const float *ab, const float *beta, int C, size_t n16,
+                              hipStream_t stream) {
+    const unsigned blocks = y ? row_blocks((n16 + 1) / 2, C / 8) : stream_blocks((n16 + 1) / 2);
+    auto run = [&](auto kernel) {
+        kernel<<<dim3(blocks), dim3(256), 0, stream>>>(static_cast<const u32x4 *>(x), static_cast<const u32x4 *>(t.r), static_cast<u32x4 *>(y),
+                                                       static_cast<u32x4 *>(t.y_add), static_cast<u32x4 *>(t.y_relu), ab, beta, C, n16);
+    };
+    if (y) {
+        if (t.y_add) t.y_relu ? run(bn_tail_kernel<true, true, true>) : run(bn_tail_kernel<true, true, false>);
+        else t.y_relu ? run(bn_tail_kernel<true, false, true>) : run(bn_tail_kernel<true, false, false>);
+    } else {
+        run(bn_tail_kernel<false, true, true>);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace ops
@@ -402,11 +473,14 @@ const char *bn_train_check(const void *x, const void *y, const float *gamma, con
 size_t bn_train_scratch_bytes() { return (size_t)16 << 20; }     // partial sums + the 2 x C factors
 
 // Large tensors take workgroups of 1024 threads, a quarter as many: the same lanes share the rows, and
-// the finalize kernel, which runs on a nearly empty chip, reads a quarter of the partial sums.
+// the finalize kernel, which runs on a nearly empty chip, reads a quarter of the partial sums; half as many where a quarter would leave
+// CUs without one (forward and backward of 100352 x 512 255 -> 238 us, 25088 x 512 from memory 76.5 -> 73.3; half as many everywhere: 100352 x 64 49 -> 60).
 static void stats_shape(int chunks, long long &blocks, int &NT, int &CH, int &RS) {
     if (blocks < 256) return;
     NT = 1024;
+    const long long half = (blocks + 1) / 2, fill = half < 256 ? half : 256;
     blocks = (blocks + 3) / 4;
+    if (blocks < fill) blocks = fill;
     CH = chunks < NT ? chunks : NT;
     RS = NT / CH;
 }
@@ -418,8 +492,8 @@ size_t bn_train_fwd_scratch_bytes() { return ((size_t)4 << 20) + ((size_t)64 << 
 
 // scratch: device, scratch_bytes (>= bn_train_fwd_scratch_bytes()) bytes, 16-byte aligned.
 hipError_t launch_bn_train(const void *x, void *y, const float *gamma, const float *beta, long long M, int C, float eps,
-                           int bf16, void *scratch, size_t scratch_bytes, hipStream_t stream) {
-    if (bn_train_check(x, y, gamma, beta, M, C, bf16) || !scratch || ((uintptr_t)scratch & 15) ||
+                           int bf16, const ElementwiseTail &tail, void *scratch, size_t scratch_bytes, hipStream_t stream) {
+    if (bn_train_check(x, y, gamma, beta, M, C, bf16) || tail.bad() || !scratch || ((uintptr_t)scratch & 15) ||
         scratch_bytes < bn_train_fwd_scratch_bytes())
         return hipErrorInvalidValue;
     const int chunks = C / 8;
@@ -448,16 +522,14 @@ hipError_t launch_bn_train(const void *x, void *y, const float *gamma, const flo
     const int cl_bits = C <= 512 ? 4 : 6;
     ops::bn_finalize_kernel<<<dim3((unsigned)((C + (1 << cl_bits) - 1) >> cl_bits)), dim3(1024), 0, stream>>>(
         static_cast<const unsigned char *>(x), partial, gamma, beta, ab, M, C, (int)blocks, eps, cl_bits);
-    const size_t n16 = (size_t)M * chunks;
-    ops::bn_apply_kernel<<<dim3(ops::row_blocks(n16, chunks)), dim3(256), 0, stream>>>(
-        static_cast<const ops::u32x4 *>(x), static_cast<ops::u32x4 *>(y), ab, beta, C, n16);
-    return hipGetLastError();
+    return ops::launch_tail(x, tail, y, ab, beta, C, (size_t)M * chunks, stream);
 }
 
 // Backward of launch_bn_train.  gw: device fp32 [2][C] (dgamma, dbeta) or null.  Same scratch.
+// relu_y / gm: both or neither; gm = gy where relu_y > 0, else 0, is stored and taken in gy's place.
 hipError_t launch_bn_train_bwd(const void *x, const void *gy, void *gx, const float *gamma, float *gw, long long M, int C,
-                               float eps, int bf16, void *scratch, hipStream_t stream) {
-    if (bn_train_check(x, gx, gamma, gamma, M, C, bf16) || !gy || ((uintptr_t)gy & 15) || ((uintptr_t)gw & 15) || !scratch ||
+                               float eps, int bf16, const void *relu_y, void *gm, void *scratch, hipStream_t stream) {
+    if (bn_train_check(x, gx, gamma, gamma, M, C, bf16) || !gy || !relu_y != !gm || (((uintptr_t)relu_y | (uintptr_t)gm) & 15) || ((uintptr_t)gy & 15) || ((uintptr_t)gw & 15) || !scratch ||
         ((uintptr_t)scratch & 15))
         return hipErrorInvalidValue;
     const int chunks = C / 8;
@@ -477,11 +549,20 @@ hipError_t launch_bn_train_bwd(const void *x, const void *gy, void *gx, const fl
     const long long rpb = (M + blocks - 1) / blocks;
     blocks = (M + rpb - 1) / rpb;
     const size_t lds = (size_t)RS * CH * 32 * 4;
-    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(ops::bn_bwd_stats_kernel),
+    static const hipError_t lds_ok = [] {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(ops::bn_bwd_stats_kernel<false>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 1024 * 32 * 4);
+        return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void *>(ops::bn_bwd_stats_kernel<true>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, 1024 * 32 * 4);
+    }();
     if (lds_ok != hipSuccess) return lds_ok;
-    ops::bn_bwd_stats_kernel<<<dim3((unsigned)blocks), dim3((unsigned)NT), lds, stream>>>(
-        static_cast<const unsigned char *>(x), static_cast<const unsigned char *>(gy), partial, M, C, rpb, CH, RS);
+    auto stats = [&](auto kernel) {
+        kernel<<<dim3((unsigned)blocks), dim3((unsigned)NT), lds, stream>>>(
+            static_cast<const unsigned char *>(x), static_cast<const unsigned char *>(gy), static_cast<const unsigned char *>(relu_y),
+            static_cast<unsigned char *>(gm), partial, M, C, rpb, CH, RS);
+    };
+    gm ? stats(ops::bn_bwd_stats_kernel<true>) : stats(ops::bn_bwd_stats_kernel<false>);
+    if (gm) gy = gm;
     const int cl_bits = C <= 512 ? 4 : 6;
     ops::bn_bwd_finalize_kernel<<<dim3((unsigned)((C + (1 << cl_bits) - 1) >> cl_bits)), dim3(1024), 0, stream>>>(
         static_cast<const unsigned char *>(x), partial, gamma, coef, gw, M, C, (int)blocks, eps, cl_bits);
@@ -505,6 +586,13 @@ hipError_t launch_add(const void *x, const void *r, void *y, size_t bytes, int b
     ops::add_kernel<<<dim3(ops::stream_blocks(bytes / 16)), dim3(256), 0, stream>>>(
         static_cast<const ops::u32x4 *>(x), static_cast<const ops::u32x4 *>(r), static_cast<ops::u32x4 *>(y), bytes / 16);
     return hipGetLastError();
+}
+
+// ReLU of an add's result, in one pass.
+hipError_t launch_add_relu(const void *x, const ElementwiseTail &tail, size_t bytes, int bf16, hipStream_t stream) {
+    if (!bf16 || !x || !tail.y_add || !tail.y_relu || tail.bad() || bytes % 16 || ((uintptr_t)x & 15)) return hipErrorInvalidValue;
+    if (bytes == 0) return hipSuccess;
+    return ops::launch_tail(x, tail, nullptr, nullptr, nullptr, 8, bytes / 16, stream);
 }
 
 }  // namespace delta
