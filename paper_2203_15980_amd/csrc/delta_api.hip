@@ -123,6 +123,7 @@ struct delta_ctx {
     delta_stats_t st;
     bool skip_copies = false;
     void *bn_scratch = nullptr;                    // partial sums of DELTA_OP_BATCHNORM, allocated on first use
+    void *loss_scratch = nullptr;                  // counter and per-image losses of DELTA_OP_SOFTMAX_CE (null: one workgroup does it)
     void *static_scratch = nullptr;                // this GPU's copy of the file-scope scratch array (delta_batchnorm_static)
     float *ones = nullptr, *zeros = nullptr;       // kMaxChannels floats each (identity scale/shift of the data gradient)
     uint64_t ev_seq = 0;
@@ -534,6 +535,14 @@ delta_status delta_create(void *arena_dev, uint64_t arena_bytes, void *compute_s
             (void)hipGetLastError();
             c->static_scratch = nullptr;            // delta_batchnorm_static reports it; everything else works
         }
+        // here and not on first use, which may be inside a capture; its counter has to start at zero
+        const unsigned char zero[256] = {0};
+        if (hipMalloc(&c->loss_scratch, delta::softmax_ce_scratch_bytes(delta::kLossImages, 8, 1)) != hipSuccess ||
+            hipMemcpy(c->loss_scratch, zero, sizeof zero, hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipGetLastError();
+            if (c->loss_scratch) (void)hipFree(c->loss_scratch);
+            c->loss_scratch = nullptr;
+        }
         Block b;
         b.size = c->arena_bytes;
         c->free_blocks[0] = b;
@@ -555,6 +564,7 @@ void delta_destroy(delta_ctx *c) {
             (void)hipEventDestroy(c->timed[i].stop);
         }
         if (c->bn_scratch) (void)hipFree(c->bn_scratch);
+        if (c->loss_scratch) (void)hipFree(c->loss_scratch);
         if (c->ones) (void)hipFree(c->ones);
         if (c->zeros) (void)hipFree(c->zeros);
         (void)hipStreamDestroy(c->stream[S_D2H]);
@@ -1064,7 +1074,7 @@ delta_status delta_recompute_segment(delta_ctx *c, const delta_layer_desc *layer
             break;
         default:
             HIP_TRY(c, delta::launch_softmax_ce(xp, rp, L.N, L.Cin, L.dtype == DELTA_DTYPE_BF16,
-                                                reinterpret_cast<float *>(yp), c->stream[S_COMPUTE]));
+                                                reinterpret_cast<float *>(yp), c->loss_scratch, c->stream[S_COMPUTE]));
             break;
         }
         c->st.recompute_launches += done;
@@ -1696,22 +1706,7 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
                 break;
             }
             default:
-                if (gxp) HIP_TRY(c, delta::launch_dense_bwd(xp, L.w, L.scale, gyp, gxp, nullptr, L.N, L.Cin, L.Cout, s));
-                if (D.gw) {                                     // the weight gradient beside the chain, like the convolutions'
-                    const bool aside = 2ull * (uint64_t)L.N * L.Cin * L.Cout >= kAsideFlops;
-                    hipStream_t gs = aside ? c->stream[S_AUX] : s;
-                    if (aside) {
-                        Ev ready;
-                        if ((r = new_event(c, s, &ready)) != DELTA_OK) return r;
-                        HIP_TRY(c, hipStreamWaitEvent(gs, ready.e, 0));
-                    }
-                    HIP_TRY(c, delta::launch_dense_bwd(xp, L.w, L.scale, gyp, nullptr, static_cast<float *>(D.gw), L.N, L.Cin,
-                                                       L.Cout, gs));
-                    if (aside) {
-                        if ((r = new_event(c, gs, &c->aux_tail)) != DELTA_OK) return r;
-                        c->tensors[L.x].aux_done = c->tensors[D.gy].aux_done = c->aux_tail;
-                    }
-                }
+                HIP_TRY(c, delta::launch_dense_bwd(xp, L.w, L.scale, gyp, gxp, static_cast<float *>(D.gw), L.N, L.Cin, L.Cout, s));
                 break;
             }
             c->st.recompute_launches += 1;

@@ -163,7 +163,9 @@ struct PoolArgs {
 const char *pool_check(const PoolArgs &a, bool global_avg);
 hipError_t launch_maxpool(const PoolArgs &a, hipStream_t stream);
 hipError_t launch_avgpool(const PoolArgs &a, hipStream_t stream);
-hipError_t launch_softmax_ce(const void *logits, const void *labels, int N, int classes, int bf16, float *out,
+constexpr int kLossImages = 16384;          // most images whose losses the scratch of launch_softmax_ce holds
+size_t softmax_ce_scratch_bytes(int N, int classes, int bf16);
+hipError_t launch_softmax_ce(const void *logits, const void *labels, int N, int classes, int bf16, float *out, void *scratch,
                              hipStream_t stream);
 
 // backward.hip: backward of the fused layer (bf16 weight gradient; data gradient through the

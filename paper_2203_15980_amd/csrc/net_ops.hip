@@ -535,9 +535,78 @@ __global__ __launch_bounds__(1024) void softmax_ce_kernel(const void *logits, co
     }
 }
 
-hipError_t launch_softmax_ce(const void *logits, const void *labels, int N, int classes, int bf16, float *out,
+// The same over several workgroups: a wavefront per image, and the workgroup that finishes last adds the images'
+// losses, every 256th to a thread, then a tree (fixed, whichever workgroup it is).  `losses`: N floats, `done`: a
+// counter that is zero between launches - the last workgroup leaves it so.  Losses and counter pass between XCDs, whose L2s know nothing of
+// each other: device-scope stores, loads and counter.  us, one workgroup | this, 1000
+// classes: 17 images 4.7 | 5.4, 32 5.2 | 5.4, 64 7.2 | 6.2, 128 11.9 | 6.7, 256 22 | 8.7, 1024 79 | 22, 4096 342 | 78: from 33 images on.
+__global__ __launch_bounds__(256) void softmax_ce_wide_kernel(const void *logits, const long long *labels, int N, int classes, float *out,
+                                                              float *losses, unsigned *done) {
+    __shared__ bool last;
+    __shared__ float part[4];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, i = blockIdx.x * 4 + wv, pieces = classes / 8;
+    if (i < N) {
+        const u32x4_s *z = reinterpret_cast<const u32x4_s *>(static_cast<const uint16_t *>(logits) + (size_t)i * classes);
+        u32x4_s v[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) v[p] = z[lane + 64 * p < pieces ? lane + 64 * p : 0];
+        const long long lab = labels[i];
+        const float zl = lab >= 0 && lab < classes ? logit_at<true>(logits, (size_t)i * classes + lab) : __builtin_nanf("");
+        float mx = -INFINITY, se = 0.f;
+        auto at = [&](int k) {
+            const uint32_t w = v[k >> 3][(k & 7) >> 1];
+            return lane + 64 * (k >> 3) < pieces ? ((k & 1) ? bhi(w) : blo(w)) : -INFINITY;
+        };
+#pragma unroll
+        for (int k = 0; k < 16; ++k) mx = fmaxf(mx, at(k));
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+#pragma unroll
+        for (int k = 0; k < 16; ++k) se += lane + 64 * (k >> 3) < pieces ? __expf(at(k) - mx) : 0.f;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
+        if (lane == 0) __hip_atomic_store(losses + i, (mx + __logf(se)) - zl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};                         // four losses in flight per lane
+    for (int k = threadIdx.x; k < N; k += 4 * 256) {
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = k + 256 * u < N ? __hip_atomic_load(losses + k + 256 * u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum[u] += v[u];
+    }
+    sum[0] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum[0] += __shfl_xor(sum[0], o);
+    if (lane == 0) part[wv] = sum[0];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        out[0] = ((part[0] + part[1]) + (part[2] + part[3])) / (float)N;
+        __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// Whether launch_softmax_ce takes scratch, and how much: the counter, then the images' losses.
+size_t softmax_ce_scratch_bytes(int N, int classes, int bf16) {
+    return bf16 && classes % 8 == 0 && classes <= 1024 && N > 32 && N <= kLossImages ? 256 + (size_t)N * 4 : 0;
+}
+
+// scratch: softmax_ce_scratch_bytes of it, its first four bytes zero, one launch at a time; or null: one workgroup.
+hipError_t launch_softmax_ce(const void *logits, const void *labels, int N, int classes, int bf16, float *out, void *scratch,
                              hipStream_t stream) {
     if (!logits || !labels || !out || N <= 0 || classes <= 0) return hipErrorInvalidValue;
+    if (scratch && softmax_ce_scratch_bytes(N, classes, bf16) && !((uintptr_t)logits & 15)) {
+        softmax_ce_wide_kernel<<<dim3((N + 3) / 4), dim3(256), 0, stream>>>(logits, static_cast<const long long *>(labels), N, classes, out,
+                                                                           reinterpret_cast<float *>(static_cast<unsigned char *>(scratch) + 256),
+                                                                           static_cast<unsigned *>(scratch));
+        return hipGetLastError();
+    }
     const auto *lab = static_cast<const long long *>(labels);
     auto run = [&](auto kernel) { kernel<<<dim3(1), dim3(1024), 0, stream>>>(logits, lab, N, classes, out); };
     const bool held = classes > 256 && classes <= 1024;

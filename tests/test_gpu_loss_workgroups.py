@@ -1,0 +1,40 @@
+"""The loss over several workgroups: image counts around its lines (32 images, the scratch's 16384) and its workgroups of four, launches
+that follow each other without a synchronisation, two contexts in turn.  Sums of N fp32 losses in 1024 chains and a tree: N / 1024 + 10
+roundings of 2^-24, at 16384 images 1.6e-6 in the worst order; 1e-5 as for the other forms."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import numeric as on
+from test_gpu_backward import _small_ctx, torch_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,classes", [(32, 1000), (33, 1000), (35, 8), (64, 512), (129, 520), (257, 1024), (16384, 16), (16385, 16)])
+def test_loss_over_workgroups(torch_mod, N, classes):  # noqa: F811
+    import paper_2203_15980_amd as dl
+    rows = [synth.f32_to_bf16_bits(synth.normal(12, k, N * classes).astype(np.float32) * 3).reshape(N, classes) for k in (1, 2)]
+    labels = [synth.make_labels(12 + k, N, classes) for k in (0, 1)]
+    loss = dl.LayerDesc(x=0, res=1, y=2, dtype=dl.DTYPE_BF16, N=N, H=1, W=1, Cin=classes, Cout=1, R=1, S=1, stride=1, pad=0, relu=0,
+                        op=dl.OP_SOFTMAX_CE)
+    ctx = []
+    for z, lab in zip(rows, labels):
+        d, put, get = _small_ctx(torch_mod, [z.nbytes, N * 8, 4])
+        put(0, z)
+        put(1, lab)
+        ctx.append((d, get))
+    for k in range(6):                                           # every launch leaves the counter as it found it
+        ctx[k % 2][0].recompute_segment([loss] * (1 + k))
+    for (d, get), z, lab in zip(ctx, rows, labels):
+        d.sync()
+        zf = on.to_f64(z, "bf16")
+        top = zf.max(1)
+        ref = float(np.mean(top + np.log(np.exp(zf - top[:, None]).sum(1)) - zf[np.arange(N), lab]))
+        first = get(2, (1,), np.float32).copy()
+        print("N %d classes %d: %.8g %.8g" % (N, classes, first[0], ref), flush=True)
+        assert abs(float(first[0]) - ref) <= 1e-5 * max(abs(ref), 1.0)
+        d.recompute_segment([loss])
+        d.sync()
+        assert np.array_equal(first, get(2, (1,), np.float32))
+        d.close()
