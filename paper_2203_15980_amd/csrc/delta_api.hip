@@ -16,6 +16,7 @@
 //   - an offloaded tensor carries the event of its D2H copy; a reload waits for it.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <chrono>
 #include <cstdarg>
 #include <cstdio>
@@ -77,6 +78,7 @@ struct Tensor {
     std::vector<Ev> d2h_piece;      // when that copy went out in pieces: one per piece but the last
     Ev h2d_done;                    // pending Reload the compute stream has not waited for
     Ev aux_done;                    // last weight-gradient launch on S_AUX that reads this tensor
+    bool rests = false;             // read by a weight gradient of that size on the compute stream: its block returns as if by S_AUX (arena_free)
 };
 
 struct Timed {
@@ -102,6 +104,13 @@ constexpr size_t kStaticScratchBytes = ((size_t)4 << 20) + ((size_t)64 << 10);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void *g_static_scratch[kMaxDevices];        // per device ordinal: where that GPU keeps its copy
+// The same for the loss over several workgroups, a slot to each context that finds one free (from delta_create, which
+// has no allocation to make for it, to delta_destroy, after its streams have drained): a counter that is zero between launches, then the
+// images' losses.
+constexpr int kLossSlots = 64;
+static __device__ __align__(256) unsigned char loss_slots[kLossSlots][256 + delta::kLossImages * 4];
+static void *g_loss_slots[kMaxDevices];
+static std::atomic<uint64_t> g_loss_taken[kMaxDevices];
 
 struct delta_ctx {
     unsigned char *arena = nullptr;
@@ -123,7 +132,7 @@ struct delta_ctx {
     delta_stats_t st;
     bool skip_copies = false;
     void *bn_scratch = nullptr;                    // partial sums of DELTA_OP_BATCHNORM, allocated on first use
-    void *loss_scratch = nullptr;                  // counter and per-image losses of DELTA_OP_SOFTMAX_CE (null: one workgroup does it)
+    int loss_slot = -1;                            // this context's of the GPU's loss_slots; -1: none free, one workgroup does it
     void *static_scratch = nullptr;                // this GPU's copy of the file-scope scratch array (delta_batchnorm_static)
     float *ones = nullptr, *zeros = nullptr;       // kMaxChannels floats each (identity scale/shift of the data gradient)
     uint64_t ev_seq = 0;
@@ -210,6 +219,7 @@ void retire_events(delta_ctx *c) {
         it->second.fence = Fence();
     for (size_t i = 0; i < c->tensors.size(); ++i) {
         c->tensors[i].d2h_done = c->tensors[i].h2d_done = c->tensors[i].aux_done = Ev();
+        c->tensors[i].rests = false;
         c->tensors[i].d2h_piece.clear();
     }
     c->aux_tail = Ev();                            // every stream is idle: nothing in flight uses the caller's workspace
@@ -246,7 +256,9 @@ Ev later(const Ev &a, const Ev &b) { return a.seq > b.seq ? a : b; }
 // the blocks that rest rejoin it one by one, the longest-resting first, until something fits, so
 // the arena never fails while a fitting block exists (at the price of some fragmentation: resting
 // blocks do not merge with their neighbours).  Which block a tensor gets depends on the order of
-// calls only, never on timing: a replay that fits once fits every time.
+// calls only, never on timing: a replay that fits once fits every time.  Nor does it depend on which kernels a layer's gradients take:
+// what a weight gradient worth the second stream has read rests also where it ran on the compute stream, beside the data gradient, so that
+// an arena sized for a plan fits whatever the dispatch does.
 const size_t kCooling = 4;
 
 void insert_free(delta_ctx *c, uint64_t off, Block b) {
@@ -337,7 +349,7 @@ delta_status arena_alloc(delta_ctx *c, uint64_t bytes, int for_stream, uint64_t 
     return DELTA_OK;
 }
 
-void arena_free(delta_ctx *c, uint64_t off, const Fence &f) {
+void arena_free(delta_ctx *c, uint64_t off, const Fence &f, bool rests) {
     std::map<uint64_t, uint64_t>::iterator u = c->used.find(off);
     if (u == c->used.end()) return;
     Resting r;
@@ -349,7 +361,7 @@ void arena_free(delta_ctx *c, uint64_t off, const Fence &f) {
     c->used.erase(u);
     if (f.ev[S_D2H] || f.ev[S_H2D]) {                           // a copy may still be at it: rest until needed
         c->copying.push_back(r);
-    } else if (f.ev[S_AUX]) {                                    // a weight gradient may still read it: rest a while
+    } else if (f.ev[S_AUX] || rests) {                           // a weight gradient may still read it: rest a while
         c->cooling.push_back(r);
         if (c->cooling.size() > kCooling) {
             insert_free(c, c->cooling.front().offset, c->cooling.front().block);
@@ -373,10 +385,27 @@ hipError_t static_scratch_for(int device, void **out) {
         e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess) return e;
         if (!p) return hipErrorInvalidSymbol;
+        void *slots = nullptr;
+        if (hipGetSymbolAddress(&slots, HIP_SYMBOL(loss_slots)) == hipSuccess) g_loss_slots[device] = slots;
+        else (void)hipGetLastError();
         g_static_scratch[device] = p;
     }
     *out = g_static_scratch[device];
     return hipSuccess;
+}
+
+int take_loss_slot(int device) {
+    if (device < 0 || device >= kMaxDevices || !g_loss_slots[device]) return -1;
+    uint64_t taken = g_loss_taken[device].load();
+    for (;;) {
+        int slot = 0;
+        while (slot < kLossSlots && (taken >> slot & 1)) ++slot;
+        if (slot == kLossSlots) return -1;
+        if (g_loss_taken[device].compare_exchange_weak(taken, taken | 1ull << slot)) return slot;
+    }
+}
+void *loss_scratch(const delta_ctx *c) {
+    return c->loss_slot < 0 ? nullptr : static_cast<unsigned char *>(g_loss_slots[c->device]) + (size_t)c->loss_slot * sizeof loss_slots[0];
 }
 
 delta_status check_id(delta_ctx *c, uint32_t t) {
@@ -404,7 +433,8 @@ delta_status drop_block(delta_ctx *c, Tensor &t) {
     f.ev[S_H2D] = t.h2d_done;
     f.ev[S_AUX] = t.aux_done;
     t.h2d_done = t.aux_done = Ev();
-    arena_free(c, t.offset, f);
+    arena_free(c, t.offset, f, t.rests);
+    t.rests = false;
     t.resident = false;
     return DELTA_OK;
 }
@@ -535,14 +565,7 @@ delta_status delta_create(void *arena_dev, uint64_t arena_bytes, void *compute_s
             (void)hipGetLastError();
             c->static_scratch = nullptr;            // delta_batchnorm_static reports it; everything else works
         }
-        // here and not on first use, which may be inside a capture; its counter has to start at zero
-        const unsigned char zero[256] = {0};
-        if (hipMalloc(&c->loss_scratch, delta::softmax_ce_scratch_bytes(delta::kLossImages, 8, 1)) != hipSuccess ||
-            hipMemcpy(c->loss_scratch, zero, sizeof zero, hipMemcpyHostToDevice) != hipSuccess) {
-            (void)hipGetLastError();
-            if (c->loss_scratch) (void)hipFree(c->loss_scratch);
-            c->loss_scratch = nullptr;
-        }
+        c->loss_slot = take_loss_slot(c->device);
         Block b;
         b.size = c->arena_bytes;
         c->free_blocks[0] = b;
@@ -564,7 +587,7 @@ void delta_destroy(delta_ctx *c) {
             (void)hipEventDestroy(c->timed[i].stop);
         }
         if (c->bn_scratch) (void)hipFree(c->bn_scratch);
-        if (c->loss_scratch) (void)hipFree(c->loss_scratch);
+        if (c->loss_slot >= 0) g_loss_taken[c->device].fetch_and(~(1ull << c->loss_slot));
         if (c->ones) (void)hipFree(c->ones);
         if (c->zeros) (void)hipFree(c->zeros);
         (void)hipStreamDestroy(c->stream[S_D2H]);
@@ -1074,7 +1097,7 @@ delta_status delta_recompute_segment(delta_ctx *c, const delta_layer_desc *layer
             break;
         default:
             HIP_TRY(c, delta::launch_softmax_ce(xp, rp, L.N, L.Cin, L.dtype == DELTA_DTYPE_BF16,
-                                                reinterpret_cast<float *>(yp), c->loss_scratch, c->stream[S_COMPUTE]));
+                                                reinterpret_cast<float *>(yp), loss_scratch(c), c->stream[S_COMPUTE]));
             break;
         }
         c->st.recompute_launches += done;
@@ -1406,11 +1429,15 @@ bool wgrad_aside(const delta_layer_desc &L, const delta::ConvArgs &fa) {
 // How a layer that was asked for both gradients gets them where they are small (delta::launch_small_backward):
 // OL_LAYER - one launch for both; OL_CLASS - a strided 3x3 layer whose data gradient goes by parity class: the weight gradient in the
 // launch of class (1, 1); OL_WEIGHT - such a layer where one launch makes all four classes: the weight gradient in a launch of its own, without
-// partial sums.  `fo`: the layer's own geometry, `fa` after as_stride_1, `da` the data gradient's convolution.
-enum OneLaunch { OL_NONE, OL_LAYER, OL_CLASS, OL_WEIGHT };
+// partial sums - or where they share their reads (delta::launch_joint1x1): OL_JOINT, if the workspace holds its partial sums.  `fo`: the
+// layer's own geometry, `fa` after as_stride_1, `da` the data gradient's convolution.
+enum OneLaunch { OL_NONE, OL_LAYER, OL_CLASS, OL_WEIGHT, OL_JOINT };
 OneLaunch one_launch(const delta_bwd_desc &D, const delta::ConvArgs &fo, const delta::ConvArgs &fa, const delta::ConvArgs &da) {
     if (!D.gw || D.gx == DELTA_NO_TENSOR) return OL_NONE;
-    if (!class_dgrad(D)) return delta::small_backward_applies(&da, fa) ? OL_LAYER : OL_NONE;
+    if (!class_dgrad(D)) {
+        if (delta::small_backward_applies(&da, fa)) return OL_LAYER;
+        return delta::joint1x1_applies(fa) && D.workspace_bytes >= delta::joint1x1_workspace_bytes(fa) ? OL_JOINT : OL_NONE;
+    }
     delta::ConvArgs ca;
     class_args(D.fwd, fa.bf16, 1, 1, ca);
     if (delta::dgrad_s2_applies(ca)) return delta::small_backward_applies(nullptr, fo) ? OL_WEIGHT : OL_NONE;
@@ -1569,7 +1596,9 @@ delta_status delta_backward_workspace(delta_ctx *c, const delta_layer_desc *laye
     if (layer->op != DELTA_OP_CONV) { *out_bytes = 0; return DELTA_OK; }
     if (is_stem(*layer)) { *out_bytes = delta::stem_wgrad_workspace_bytes(a); return DELTA_OK; }
     as_stride_1(*layer, a);
-    *out_bytes = backward_workspace_bytes(*layer, a);
+    *out_bytes = backward_workspace_bytes(*layer, a);            // what is needed; what the one-pass kernel can use
+    const uint64_t joint = ((uint64_t)delta::joint1x1_workspace_bytes(a) + 255) / 256 * 256;
+    if (*out_bytes < joint) *out_bytes = joint;
     return DELTA_OK;
 }
 
@@ -1707,6 +1736,7 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
             }
             default:
                 HIP_TRY(c, delta::launch_dense_bwd(xp, L.w, L.scale, gyp, gxp, static_cast<float *>(D.gw), L.N, L.Cin, L.Cout, s));
+                if (D.gw && 2ull * (uint64_t)L.N * L.Cin * L.Cout >= kAsideFlops) c->tensors[L.x].rests = c->tensors[D.gy].rests = true;
                 break;
             }
             c->st.recompute_launches += 1;
@@ -1785,6 +1815,12 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
                     else
                         HIP_TRY(c, delta::launch_conv_scatter(ca, s));
                 }
+            } else if (one == OL_JOINT) {
+                // its sums at the END of the workspace, as a strided layer's staging: weight gradients still running use the beginning
+                const uint64_t need = delta::joint1x1_workspace_bytes(fa);
+                unsigned char *sums = static_cast<unsigned char *>(D.workspace) + ((D.workspace_bytes - need) & ~(uint64_t)255);
+                if (aux_holds(c, sums, need) && (r = join_aux(c)) != DELTA_OK) return r;
+                HIP_TRY(c, delta::launch_joint1x1(da, fa, gp, static_cast<float *>(D.gw), sums, need, s));
             } else if (one == OL_LAYER) {
                 HIP_TRY(c, delta::launch_small_backward(&da, fa, gp, static_cast<float *>(D.gw), s));
             } else {
@@ -1799,6 +1835,7 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
         if (one != OL_NONE) {
             if (one == OL_WEIGHT) HIP_TRY(c, delta::launch_small_backward(nullptr, fo, c->arena + tgy.offset, static_cast<float *>(D.gw), s));
             c->st.recompute_flops += 2ull * (uint64_t)fo.M * fo.R * fo.S * fo.Cin * fo.Cout;
+            if (wgrad_aside(L, fa)) c->tensors[L.x].rests = (class_wgrad(D, fo) ? tgy : c->tensors[D.gpre]).rests = true;
         } else if (D.gw) {
             Tensor &tx = c->tensors[L.x];
             if ((r = compute_uses(c, tx)) != DELTA_OK) return r;
@@ -1911,9 +1948,10 @@ delta_status delta_backward_kernel(delta_ctx *c, const delta_bwd_desc *desc, cha
         fo.M = L.N * fo.P * fo.Q;
         const OneLaunch one = one_launch(D, fo, fa, da);
         if (one == OL_LAYER) snprintf(gx, sizeof gx, "gx: %s%s", delta::small_backward_name(fa), strided_1x1(L) ? " + spread_add" : "");
+        if (one == OL_JOINT) snprintf(gx, sizeof gx, "gx: joint1x1 bf16");
         if (one != OL_NONE)
-            snprintf(gw, sizeof gw, "; gw: %s%s", delta::small_backward_name(fa),
-                     one == OL_LAYER ? ", the same launch" : one == OL_CLASS ? ", the launch of one class" : ", compute stream");
+            snprintf(gw, sizeof gw, "; gw: %s%s", one == OL_JOINT ? "joint1x1 bf16" : delta::small_backward_name(fa),
+                     one == OL_LAYER || one == OL_JOINT ? ", the same launch" : one == OL_CLASS ? ", the launch of one class" : ", compute stream");
         else
             snprintf(gw, sizeof gw, "%sgw: %s%s", gx[0] ? "; " : "", class_wgrad(D, fo) ? "wgrad3x3 stride 2 bf16" : delta::wgrad_kernel_name(fa),
                      wgrad_aside(L, fa) ? ", second stream" : ", compute stream");

@@ -163,7 +163,7 @@ struct PoolArgs {
 const char *pool_check(const PoolArgs &a, bool global_avg);
 hipError_t launch_maxpool(const PoolArgs &a, hipStream_t stream);
 hipError_t launch_avgpool(const PoolArgs &a, hipStream_t stream);
-constexpr int kLossImages = 16384;          // most images whose losses the scratch of launch_softmax_ce holds
+constexpr int kLossImages = 16384;          // most images whose losses the scratch of launch_softmax_ce holds (256 + 4 bytes each)
 size_t softmax_ce_scratch_bytes(int N, int classes, int bf16);
 hipError_t launch_softmax_ce(const void *logits, const void *labels, int N, int classes, int bf16, float *out, void *scratch,
                              hipStream_t stream);
@@ -194,10 +194,16 @@ int wgrad_splits(long long pixels, int tiles, double pixel_ns, double sums_ns);
 const char *wgrad1x1_check(const ConvArgs &a);
 size_t wgrad1x1_workspace_bytes(const ConvArgs &a);
 hipError_t launch_wgrad1x1(const ConvArgs &a, const void *g, float *gw, void *workspace, size_t workspace_bytes, hipStream_t stream);
+hipError_t launch_wgrad1x1_reduce(const float *partial, const float *scale, float *gw, int K, int C, int kt, int ct, int nsplit, hipStream_t stream);
 const char *wgrad3x3_check(const ConvArgs &a);
 size_t wgrad3x3_workspace_bytes(const ConvArgs &a);
 hipError_t launch_wgrad3x3(const ConvArgs &a, const void *g, float *gw, void *workspace, size_t workspace_bytes, hipStream_t stream);
 
+// joint1x1.hip: both gradients of a 1x1 stride-1 bf16 layer in one pass over its tensors (da: the data gradient's convolution, fa: the layer)
+bool joint1x1_applies(const ConvArgs &fa);
+size_t joint1x1_workspace_bytes(const ConvArgs &fa);
+hipError_t launch_joint1x1(const ConvArgs &da, const ConvArgs &fa, const void *g, float *gw, void *workspace, size_t workspace_bytes,
+                           hipStream_t stream);
 // small_backward.hip: both gradients of a layer that cannot fill the chip in one launch (da: the data gradient's convolution
 // or null for the weight gradient alone, fa: the layer as
 // launch_wgrad or launch_wgrad_s2 takes it)

@@ -202,7 +202,7 @@ __global__ __launch_bounds__(512) void wgrad1x1_kernel(Args a) {
 
 // gw[k][c] = scale_k * sum over the splits of the partial sums, in a fixed order.  64 consecutive f32x4 of the blob (one per
 // lane) are shared by G wavefronts (wavefront g adds splits g, g + G, ..., four loads in flight), whose G sums are then
-// added in the order of g; a workgroup of 8 wavefronts takes 8 / G groups.  G follows the number of splits (about
+// added in a fixed tree; a workgroup of 8 wavefronts takes 8 / G groups.  G follows the number of splits (about
 // four loads per lane): with few splits (the wide layers: 4 or 16) every wavefront still has loads to issue, with many
 // (256) the loads of a group are spread over the whole workgroup.  (Splitting a wavefront's lanes over four splits as
 // well makes this kernel faster alone, 4 us at best, and the backward pass 3 % slower: beside the data-gradient
@@ -223,15 +223,21 @@ __global__ __launch_bounds__(512) void wgrad_reduce_kernel(const float *partial,
     for (; sp + 3 * G < nsplit; sp += 4 * G) {                   // four independent loads in flight
         const f32x4 v0 = src[(size_t)sp * per_split], v1 = src[(size_t)(sp + G) * per_split];
         const f32x4 v2 = src[(size_t)(sp + 2 * G) * per_split], v3 = src[(size_t)(sp + 3 * G) * per_split];
-        sum += v0; sum += v1; sum += v2; sum += v3;
+        sum += (v0 + v1) + (v2 + v3);                            // in pairs: fewer roundings of the whole sum
     }
     for (; sp < nsplit; sp += G) sum += src[(size_t)sp * per_split];
     if constexpr (G > 1) {
         part[wave][lane] = sum;
         __syncthreads();
         if (grp != 0) return;
+        f32x4 level[G];
 #pragma unroll
-        for (int g = 1; g < G; ++g) sum += part[wave + g][lane];
+        for (int g = 0; g < G; ++g) level[g] = part[wave + g][lane];
+#pragma unroll
+        for (int n = G / 2; n; n /= 2)
+#pragma unroll
+            for (int g = 0; g < n; ++g) level[g] += level[g + n];
+        sum = level[0];
     }
     // idx = (((tile * pairs + pair) * 4 + quadrant) * 4 + e4) * 64 + lane
     const int i = (int)(idx >> 6), e4 = i & 3, quadrant = (i >> 2) & 3, pair = (i >> 4) % pairs, tile = (i >> 4) / pairs;
@@ -321,14 +327,20 @@ hipError_t launch_wgrad1x1(const ConvArgs &a, const void *g, float *gw, void *wo
     default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
-    const size_t groups = (size_t)(a.Cout / 64) * (a.Cin / 64) * 16;
-    const int G = p.nsplit <= 4 ? 1 : p.nsplit <= 8 ? 2 : p.nsplit <= 16 ? 4 : 8;
+    return launch_wgrad1x1_reduce(w.partial, a.scale, gw, a.Cout, a.Cin, p.kt, p.ct, p.nsplit, stream);
+}
+
+// Partial sums of `nsplit` splits, [nsplit][K C / (4096 kt ct)][kt ct][4 tiles][4][64 lanes] f32x4 (wgrad1x1_kernel's layout): gw = scale * their sum.
+hipError_t launch_wgrad1x1_reduce(const float *partial, const float *scale, float *gw, int K, int C, int kt, int ct, int nsplit, hipStream_t stream) {
+    const size_t groups = (size_t)(K / 64) * (C / 64) * 16;
+    const int G = nsplit <= 4 ? 1 : nsplit <= 8 ? 2 : nsplit <= 16 ? 4 : 8;
     const dim3 grid((unsigned)(groups / (8 / G))), block(512);
+    auto run = [&](auto kernel) { kernel<<<grid, block, 0, stream>>>(partial, scale, gw, K, C, kt, ct, nsplit); };
     switch (G) {
-    case 1: wg1::wgrad_reduce_kernel<1><<<grid, block, 0, stream>>>(w.partial, a.scale, gw, a.Cout, a.Cin, p.kt, p.ct, p.nsplit); break;
-    case 2: wg1::wgrad_reduce_kernel<2><<<grid, block, 0, stream>>>(w.partial, a.scale, gw, a.Cout, a.Cin, p.kt, p.ct, p.nsplit); break;
-    case 4: wg1::wgrad_reduce_kernel<4><<<grid, block, 0, stream>>>(w.partial, a.scale, gw, a.Cout, a.Cin, p.kt, p.ct, p.nsplit); break;
-    default: wg1::wgrad_reduce_kernel<8><<<grid, block, 0, stream>>>(w.partial, a.scale, gw, a.Cout, a.Cin, p.kt, p.ct, p.nsplit); break;
+    case 1: run(wg1::wgrad_reduce_kernel<1>); break;
+    case 2: run(wg1::wgrad_reduce_kernel<2>); break;
+    case 4: run(wg1::wgrad_reduce_kernel<4>); break;
+    default: run(wg1::wgrad_reduce_kernel<8>); break;
     }
     return hipGetLastError();
 }

@@ -1,0 +1,90 @@
+"""Both gradients of a 1x1 layer in one pass over its tensors: every tile the kernel has (64 KT x 64 CT of gradient and input channels, both chunk
+sizes), slices of the input channels, chunks that are whole, one short and one pixel, with and without gx_add and mask.  Reference and bounds as
+in the helper (the sums here have up to 25088 terms: 1e-5 is 2^-24 sqrt(25088) with a margin of one)."""
+import numpy as np
+import pytest
+
+from test_gpu_small_backward import test_both_gradients_match_float64 as both
+from test_gpu_parity import make_delta, torch_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+JOINT = "joint1x1 bf16, the same launch"
+CASES = [
+    # dtype  N   H    W   Cin Cout R stride add mask
+    ("bf16", 1, 128, 200,  64,  64, 1, 1, True,  True,  JOINT),     # 25600 pixels: whole chunks of 64
+    ("bf16", 1, 131, 193,  64,  64, 1, 1, False, True,  JOINT),     # 25283: 3 of the last chunk's 64
+    ("bf16", 3,  97,  89, 128,  64, 1, 1, True,  False, JOINT),
+    ("bf16", 1, 131, 193, 256,  64, 1, 1, True,  True,  JOINT),     # chunks of 32
+    ("bf16", 1, 151, 167, 256,  64, 1, 1, False, False, JOINT),     # 25217: one pixel of the last chunk
+    ("bf16", 3,  97,  89, 192,  64, 1, 1, True,  True,  JOINT),     # three slices of 64 input channels
+    ("bf16", 1, 131, 193,  64, 128, 1, 1, True,  True,  JOINT),
+    ("bf16", 1, 131, 193, 128, 128, 1, 1, False, True,  JOINT),
+    ("bf16", 1, 131, 193, 256, 128, 1, 1, True,  True,  JOINT),
+    ("bf16", 1, 131, 193, 512, 128, 1, 1, False, True,  JOINT),     # two slices of 256
+    ("bf16", 1, 131, 193,  64, 256, 1, 1, False, True,  JOINT),
+    ("bf16", 1, 131, 193,  64, 256, 1, 1, True,  True,  JOINT),
+    ("bf16", 1, 131, 193, 128, 256, 1, 1, True,  False, JOINT),
+    ("bf16", 1, 131, 193,  64, 512, 1, 1, False, True,  JOINT),
+    ("bf16", 1, 131, 193, 128, 512, 1, 1, True,  True,  JOINT),     # two slices of 64
+    ("bf16", 1,  64,  65,  64,  64, 1, 1, True,  True,  JOINT),     # 65 chunks: 33 workers of two, the last has one
+    ("bf16", 1,  79,  89, 1024, 256, 1, 1, True, True,  JOINT),     # eight slices of 128; 31 workers, the longest with eight chunks
+    ("bf16", 1,  79,  89, 1152, 256, 1, 1, True, True,  "wgrad1x1 bf16, second stream"),      # nine slices
+    ("bf16", 1,  95,  95, 128, 512, 1, 1, False, True,  JOINT),     # 9025 pixels
+    ("bf16", 1,  95,  94, 128, 512, 1, 1, False, True,  "wgrad1x1 bf16, second stream"),
+    ("bf16", 1,  95,  95, 192, 512, 1, 1, False, True,  "wgrad1x1 bf16, second stream"),      # three slices of 64
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_%dx%dx%d_%d_%d_r%d_s%d" % c[:8])
+def test_every_tile_matches_float64(torch_mod, case):  # noqa: F811
+    both(torch_mod, case)
+
+
+def test_sums_share_a_workspace_with_the_second_stream(torch_mod):  # noqa: F811
+    """A 3x3 weight gradient on the second stream and the one-pass kernel in turn, on a workspace that holds one at a time and on one that
+    holds both: the bits are those of runs with a synchronisation between, and a workspace too small for the one-pass kernel's sums takes the two
+    kernels."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    N, H, W, C, K = 16, 56, 56, 64, 256
+    sizes = [N * H * W * C * 2, N * H * W * K * 2, N * H * W * K * 2, N * H * W * C * 2, N * H * W * C * 2]       # x, y, gy, gx, 3x3's gy
+    d = make_delta(torch, sum(sizes) + N * H * W * C * 4 + (2 << 20))
+    d.bind(sizes + [N * H * W * C * 2])                          # 5: the 3x3 layer's gx
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    for t in (0, 2, 4):
+        d.alloc(t)
+        d.arena[d.tensor_ptr(t) - d.arena.data_ptr():][:sizes[t]].view(torch.bfloat16).normal_(generator=gen)
+    d.alloc(1)
+    one, w = torch.ones(K, device="cuda:0"), torch.randn(K * C * 9, device="cuda:0", generator=gen).to(torch.bfloat16)
+    lay = lambda y, co, R: dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=y, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=one.data_ptr(),      # noqa: E731
+                                        shift=one.data_ptr(), N=N, H=H, W=W, Cin=C, Cout=co, R=R, S=R, stride=1, pad=R // 2, relu=0)
+    f1, f3 = lay(1, K, 1), lay(4, C, 3)
+    n1, n3 = d.backward_workspace(f1), d.backward_workspace(f3)
+
+    def run(ws, apart):
+        gws = [torch.full((K * C * 9,), float("nan"), device="cuda:0") for _ in range(4)]
+        b = lambda f, gy, gx, i: dl.BwdDesc(fwd=f, gy=gy, gpre=gy, gx=gx, gx_add=dl.NO_TENSOR, wt=w.data_ptr(), gw=gws[i].data_ptr(),  # noqa: E731
+                                            workspace=ws.data_ptr(), workspace_bytes=ws.numel())
+        descs = [b(f3, 4, 5, 0), b(f1, 2, 3, 1), b(f3, 4, 5, 2), b(f1, 2, 3, 3)]
+        torch.cuda.synchronize()
+        for part in ([[x] for x in descs] if apart else [descs]):
+            d.backward_segment(part)
+            if apart:
+                d.backward_join()
+                d.sync()
+        d.backward_join()
+        d.sync()
+        name = d.backward_kernel(descs[1])
+        return name, [g.cpu().numpy()[:K * C if i & 1 else C * C * 9] for i, g in enumerate(gws)]
+    for nbytes in (max(n1, n3), n1 + n3 + 256):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda:0")
+        name, ref = run(ws, True)
+        assert name.endswith(JOINT) and all(np.all(np.isfinite(r)) for r in ref)
+        assert np.array_equal(ref[0], ref[2]) and np.array_equal(ref[1], ref[3])
+        for _ in range(3):
+            assert all(np.array_equal(a, b) for a, b in zip(run(ws, False)[1], ref))
+    name, small = run(torch.empty(n1 - 256, dtype=torch.uint8, device="cuda:0"), False)
+    assert "wgrad1x1" in name
+    assert float(np.max(np.abs(small[1] - ref[1])) / np.max(np.abs(ref[1]))) <= 1e-5
+    d.close()

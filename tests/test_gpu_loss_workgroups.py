@@ -38,3 +38,24 @@ def test_loss_over_workgroups(torch_mod, N, classes):  # noqa: F811
         d.sync()
         assert np.array_equal(first, get(2, (1,), np.float32))
         d.close()
+
+
+def test_more_contexts_than_slots(torch_mod):  # noqa: F811
+    """Contexts beyond those that find a slot for their losses take one workgroup; a slot given back is taken again."""
+    import paper_2203_15980_amd as dl
+    N, classes = 64, 1000
+    z, lab = synth.f32_to_bf16_bits(synth.normal(12, 1, N * classes).astype(np.float32) * 3).reshape(N, classes), synth.make_labels(12, N, classes)
+    loss = dl.LayerDesc(x=0, res=1, y=2, dtype=dl.DTYPE_BF16, N=N, H=1, W=1, Cin=classes, Cout=1, R=1, S=1, stride=1, pad=0, relu=0,
+                        op=dl.OP_SOFTMAX_CE)
+    got = []
+    for count in (67, 3):
+        ctx = [_small_ctx(torch_mod, [z.nbytes, N * 8, 4], mb=1) for _ in range(count)]
+        for d, put, get in ctx:
+            put(0, z)
+            put(1, lab)
+            d.recompute_segment([loss])
+        for d, put, get in ctx:
+            d.sync()
+            got.append(float(get(2, (1,), np.float32)[0]))
+            d.close()
+    assert max(got) - min(got) <= 1e-5 * max(got) and got[0] == got[67]

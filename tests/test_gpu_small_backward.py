@@ -30,7 +30,7 @@ CASES = [
     ("bf16", 1,  2,   2,   64,  64, 3, 2, False, False, CLASS),
     ("bf16", 2,  9,  12,  128, 128, 3, 2, True,  True,  OWN),        # its data gradient in one launch
     ("bf16", 1,  64, 64,   64,  64, 1, 1, False, True,  SAME),       # 4096 positions: the last that go this way with few tiles of gw
-    ("bf16", 1,  64, 65,   64,  64, 1, 1, False, True,  "wgrad1x1 bf16, compute stream"),
+    ("bf16", 1,  64, 65,   64,  64, 1, 1, False, True,  "joint1x1 bf16, the same launch"),
     ("bf16", 1,  64, 100, 256, 256, 1, 1, False, True,  SAME),       # 6400: the last with 64
     ("bf16", 1,  56, 56,  256,  64, 1, 1, True,  True,  SAME),
     ("f32",  1,  1,   1,   32,  64, 1, 1, True,  True,  SAME),
