@@ -256,9 +256,9 @@ __global__ __launch_bounds__(1024) void wgrad_f32_kernel(const float *x, const f
 template <int T, bool TAPS>
 __global__ __launch_bounds__(1024) void wgrad_f32_flat_kernel(const float *x, const float *g, const float *scale, float *gw, int H, int W, int C,
                                                               int K, int R, int pad, int M, Divisor dhw, Divisor dw) {
-    __shared__ float part[16 * T * T * 256];
+    __shared__ float part[16 * T * T * 256], factors[64];
     wgrad_f32_tile<T, TAPS, 16>(x, g, scale, gw, H, W, C, K, R, pad, M, dhw, dw, blockIdx.x * (16 * T), blockIdx.y * (16 * T), blockIdx.z, threadIdx.x,
-                                part);
+                                part, factors);
 }
 
 }  // namespace bwd

@@ -17,7 +17,8 @@
 //    lines and the load unit then moves 13 bytes a cycle and CU: 2048 -> 512 at M = 784 20 us that way;
 //  * padding taps, pixels past M, channels past Cout and steps past the end are offsets outside the buffer
 //    descriptors, which load zeros, as in conv_igemm.hip;
-//  * residual and mask are requested before the first step, scale and shift before the sums meet.
+//  * residual and mask are requested before the first step, scale and shift too, straight into LDS: requested where they are needed they
+//    were one more round trip to memory at the end (three fp32 bottlenecks, 21 launches with it: 177 -> 173 us; an encoder layer of 1 x 77, four: 41.4 -> 40.1).
 // Operands are re-read from the L1 / L2 by every tile that needs them (64 FLOP per byte loaded), which
 // is what ends the kernel's range: see splitk_applies for where the lines lie and what both sides measured.
 #include <hip/hip_runtime.h>
@@ -33,7 +34,8 @@ template <bool BF16, int KW, int AHEAD>
 __global__ __launch_bounds__(KW * 64) void conv_splitk_kernel(ConvArgs a, int tiles_m, int tiles_n, int pixels_first,
                                                               Divisors inv) {
     __shared__ __align__(16) unsigned char smem[KW * kWaveLds];
-    conv_tile<BF16, KW, AHEAD>(a, tiles_m, tiles_n, pixels_first, inv, xcd_run(blockIdx.x, gridDim.x), threadIdx.x, smem);
+    __shared__ __align__(16) float factors[64];
+    conv_tile<BF16, KW, AHEAD>(a, tiles_m, tiles_n, pixels_first, inv, xcd_run(blockIdx.x, gridDim.x), threadIdx.x, smem, factors);
 }
 
 template <bool BF16, int KW, int AHEAD>

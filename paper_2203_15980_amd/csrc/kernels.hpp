@@ -51,6 +51,12 @@ __device__ __forceinline__ void load_lds_b128(const unsigned char *base, uint32_
                  :: "v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
 }
 
+// 4 bytes per lane: lane l's land at byte `lds` + 4 l.
+__device__ __forceinline__ void load_lds_b32(const void *at, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
+                 :: "v"(at), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
+}
+
 // The test behind every ReLU mask of the backward pass.  bf16: greater than zero <=> sign bit clear,
 // not zero and not NaN.  Returns the bits of `v` (two bf16 values) with the halves cleared whose
 // half of `m` fails it.

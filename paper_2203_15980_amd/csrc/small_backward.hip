@@ -51,10 +51,14 @@ struct WeightArgs {
 
 // bf16: 32 TW x 32 TW of (k, c) of one tap.  PLAIN: 1x1, stride 1 - position m reads pixel m.
 template <int TW, bool PLAIN>
-__device__ __forceinline__ void weight_tile(const WeightArgs &a, int k0, int c0, int tap, int tid, unsigned char *smem) {
+__device__ __forceinline__ void weight_tile(const WeightArgs &a, int k0, int c0, int tap, int tid, unsigned char *smem, float *factors) {
     constexpr int kRows = 16 / TW, kStep = 2 * kRows;            // rows of 64 TW bytes per load instruction; positions of a step: two of those
     constexpr int kPitch = 64 * TW, kAhead = 2;                  // steps in flight (128 registers: two workgroups to a CU)
     const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wv == 0) {                                               // scale of the tile's channels, straight into LDS
+        typedef __attribute__((address_space(3))) float *lptr_t;
+        load_lds_b32(a.scale + k0 + (lane & (32 * TW - 1)), (uint32_t)(uintptr_t)(lptr_t)factors);
+    }
     const __amdgpu_buffer_rsrc_t grsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.g), 0, (int)((uint32_t)a.M * (uint32_t)a.K * 2u), 0x00020000);
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, (int)a.xbytes, 0x00020000);
     const int row = lane / (4 * TW), seg = lane % (4 * TW);
@@ -148,6 +152,7 @@ __device__ __forceinline__ void weight_tile(const WeightArgs &a, int k0, int c0,
                 if constexpr (kSums == 4) v = (v + acc[1][0][0]) + (acc[2][0][0] + acc[3][0][0]);
                 *reinterpret_cast<f32x4 *>(stg + u * 4096 + e4 * 1024 + lane * 16) = f32x4{v[4 * e4], v[4 * e4 + 1], v[4 * e4 + 2], v[4 * e4 + 3]};
             }
+        if (at == 0 && wv == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid < kPer * 256) {
             f32x4 part[8];
@@ -155,9 +160,10 @@ __device__ __forceinline__ void weight_tile(const WeightArgs &a, int k0, int c0,
             for (int v = 0; v < 8; ++v) part[v] = *reinterpret_cast<const f32x4 *>(smem + v * splitk::kWaveLds + tid * 16);
             const f32x4 sum = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
             const int tile = at + (tid >> 8), e4 = (tid >> 6) & 3;
-            const int k = k0 + 32 * (tile / TW) + 8 * e4 + 4 * (lane >> 5), c = c0 + 32 * (tile % TW) + (lane & 31);
+            const int kl = 32 * (tile / TW) + 8 * e4 + 4 * (lane >> 5), k = k0 + kl, c = c0 + 32 * (tile % TW) + (lane & 31);
+            const f32x4 sc = *reinterpret_cast<const f32x4 *>(factors + kl);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) a.gw[((size_t)(k + e) * taps + tap) * a.C + c] = sum[e] * a.scale[k + e];
+            for (int e = 0; e < 4; ++e) a.gw[((size_t)(k + e) * taps + tap) * a.C + c] = sum[e] * sc[e];
         }
     }
 }
@@ -167,21 +173,23 @@ template <bool BF16, int KW, int TW, bool PLAIN>
 __global__ __launch_bounds__(512) void small_backward_kernel(ConvArgs da, int tiles_m, int tiles_n, int pixels_first, splitk::Divisors inv,
                                                              WeightArgs w) {
     __shared__ __align__(16) unsigned char smem[kLds];
+    __shared__ __align__(16) float factors[128];
     const int tid = threadIdx.x;
     if ((int)blockIdx.x < w.blocks) {
         const int logical = (int)splitk::xcd_run(blockIdx.x, w.blocks);
         const int at = divide(logical, w.taps), tap = logical - at * (w.R * w.R), kt = divide(at, w.dct), ct = at - kt * w.ctiles;
         if constexpr (BF16)
-            weight_tile<TW, PLAIN>(w, kt * 32 * TW, ct * 32 * TW, tap, tid, smem);
+            weight_tile<TW, PLAIN>(w, kt * 32 * TW, ct * 32 * TW, tap, tid, smem, factors);
         else
             wgrad_f32_tile<TW, !PLAIN, 8>(static_cast<const float *>(w.x), static_cast<const float *>(w.g), w.scale, w.gw, w.P, w.Q, w.C, w.K, w.R,
-                                          w.pad, w.M, w.pq, w.q, kt * 16 * TW, ct * 16 * TW, tap, tid, reinterpret_cast<float *>(smem));
+                                          w.pad, w.M, w.pq, w.q, kt * 16 * TW, ct * 16 * TW, tap, tid, reinterpret_cast<float *>(smem), factors);
         return;
     }
     constexpr int kGroups = 8 / KW;                              // tiles of gx to a workgroup
     const int group = __builtin_amdgcn_readfirstlane(tid / (KW * 64));
     const unsigned logical = splitk::xcd_run(blockIdx.x - w.blocks, gridDim.x - w.blocks) * kGroups + group;
-    splitk::conv_tile<BF16, KW, 2>(da, tiles_m, tiles_n, pixels_first, inv, logical, tid & (KW * 64 - 1), smem + group * KW * splitk::kWaveLds);
+    splitk::conv_tile<BF16, KW, 2>(da, tiles_m, tiles_n, pixels_first, inv, logical, tid & (KW * 64 - 1), smem + group * KW * splitk::kWaveLds,
+                                   factors + group * 64);
 }
 
 template <bool BF16, int KW, int TW, bool PLAIN>

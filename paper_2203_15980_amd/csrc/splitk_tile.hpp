@@ -49,7 +49,7 @@ __device__ __forceinline__ void mma(const u32x4 w, const u32x4 x, f32x16 &acc) {
     }
 }
 
-struct Divisors { Divisor pq, q, cs, s; };
+struct Divisors { Divisor pq, q, cs, s, tiles; };      // tiles: along the axis that walks fastest
 
 // Contiguous runs of tiles per XCD (workgroup number % 8): the tile of workgroup `block` of `blocks`.
 __device__ __forceinline__ unsigned xcd_run(unsigned block, unsigned blocks) {
@@ -57,22 +57,28 @@ __device__ __forceinline__ unsigned xcd_run(unsigned block, unsigned blocks) {
     return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
 }
 
-// Tile `logical` of the output by KW wavefronts (thread `tid` of KW * 64, smem: KW * kWaveLds bytes of their own); a number past the last
-// tile computes nothing.  The axis that walks fastest is the one whose operand is smaller, so that an XCD reads its share of the
+// Tile `logical` of the output by KW wavefronts (thread `tid` of KW * 64, smem: KW * kWaveLds bytes of their own, factors: 256 more); a number
+// past the last tile computes nothing.  The axis that walks fastest is the one whose operand is smaller, so that an XCD reads its share of the
 // larger one once.  One barrier, which the whole workgroup has to reach.
 // wR, wS, w_r0, w_s0, w_step of `a` are filled by the launcher for every form (see ConvArgs).
 // AHEAD: steps in flight per wavefront.
 template <bool BF16, int KW, int AHEAD>
 __device__ __forceinline__ void conv_tile(const ConvArgs &a, int tiles_m, int tiles_n, int pixels_first, const Divisors &inv,
-                                          unsigned logical, int tid, unsigned char *smem) {
+                                          unsigned logical, int tid, unsigned char *smem, float *factors) {
     constexpr int ES = BF16 ? 2 : 4;
     const int lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
-    const int tm = pixels_first ? (int)(logical % tiles_m) : (int)(logical / tiles_n);
-    const int tn = pixels_first ? (int)(logical / tiles_m) : (int)(logical % tiles_n);
+    const int slow = divide((int)logical, inv.tiles), fast = (int)logical - slow * (pixels_first ? tiles_m : tiles_n);
+    const int tm = pixels_first ? fast : slow, tn = pixels_first ? slow : fast;
     const int m0 = tm * kTile, n0 = tn * kTile;
 
+    // scale, then shift of the tile's 32 channels: straight into LDS, where they need no register until the end
+    if (wv == 0) {
+        const int c = n0 + l32 < a.Cout ? n0 + l32 : a.Cout - 1;
+        typedef __attribute__((address_space(3))) float *lptr_t;
+        load_lds_b32((half ? a.shift : a.scale) + c, (uint32_t)(uintptr_t)(lptr_t)factors);
+    }
     // ---- epilogue operands of this thread: pixel m0 + tid / 8, channels n0 + 4 * (tid % 8) .. + 3
     const int PQ = a.P * a.Q;
     const int em = m0 + (tid >> 3), ec = n0 + 4 * (tid & 7);
@@ -184,13 +190,10 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int tiles_m, int ti
         const f32x4 v = {acc[4 * rb], acc[4 * rb + 1], acc[4 * rb + 2], acc[4 * rb + 3]};
         *reinterpret_cast<f32x4 *>(part + l32 * kPitch + 8 * rb + 4 * half) = v;
     }
-    f32x4 esc = {0.f, 0.f, 0.f, 0.f}, esh = {0.f, 0.f, 0.f, 0.f};
-    if (finishes) {                                              // only now: two workgroups of 8 wavefronts fit a CU with 128 registers
-        esc = *reinterpret_cast<const f32x4 *>(a.scale + ec);
-        esh = *reinterpret_cast<const f32x4 *>(a.shift + ec);
-    }
+    if (wv == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the factors, long since
     __syncthreads();
     if (!finishes) return;
+    const f32x4 esc = *reinterpret_cast<const f32x4 *>(factors + 4 * (tid & 7)), esh = *reinterpret_cast<const f32x4 *>(factors + 32 + 4 * (tid & 7));
     const unsigned char *sum0 = smem + ((tid >> 3) * kPitch + 4 * (tid & 7)) * 4;
     f32x4 v = *reinterpret_cast<const f32x4 *>(sum0);
 #pragma unroll
@@ -228,10 +231,11 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int tiles_m, int ti
 inline long long tiles_of(const ConvArgs &a) {
     return (((long long)a.M + kTile - 1) / kTile) * ((a.Cout + kTile - 1) / kTile);
 }
-inline Divisors divisors_of(const ConvArgs &a) {
-    return Divisors{make_divisor(a.P * a.Q), make_divisor(a.Q), make_divisor(a.Cin * (a.bf16 ? 2 : 4) / kStepBytes), make_divisor(a.S)};
-}
 inline bool weights_larger(const ConvArgs &a) { return (long long)a.Cout * a.R * a.S * a.Cin > (long long)a.N * a.H * a.W * a.Cin; }
+inline Divisors divisors_of(const ConvArgs &a) {
+    return Divisors{make_divisor(a.P * a.Q), make_divisor(a.Q), make_divisor(a.Cin * (a.bf16 ? 2 : 4) / kStepBytes), make_divisor(a.S),
+                    make_divisor(((weights_larger(a) ? a.M : a.Cout) + kTile - 1) / kTile)};
+}
 
 }  // namespace splitk
 }  // namespace delta

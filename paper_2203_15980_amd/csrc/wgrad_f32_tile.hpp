@@ -16,16 +16,21 @@ namespace delta {
 // 2 x 32 x 32 positions, us by the form with 64-bit addresses -> this one: 64 -> 256 10.0 -> 7.0, 256 -> 64 10.0 -> 9.1, 64 -> 64 10.0 -> 6.5, 3x3
 // 64 -> 64 10.0 -> 9.6.
 // Two sums in turn and a tree over the wavefronts: 2.1e-7 from 64 bits (norm) at 2048 positions whether 8 or 16 wavefronts share them.
-// part: kWaves T T 256 floats of LDS.
+// part: kWaves T T 256 floats of LDS, factors: 64 more.
 template <int T, bool TAPS, int kWaves>
 __device__ __forceinline__ void wgrad_f32_tile(const float *x, const float *g, const float *scale, float *gw, int H, int W, int C, int K, int R,
-                                               int pad, int M, Divisor dhw, Divisor dw, int k0, int c0, int tap, int tid, float *part) {
+                                               int pad, int M, Divisor dhw, Divisor dw, int k0, int c0, int tap, int tid, float *part,
+                                               float *factors) {
     typedef uint32_t uvec __attribute__((ext_vector_type(T)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     constexpr int kOutOfRange = (int)0x80000000;                 // outside both buffer descriptors
     constexpr int kSteps = T == 1 && !TAPS ? 16 : 8;
     const int lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wv == 0) {                                               // scale of the tile's channels, straight into LDS
+        typedef __attribute__((address_space(3))) float *lptr_t;
+        load_lds_b32(scale + k0 + (lane & (16 * T - 1)), (uint32_t)(uintptr_t)(lptr_t)factors);
+    }
     const int dr = TAPS ? tap / R - pad : 0, ds = TAPS ? tap % R - pad : 0;
     const int per = ((M + kWaves - 1) / kWaves + 3) / 4 * 4;
     const int first = wv * per, end = first + per < M ? first + per : M;
@@ -85,6 +90,7 @@ __device__ __forceinline__ void wgrad_f32_tile(const float *x, const float *g, c
         for (int j = 0; j < T; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) part[wv * (T * T * 256) + ((i * T + j) * 4 + e) * 64 + lane] = acc[0][i][j][e] + acc[1][i][j][e];
+    if (wv == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
     for (int at = tid; at < T * T * 256; at += kWaves * 64) {
@@ -96,8 +102,8 @@ __device__ __forceinline__ void wgrad_f32_tile(const float *x, const float *g, c
 #pragma unroll
             for (int v = 0; v < n; ++v) level[v] += level[v + n];
         // lane of this sum: column (c) l % 16, row (k) 4 (l / 16) + e of the tile's (i, j) interleave
-        const int k = k0 + T * (4 * quad + ((at >> 6) & 3)) + (at >> 8) / T, c = c0 + T * l16 + (at >> 8) % T;
-        gw[((size_t)k * R * R + tap) * C + c] = level[0] * scale[k];
+        const int kl = T * (4 * quad + ((at >> 6) & 3)) + (at >> 8) / T, k = k0 + kl, c = c0 + T * l16 + (at >> 8) % T;
+        gw[((size_t)k * R * R + tap) * C + c] = level[0] * factors[kl];
     }
 }
 
