@@ -229,14 +229,15 @@ bool small_backward_applies(const ConvArgs *da, const ConvArgs &fa) {
     //     1x1 2048 -> 512  M = 49 15 | 6.8    392 22 | 15    784 31 | 23 (21)    1176 31 | 32 (27)    1568 30 | 40 (35)
     //     3x3 256 -> 256   M = 196 20 | 7.9   784 25 | 11    1568 32 | 16 (18)   3136 38 | 24 (28)    6272 45 | 42 (49)
     //     3x3 512 -> 512   M = 49 27 | 16     392 32 | 23 (17)   784 41 | 26 (27)   1568 47 | 44 (46)
-    //   From 1 GFLOP on the left side is two streams and the host's 30 us for them; the line at 26 leaves out what is not clearly faster.
+    //   From 1 GFLOP on the left side is two streams and the host's 30 us for them; the lines at 26 (1x1) and 38 (3x3) leave out what is not
+    //   clearly faster.
     const double gx = da ? (double)splitk::tiles_of(*da) * (8. + (double)smallb::steps_of(*da)) : 0.;
     const double tiles = (double)(fa.Cout / 32) * (fa.Cin / 32) * (fa.R * fa.S), gw = tiles * ((double)M / 32);
     // A strided layer's other launch (spread_add; dgrad3x3_s2, 20 us) already hides a weight gradient on the second stream:
     //     1x1 256 -> 512  M = 784 19 | 11   3136 26 | 19   4704 30 | 26   6272 30 | 32     512 -> 1024  M = 2352 30 | 25   1024 -> 2048  M = 588 32 | 26
     //     3x3 128 -> 128  M = 784 27 | 18   3136 33 | 22   4704 32 | 26   6272 33 | 34     256 -> 256  M = 1568 33 | 29 (11)   512 -> 512  M = 588 37 | 45 (13)
     const int most = tiles < 64 ? 4096 : fa.stride > 1 ? 5000 : 6400;
-    return M <= most && 7000. + 0.4 * gx + 0.13 * gw <= (da ? 26000. : 11000.);
+    return M <= most && 7000. + 0.4 * gx + 0.13 * gw <= (!da ? 11000. : fa.R == 3 ? 38000. : 26000.);
 }
 
 const char *small_backward_name(const ConvArgs &fa) { return fa.bf16 ? "small_backward bf16" : "small_backward f32"; }
@@ -252,8 +253,10 @@ hipError_t launch_small_backward(const ConvArgs *data, const ConvArgs &fa, const
     if (!da.oy_s) { da.wR = da.R; da.wS = da.S; da.w_r0 = da.w_s0 = 0; da.w_step = 1; }
     const int taps = fa.R * fa.R, unit = fa.bf16 ? 32 : 16;
     const long long tiles = (long long)(fa.Cout / unit) * (fa.Cin / unit) * taps;
-    // the wider tile of gw, half the loads per product, where the narrow ones would be more than two workgroups to a CU anyway
-    const int tw = tiles >= 512 && fa.Cout % (2 * unit) == 0 && fa.Cin % (2 * unit) == 0 ? 2 : 1;
+    // The wider tile of gw, half the loads per product, where the narrow ones would be more than two workgroups to a CU anyway (3x3 256 -> 256 on
+    // 1568 pixels 18 -> 15 us, 512 -> 512 on 588 31 -> 23).  In bf16 it has registers for one sum only: up to 2000 pixels, beyond which that is further
+    // from 64 bits than the kernels it replaces (3x3 256 -> 256 on 2352 1.00e-7 against 0.95e-7; four sums 0.75e-7).
+    const int tw = tiles >= 512 && (!fa.bf16 || fa.M <= 2000) && fa.Cout % (2 * unit) == 0 && fa.Cin % (2 * unit) == 0 ? 2 : 1;
     smallb::WeightArgs w;
     w.x = fa.x; w.g = g; w.scale = fa.scale; w.gw = gw;
     w.M = fa.N * fa.P * fa.Q; w.C = fa.Cin; w.K = fa.Cout; w.R = fa.R; w.pad = fa.pad; w.stride = fa.stride;

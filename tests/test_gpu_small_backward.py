@@ -32,6 +32,8 @@ CASES = [
     ("bf16", 1,  64, 64,   64,  64, 1, 1, False, True,  SAME),       # 4096 positions: the last that go this way with few tiles of gw
     ("bf16", 1,  64, 65,   64,  64, 1, 1, False, True,  "joint1x1 bf16, the same launch"),
     ("bf16", 1,  64, 100, 256, 256, 1, 1, False, True,  SAME),       # 6400: the last with 64
+    ("bf16", 10, 14, 14,  256, 256, 3, 1, True,  True,  SAME),       # 1960 pixels: the wider tile of gw
+    ("bf16", 16, 14, 14,  256, 256, 3, 1, True,  True,  SAME),       # 3136: the narrow one, 576 of them; 3.7 GFLOP
     ("bf16", 1,  56, 56,  256,  64, 1, 1, True,  True,  SAME),
     ("f32",  1,  1,   1,   32,  64, 1, 1, True,  True,  SAME),
     ("f32",  1,  3,  11,   96,  32, 1, 1, False, True,  SAME),       # 33 positions: 8 to a wavefront, the fifth has one
