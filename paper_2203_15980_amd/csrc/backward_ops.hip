@@ -430,117 +430,214 @@ __global__ __launch_bounds__(256) void softmax_ce_bwd_kernel(const uint16_t *log
 }
 
 // ---------------------------------------------------------------- classifier z = x w^T + bias
-// Both gradients are small products (0.5 GFLOP for 128 images, 2048 -> 1000) whose operands all sit in the L2; they run on the
-// fp32 MFMA (16x16x4), so that gy * scale and every sum keep 32 bits, and read each operand once per tile.  Neither reads the other, and
-// each is a chain of round trips and MFMAs that leaves most of a CU's issue slots empty: one launch runs the tiles of both
-// side by side (128 images: two launches of 12 us -> one of 18.8).
-//
-// gx[n][c] = sum_k gy[n][k] * scale_k * w[k][c].  A workgroup owns 16 images x 64 channels; its 8 wavefronts split the
-// classes (wavefront v takes steps v, v + 8, ... of 16) and their sums are added in the order of v.  In a step, MFMA
-// e takes classes 4 * (lane / 16) + e of the 16, so that a lane reads 8 contiguous bytes of gy; a lane's four
-// channels are contiguous, and four accumulators take one each.  31 -> 11 us (kernel trace): a workgroup per image read all of w.
-__device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_t *w, const float *scale, uint16_t *gx, int N, int Cin, int Cout,
-                                               unsigned block) {
-    constexpr int kWaves = 8;
-    __shared__ float part[kWaves][16][64];
-    const int cblocks = (Cin + 63) / 64;
-    const int n0 = (int)(block / cblocks) * 16, c0 = (int)(block % cblocks) * 64;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l16 = lane & 15, quad = lane >> 4;
-    const bool nin = n0 + l16 < N, cin = c0 + 4 * l16 < Cin;     // Cin and Cout are multiples of 8
-    const uint16_t *gp = gy + (size_t)(nin ? n0 + l16 : 0) * Cout;
-    const uint16_t *wp = w + (cin ? c0 + 4 * l16 : 0);
-    f32x4 acc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-    for (int k0 = 16 * wv; k0 < Cout; k0 += 16 * kWaves) {
-        const int k = k0 + 4 * quad;
-        const bool kin = k < Cout;                               // this lane's four classes, together
-        const int kc = kin ? k : 0;
-        const u32x2 g = *reinterpret_cast<const u32x2 *>(gp + kc);
-        const f32x4 sc = *reinterpret_cast<const f32x4 *>(scale + kc);
-        u32x2 wv4[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) wv4[e] = *reinterpret_cast<const u32x2 *>(wp + (size_t)(kc + e) * Cin);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float gf = (e & 1) ? hi16(g[e >> 1]) : lo16(g[e >> 1]);
-            const float ga = nin && kin ? gf * sc[e] : 0.f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float wf = (j & 1) ? hi16(wv4[e][j >> 1]) : lo16(wv4[e][j >> 1]);
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga, cin && kin ? wf : 0.f, acc[j], 0, 0, 0);
-            }
-        }
-    }
-    // acc[j]: image 4 * quad + e, channel 4 * l16 + j
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        *reinterpret_cast<f32x4 *>(&part[wv][4 * quad + e][4 * l16]) = f32x4{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
-    __syncthreads();
-    const int n = threadIdx.x >> 4, c = 4 * (threadIdx.x & 15);
-    if (threadIdx.x >= 256 || n0 + n >= N || c0 + c >= Cin) return;
-    f32x4 v = *reinterpret_cast<const f32x4 *>(&part[0][n][c]);
-#pragma unroll
-    for (int g = 1; g < kWaves; ++g) v += *reinterpret_cast<const f32x4 *>(&part[g][n][c]);
-    *reinterpret_cast<u32x2 *>(gx + (size_t)(n0 + n) * Cin + c0 + c) = u32x2{pack2(v.x, v.y), pack2(v.z, v.w)};
+//   gx[n][c] = sum_k gy[n][k] * scale_k * w[k][c]          gw[k][c] = scale_k * sum_n gy[n][k] * x[n][c], then sum_n gy[n][k]
+// Both are small products (0.5 GFLOP for 128 images, 2048 -> 1000) whose operands all sit in the L2; neither reads the other, and one launch
+// runs the tiles of both side by side.  Eight wavefronts to a tile split its reduction, and their sums meet in LDS in a fixed tree; operands
+// whose reduction index is the row in memory go through LDS that only their wavefront uses and come back transposed (ds_read_b64_tr_b16).
+//  * gw: 64 x 64 of (k, c), bf16 MFMAs (exact products, fp32 sums); the tiles of c = 0 also add gy up, in order, for the bias.
+//  * gx: 32 images x 32 channels.  gy * scale keeps its 32 bits: it is split into three bf16 parts (8 + 8 + 8 bits, exact), each of
+//    which multiplies w.
+// What bounds it is the chain of launch, two round trips and a combine.  On the fp32 MFMA, which takes neither splitting nor transposing, the
+// 128 images took 18.8 us (two launches of 12 before that), a third of it MFMA issue: now 13.3 (head of 128 images 46.6 -> 41.2).
+static constexpr int kDensePitch = 128;                          // bytes of a staged row of 64 channels
+__device__ __forceinline__ int dense_flip(int row) { return (row >> 1) & 1; }    // which way a row's two 64-byte halves lie (see wgrad1x1.hip)
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef s16x4 __attribute__((address_space(3))) * dense_lds_ptr;
+__device__ __forceinline__ s16x8 dense_tr_read(const unsigned char *p, int four_rows) {
+    return __builtin_shufflevector(__builtin_amdgcn_ds_read_tr16_b64_v4i16((dense_lds_ptr)p),
+                                   __builtin_amdgcn_ds_read_tr16_b64_v4i16((dense_lds_ptr)(p + four_rows)), 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// One wavefront's LDS instructions execute in order; this only keeps the compiler from moving them.
+__device__ __forceinline__ void dense_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// gw[k][c] = scale_k * sum_n gy[n][k] * x[n][c] (fp32).  A wavefront owns 16 classes x 64 channels and all images (four per MFMA);
-// the workgroup's eight take neighbouring channels.  The wavefronts of channel 0 also write the bias gradient
-// sum_n gy[n][k] behind the weights.  52 -> 12 us (kernel trace): a thread per (k, 8 channels) read gy one value per image and step.
+// smem: 64 KB.
 __device__ __forceinline__ void dense_bwd_weight(const uint16_t *gy, const uint16_t *x, const float *scale, float *gw, int N, int Cin, int Cout,
-                                                 unsigned block) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l16 = lane & 15, quad = lane >> 4;
-    const int cblocks = (Cin + 511) / 512;
-    const int k0 = (int)(block / cblocks) * 16, c0 = ((int)(block % cblocks) * 8 + wv) * 64;
-    const bool kin = k0 + l16 < Cout, cin = c0 + 4 * l16 < Cin;
-    const uint16_t *gp = gy + (kin ? k0 + l16 : 0), *xp = x + (cin ? c0 + 4 * l16 : 0);
-    f32x4 acc[4];
-    float gsum = 0.f;
+                                                 unsigned block, unsigned char *smem) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cblocks = (Cin + 63) / 64, k0 = (int)(block / cblocks) * 64, c0 = (int)(block % cblocks) * 64;
+    // a step is 16 images; a lane fetches 16 bytes of rows lane / 8 and 8 + lane / 8 of both operands (channel counts are multiples of 8)
+    const int row = lane >> 3, seg = lane & 7;
+    const bool kin = k0 + seg * 8 < Cout, cin = c0 + seg * 8 < Cin;
+    unsigned char *stg = smem + wv * 8192;                       // 16 rows of gy, then of x; later this wavefront's sums, two tiles at a time
+    unsigned char *put = stg + row * kDensePitch + (((seg >> 2) ^ dense_flip(row)) << 6) + (seg & 3) * 16;     // row + 8: the same flip
+    const int srow = 8 * (lane >> 5) + ((lane & 15) >> 2), scol = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    const unsigned char *get = stg + srow * kDensePitch + scol;
+    f32x16 acc[2][2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr int kSteps = 8;                                    // of four images, in flight together
-    for (int n0 = 0; n0 < N; n0 += 4 * kSteps) {
-        uint32_t g[kSteps];
-        u32x2 xv[kSteps];
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
-            const int n = n0 + 4 * u + quad;
-            const size_t row = n < N ? n : 0;
-            g[u] = gp[row * Cout];
-            xv[u] = *reinterpret_cast<const u32x2 *>(xp + row * Cin);
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    u32x4 gb[2], xb[2];
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    auto fetch = [&](int n0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int n = n0 + 8 * u + row;
+            gb[u] = n < N && kin ? *reinterpret_cast<const u32x4 *>(gy + (size_t)n * Cout + k0 + seg * 8) : zero;
+            xb[u] = n < N && cin ? *reinterpret_cast<const u32x4 *>(x + (size_t)n * Cin + c0 + seg * 8) : zero;
+        }
+    };
+    fetch(16 * wv);
+    for (int n0 = 16 * wv; n0 < N; n0 += 128) {
+        dense_fence();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            *reinterpret_cast<u32x4 *>(put + u * 8 * kDensePitch) = gb[u];
+            *reinterpret_cast<u32x4 *>(put + 2048 + u * 8 * kDensePitch) = xb[u];
+        }
+        fetch(n0 + 128);
+        dense_fence();
+        s16x8 gf[2], xf[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int at = (h ^ dense_flip(srow)) << 6;
+            gf[h] = dense_tr_read(get + at, 4 * kDensePitch);    // row + 4: the same flip
+            xf[h] = dense_tr_read(get + 2048 + at, 4 * kDensePitch);
         }
 #pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
-            const bool nin = n0 + 4 * u + quad < N;
-            const float ga = nin && kin ? __uint_as_float(g[u] << 16) : 0.f;
-            gsum += ga;
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float xf = (j & 1) ? hi16(xv[u][j >> 1]) : lo16(xv[u][j >> 1]);
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga, nin && cin ? xf : 0.f, acc[j], 0, 0, 0);
-            }
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, gf[i]), __builtin_bit_cast(bf16x8, xf[j]), acc[i][j], 0, 0, 0);
+    }
+    // lane: column (c) l % 32, rows (k) 8 e4 + 4 (l / 32) + e of a 32 x 32 tile in register 4 e4 + e
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (i) __syncthreads();                                  // the sums before are read
+        dense_fence();
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4)
+                *reinterpret_cast<f32x4 *>(stg + j * 4096 + e4 * 1024 + lane * 16) =
+                    f32x4{acc[i][j][4 * e4], acc[i][j][4 * e4 + 1], acc[i][j][4 * e4 + 2], acc[i][j][4 * e4 + 3]};
+        __syncthreads();
+        f32x4 part[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) part[v] = *reinterpret_cast<const f32x4 *>(smem + v * 8192 + tid * 16);
+        const f32x4 sum = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
+        const int k = k0 + 32 * i + 8 * ((tid >> 6) & 3) + 4 * (lane >> 5), c = c0 + 32 * (tid >> 8) + (lane & 31);
+        if (k < Cout && c < Cin) {                               // four classes, inside or outside together
+            const f32x4 sc = *reinterpret_cast<const f32x4 *>(scale + k);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) gw[(size_t)(k + e) * Cin + c] = sum[e] * sc[e];
         }
     }
-    // acc[j]: class 4 * quad + e, channel 4 * l16 + j
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int k = k0 + 4 * quad + e;
-        if (k >= Cout || !cin) continue;
-        const float sc = scale[k];
-        *reinterpret_cast<f32x4 *>(gw + (size_t)k * Cin + c0 + 4 * l16) = f32x4{acc[0][e] * sc, acc[1][e] * sc, acc[2][e] * sc, acc[3][e] * sc};
+    if (c0 == 0) {                                               // the bias: eight threads to a class, every eighth image each
+        const int k = k0 + (tid & 63), g = tid >> 6;
+        float sum = 0.f;
+        if (k < Cout)
+            for (int n = g; n < N; n += 8) sum += __uint_as_float((uint32_t)gy[(size_t)n * Cout + k] << 16);
+        __syncthreads();
+        float *part = reinterpret_cast<float *>(smem);
+        part[tid] = sum;
+        __syncthreads();
+        if (tid < 64 && k < Cout) {
+            for (int v = 1; v < 8; ++v) sum += part[v * 64 + tid];
+            gw[(size_t)Cout * Cin + k] = sum;
+        }
     }
-    gsum += __shfl_xor(gsum, 16);
-    gsum += __shfl_xor(gsum, 32);
-    if (c0 == 0 && quad == 0 && kin) gw[(size_t)Cout * Cin + k0 + l16] = gsum;
 }
 
-// The first `weight_blocks` workgroups tiles of gw, the others tiles of gx.
+// smem: 64 KB.
+__device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_t *w, const float *scale, uint16_t *gx, int N, int Cin, int Cout,
+                                               unsigned block, unsigned char *smem) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
+    const int cblocks = (Cin + 31) / 32, n0 = (int)(block / cblocks) * 32, c0 = (int)(block % cblocks) * 32;
+    // a step is 32 classes: w's rows (64 bytes of 32 channels) through LDS, gy and scale straight into the MFMA's layout (image l % 32, classes
+    // 16 q + 8 (l / 32) .. + 7)
+    const int row = lane >> 2, seg = lane & 3;
+    const bool cin = c0 + seg * 8 < Cin;
+    const uint16_t *gp = gy + (size_t)(n0 + l32 < N ? n0 + l32 : N - 1) * Cout;      // past the last image: that image, not stored
+    unsigned char *stg = smem + wv * 8192;
+    unsigned char *put = stg + row * 64 + seg * 16;
+    const unsigned char *get = stg + (8 * half + ((lane & 15) >> 2)) * 64 + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    u32x4 wb[2], gb[2];
+    f32x4 sb[2][2];
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int kr = k0 + 16 * u + row, kg = k0 + 16 * u + 8 * half;           // Cout is a multiple of 8
+            wb[u] = kr < Cout && cin ? *reinterpret_cast<const u32x4 *>(w + (size_t)kr * Cin + c0 + seg * 8) : zero;
+            const bool in = kg < Cout;
+            gb[u] = in ? *reinterpret_cast<const u32x4 *>(gp + kg) : zero;
+            sb[u][0] = *reinterpret_cast<const f32x4 *>(scale + (in ? kg : 0));
+            sb[u][1] = *reinterpret_cast<const f32x4 *>(scale + (in ? kg + 4 : 0));
+        }
+    };
+    fetch(32 * wv);
+    for (int k0 = 32 * wv; k0 < Cout; k0 += 256) {
+        dense_fence();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) *reinterpret_cast<u32x4 *>(put + u * 1024) = wb[u];
+        u32x4 parts[2][3];
+        uint32_t rest = 0u;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {                        // two classes at a time
+                uint32_t bits[2][3];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float v = (h ? hi16(gb[u][p]) : lo16(gb[u][p])) * sb[u][p >> 1][2 * (p & 1) + h];
+                    bits[h][0] = __float_as_uint(v) & 0xFFFF0000u;                                       // cut off, not rounded: never overflows
+                    const float r1 = v - __uint_as_float(bits[h][0]);                                    // exact, and so is the next
+                    bits[h][1] = __float_as_uint(r1) & 0xFFFF0000u;
+                    bits[h][2] = __float_as_uint(r1 - __uint_as_float(bits[h][1]));
+                    if ((bits[h][0] & 0x7F800000u) == 0x7F800000u) bits[h][1] = bits[h][2] = 0u;         // an Inf or NaN is its first part
+                    rest |= bits[h][1] | bits[h][2];
+                }
+#pragma unroll
+                for (int q = 0; q < 3; ++q) parts[u][q][p] = bits[0][q] >> 16 | (bits[1][q] & 0xFFFF0000u);
+            }
+        const bool split = __any(rest != 0u);                    // scale = 1: gy is its own first part
+        fetch(k0 + 256);
+        dense_fence();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bf16x8 wf = __builtin_bit_cast(bf16x8, dense_tr_read(get + u * 1024, 4 * 64));
+            if (split) {                                         // the small parts first
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, __builtin_bit_cast(bf16x8, parts[u][2]), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, __builtin_bit_cast(bf16x8, parts[u][1]), acc, 0, 0, 0);
+            }
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, __builtin_bit_cast(bf16x8, parts[u][0]), acc, 0, 0, 0);
+        }
+    }
+    // lane: image l % 32, channels 8 rb + 4 (l / 32) + e in register 4 rb + e
+    dense_fence();
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+        *reinterpret_cast<f32x4 *>(stg + l32 * 144 + (8 * rb + 4 * half) * 4) = f32x4{acc[4 * rb], acc[4 * rb + 1], acc[4 * rb + 2], acc[4 * rb + 3]};
+    __syncthreads();
+    const int n = n0 + (tid >> 3), c = c0 + 4 * (tid & 7);
+    if (tid >= 256 || n >= N || c >= Cin) return;
+    f32x4 part[8];
+#pragma unroll
+    for (int v = 0; v < 8; ++v) part[v] = *reinterpret_cast<const f32x4 *>(smem + v * 8192 + (tid >> 3) * 144 + (tid & 7) * 16);
+    const f32x4 v = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
+    *reinterpret_cast<u32x2 *>(gx + (size_t)n * Cin + c) = u32x2{pack2(v.x, v.y), pack2(v.z, v.w)};
+}
+
+// The first `data_blocks` workgroups tiles of gx, whose reductions are longer, the others tiles of gw.
 __global__ __launch_bounds__(512) void dense_bwd_kernel(const uint16_t *gy, const uint16_t *w, const uint16_t *x, const float *scale,
-                                                        uint16_t *gx, float *gw, int N, int Cin, int Cout, unsigned weight_blocks) {
-    if (blockIdx.x < weight_blocks) dense_bwd_weight(gy, x, scale, gw, N, Cin, Cout, blockIdx.x);
-    else dense_bwd_data(gy, w, scale, gx, N, Cin, Cout, blockIdx.x - weight_blocks);
+                                                        uint16_t *gx, float *gw, int N, int Cin, int Cout, unsigned data_blocks) {
+    __shared__ __align__(16) unsigned char smem[8 * 8192];
+    if (blockIdx.x < data_blocks) dense_bwd_data(gy, w, scale, gx, N, Cin, Cout, blockIdx.x, smem);
+    else dense_bwd_weight(gy, x, scale, gw, N, Cin, Cout, blockIdx.x - data_blocks, smem);
 }
 
 }  // namespace bops
@@ -594,12 +691,12 @@ hipError_t launch_dense_bwd(const void *x, const void *w, const float *scale, co
     if (!w || !scale || !gy || N <= 0 || Cin <= 0 || Cout <= 0 || Cin % 8 || Cout % 8) return hipErrorInvalidValue;
     if (((uintptr_t)x | (uintptr_t)w | (uintptr_t)scale | (uintptr_t)gy | (uintptr_t)gx | (uintptr_t)gw) & 15) return hipErrorInvalidValue;
     if (gw && !x) return hipErrorInvalidValue;
-    const long long data = gx ? ((long long)N + 15) / 16 * ((Cin + 63) / 64) : 0, weight = gw ? ((long long)Cout + 15) / 16 * ((Cin + 511) / 512) : 0;
+    const long long data = gx ? ((long long)N + 31) / 32 * ((Cin + 31) / 32) : 0, weight = gw ? ((long long)Cout + 63) / 64 * ((Cin + 63) / 64) : 0;
     if (data + weight > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     if (data + weight == 0) return hipSuccess;
     bops::dense_bwd_kernel<<<dim3((unsigned)(data + weight)), dim3(512), 0, stream>>>(
         static_cast<const uint16_t *>(gy), static_cast<const uint16_t *>(w), static_cast<const uint16_t *>(x), scale, static_cast<uint16_t *>(gx), gw,
-        N, Cin, Cout, (unsigned)weight);
+        N, Cin, Cout, (unsigned)data);
     return hipGetLastError();
 }
 
