@@ -611,8 +611,14 @@ __device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_
         for (int u = 0; u < 2; ++u) {
             const bf16x8 wf = __builtin_bit_cast(bf16x8, dense_tr_read(get + u * 1024, 4 * 64));
             if (split) {                                         // the small parts first
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, __builtin_bit_cast(bf16x8, parts[u][2]), acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, __builtin_bit_cast(bf16x8, parts[u][1]), acc, 0, 0, 0);
+                u32x4 fin = __builtin_bit_cast(u32x4, wf);       // an infinite weight meets the first part alone: a small one may be a zero
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    if ((fin[p] & 0x7F80u) == 0x7F80u) fin[p] &= 0xFFFF0000u;
+                    if ((fin[p] & 0x7F800000u) == 0x7F800000u) fin[p] &= 0xFFFFu;
+                }
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fin), __builtin_bit_cast(bf16x8, parts[u][2]), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fin), __builtin_bit_cast(bf16x8, parts[u][1]), acc, 0, 0, 0);
             }
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, __builtin_bit_cast(bf16x8, parts[u][0]), acc, 0, 0, 0);
         }

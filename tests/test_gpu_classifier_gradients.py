@@ -50,3 +50,30 @@ def test_gradients_at_tile_edges(torch_mod, N, Cin, Cout, kind):  # noqa: F811
     print(N, Cin, Cout, kind, errs, flush=True)
     assert errs[0] <= 4e-3 and errs[1] <= 1e-5 and errs[2] <= 1e-5
     d.close()
+
+
+def test_infinite_weights_meet_the_first_part_alone(torch_mod):  # noqa: F811
+    """gy * scale in three parts: a part of zero must not make a NaN of an infinite weight.  Even classes' scale is one (their small parts are zeros)."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    N, Cin, Cout = 33, 64, 72
+    x, w, g = _bits(32, 1, (N, 1, 1, Cin)), _bits(32, 2, (Cout, 1, 1, Cin), 0.05), _bits(32, 3, (N, Cout))
+    g[(g & 0x7FFF) == 0] = 0x3F80
+    scale = np.where(np.arange(Cout) % 2 == 0, 1.0, np.abs(synth.normal(32, 4, Cout)) + 0.5).astype(np.float32)
+    for k, c, v in ((0, 3, 0x7F80), (5, 17, 0xFF80), (70, 40, 0x7F80), (71, 63, 0xFF80)):
+        w[k, 0, 0, c] = v
+    d, put, get = _small_ctx(torch, [x.nbytes, g.nbytes, g.nbytes, x.nbytes])
+    put(0, x)
+    put(2, g)
+    wd, sc, bd = _dev(torch, w), _dev(torch, scale), torch.zeros(Cout, device="cuda:0")
+    fc = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=wd.data_ptr(), scale=sc.data_ptr(), shift=bd.data_ptr(), N=N, H=1, W=1,
+                      Cin=Cin, Cout=Cout, R=1, S=1, stride=1, pad=0, relu=0)
+    d.backward_segment([dl.BwdDesc(fwd=fc, gy=2, gpre=2, gx=3, gx_add=dl.NO_TENSOR, gw=None)])
+    d.sync()
+    got = on.to_f64(get(3, (N, Cin)), "bf16")
+    ref = (on.to_f64(g, "bf16") * scale.astype(np.float64)) @ on.to_f64(w, "bf16").reshape(Cout, Cin)
+    inf = np.isinf(ref)
+    assert inf.sum() == 4 * N and not np.isnan(ref).any()
+    assert np.array_equal(got[inf], ref[inf])
+    assert np.max(np.abs(got[~inf] - ref[~inf])) <= 4e-3 * np.max(np.abs(ref[~inf]))
+    d.close()
