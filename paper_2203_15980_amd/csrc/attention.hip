@@ -9,8 +9,8 @@
 // Layout.  qkv [N, S, 3H] bf16: q = columns [0,H), k = [H,2H), v = [2H,3H); head h owns columns
 // [64h, 64h+64) of each (d = 64).  ctx [N, S, H] bf16.
 //
-// A workgroup (8 wavefronts) takes one (image, head) and a block of 256 queries; a wavefront owns
-// 32 queries.  K and V of the head stream through LDS in blocks of 64 keys, two buffers; block
+// A workgroup (8, 4 or 2 wavefronts: attention_waves below) takes one (image, head) and a block of 256, 128 or 64
+// queries; a wavefront owns 32 queries, and its arithmetic is the same in all three.  K and V of the head stream through LDS in blocks of 64 keys, two buffers; block
 // b + 1 waits in registers (requested a block earlier) while block b is multiplied, so only the
 // first block's latency is exposed (staging all 512 keys up front cost 20 of 68 us at batch 32 x
 // 512).  Everything is computed TRANSPOSED so that a lane owns one query:
@@ -47,8 +47,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 static constexpr int kD = 64;                    // head dimension
 static constexpr int kChunk = 64;                // keys per block (one online-softmax step)
 static constexpr int kKT = kChunk / 32;          // 32-key tiles per block
-static constexpr int kWaves = 8, kQB = kWaves * 32;   // queries per workgroup (4 wavefronts, two workgroups per CU: 4 % slower)
-static constexpr int kPieces = kChunk * 8 / (kWaves * 64);   // 16-byte pieces of K (and of V) per thread and block
+static constexpr int kWaveQ = 32;                // queries per wavefront
+static constexpr int kCUs = 256;
 static constexpr int kPitch = kD * 2 + 16;       // LDS row pitch in bytes (144: conflict-free b128 rows)
 static constexpr int kBufBytes = 2 * kChunk * kPitch;   // K and V of one block: 18 KB
 
@@ -64,10 +64,13 @@ struct AttnArgs {
     float scale_log2e;                           // log2(e) / sqrt(d)
 };
 
-// Two workgroups per CU (<= 128 registers per lane, 36 KB of LDS each): four wavefronts per SIMD, so that
+// Two workgroups of 8 wavefronts per CU (<= 128 registers per lane, 36 KB of LDS each): four wavefronts per SIMD, so that
 // one wavefront's softmax arithmetic runs under another's MFMAs.  With 128-key blocks (172 registers,
 // one workgroup per CU) the same kernel took 54 instead of 45 us at batch 32 x 512.
+template <int kWaves>
 __global__ __launch_bounds__(kWaves * 64, 2) void attention_kernel(AttnArgs a) {
+    constexpr int kQB = kWaves * kWaveQ;                         // queries per workgroup
+    constexpr int kPieces = kChunk * 8 / (kWaves * 64);          // 16-byte pieces of K (and of V) per thread and block
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
@@ -106,7 +109,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_kernel(AttnArgs a) {
     // ---- K/V blocks of 64 keys move global -> registers -> LDS one block ahead of the arithmetic:
     // while block b is multiplied out of buffer b % 2, block b + 1 sits in registers (requested a
     // whole block earlier) and is stored into the other buffer at the start of the next round.
-    // 64 rows x 8 pieces x 2 operands / 512 threads = 2 pieces per thread.
+    // 64 rows x 8 pieces x 2 operands / 512 threads = 2 pieces per thread with 8 wavefronts.
     const int nblocks = (a.S + kChunk - 1) / kChunk;
     u32x4 rk[kPieces], rv[kPieces];
     auto fetch = [&](int blk) {                  // rows past S (or blocks past the end): zeros
@@ -235,13 +238,39 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_kernel(AttnArgs a) {
 
 }  // namespace attn
 
+// Wavefronts per workgroup.  Eight share a block of K and V among 256 queries, which is what counts on a full chip; where
+// their workgroups are too few or too ragged, smaller ones finish earlier (same results, bit for bit; us, 12 heads):
+//  * all workgroups of 2 (4) wavefronts have a CU of their own: a CU's own chain of blocks is shorter with fewer wavefronts
+//    on it.  1 x 256: 9.2 (8), 6.9 (4), 6.5 (2); 1 x 512: 13.9, 10.3, 10.3; 4 x 1024 with 384 workgroups of 4: 25.2, 28.5.
+//    Past 384 positions four are level with two or better: 1 x 1024 23.1, 17.5, 18.2;
+//  * up to 128 positions half of the eight wavefronts would have no query: 64 x 128 16.2, 12.2, 18.3; 64 x 64 8.7, 6.1, 6.6;
+//  * a CU's largest share of queries is smaller with 128 to a workgroup: 12 x 384 20.8, 15.7; 24 x 512 40.6, 38.4; where the
+//    shares are the same eight win (16 x 1024 72.8, 81.3), and on short sequences, where each workgroup's
+//    first loads count for more (32 x 192 12.7, 14.6).
+int attention_waves(int N, int S, int heads) {
+    const long long rows = (long long)N * heads;
+    auto groups = [&](int waves) { return rows * ((S + waves * attn::kWaveQ - 1) / (waves * attn::kWaveQ)); };
+    auto share = [&](int waves) { return (groups(waves) + attn::kCUs - 1) / attn::kCUs * waves; };
+    if (S <= 384 && groups(2) <= attn::kCUs) return 2;
+    if (S <= 128 || groups(4) <= attn::kCUs) return 4;
+    return S > 192 && share(4) < share(8) ? 4 : 8;
+}
+
 // nullptr when supported, else the reason.  Geometry: N images, S positions, `heads` heads of 64.
 const char *attention_check(const void *qkv, const void *ctx, int N, int S, int heads, int bf16) {
     if (!bf16) return "attention is bf16 only";
     if (N <= 0 || S <= 0 || heads <= 0) return "non-positive dimension";
     if (!qkv || !ctx || (((uintptr_t)qkv | (uintptr_t)ctx) & 15)) return "pointers must be non-null and 16-byte aligned";
-    if ((long long)N * heads * ((S + attn::kQB - 1) / attn::kQB) > 0x7FFFFFFFLL) return "too many workgroups";
+    if ((long long)N * heads * ((S + 255) / 256) > 0x7FFFFFFFLL) return "too many workgroups";
     return nullptr;
+}
+
+template <int kWaves>
+static hipError_t launch_waves(const attn::AttnArgs &a, hipStream_t stream) {
+    constexpr int kQB = kWaves * attn::kWaveQ;
+    const long long blocks = (long long)a.N * a.heads * ((a.S + kQB - 1) / kQB);
+    attn::attention_kernel<kWaves><<<dim3((unsigned)blocks), dim3(kWaves * 64), 2 * attn::kBufBytes, stream>>>(a);   // two buffers of one block: 36 KB
+    return hipGetLastError();
 }
 
 hipError_t launch_attention(const void *qkv, void *ctx, int N, int S, int heads, int bf16, hipStream_t stream) {
@@ -251,17 +280,11 @@ hipError_t launch_attention(const void *qkv, void *ctx, int N, int S, int heads,
     a.ctx = static_cast<unsigned char *>(ctx);
     a.N = N; a.S = S; a.heads = heads;
     a.scale_log2e = 1.4426950408889634f / 8.0f;          // log2(e) / sqrt(64)
-    const size_t lds = (size_t)2 * attn::kBufBytes;      // two buffers of one block: 36 KB
-    static bool raised = false;
-    if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn::attention_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        raised = true;
+    switch (attention_waves(N, S, heads)) {
+    case 2: return launch_waves<2>(a, stream);
+    case 4: return launch_waves<4>(a, stream);
+    default: return launch_waves<8>(a, stream);
     }
-    const long long blocks = (long long)N * heads * ((S + attn::kQB - 1) / attn::kQB);
-    attn::attention_kernel<<<dim3((unsigned)blocks), dim3(attn::kWaves * 64), lds, stream>>>(a);
-    return hipGetLastError();
 }
 
 }  // namespace delta

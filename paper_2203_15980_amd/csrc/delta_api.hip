@@ -1891,7 +1891,12 @@ delta_status delta_layer_kernel(delta_ctx *c, const delta_layer_desc *layer, cha
     case DELTA_OP_MAXPOOL: name = "maxpool"; break;
     case DELTA_OP_AVGPOOL: name = "avgpool"; break;
     case DELTA_OP_SOFTMAX_CE: name = "softmax_ce"; break;
-    case DELTA_OP_ATTENTION: name = "attention bf16 (256 queries x 8 waves, K/V in LDS)"; break;
+    case DELTA_OP_ATTENTION: {
+        const int waves = delta::attention_waves(layer->N, layer->H, layer->R);
+        name = waves == 8 ? "attention bf16 (256 queries x 8 waves, K/V in LDS)"
+             : waves == 4 ? "attention bf16 (128 queries x 4 waves, K/V in LDS)" : "attention bf16 (64 queries x 2 waves, K/V in LDS)";
+        break;
+    }
     case DELTA_OP_LAYERNORM: name = "layernorm bf16"; break;
     case DELTA_OP_BATCHNORM: name = "batchnorm (batch statistics) bf16: stats + finalize + apply"; break;
     case DELTA_OP_RELU: name = "relu bf16"; break;

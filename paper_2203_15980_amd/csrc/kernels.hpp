@@ -127,6 +127,7 @@ const char *bottleneck_block_check(const BlockArgs &a);
 hipError_t launch_bottleneck_block(const BlockArgs &a, hipStream_t stream);
 // attention.hip: fused multi-head self-attention, head dimension 64, bf16.  qkv [N,S,3*64*heads], ctx [N,S,64*heads]
 const char *attention_check(const void *qkv, const void *ctx, int N, int S, int heads, int bf16);
+int attention_waves(int N, int S, int heads);       // wavefronts (of 32 queries) per workgroup
 hipError_t launch_attention(const void *qkv, void *ctx, int N, int S, int heads, int bf16, hipStream_t stream);
 // transformer_ops.hip: layer normalisation over the last axis of [rows, C], bf16
 const char *layernorm_check(const void *x, const void *y, const float *gamma, const float *beta, long long rows, int C,
