@@ -357,8 +357,8 @@ typedef struct delta_bwd_desc {
     const void *wt;            /* device: weights prepared by delta_bwd_weights (needed when gx is set) */
     void *gw;                  /* device, fp32 [Cout][R][S][Cin]: receives dL/dw (overwritten), or NULL */
     void *workspace;           /* device scratch, 256-byte aligned: the weight gradient's partial sums (from
-                                  its start) and, for a strided 1x1 layer, its staging tensor (at its
-                                  end); needed when gw is set or (strided 1x1) gx is set.  A strided 1x1
+                                  its start; at its end where both gradients are made in one pass) and,
+                                  for a strided 1x1 layer, its staging tensor (at its end); needed when gw is set or (strided 1x1) gx is set.  A strided 1x1
                                   layer whose staging bytes overlap what weight gradients still in flight
                                   use makes the compute stream wait for them: one workspace of (largest
                                   partial sums + largest staging tensor) for all layers avoids that */
@@ -374,8 +374,9 @@ delta_status delta_backward_workspace(delta_ctx *ctx, const delta_layer_desc *la
 /* Runs the descriptors in order on the compute stream.  Everything is validated before the first
  * launch.  Output tensors are allocated from the arena when not resident (DELTA_ERR_OOM_ARENA);
  * a non-resident input is DELTA_ERR_STATE.
- * Weight gradients of convolutions and of the classifier (gw) of 1 GFLOP and more are the exception to "on the compute
- * stream": nothing later in the backward pass reads them, so they run on a stream of the library's own, beside the
+ * Weight gradients of convolutions (gw) of 1 GFLOP and more are the exception to "on the compute
+ * stream", unless they are made in the data gradient's own launch (delta_backward_kernel says which): nothing later in the
+ * backward pass reads them, so they run on a stream of the library's own, beside the
  * data-gradient chain, each after the launches that produce its inputs.  The arena accounts for
  * these readers when a tensor is released or rewritten.  The gw buffers and the workspace are the
  * caller's: their contents are ordered for later work on the compute stream only after
