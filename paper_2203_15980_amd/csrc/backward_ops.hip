@@ -568,6 +568,7 @@ __device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_
     u32x4 wb[2], gb[2];
     f32x4 sb[2][2];
     const u32x4 zero = {0u, 0u, 0u, 0u};
+    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -575,8 +576,8 @@ __device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_
             wb[u] = kr < Cout && cin ? *reinterpret_cast<const u32x4 *>(w + (size_t)kr * Cin + c0 + seg * 8) : zero;
             const bool in = kg < Cout;
             gb[u] = in ? *reinterpret_cast<const u32x4 *>(gp + kg) : zero;
-            sb[u][0] = *reinterpret_cast<const f32x4 *>(scale + (in ? kg : 0));
-            sb[u][1] = *reinterpret_cast<const f32x4 *>(scale + (in ? kg + 4 : 0));
+            sb[u][0] = in ? *reinterpret_cast<const f32x4 *>(scale + kg) : zero4;    // past the last class both factors are zero
+            sb[u][1] = in ? *reinterpret_cast<const f32x4 *>(scale + kg + 4) : zero4;
         }
     };
     fetch(32 * wv);

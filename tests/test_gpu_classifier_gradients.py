@@ -77,3 +77,26 @@ def test_infinite_weights_meet_the_first_part_alone(torch_mod):  # noqa: F811
     assert np.array_equal(got[inf], ref[inf])
     assert np.max(np.abs(got[~inf] - ref[~inf])) <= 4e-3 * np.max(np.abs(ref[~inf]))
     d.close()
+
+
+@pytest.mark.parametrize("N,Cin,Cout", [(1, 64, 8), (33, 64, 72), (17, 128, 1000), (32, 64, 264)])
+def test_an_infinite_scale_stays_with_its_class(torch_mod, N, Cin, Cout):  # noqa: F811
+    """Lanes whose classes lie past the last read other classes' scale: whatever it is, it must not reach the sums."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    w, g = _bits(33, 2, (Cout, 1, 1, Cin), 0.05), _bits(33, 3, (N, Cout))
+    w[(w & 0x7FFF) == 0] = 0x3D00
+    g[(g & 0x7FFF) == 0] = 0x3F80
+    scale = np.ones(Cout, np.float32)
+    scale[2] = np.inf
+    d, put, get = _small_ctx(torch, [N * Cin * 2, g.nbytes, g.nbytes, N * Cin * 2])
+    put(2, g)
+    wd, sc, bd = _dev(torch, w), _dev(torch, scale), torch.zeros(Cout, device="cuda:0")
+    fc = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=wd.data_ptr(), scale=sc.data_ptr(), shift=bd.data_ptr(), N=N, H=1, W=1,
+                      Cin=Cin, Cout=Cout, R=1, S=1, stride=1, pad=0, relu=0)
+    d.backward_segment([dl.BwdDesc(fwd=fc, gy=2, gpre=2, gx=3, gx_add=dl.NO_TENSOR, gw=None)])
+    d.sync()
+    got = on.to_f64(get(3, (N, Cin)), "bf16")
+    wf, gf = on.to_f64(w, "bf16").reshape(Cout, Cin), on.to_f64(g, "bf16")
+    assert np.array_equal(got, np.sign(gf[:, 2:3]) * np.sign(wf[2])[None] * np.inf)
+    d.close()
