@@ -1729,6 +1729,7 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
                         break;
                     }
                     HIP_TRY(c, delta::launch_relu_mask(c->arena + ty.offset, gyp, gxp, c->tensors[D.gy].bytes, 1, s));
+                    c->st.recompute_launches += 1;
                     return room;
                 }
                 HIP_TRY(c, delta::launch_relu_mask(c->arena + ty.offset, gyp, gxp, c->tensors[D.gy].bytes, 1, s));

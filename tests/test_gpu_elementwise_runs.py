@@ -106,3 +106,33 @@ def test_a_run_without_room_goes_as_far_as_it_can(torch_mod):  # noqa: F811
     d.sync()
     assert np.array_equal(first, at(2).cpu().numpy())
     d.close()
+
+
+def test_a_masked_gradient_without_room_behind_it_is_stored_and_counted(torch_mod):  # noqa: F811
+    """The arena holds the ReLU's gradient and not the normalisation's: as one by one, the first is made and counted, the status says that
+    the second has no room."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    N, H, W, C = 1, 16, 16, 512
+    n = N * H * W * C * 2
+    one = torch.ones(C, device="cuda:0")
+    same = dict(dtype=dl.DTYPE_BF16, N=N, H=H, W=W, Cin=C, Cout=C, R=1, S=1, stride=1, pad=0, relu=0)
+    bn = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, scale=one.data_ptr(), shift=one.data_ptr(), op=dl.OP_BATCHNORM, eps=1e-5, **same)
+    relu = dl.LayerDesc(x=1, res=dl.NO_TENSOR, y=2, op=dl.OP_RELU, **same)
+    descs = [dl.BwdDesc(fwd=relu, gy=3, gpre=3, gx=4, gx_add=dl.NO_TENSOR), dl.BwdDesc(fwd=bn, gy=4, gpre=4, gx=5, gx_add=dl.NO_TENSOR)]
+    got = []
+    for together in (False, True):
+        d = dl.Delta(torch.empty(4 * n + n // 2, dtype=torch.uint8, device="cuda:0"), torch.cuda.current_stream().cuda_stream)
+        d.bind([n] * 6)
+        at = lambda t: d.arena[d.tensor_ptr(t) - d.arena.data_ptr():][:n]        # noqa: E731
+        for t in (0, 2, 3):
+            d.alloc(t)
+            at(t).copy_(_dev(torch, _bits(71, t, (N, H, W, C)).view(np.uint8).reshape(-1)))
+        with pytest.raises(dl.DeltaError) as e:
+            for part in ([descs] if together else [[x] for x in descs]):
+                d.backward_segment(part)
+        d.sync()
+        got.append((e.value.status, d.stats()["recompute_launches"], at(4).cpu().numpy().copy()))
+        d.close()
+    assert got[0][0] == got[1][0] == dl.ERR_OOM_ARENA and got[0][1] == got[1][1] == 1
+    assert np.array_equal(got[0][2], got[1][2])
