@@ -1835,7 +1835,8 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
         }
         if (one != OL_NONE) {
             if (one == OL_WEIGHT) HIP_TRY(c, delta::launch_small_backward(nullptr, fo, c->arena + tgy.offset, static_cast<float *>(D.gw), s));
-            c->st.recompute_flops += 2ull * (uint64_t)fo.M * fo.R * fo.S * fo.Cin * fo.Cout;
+            const uint64_t rows = one == OL_CLASS || one == OL_WEIGHT ? fo.M : fa.M;         // as launched: on gy, or on the gradient spread to x's resolution
+            c->st.recompute_flops += 2ull * rows * fo.R * fo.S * fo.Cin * fo.Cout;
             if (wgrad_aside(L, fa)) c->tensors[L.x].rests = (class_wgrad(D, fo) ? tgy : c->tensors[D.gpre]).rests = true;
         } else if (D.gw) {
             Tensor &tx = c->tensors[L.x];

@@ -135,3 +135,39 @@ def test_padding_spreads_no_infinity(torch_mod):  # noqa: F811
     d.sync()
     assert bool((gw[0, 0, 0] == (H - 1) * (W - 1)).all()) and bool(torch.isinf(gw[0, 1, 1]).all()) and bool(torch.isfinite(gw[1:]).all())
     d.close()
+
+
+@pytest.mark.parametrize("form", [(64, 64, 1, 1, False), (64, 128, 3, 1, False), (128, 64, 1, 2, False), (64, 64, 3, 2, True), (128, 128, 3, 2, True)],
+                         ids=lambda f: "%d_%d_r%d_s%d_relu%d" % f)
+def test_both_gradients_count_the_work_of_either(torch_mod, form):  # noqa: F811
+    """recompute_flops counts the work as launched: for both gradients together what they count one by one (a strided 3x3 layer with a ReLU mask of
+    its own runs both on the spread gradient, at the input's resolution)."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    Cin, Cout, R, stride, relu = form
+    N, H, W = 2, 9, 12
+    P, Q = (H - 1) // stride + 1, (W - 1) // stride + 1
+    xb, yb = N * H * W * Cin * 2, N * P * Q * Cout * 2
+    nbytes = [xb, yb, yb, xb, N * H * W * Cout * 2]
+    d = make_delta(torch, sum(nbytes) + (2 << 20))
+    d.bind(nbytes)
+    for t in (0, 1, 2):
+        d.alloc(t)
+        d.arena[d.tensor_ptr(t) - d.arena.data_ptr():][:nbytes[t]].view(torch.bfloat16).normal_()
+    w, one = torch.randn(Cout * R * R * Cin, device="cuda:0").bfloat16(), torch.ones(max(Cin, Cout), device="cuda:0")
+    fwd = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=one.data_ptr(), shift=one.data_ptr(), N=N, H=H, W=W,
+                       Cin=Cin, Cout=Cout, R=R, S=R, stride=stride, pad=R // 2, relu=int(relu))
+    ws, gw = torch.empty(max(d.backward_workspace(fwd), 256), dtype=torch.uint8, device="cuda:0"), torch.empty(Cout * R * R * Cin, device="cuda:0")
+    count = {}
+    for what in ("both", "gx", "gw"):
+        desc = dl.BwdDesc(fwd=fwd, gy=2, gpre=4 if relu else 2, gx=dl.NO_TENSOR if what == "gw" else 3, gx_add=dl.NO_TENSOR, wt=w.data_ptr(),
+                          gw=None if what == "gx" else gw.data_ptr(), workspace=ws.data_ptr(), workspace_bytes=ws.numel())
+        if what == "both":
+            assert d.backward_kernel(desc).endswith(SAME), d.backward_kernel(desc)
+        before = d.stats()["recompute_flops"]
+        torch.cuda.synchronize()
+        d.backward_segment([desc])
+        d.sync()
+        count[what] = d.stats()["recompute_flops"] - before
+    assert count["both"] == count["gx"] + count["gw"], count
+    d.close()
