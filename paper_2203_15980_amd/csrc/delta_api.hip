@@ -404,8 +404,17 @@ int take_loss_slot(int device) {
         if (g_loss_taken[device].compare_exchange_weak(taken, taken | 1ull << slot)) return slot;
     }
 }
+// Null: one workgroup does it.  So also into a graph under capture: its replays are ordered with neither the context's other launches nor
+// each other and may outlive the context, and two launches that share a slot would count each other's workgroups.
 void *loss_scratch(const delta_ctx *c) {
-    return c->loss_slot < 0 ? nullptr : static_cast<unsigned char *>(g_loss_slots[c->device]) + (size_t)c->loss_slot * sizeof loss_slots[0];
+    if (c->loss_slot < 0) return nullptr;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream[S_COMPUTE], &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (capture != hipStreamCaptureStatusNone) return nullptr;
+    return static_cast<unsigned char *>(g_loss_slots[c->device]) + (size_t)c->loss_slot * sizeof loss_slots[0];
 }
 
 delta_status check_id(delta_ctx *c, uint32_t t) {

@@ -59,3 +59,56 @@ def test_more_contexts_than_slots(torch_mod):  # noqa: F811
             got.append(float(get(2, (1,), np.float32)[0]))
             d.close()
     assert max(got) - min(got) <= 1e-5 * max(got) and got[0] == got[67]
+
+
+def test_captured_losses_keep_off_the_contexts_scratch(torch_mod):  # noqa: F811
+    """A graph that holds a loss is replayed on one stream while its context computes losses on another, and again after that context is
+    closed and another one has its place: every result is the one computed alone."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    N, classes = 129, 1000
+    z, lab = synth.f32_to_bf16_bits(synth.normal(13, 1, N * classes).astype(np.float32) * 3).reshape(N, classes), synth.make_labels(13, N, classes)
+    zf = on.to_f64(z, "bf16")
+    top = zf.max(1)
+    ref = float(np.mean(top + np.log(np.exp(zf - top[:, None]).sum(1)) - zf[np.arange(N), lab]))
+    near = lambda v: abs(v - ref) <= 1e-5 * max(abs(ref), 1.0)                   # noqa: E731
+    loss = lambda y: dl.LayerDesc(x=0, res=1, y=y, dtype=dl.DTYPE_BF16, N=N, H=1, W=1, Cin=classes, Cout=1, R=1, S=1, stride=1, pad=0,      # noqa: E731
+                                  relu=0, op=dl.OP_SOFTMAX_CE)
+    main, side, keep = torch.cuda.Stream(), torch.cuda.Stream(), []
+
+    def context():
+        arena = torch.empty(1 << 20, dtype=torch.uint8, device="cuda:0")
+        keep.append(arena)                                       # the graph's tensors outlive the context
+        d = dl.Delta(arena, main.cuda_stream)
+        d.bind([z.nbytes, N * 8, 4, 4])
+        view = [arena[d.alloc(t) - arena.data_ptr():][:n] for t, n in enumerate((z.nbytes, N * 8, 4, 4))]
+        view[0].copy_(torch.from_numpy(z.view(np.uint8).reshape(-1)))
+        view[1].copy_(torch.from_numpy(lab.view(np.uint8).reshape(-1)))
+        torch.cuda.synchronize()
+        return d, view[2].view(torch.float32), view[3].view(torch.float32)
+    d, eager, held = context()
+    d.recompute_segment([loss(2)])
+    torch.cuda.synchronize()
+    alone = float(eager[0])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=main):
+        d.recompute_segment([loss(3)])
+    graph.replay()
+    torch.cuda.synchronize()
+    replayed = float(held[0])
+    assert near(alone) and near(replayed)
+    for second in (False, True):
+        if second:
+            d.close()
+            d, eager, _ = context()
+        for _ in range(5):
+            held.fill_(float("nan"))
+            eager.fill_(float("nan"))
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                for _ in range(4):
+                    graph.replay()
+            d.recompute_segment([loss(2)] * 16)
+            torch.cuda.synchronize()
+            assert float(eager[0]) == alone and float(held[0]) == replayed
+    d.close()
