@@ -1049,14 +1049,20 @@ delta_status delta_recompute_segment(delta_ctx *c, const delta_layer_desc *layer
         if ((r = claim_output(c, ty)) != DELTA_OK) return r;
         unsigned char *xp = c->arena + tx.offset, *yp = c->arena + ty.offset;
         unsigned char *rp = L.res != DELTA_NO_TENSOR ? c->arena + c->tensors[L.res].offset : nullptr;
-        // the run's other outputs; one that finds no room ends the run, which is launched as far as it got
+        const long long rows = (long long)L.N * L.H * L.W;
+        if (L.op == DELTA_OP_BATCHNORM) {            // its statistics need x alone: they run before the waits of the rest of the run
+            if (!c->bn_scratch) HIP_TRY(c, hipMalloc(&c->bn_scratch, delta::bn_train_scratch_bytes()));
+            HIP_TRY(c, delta::launch_bn_factors(xp, L.scale, L.shift, rows, L.Cin, L.eps, 1, c->bn_scratch, delta::bn_train_scratch_bytes(),
+                                                c->stream[S_COMPUTE]));
+        }
+        // the run's other operands and outputs; where one is not to be had (no room) the run ends, and is launched as far as it got
         const uint32_t run = elementwise_run(layers, n_layers, i);
         delta::ElementwiseTail tail;
         delta_status tail_status = DELTA_OK;
         uint32_t done = 1;
         for (; done < run; ++done) {
             const delta_layer_desc &next = layers[i + done];
-            if (next.res != DELTA_NO_TENSOR && (r = compute_uses(c, c->tensors[next.res])) != DELTA_OK) return r;
+            if (next.res != DELTA_NO_TENSOR && (tail_status = compute_uses(c, c->tensors[next.res])) != DELTA_OK) break;
             if ((tail_status = claim_output(c, c->tensors[next.y])) != DELTA_OK) break;
             void *at = c->arena + c->tensors[next.y].offset;
             if (next.op == DELTA_OP_RELU) {
@@ -1084,9 +1090,7 @@ delta_status delta_recompute_segment(delta_ctx *c, const delta_layer_desc *layer
             HIP_TRY(c, delta::launch_attention(xp, yp, L.N, L.H, L.R, L.dtype == DELTA_DTYPE_BF16, c->stream[S_COMPUTE]));
             break;
         case DELTA_OP_BATCHNORM:
-            if (!c->bn_scratch) HIP_TRY(c, hipMalloc(&c->bn_scratch, delta::bn_train_scratch_bytes()));
-            HIP_TRY(c, delta::launch_bn_train(xp, yp, L.scale, L.shift, (long long)L.N * L.H * L.W, L.Cin, L.eps, 1, tail,
-                                              c->bn_scratch, delta::bn_train_scratch_bytes(), c->stream[S_COMPUTE]));
+            HIP_TRY(c, delta::launch_bn_apply(xp, yp, L.shift, rows, L.Cin, 1, tail, c->bn_scratch, c->stream[S_COMPUTE]));
             break;
         case DELTA_OP_RELU:
             HIP_TRY(c, delta::launch_relu(xp, yp, ty.bytes, 1, c->stream[S_COMPUTE]));
@@ -1140,9 +1144,10 @@ delta_status delta_batchnorm_static(delta_ctx *c, const void *x, void *y, const 
     }
     // Nothing in the scratch has to start at zero: every partial sum and factor the later kernels of
     // this call read is written by an earlier kernel of this call.
-    HIP_TRY(c, delta::launch_bn_train(x, y, gamma, beta, (long long)rows, (int)channels, eps, 1, delta::ElementwiseTail(),
-                                      c->static_scratch,
-                                      kStaticScratchBytes, c->stream[S_COMPUTE]));
+    HIP_TRY(c, delta::launch_bn_factors(x, gamma, beta, (long long)rows, (int)channels, eps, 1, c->static_scratch, kStaticScratchBytes,
+                                        c->stream[S_COMPUTE]));
+    HIP_TRY(c, delta::launch_bn_apply(x, y, beta, (long long)rows, (int)channels, 1, delta::ElementwiseTail(), c->static_scratch,
+                                      c->stream[S_COMPUTE]));
     return DELTA_OK;
 }
 

@@ -145,8 +145,10 @@ struct ElementwiseTail {
     void *y_add = nullptr, *y_relu = nullptr;
     bool bad() const { return !r != !y_add || (((uintptr_t)r | (uintptr_t)y_add | (uintptr_t)y_relu) & 15); }
 };
-hipError_t launch_bn_train(const void *x, void *y, const float *gamma, const float *beta, long long M, int C, float eps,
-                           int bf16, const ElementwiseTail &tail, void *scratch, size_t scratch_bytes, hipStream_t stream);
+hipError_t launch_bn_factors(const void *x, const float *gamma, const float *beta, long long M, int C, float eps, int bf16, void *scratch,
+                             size_t scratch_bytes, hipStream_t stream);
+hipError_t launch_bn_apply(const void *x, void *y, const float *beta, long long M, int C, int bf16, const ElementwiseTail &tail,
+                           const void *scratch, hipStream_t stream);
 hipError_t launch_bn_train_bwd(const void *x, const void *gy, void *gx, const float *gamma, float *gw, long long M, int C,
                                float eps, int bf16, const void *relu_y, void *gm, void *scratch, hipStream_t stream);
 hipError_t launch_add_relu(const void *x, const ElementwiseTail &tail, size_t bytes, int bf16, hipStream_t stream);

@@ -490,11 +490,11 @@ static void stats_shape(int chunks, long long &blocks, int &NT, int &CH, int &RS
 // decomposition - and with it the bits of the result - against a larger one.
 size_t bn_train_fwd_scratch_bytes() { return ((size_t)4 << 20) + ((size_t)64 << 10); }
 
-// scratch: device, scratch_bytes (>= bn_train_fwd_scratch_bytes()) bytes, 16-byte aligned.
-hipError_t launch_bn_train(const void *x, void *y, const float *gamma, const float *beta, long long M, int C, float eps,
-                           int bf16, const ElementwiseTail &tail, void *scratch, size_t scratch_bytes, hipStream_t stream) {
-    if (bn_train_check(x, y, gamma, beta, M, C, bf16) || tail.bad() || !scratch || ((uintptr_t)scratch & 15) ||
-        scratch_bytes < bn_train_fwd_scratch_bytes())
+// The per-channel factors of the normalisation, from x alone, at the start of the scratch (device, scratch_bytes >= bn_train_fwd_scratch_bytes()
+// bytes, 16-byte aligned): launch_bn_apply reads them there.  Two functions, so that what only the second needs is waited for between them.
+hipError_t launch_bn_factors(const void *x, const float *gamma, const float *beta, long long M, int C, float eps, int bf16, void *scratch,
+                             size_t scratch_bytes, hipStream_t stream) {
+    if (bn_train_check(x, x, gamma, beta, M, C, bf16) || !scratch || ((uintptr_t)scratch & 15) || scratch_bytes < bn_train_fwd_scratch_bytes())
         return hipErrorInvalidValue;
     const int chunks = C / 8;
     int NT = 256;
@@ -522,10 +522,17 @@ hipError_t launch_bn_train(const void *x, void *y, const float *gamma, const flo
     const int cl_bits = C <= 512 ? 4 : 6;
     ops::bn_finalize_kernel<<<dim3((unsigned)((C + (1 << cl_bits) - 1) >> cl_bits)), dim3(1024), 0, stream>>>(
         static_cast<const unsigned char *>(x), partial, gamma, beta, ab, M, C, (int)blocks, eps, cl_bits);
-    return ops::launch_tail(x, tail, y, ab, beta, C, (size_t)M * chunks, stream);
+    return hipGetLastError();
 }
 
-// Backward of launch_bn_train.  gw: device fp32 [2][C] (dgamma, dbeta) or null.  Same scratch.
+// y = the normalisation of x, and the tail's results.  scratch: as launch_bn_factors left it.
+hipError_t launch_bn_apply(const void *x, void *y, const float *beta, long long M, int C, int bf16, const ElementwiseTail &tail,
+                           const void *scratch, hipStream_t stream) {
+    if (bn_train_check(x, y, beta, beta, M, C, bf16) || tail.bad() || !scratch || ((uintptr_t)scratch & 15)) return hipErrorInvalidValue;
+    return ops::launch_tail(x, tail, y, static_cast<const float *>(scratch), beta, C, (size_t)M * (C / 8), stream);
+}
+
+// Backward of the normalisation.  gw: device fp32 [2][C] (dgamma, dbeta) or null.  Same scratch.
 // relu_y / gm: both or neither; gm = gy where relu_y > 0, else 0, is stored and taken in gy's place.
 hipError_t launch_bn_train_bwd(const void *x, const void *gy, void *gx, const float *gamma, float *gw, long long M, int C,
                                float eps, int bf16, const void *relu_y, void *gm, void *scratch, hipStream_t stream) {

@@ -136,3 +136,42 @@ def test_a_masked_gradient_without_room_behind_it_is_stored_and_counted(torch_mo
         d.close()
     assert got[0][0] == got[1][0] == dl.ERR_OOM_ARENA and got[0][1] == got[1][1] == 1
     assert np.array_equal(got[0][2], got[1][2])
+
+
+def test_statistics_do_not_wait_for_the_residual(torch_mod):  # noqa: F811
+    """Normalisation and add in one pass while the residual is still being reloaded: the statistics need x alone and run beside the copy, only
+    the pass over the elements waits for it.  128 MB over the host link take milliseconds, the statistics a fraction of one."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    N, H, W, C = 32, 64, 64, 512
+    n = N * H * W * C * 2
+    d = dl.Delta(torch.empty(5 * n, dtype=torch.uint8, device="cuda:0"), torch.cuda.current_stream().cuda_stream)
+    d.bind([n] * 4)
+    one = torch.ones(C, device="cuda:0")
+    same = dict(dtype=dl.DTYPE_BF16, N=N, H=H, W=W, Cin=C, Cout=C, R=1, S=1, stride=1, pad=0, relu=0)
+    bn = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=2, scale=one.data_ptr(), shift=one.data_ptr(), op=dl.OP_BATCHNORM, eps=1e-5, **same)
+    add = dl.LayerDesc(x=2, res=1, y=3, op=dl.OP_ADD, **same)
+    for t in (0, 1):
+        d.alloc(t)
+        d.arena[d.tensor_ptr(t) - d.arena.data_ptr():][:n].view(torch.bfloat16).normal_()
+    for t in (2, 3):
+        d.alloc(t)
+    d.recompute_segment([bn, add])                               # whatever is allocated on first use
+    d.sync()
+    d.release(1, dl.EV_OFFLOAD)
+    d.sync()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU, torch.profiler.ProfilerActivity.CUDA]) as prof:
+        d.prefetch(1)
+        d.recompute_segment([bn, add])
+        d.sync()
+        torch.cuda.synchronize()
+    spans = {}
+    for e in prof.events():
+        for key in ("HtoD", "bn_stats_kernel", "bn_finalize_kernel", "bn_tail_kernel"):
+            if key in e.name and e.device_type == torch.autograd.DeviceType.CUDA:
+                spans[key] = (e.time_range.start, e.time_range.end)
+    print(spans, flush=True)
+    if len(spans) < 4:
+        pytest.skip("the profiler saw no kernels here: %s" % sorted({e.name for e in prof.events()})[:20])
+    assert spans["bn_finalize_kernel"][1] < spans["HtoD"][1] <= spans["bn_tail_kernel"][0]
+    d.close()
