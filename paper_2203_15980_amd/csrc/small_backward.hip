@@ -217,8 +217,19 @@ bool small_backward_applies(const ConvArgs *da, const ConvArgs &fa) {
     if (da && (da->bf16 != fa.bf16 || da->R > 8 || da->S > 8 || (long long)da->N * da->H * da->W * da->Cin * es > 0x7FFFFFFFLL)) return false;
     // Where the line lies, measured as us per layer in a segment of such layers: two or three launches | this one.
     //   fp32 (2 images, 1x1 64 -> 256 | 256 -> 64 | 3x3 64 -> 64): M = 512 11 9.8 12 | 7.2 7.1 8.2; M = 2048 13 13 17 | 7.5 10.6 13.7; M = 8192 33 45 39 | 24 26 33.
-    //   The line at 8192 keeps the sums as short as the sixteen wavefronts' of the other route.
-    if (!fa.bf16) return M <= 8192;
+    //   8192 keeps the sums as short as the sixteen wavefronts' of the other route.  Beyond that the number of 32 x 32 tiles of gx counts, here in
+    //   brackets: on a full chip the 128 x 128 tiles of the other route load a quarter per product, all the more where a tile's wavefronts have a step or two each.
+    //     2 steps of the reduction   2048 -> 64   M = 8192 [16384] 138 | 127
+    //     4    1024 -> 128  M = 2048 [2048] 39 | 25   8192 [8192] 90 | 86     512 -> 128  M = 6144 [3072] 45 | 43   8192 [4096] 50 | 55
+    //          2048 -> 128  M = 1024 [2048] 29 | 24   1536 [3072] 32 | 37   4096 [8192] 61 | 84
+    //     8    512 -> 256   M = 3072 [1536] 48 | 35   4096 [2048] 43 | 44   1024 -> 256  M = 1536 [1536] 40 | 35   2048 [2048] 42 | 44   4096 [4096] 50 | 83
+    //     16   512 -> 512   M = 4096 [2048] 65 | 54   6144 [3072] 70 | 79   2048 -> 512  M = 1024 [2048] 59 | 56   1536 [3072] 68 | 82   8192 [16384] 317 | 445
+    //     64   512 -> 2048  M = 4096 [2048] 180 | 173   6144 [3072] 230 | 256     144 (3x3)  512 -> 512  M = 4096 [2048] 421 | 389   6144 [3072] 565 | 581
+    //   Where some hundred tiles leave a ragged last round the lines are not exact: 256 -> 1024 M = 2048 [512] 28 | 31, 128 -> 2048 M = 3072 [384] 39 | 48.
+    if (!fa.bf16) {
+        const long long steps = da ? smallb::steps_of(*da) : 0, line = steps >= 8 && steps < 16 ? 1536 : 2048;
+        return M <= 8192 && (steps < 4 || splitk::tiles_of(*da) <= line);
+    }
     //   bf16: a workgroup walks all positions of its tile of gw, about 2 us per 1000 up to some 8000, beyond which it waits for memory:
     //     1x1 64 -> 256  M = 3136 14.5 | 7.5   6272 15.7 | 11   12544 17.6 | 28     3x3 64 -> 64  M = 6272 20 | 15   12544 23 | 25
     //   With few tiles of gw the other route has many short splits: at M = 6272 it is nearer to 64 bits (9.2e-8 | 9.6e-8 of the norm, 8.6 | 8.0

@@ -43,6 +43,13 @@ CASES = [
     ("f32",  2,  6,  11,  256, 128, 3, 1, True,  True,  SAME),       # 32 x 32 tiles
     ("f32",  1,  64, 128,  32,  32, 1, 1, False, True,  SAME),       # 8192 positions: the last that go this way
     ("f32",  1,  64, 129,  32,  32, 1, 1, False, True,  "wgrad_f32 16x16, 32-bit offsets, compute stream"),
+    ("f32",  1,  48,  32, 2048, 64, 1, 1, True,  True,  SAME),       # two steps: no line for the tiles of gx, 3072 here
+    ("f32",  1,  64,  32, 1024, 128, 1, 1, False, True, SAME),       # four steps: 2048 tiles are the last
+    ("f32",  1,   3, 683, 1024, 128, 1, 1, False, True, "wgrad_f32 16x16, 32-bit offsets, compute stream"),
+    ("f32",  1,  48,  32, 1024, 256, 1, 1, True,  True, SAME),       # eight: 1536
+    ("f32",  1,  29,  53, 1024, 256, 1, 1, True,  True, "wgrad_f32 32x32, 32-bit offsets, compute stream"),
+    ("f32",  1,  64,  64, 512, 512, 1, 1, False,  True, SAME),       # sixteen: 2048
+    ("f32",  1,  17, 241, 512, 512, 1, 1, False,  True, "wgrad_f32 32x32, 32-bit offsets, second stream"),
 ]
 
 
