@@ -15,7 +15,8 @@ namespace delta {
 // Two rounds in flight in two register sets were slower (7 % of a stack of such layers: the address arithmetic doubles).
 // 2 x 32 x 32 positions, us by the form with 64-bit addresses -> this one: 64 -> 256 10.0 -> 7.0, 256 -> 64 10.0 -> 9.1, 64 -> 64 10.0 -> 6.5, 3x3
 // 64 -> 64 10.0 -> 9.6.
-// Two sums in turn and a tree over the wavefronts: 2.1e-7 from 64 bits (norm) at 2048 positions whether 8 or 16 wavefronts share them.
+// Two sums and a tree over the wavefronts: 2.1e-7 from 64 bits (norm) at 2048 positions whether 8 or 16 wavefronts share them; 512 -> 512 on 8192
+// positions 2.1e-7, with one sum 2.9e-7.
 // part: kWaves T T 256 floats of LDS, factors: 64 more.
 template <int T, bool TAPS, int kWaves>
 __device__ __forceinline__ void wgrad_f32_tile(const float *x, const float *g, const float *scale, float *gw, int H, int W, int C, int K, int R,
@@ -49,47 +50,68 @@ __device__ __forceinline__ void wgrad_f32_tile(const float *x, const float *g, c
     const int hstep = 4 / W % H, wstep = 4 % W;                  // four positions on: at most one carry each
     uint32_t goff = ((uint32_t)m * (uint32_t)K + (uint32_t)(k0 + T * l16)) * 4u;
     uint32_t xoff = ((uint32_t)(m + dr * W + ds) * (uint32_t)C + (uint32_t)(c0 + T * l16)) * 4u;
-    f32x4 acc[2][T][T];                                          // steps in turn: sums half as long, and no product waits for the one before it
+    // Two sums half as long instead of one: of every other step, in registers of their own - or, where those would be the ones that the steps in
+    // flight need (16 wavefronts, T = 2: the compiler then fetched each step when it was used, 512 -> 512 on 8192 positions 55 -> 69 us), of the
+    // first half of the run, which waits in this wavefront's part of the LDS.
+    constexpr int kSums = T == 2 && kWaves == 16 ? 1 : 2;
+    f32x4 acc[kSums][T][T];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < kSums; ++u)
 #pragma unroll
         for (int i = 0; i < T; ++i)
 #pragma unroll
             for (int j = 0; j < T; ++j) acc[u][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int m0 = first; m0 < end; m0 += 4 * kSteps) {
-        uvec gv[kSteps], xv[kSteps];
+    float *mine = part + wv * (T * T * 256) + lane;
+    int m0 = first, stop = kSums == 2 || end <= first ? end : first + (end - first) / 2 / (4 * kSteps) * (4 * kSteps);
+    for (;;) {
+        for (; m0 < stop; m0 += 4 * kSteps) {
+            uvec gv[kSteps], xv[kSteps];
 #pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
-            bool in = m < end;
-            if constexpr (TAPS) in = in & ((unsigned)(h + dr) < (unsigned)H) & ((unsigned)(w + ds) < (unsigned)W);
-            gv[u] = fetch(grsrc, in ? goff : (uint32_t)kOutOfRange);        // both zero: no Inf of one meets a zero of the other
-            xv[u] = fetch(xrsrc, in ? xoff : (uint32_t)kOutOfRange);
-            m += 4;
-            goff += (uint32_t)K * 16u;
-            xoff += (uint32_t)C * 16u;
-            if constexpr (TAPS) {
-                w += wstep;
-                const bool carry = w >= W;
-                w -= carry ? W : 0;
-                h += hstep + (carry ? 1 : 0);
-                h -= h >= H ? H : 0;
+            for (int u = 0; u < kSteps; ++u) {
+                bool in = m < end;
+                if constexpr (TAPS) in = in & ((unsigned)(h + dr) < (unsigned)H) & ((unsigned)(w + ds) < (unsigned)W);
+                gv[u] = fetch(grsrc, in ? goff : (uint32_t)kOutOfRange);        // both zero: no Inf of one meets a zero of the other
+                xv[u] = fetch(xrsrc, in ? xoff : (uint32_t)kOutOfRange);
+                m += 4;
+                goff += (uint32_t)K * 16u;
+                xoff += (uint32_t)C * 16u;
+                if constexpr (TAPS) {
+                    w += wstep;
+                    const bool carry = w >= W;
+                    w -= carry ? W : 0;
+                    h += hstep + (carry ? 1 : 0);
+                    h -= h >= H ? H : 0;
+                }
             }
+#pragma unroll
+            for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j)
+                        acc[u % kSums][i][j] =
+                            __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(gv[u][i]), __uint_as_float(xv[u][j]), acc[u % kSums][i][j], 0, 0, 0);
         }
+        if (kSums == 2 || stop == end) break;
 #pragma unroll
-        for (int u = 0; u < kSteps; ++u)
+        for (int i = 0; i < T; ++i)
 #pragma unroll
-            for (int i = 0; i < T; ++i)
+            for (int j = 0; j < T; ++j) {
 #pragma unroll
-                for (int j = 0; j < T; ++j)
-                    acc[u & 1][i][j] =
-                        __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(gv[u][i]), __uint_as_float(xv[u][j]), acc[u & 1][i][j], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) mine[((i * T + j) * 4 + e) * 64] = acc[0][i][j][e];
+                acc[0][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        stop = end;
     }
 #pragma unroll
     for (int i = 0; i < T; ++i)
 #pragma unroll
         for (int j = 0; j < T; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) part[wv * (T * T * 256) + ((i * T + j) * 4 + e) * 64 + lane] = acc[0][i][j][e] + acc[1][i][j][e];
+            for (int e = 0; e < 4; ++e) {
+                float *at = mine + ((i * T + j) * 4 + e) * 64;
+                *at = acc[0][i][j][e] + (kSums == 2 ? acc[kSums - 1][i][j][e] : end > first ? *at : 0.f);
+            }
     if (wv == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll

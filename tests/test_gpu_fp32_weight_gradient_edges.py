@@ -30,6 +30,10 @@ FORMS = [
     (2,  9,   7,   512, 512, 1, 1, "32x32, 32-bit offsets"),
     (2,  6,   5,   96,  256, 3, 1, "16x16, 32-bit offsets"),        # 216 tiles of 32 x 32: too few
     (2,  6,   5,   128, 256, 3, 1, "32x32, 32-bit offsets"),        # 288
+    (1,  7,   7,   512, 512, 1, 1, "32x32, 32-bit offsets"),        # the last three wavefronts have no position
+    (1,  33,  31,  512, 512, 1, 1, "32x32, 32-bit offsets"),        # 64 positions each, 63 the last: two rounds, one in each sum
+    (1,  25,  41,  256, 1024, 1, 1, "32x32, 32-bit offsets"),       # 68, the last 5: three rounds, the first in its own sum; none for the last
+    (1,  41,  53,  128, 256, 3, 1, "32x32, 32-bit offsets"),        # 136: two rounds of five, taps
     (3,  9,   7,   512, 512, 1, 2, "32x32, 64-bit addresses"),
     (2,  8,   11,  64,  48,  1, 3, "16x16, 64-bit addresses"),
     (33, 256, 256, 256, 16,  1, 1, "16x16, 64-bit addresses"),      # x of 2.06 GiB
