@@ -473,14 +473,16 @@ const char *bn_train_check(const void *x, const void *y, const float *gamma, con
 size_t bn_train_scratch_bytes() { return (size_t)16 << 20; }     // partial sums + the 2 x C factors
 
 // Large tensors take workgroups of 1024 threads, a quarter as many: the same lanes share the rows, and
-// the finalize kernel, which runs on a nearly empty chip, reads a quarter of the partial sums; half as many where a quarter would leave
-// CUs without one (forward and backward of 100352 x 512 255 -> 238 us, 25088 x 512 from memory 76.5 -> 73.3; half as many everywhere: 100352 x 64 49 -> 60).
-static void stats_shape(int chunks, long long &blocks, int &NT, int &CH, int &RS) {
+// the finalize kernel, which runs on a nearly empty chip, reads a quarter of the partial sums.  Half as many where a quarter would leave CUs without one
+// and every workgroup at least twelve rounds of its lanes: below that the finalize kernel loses more than the statistics gain.  us with a quarter | half:
+// forward and backward, from memory: 100352 x 512 262 | 245, 50176 x 512 137 | 123, 12544 x 1024 95 | 81, 6272 x 1024 59 | 53, 25088 x 512 77 | 74 (in the
+// caches 64 | 66); the backward alone at that last size 33 | 35, and with fewer rounds 12544 x 512 24 | 25, 25088 x 256 23 | 25, 100352 x 64 25 | 27.
+static void stats_shape(int chunks, long long M, long long &blocks, int &NT, int &CH, int &RS) {
     if (blocks < 256) return;
     NT = 1024;
-    const long long half = (blocks + 1) / 2, fill = half < 256 ? half : 256;
+    const long long half = (blocks + 1) / 2 < 256 ? (blocks + 1) / 2 : 256;
     blocks = (blocks + 3) / 4;
-    if (blocks < fill) blocks = fill;
+    if (blocks < half && M * chunks >= blocks * (12 * 1024)) blocks = half;
     CH = chunks < NT ? chunks : NT;
     RS = NT / CH;
 }
@@ -510,7 +512,7 @@ hipError_t launch_bn_factors(const void *x, const float *gamma, const float *bet
     if (blocks > cap) blocks = cap;
     if (blocks > (long long)room) blocks = (long long)room;
     if (blocks < 1) return hipErrorInvalidValue;
-    stats_shape(chunks, blocks, NT, CH, RS);
+    stats_shape(chunks, M, blocks, NT, CH, RS);
     const long long rpb = (M + blocks - 1) / blocks;
     blocks = (M + rpb - 1) / rpb;
     const size_t lds = (size_t)RS * CH * 16 * 4;
@@ -552,7 +554,7 @@ hipError_t launch_bn_train_bwd(const void *x, const void *gy, void *gx, const fl
     if (blocks > cap) blocks = cap;
     if (blocks > (long long)room) blocks = (long long)room;
     if (blocks < 1) return hipErrorInvalidValue;
-    stats_shape(chunks, blocks, NT, CH, RS);
+    stats_shape(chunks, M, blocks, NT, CH, RS);
     const long long rpb = (M + blocks - 1) / blocks;
     blocks = (M + rpb - 1) / rpb;
     const size_t lds = (size_t)RS * CH * 32 * 4;
