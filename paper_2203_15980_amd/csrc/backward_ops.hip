@@ -549,17 +549,19 @@ __device__ __forceinline__ void dense_bwd_weight(const uint16_t *gy, const uint1
     }
 }
 
-// smem: 64 KB.
+// KW wavefronts (thread `tid` of KW * 64) to a tile; smem: LDS of `each` bytes per wavefront.  A tile past the last stores nothing.
+template <int KW>
 __device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_t *w, const float *scale, uint16_t *gx, int N, int Cin, int Cout,
-                                               unsigned block, unsigned char *smem) {
-    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
-    const int cblocks = (Cin + 31) / 32, n0 = (int)(block / cblocks) * 32, c0 = (int)(block % cblocks) * 32;
+                                               unsigned block, int tid, unsigned char *smem, int each) {
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
+    const unsigned cblocks = (Cin + 31) / 32, n0 = block / cblocks * 32;
+    const int c0 = (int)(block % cblocks) * 32;
     // a step is 32 classes: w's rows (64 bytes of 32 channels) through LDS, gy and scale straight into the MFMA's layout (image l % 32, classes
     // 16 q + 8 (l / 32) .. + 7)
     const int row = lane >> 2, seg = lane & 3;
     const bool cin = c0 + seg * 8 < Cin;
-    const uint16_t *gp = gy + (size_t)(n0 + l32 < N ? n0 + l32 : N - 1) * Cout;      // past the last image: that image, not stored
-    unsigned char *stg = smem + wv * 8192;
+    const uint16_t *gp = gy + (size_t)(n0 + l32 < (unsigned)N ? n0 + l32 : N - 1) * Cout;      // past the last image: that image, not stored
+    unsigned char *stg = smem + wv * each;
     unsigned char *put = stg + row * 64 + seg * 16;
     const unsigned char *get = stg + (8 * half + ((lane & 15) >> 2)) * 64 + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
     f32x16 acc;
@@ -568,7 +570,7 @@ __device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_
     u32x4 wb[2], gb[2];
     f32x4 sb[2][2];
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(scale), 0, Cout * 4, 0x00020000);
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -576,12 +578,13 @@ __device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_
             wb[u] = kr < Cout && cin ? *reinterpret_cast<const u32x4 *>(w + (size_t)kr * Cin + c0 + seg * 8) : zero;
             const bool in = kg < Cout;
             gb[u] = in ? *reinterpret_cast<const u32x4 *>(gp + kg) : zero;
-            sb[u][0] = in ? *reinterpret_cast<const f32x4 *>(scale + kg) : zero4;    // past the last class both factors are zero
-            sb[u][1] = in ? *reinterpret_cast<const f32x4 *>(scale + kg + 4) : zero4;
+#pragma unroll
+            for (int q = 0; q < 2; ++q)                          // past the last class both factors are zero
+                sb[u][q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(srsrc, (kg + 4 * q) * 4, 0, 0));
         }
     };
     fetch(32 * wv);
-    for (int k0 = 32 * wv; k0 < Cout; k0 += 256) {
+    for (int k0 = 32 * wv; k0 < Cout; k0 += 32 * KW) {
         dense_fence();
 #pragma unroll
         for (int u = 0; u < 2; ++u) *reinterpret_cast<u32x4 *>(put + u * 1024) = wb[u];
@@ -606,7 +609,7 @@ __device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_
                 for (int q = 0; q < 3; ++q) parts[u][q][p] = bits[0][q] >> 16 | (bits[1][q] & 0xFFFF0000u);
             }
         const bool split = __any(rest != 0u);                    // scale = 1: gy is its own first part
-        fetch(k0 + 256);
+        fetch(k0 + 32 * KW);
         dense_fence();
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -630,21 +633,36 @@ __device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_
     for (int rb = 0; rb < 4; ++rb)
         *reinterpret_cast<f32x4 *>(stg + l32 * 144 + (8 * rb + 4 * half) * 4) = f32x4{acc[4 * rb], acc[4 * rb + 1], acc[4 * rb + 2], acc[4 * rb + 3]};
     __syncthreads();
-    const int n = n0 + (tid >> 3), c = c0 + 4 * (tid & 7);
-    if (tid >= 256 || n >= N || c >= Cin) return;
-    f32x4 part[8];
 #pragma unroll
-    for (int v = 0; v < 8; ++v) part[v] = *reinterpret_cast<const f32x4 *>(smem + v * 8192 + (tid >> 3) * 144 + (tid & 7) * 16);
-    const f32x4 v = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
-    *reinterpret_cast<u32x2 *>(gx + (size_t)n * Cin + c) = u32x2{pack2(v.x, v.y), pack2(v.z, v.w)};
+    for (int at = tid; at < 256; at += KW * 64) {
+        const unsigned n = n0 + (at >> 3);
+        const int c = c0 + 4 * (at & 7);
+        if (n >= (unsigned)N || c >= Cin) continue;
+        f32x4 part[KW];
+#pragma unroll
+        for (int v = 0; v < KW; ++v) part[v] = *reinterpret_cast<const f32x4 *>(smem + v * each + (at >> 3) * 144 + (at & 7) * 16);
+#pragma unroll
+        for (int half_of = 1; half_of < KW; half_of *= 2)        // neighbours first: ((0 + 1) + (2 + 3)) + ...
+#pragma unroll
+            for (int v = 0; v < KW; v += 2 * half_of) part[v] += part[v + half_of];
+        *reinterpret_cast<u32x2 *>(gx + (size_t)n * Cin + c) = u32x2{pack2(part[0].x, part[0].y), pack2(part[0].z, part[0].w)};
+    }
 }
 
-// The first `data_blocks` workgroups tiles of gx, whose reductions are longer, the others tiles of gw.
+// The first `data_blocks` workgroups tiles of gx, whose reductions are longer, the others tiles of gw.  With few classes a tile of gx has steps for KW
+// of the eight wavefronts, and a workgroup takes 8 / KW tiles.  gx alone, us with eight to a tile | this: 4096 x 768, 8 classes 13.0 | 5.3,
+// 4096 x 2048, 40 classes 34 | 15; up to 512 tiles eight are better: 128 x 512, 32 classes 3.0 | 3.5, 512 x 768, 24 classes 3.4 | 3.7.
+template <int KW, bool WEIGHT>
 __global__ __launch_bounds__(512) void dense_bwd_kernel(const uint16_t *gy, const uint16_t *w, const uint16_t *x, const float *scale,
                                                         uint16_t *gx, float *gw, int N, int Cin, int Cout, unsigned data_blocks) {
-    __shared__ __align__(16) unsigned char smem[8 * 8192];
-    if (blockIdx.x < data_blocks) dense_bwd_data(gy, w, scale, gx, N, Cin, Cout, blockIdx.x, smem);
-    else dense_bwd_weight(gy, x, scale, gw, N, Cin, Cout, blockIdx.x - data_blocks, smem);
+    constexpr int kEach = WEIGHT ? 8192 : 32 * 144;
+    __shared__ __align__(16) unsigned char smem[8 * kEach];
+    if (!WEIGHT || blockIdx.x < data_blocks) {
+        const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / (KW * 64));
+        dense_bwd_data<KW>(gy, w, scale, gx, N, Cin, Cout, blockIdx.x * (8 / KW) + group, threadIdx.x & (KW * 64 - 1), smem + group * KW * kEach, kEach);
+    } else {
+        dense_bwd_weight(gy, x, scale, gw, N, Cin, Cout, blockIdx.x - data_blocks, smem);
+    }
 }
 
 }  // namespace bops
@@ -698,12 +716,21 @@ hipError_t launch_dense_bwd(const void *x, const void *w, const float *scale, co
     if (!w || !scale || !gy || N <= 0 || Cin <= 0 || Cout <= 0 || Cin % 8 || Cout % 8) return hipErrorInvalidValue;
     if (((uintptr_t)x | (uintptr_t)w | (uintptr_t)scale | (uintptr_t)gy | (uintptr_t)gx | (uintptr_t)gw) & 15) return hipErrorInvalidValue;
     if (gw && !x) return hipErrorInvalidValue;
-    const long long data = gx ? ((long long)N + 31) / 32 * ((Cin + 31) / 32) : 0, weight = gw ? ((long long)Cout + 63) / 64 * ((Cin + 63) / 64) : 0;
-    if (data + weight > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+    const long long tiles = ((long long)N + 31) / 32 * ((Cin + 31) / 32);
+    // wavefronts to a tile of gx: those that have a step of 32 classes; all eight where every tile finds its place at once (they share the store)
+    const int kw = tiles <= 512 ? 8 : Cout <= 32 ? 1 : Cout <= 64 ? 2 : Cout <= 128 ? 4 : 8;
+    const long long data = gx ? (tiles + 8 / kw - 1) / (8 / kw) : 0, weight = gw ? ((long long)Cout + 63) / 64 * ((Cin + 63) / 64) : 0;
+    if (tiles > 0x7FFFFFFFLL || data + weight > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     if (data + weight == 0) return hipSuccess;
-    bops::dense_bwd_kernel<<<dim3((unsigned)(data + weight)), dim3(512), 0, stream>>>(
-        static_cast<const uint16_t *>(gy), static_cast<const uint16_t *>(w), static_cast<const uint16_t *>(x), scale, static_cast<uint16_t *>(gx), gw,
-        N, Cin, Cout, (unsigned)data);
+    auto run = [&](auto kernel) {
+        kernel<<<dim3((unsigned)(data + weight)), dim3(512), 0, stream>>>(static_cast<const uint16_t *>(gy), static_cast<const uint16_t *>(w),
+                                                                         static_cast<const uint16_t *>(x), scale, static_cast<uint16_t *>(gx), gw, N,
+                                                                         Cin, Cout, (unsigned)data);
+    };
+    if (gw) kw == 1 ? run(bops::dense_bwd_kernel<1, true>) : kw == 2 ? run(bops::dense_bwd_kernel<2, true>)
+          : kw == 4 ? run(bops::dense_bwd_kernel<4, true>) : run(bops::dense_bwd_kernel<8, true>);
+    else kw == 1 ? run(bops::dense_bwd_kernel<1, false>) : kw == 2 ? run(bops::dense_bwd_kernel<2, false>)
+       : kw == 4 ? run(bops::dense_bwd_kernel<4, false>) : run(bops::dense_bwd_kernel<8, false>);
     return hipGetLastError();
 }
 

@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kind", ["ones", "odd", "apart"])
-@pytest.mark.parametrize("N,Cin,Cout", [(1, 64, 8), (16, 64, 72), (17, 128, 1000), (31, 192, 40), (32, 64, 264), (33, 320, 1000), (129, 64, 520), (520, 128, 24)])
+@pytest.mark.parametrize("N,Cin,Cout", [(1, 64, 8), (16, 64, 72), (17, 128, 1000), (31, 192, 40), (32, 64, 264), (33, 320, 1000), (129, 64, 520), (520, 128, 24),
+                                        (577, 960, 24), (578, 960, 40), (545, 960, 120)])      # 570, 570, 540 tiles of gx: 8, 4, 2 to a workgroup
 def test_gradients_at_tile_edges(torch_mod, N, Cin, Cout, kind):  # noqa: F811
     torch = torch_mod
     import paper_2203_15980_amd as dl
