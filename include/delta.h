@@ -157,7 +157,10 @@ enum { DELTA_FUSE_NONE = 0, DELTA_FUSE_BLOCK = 1, DELTA_FUSE_NO_STORE = 2 };
  * operators use x, y, N, H, W, Cin (= Cout), R, S, stride, pad and ignore w/scale/shift/res.
  * DELTA_OP_SOFTMAX_CE reads logits x [N, Cin] (storage dtype) and int64 labels in tensor
  * `res` [N], and writes one fp32 (the mean loss) to y.  x, res, y are tensor ids of the
- * bound table.
+ * bound table.  The images' losses are added in a fixed order for each of two kernels: several workgroups
+ * (bf16, 33 to 16384 images, classes a multiple of 8 up to 1024) with a slot of the GPU's scratch that the
+ * context holds, or one workgroup - which also serves launches captured into a graph and contexts beyond
+ * the 64 on a GPU that find a slot; between the two the mean differs by fp32 rounding.
  * Transformer encoder layers (the paper's BERT-base workload, Sec. 5.2; the layer itself is the
  * published post-LN encoder): a linear layer y = act(x w^T + bias + res) is DELTA_OP_CONV with
  * H = sequence length, W = R = S = stride = 1, pad = 0, w [Cout][Cin], scale = ones, shift = bias.
@@ -193,7 +196,7 @@ typedef struct {
     uint64_t d2h_bytes, h2d_bytes;         /* copied since the last delta_stats_reset */
     uint64_t d2h_copies, h2d_copies;
     double d2h_ms, h2d_ms;                 /* sum of copy durations (device timestamps) */
-    uint64_t recompute_launches, recompute_flops;
+    uint64_t recompute_launches, recompute_flops;   /* operators run (a fused block is one), and their flops as launched */
     uint64_t releases_evict, releases_offload, releases_free;
     uint64_t pinned_bytes;
     uint64_t arena_extent_high_water;      /* highest arena offset handed to a tensor placed from the bottom (fragmentation) */
@@ -358,18 +361,23 @@ typedef struct delta_bwd_desc {
     void *gw;                  /* device, fp32 [Cout][R][S][Cin]: receives dL/dw (overwritten), or NULL */
     void *workspace;           /* device scratch, 256-byte aligned: the weight gradient's partial sums (from
                                   its start; at its end where both gradients are made in one pass) and,
-                                  for a strided 1x1 layer, its staging tensor (at its end); needed when gw is set or (strided 1x1) gx is set.  A strided 1x1
-                                  layer whose staging bytes overlap what weight gradients still in flight
-                                  use makes the compute stream wait for them: one workspace of (largest
-                                  partial sums + largest staging tensor) for all layers avoids that */
-    uint64_t workspace_bytes;  /* at least what delta_backward_workspace reports */
+                                  for a strided 1x1 layer, its staging tensor (at its end); needed when gw is
+                                  set or (strided 1x1) gx is set.  A layer whose bytes at the end (staging, or
+                                  the sums of one pass) overlap what weight gradients still in flight use makes
+                                  the compute stream wait for them: one workspace of (largest partial sums +
+                                  largest use of the end) for all layers avoids that; twice the largest
+                                  delta_backward_workspace always does */
+    uint64_t workspace_bytes;  /* what delta_backward_workspace reports, or more.  Where that is more than the layer's
+                                  partial sums and staging (both gradients of a 1x1 layer in one pass), the two kernels that
+                                  run instead need only those, and fewer bytes are accepted down to them */
 } delta_bwd_desc;
 
 /* wt[c][R-1-r][S-1-s][k] = w[k][r][s][c] * scale[k] in the layer's storage type (same byte count as
  * w): with these weights the data gradient is a forward convolution of gpre.  Device pointers;
  * runs on the compute stream. */
 delta_status delta_bwd_weights(delta_ctx *ctx, const delta_layer_desc *layer, void *wt);
-/* Bytes of workspace delta_backward_segment needs for this layer (0 for operators that need none). */
+/* Bytes of workspace with which delta_backward_segment runs this layer as it does best (0 for operators that need none).
+ * Not part of the arena: about 34 MB for 256 -> 128 or 512 -> 128 channels at 128 x 56 x 56 or 128 x 28 x 28. */
 delta_status delta_backward_workspace(delta_ctx *ctx, const delta_layer_desc *layer, uint64_t *out_bytes);
 /* Runs the descriptors in order on the compute stream.  Everything is validated before the first
  * launch.  Output tensors are allocated from the arena when not resident (DELTA_ERR_OOM_ARENA);
@@ -381,7 +389,13 @@ delta_status delta_backward_workspace(delta_ctx *ctx, const delta_layer_desc *la
  * these readers when a tensor is released or rewritten.  The gw buffers and the workspace are the
  * caller's: their contents are ordered for later work on the compute stream only after
  * delta_backward_join (or complete after delta_sync with DELTA_SYNC_COMPUTE), and descriptors of one
- * context must keep using the same workspace or join in between. */
+ * context must keep using the same workspace or join in between.
+ * Which kernels a layer's gradients take follows from its sizes, from whether gx and gw are both asked for and from
+ * workspace_bytes; the same descriptor gives the same bits every time, but gx beside gw may differ from gx alone by
+ * the order of fp32 sums, i.e. in bf16 by a rounding of few entries.  Where gpre is a tensor of its own it is written, also
+ * by a strided 3x3 layer whose gradients both run at the output's resolution and do not read it.
+ * delta_stats counts operators in recompute_launches, here and in delta_recompute_segment: where several run as one
+ * pass (batch normalisation, add and ReLU; ReLU's and batch normalisation's backward) each of them counts. */
 delta_status delta_backward_segment(delta_ctx *ctx, const delta_bwd_desc *descs, uint32_t n);
 /* Orders the compute stream after every weight gradient enqueued so far (no host wait): work given
  * to the compute stream afterwards may read the gw buffers and reuse the workspace. */

@@ -1914,7 +1914,7 @@ delta_status delta_layer_kernel(delta_ctx *c, const delta_layer_desc *layer, cha
         break;
     }
     case DELTA_OP_LAYERNORM: name = "layernorm bf16"; break;
-    case DELTA_OP_BATCHNORM: name = "batchnorm (batch statistics) bf16: stats + finalize + apply"; break;
+    case DELTA_OP_BATCHNORM: name = "batchnorm (batch statistics) bf16: stats + finalize + one pass (with an add and ReLU that follow)"; break;
     case DELTA_OP_RELU: name = "relu bf16"; break;
     case DELTA_OP_ADD: name = "add bf16"; break;
     default: break;

@@ -9,10 +9,10 @@
 //    chunks w, w + workers, ...); a layer of more channels is several slices of C, the slices of a worker on one XCD, where
 //    they share gpre in the L2;
 //  * a chunk's rows of gpre, x and gx_add go from memory straight into LDS (global_load_lds) through a ring of S chunks, S - 1 of them in
-//    flight per CU (72-120 KB): that is what keeps the memory busy while the chunk before is multiplied (0.5 us of a chunk's 2.5);
+//    flight per CU (48-120 KB): that is what keeps the memory busy while the chunk before is multiplied (0.5 us of a chunk's 2.5);
 //  * gw: as in wgrad1x1.hip, transposing LDS reads, sums in registers for the whole launch (at most 64 a lane), partial sums to the workspace
 //    in that kernel's layout, whose reduction adds them in the order of the workers and applies scale;
-//  * gx: 16x16x32 MFMAs with the wavefront's rows of wt in registers for the whole launch (16-64), gpre from LDS; the epilogue finds gx_add
+//  * gx: 16x16x32 MFMAs with the wavefront's rows of wt in registers for the whole launch (8-64), gpre from LDS; the epilogue finds gx_add
 //    and the mask in LDS too, leaves bf16 rows there (in gx_add's place where there is one) and the rows leave as whole lines;
 //  * LDS rows: the 64-byte groups of a row are permuted by the row's low bits, the 16-byte pieces of a group by the next two, so that the four
 //    rows a transposing read touches and the sixteen a gx read touches spread over the banks; the direct load fixes where a lane's
@@ -61,7 +61,7 @@ template <int KT, int CT, bool ADD> struct Shape {
     static constexpr int kSlabs = 4 * CT, SW = kSlabs > 8 ? kSlabs / 8 : 1, PG = kSlabs < 8 ? 8 / kSlabs : 1, kPT = kPixels / 16 / PG;
     static constexpr int kSums = QS > 1 ? (QS - 1) * WK * WC * TK * TC * 4096 : 0;
     static constexpr int kLds = kStages * kSlice + kOut > kSums ? kStages * kSlice + kOut : kSums;
-    static_assert(kStages >= 2 && kLds <= 160 * 1024 && kSlice % 1024 == 0 && (kStages - 2) * kLoads + (kStages - 1) * kStores <= 63, "LDS, vmcnt");
+    static_assert(kStages >= 3 && kLds <= 160 * 1024 && kSlice % 1024 == 0 && (kStages - 2) * kLoads + (kStages - 1) * kStores <= 63, "LDS, vmcnt");
 };
 
 // How the 64-byte groups of a row of T * 128 bytes are permuted, and the 16-byte pieces of a group.
@@ -335,7 +335,9 @@ hipError_t launch(const Args &w, hipStream_t stream) {
 //   of a bottleneck's backward pass still wins (282 us with this layer on two kernels, 278 with it here)
 //   512 -> 256  M = 25088 39 43 | 36 37; but 512 -> 512, 1024 -> 512 and 2048 -> 512 on 12544 and 25088 pixels 31 to 77 | 37 to 90: with 512 gradient
 //   channels a slice holds 64 input channels, and from four slices on gpre's way through the L2 to each of them is what it costs.
-// 4000 pixels and less are small_backward.hip's.
+// small_backward.hip comes first: it takes the smaller layers by its own price, to 4096 or 6400 pixels at most.  Below 4000 pixels (9000 with 512 gradient
+// channels) what it leaves goes to two kernels.  Both lines lie higher than they have to: 1024 -> 256 on 3332 to 3920 pixels 32 | 24 to 27, 128 -> 512 on
+// 7840 and 8624 32 | 25 to 27, but 128 -> 512 on 7056 21.5 | 23.7 and 64 -> 512 on 7056 and 8624 18.4 21.5 | 20.0 22.3 (one stream, below 1 GFLOP).
 bool joint1x1_applies(const ConvArgs &fa) {
     joint::Plan p;
     return joint::plan_for(fa, p) && (p.kt == 8 ? p.slices <= 2 && fa.M >= 9000 : p.slices <= 8 && fa.M >= 4000);

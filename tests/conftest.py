@@ -1,4 +1,3 @@
-import gc
 import os
 import sys
 
@@ -26,9 +25,3 @@ def pytest_collection_modifyitems(config, items):
     for it in items:
         if "gpu" in it.keywords:
             it.add_marker(skip)
-
-
-def pytest_runtest_setup(item):
-    """The test that reads the allocator's counter twice: what earlier tests left in reference cycles goes before the first reading."""
-    if "test_zz_no_alloc" in item.nodeid:
-        gc.collect()

@@ -88,3 +88,48 @@ def test_sums_share_a_workspace_with_the_second_stream(torch_mod):  # noqa: F811
     assert "wgrad1x1" in name
     assert float(np.max(np.abs(small[1] - ref[1])) / np.max(np.abs(ref[1]))) <= 1e-5
     d.close()
+
+
+@pytest.mark.parametrize("Cin,Cout,H,W,add", [(64, 128, 131, 193, True), (256, 64, 151, 167, False), (128, 512, 95, 95, True)])
+def test_infinities_in_the_last_pixel(torch_mod, Cin, Cout, H, W, add):  # noqa: F811
+    """The last chunk's rows past the last pixel are fetched from that pixel and cleared: an infinite input and an infinite gradient there reach
+    their own column and row of gw and their own pixel of gx, as in float64, and nothing else."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    M = H * W
+    nbytes = [M * Cin * 2, M * Cout * 2, M * Cout * 2, M * Cin * 2, M * Cin * 2]       # x, y, gy, gx, gx_add
+    d = make_delta(torch, sum(nbytes) + (2 << 20))
+    d.bind(nbytes)
+    gen = torch.Generator(device="cuda:0").manual_seed(41)
+    view = {}
+    for t, C in ((0, Cin), (2, Cout), (4, Cin)):
+        d.alloc(t)
+        view[t] = d.arena[d.tensor_ptr(t) - d.arena.data_ptr():][:nbytes[t]].view(torch.bfloat16).reshape(M, C)
+        view[t].normal_(generator=gen)
+        view[t].masked_fill_(view[t] == 0, 0.5)
+    d.alloc(1)
+    view[0][-1, 3], view[2][-1, 5] = float("inf"), float("-inf")
+    wt = torch.randn(Cin, Cout, device="cuda:0", generator=gen).to(torch.bfloat16)
+    wt.masked_fill_(wt == 0, 0.5)
+    scale = torch.rand(Cout, device="cuda:0", generator=gen) + 0.5
+    fwd = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=wt.data_ptr(), scale=scale.data_ptr(), shift=scale.data_ptr(), N=1, H=H, W=W,
+                       Cin=Cin, Cout=Cout, R=1, S=1, stride=1, pad=0, relu=0)
+    ws = torch.full((d.backward_workspace(fwd),), 255, dtype=torch.uint8, device="cuda:0")
+    gw = torch.full((Cout, Cin), float("nan"), device="cuda:0")
+    desc = dl.BwdDesc(fwd=fwd, gy=2, gpre=2, gx=3, gx_add=4 if add else dl.NO_TENSOR, mask_gx=1, wt=wt.data_ptr(), gw=gw.data_ptr(),
+                      workspace=ws.data_ptr(), workspace_bytes=ws.numel())
+    assert d.backward_kernel(desc).endswith(JOINT)
+    torch.cuda.synchronize()
+    d.backward_segment([desc])
+    d.sync()
+    xf, gf = view[0].double(), view[2].double()
+    ref_gw = (gf.t().contiguous() @ xf) * scale.double()[:, None]
+    ref_gx = gf @ wt.double().t().contiguous() + (view[4].double() if add else 0.0)
+    ref_gx = torch.where(xf > 0, ref_gx, torch.zeros_like(ref_gx))
+    gx = d.arena[d.tensor_ptr(3) - d.arena.data_ptr():][:nbytes[3]].view(torch.bfloat16).reshape(M, Cin).double()
+    for got, ref, most in ((gw.double(), ref_gw, 1e-5), (gx, ref_gx, 4e-3)):
+        inf = torch.isinf(ref)
+        assert bool(inf.any()) and not bool(torch.isnan(ref).any())
+        assert torch.equal(got[inf], ref[inf])
+        assert float((got[~inf] - ref[~inf]).abs().max() / ref[~inf].abs().max()) <= most
+    d.close()
