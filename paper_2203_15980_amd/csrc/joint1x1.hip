@@ -301,7 +301,10 @@ bool plan_for(const ConvArgs &fa, Plan &p) {
     // One workgroup per CU, and no more of them than have as many chunks as the longest; at least two chunks (three of 32 pixels) to a worker,
     // whose partial sums cost as much as a chunk (us with one | two | three: 64 -> 256 on 12544 pixels 17.0 | 14.3 | 14.5, 64 -> 64
     // 10.1 | 9.4 | 9.9, 256 -> 64 16.9 | 17.1 | 15.6, 128 -> 256 23.1 | 23.6 | 20.7).
-    const int most = 256 / p.slices < 1 ? 1 : 256 / p.slices, least = p.pixels == 64 ? 2 : 3;
+    // All slices of a worker are on its XCD, whose 32 CUs hold 32 / slices workers: one worker more on any of them is a second round for the whole launch
+    // (us with 256 / slices workers, this, and two kernels: 768 -> 256 on 26950 pixels 75, 47, 55; 448 -> 256 on 159936 239, 143, 167; 1280 -> 128 on 68992
+    // 189, 131, 168).
+    const int most = p.slices > 32 ? 8 : 32 / p.slices * 8, least = p.pixels == 64 ? 2 : 3;
     int each = (p.nchunks + most - 1) / most;
     if (each < least) each = least;
     p.workers = (p.nchunks + each - 1) / each;

@@ -28,6 +28,9 @@ CASES = [
     ("bf16", 1, 131, 193,  64, 512, 1, 1, False, True,  JOINT),
     ("bf16", 1, 131, 193, 128, 512, 1, 1, True,  True,  JOINT),     # two slices of 64
     ("bf16", 1,  64,  65,  64,  64, 1, 1, True,  True,  JOINT),     # 65 chunks: 33 workers of two, the last has one
+    ("bf16", 1, 131, 193, 320,  64, 1, 1, True,  True,  JOINT),     # five of 64: 48 workers, six to an XCD of 32 CUs
+    ("bf16", 1, 131, 193, 768, 256, 1, 1, False, True,  JOINT),     # six of 128: 40 workers
+    ("bf16", 1,  97,  89, 448, 256, 1, 1, True,  True,  JOINT),     # seven of 64: 32 workers
     ("bf16", 1,  79,  89, 1024, 256, 1, 1, True, True,  JOINT),     # eight slices of 128; 31 workers, the longest with eight chunks
     ("bf16", 1,  79,  89, 1152, 256, 1, 1, True, True,  "wgrad1x1 bf16, second stream"),      # nine slices
     ("bf16", 1,  95,  95, 128, 512, 1, 1, False, True,  JOINT),     # 9025 pixels
