@@ -248,7 +248,18 @@ bool small_backward_applies(const ConvArgs *da, const ConvArgs &fa) {
     //     1x1 256 -> 512  M = 784 19 | 11   3136 26 | 19   4704 30 | 26   6272 30 | 32     512 -> 1024  M = 2352 30 | 25   1024 -> 2048  M = 588 32 | 26
     //     3x3 128 -> 128  M = 784 27 | 18   3136 33 | 22   4704 32 | 26   6272 33 | 34     256 -> 256  M = 1568 33 | 29 (11)   512 -> 512  M = 588 37 | 45 (13)
     const int most = tiles < 64 ? 4096 : fa.stride > 1 ? 5000 : 6400;
-    return M <= most && 7000. + 0.4 * gx + 0.13 * gw <= (!da ? 11000. : fa.R == 3 ? 38000. : 26000.);
+    const double ns = 7000. + 0.4 * gx + 0.13 * gw;
+    if (M > most || ns > (!da ? 11000. : fa.R == 3 ? 38000. : 26000.)) return false;
+    //   The sum is right for tiles of gx that have the chip to themselves a few times over; with more of them it promises too little, and the other
+    //   route's larger tiles load less (stride 1 | 2, number of tiles of gx in brackets, other route | this one):
+    //     8 to 15 steps   1x1 2048 -> 512  M = 784 [1600] 26 | 23, 35 | 29     768 -> 512  M = 2156 [1632] 26 | 26, 29 | 33   2744 [2064] 28 | 32, 30 | 40
+    //                     1x1 1024 -> 640  M = 1568 [1568] 31 | 22, 35 | 29    512 -> 512  M = 3528 [1776] 26 | 28, 29 | 35
+    //     1 to 4          1x1 1024 -> 64   M = 3920 [3936] 23 | 20, 30 | 31    4704 [4704] 19 | 24, 32 | 36     2048 -> 256  M = 1568 [3136] 33 | 22, 34 | 32
+    //     9, 18, 36       3x3 512 -> 64    M = 4704 [2352] 34 | 33   5488 [2752] 35 | 38     512 -> 128  M = 3528 [1776] 39 | 36 (34)   3920 [1968] 36 | 41 (37)
+    //                     3x3 512 -> 256   M = 2156 [1088] 37 | 41 (36)     256 -> 256  M = 3920 [984] 43 | 37 (33)
+    if (!da || (fa.R == 3 && fa.stride > 1)) return true;        // (one class of a strided layer's gx: a quarter of its pixels, faster up to the lines above)
+    const long long line = fa.R == 3 ? (ns > 35000. ? 1024 : 2560) : smallb::steps_of(*da) >= 8 ? 1600 : 4096;
+    return splitk::tiles_of(*da) <= line;
 }
 
 const char *small_backward_name(const ConvArgs &fa) { return fa.bf16 ? "small_backward bf16" : "small_backward f32"; }

@@ -32,6 +32,16 @@ CASES = [
     ("bf16", 1,  64, 64,   64,  64, 1, 1, False, True,  SAME),       # 4096 positions: the last that go this way with few tiles of gw
     ("bf16", 1,  64, 65,   64,  64, 1, 1, False, True,  "joint1x1 bf16, the same launch"),
     ("bf16", 1,  64, 100, 256, 256, 1, 1, False, True,  SAME),       # 6400: the last with 64
+    ("bf16", 1,  40, 40, 1024, 512, 1, 1, True,  True,  SAME),       # eight steps: 1600 tiles of gx are the last
+    ("bf16", 1,   1, 1601, 1024, 512, 1, 1, True, True, "wgrad1x1 bf16, second stream"),
+    ("bf16", 1,  79, 80, 1024, 512, 1, 2, False, True,  SAME),
+    ("bf16", 1,   1, 3201, 1024, 512, 1, 2, False, True, "wgrad1x1 bf16, second stream"),
+    ("bf16", 1,  64, 64, 1024,  64, 1, 1, False, True,  SAME),       # one step: 4096
+    ("bf16", 1,  17, 241, 1024, 64, 1, 1, False, True,  "joint1x1 bf16, the same launch"),
+    ("bf16", 1,  64, 80,  512,  64, 3, 1, False, True,  SAME),       # nine: 2560
+    ("bf16", 1, 197,  26,  512,  64, 3, 1, False, True, "wgrad3x3 bf16, second stream"),         # 2576
+    ("bf16", 1,  58, 64,  512, 128, 3, 1, True,  True,  SAME),       # 1856 tiles, 34988 by the sum
+    ("bf16", 1,  47, 79,  512, 128, 3, 1, True,  True,  "wgrad3x3 bf16, second stream"),        # 1872, 35157
     ("bf16", 10, 14, 14,  256, 256, 3, 1, True,  True,  SAME),       # 1960 pixels: the wider tile of gw
     ("bf16", 16, 14, 14,  256, 256, 3, 1, True,  True,  SAME),       # 3136: the narrow one, 576 of them; 3.7 GFLOP
     ("bf16", 1,  56, 56,  256,  64, 1, 1, True,  True,  SAME),
