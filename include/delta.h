@@ -316,8 +316,8 @@ delta_status delta_set_skip_copies(delta_ctx *ctx, int32_t skip);
  * gy[n,p,q,:] * [y > 0], zero elsewhere, so that both gradients are stride-1 operations on it
  * (stride^2 times the arithmetic).  A 1x1 layer with stride > 1 only reads the input pixels
  * (stride*p, stride*q): gpre keeps the bytes of y, the weight gradient reads
- * just those, and the data gradient is computed at the output's resolution into the
- * workspace and then spread out (zeros between), gx_add added in a second bf16 rounding.
+ * just those, and the data gradient is computed at the output's resolution and stored to
+ * those pixels, zeros between; with gx_add or mask_gx it goes into the workspace first, and gx_add is added in a second bf16 rounding.
  * Other operators (bf16 only; gpre must be gy, gx_add unused):
  *   DELTA_OP_MAXPOOL   gx receives gy routed to the first maximal element of each window (scan order
  *                      r, then s); needs fwd.x resident.  With mask_gx, gx is also multiplied by [x > 0].

@@ -519,6 +519,27 @@ hipError_t launch_conv_scatter(const ConvArgs &a, hipStream_t stream) {
     return launch<false, 128, 64, 4, 1>(a, stream);
 }
 
+void as_spread(ConvArgs &a, int stride, int OH, int OW) {
+    a.oy_s = stride; a.oy_a = a.oy_b = 0; a.OH = OH; a.OW = OW;
+    a.wR = a.wS = 1; a.w_r0 = a.w_s0 = 0; a.w_step = 1;
+    a.spread = 1;
+}
+
+// Whether the kernel that launch_conv takes for these arguments can store the spread form.
+bool conv_spread_applies(const ConvArgs &a, int stride, int OH, int OW) {
+    ConvArgs sa = a;
+    as_spread(sa, stride, OH, OW);
+    if (conv_check(a) || a.oy_s || a.R != 1 || a.S != 1 || a.stride != 1 || a.res || a.mask || conv_scatter_check(sa)) return false;
+    if (splitk_before_stream(a)) return true;
+    return !conv1x1_stream_applies(a) && (conv_splitk_applies(a) || gemm_nt_applies(a));
+}
+
+hipError_t launch_conv_spread(const ConvArgs &a, hipStream_t stream) {
+    if (!a.spread || conv_scatter_check(a) || a.res || a.mask) return hipErrorInvalidValue;
+    if (splitk_before_stream(a) || conv_splitk_applies(a)) return launch_conv_splitk(a, stream);
+    return launch_gemm_nt(a, stream);
+}
+
 hipError_t launch_conv(const ConvArgs &a, hipStream_t stream) {
     if (conv_check(a) || a.oy_s) return hipErrorInvalidValue;
     if (splitk_before_stream(a)) return launch_conv_splitk(a, stream);

@@ -83,8 +83,9 @@ __device__ __forceinline__ void wave_lds_fence() {
 // BM: rows of x per workgroup, 256 or 128 (BM / 64 wavefront rows); BN: rows of w (output channels)
 // per workgroup, 256, 192 or 128 (BN / 64 wavefront columns).
 // S: LDS buffers of one K slice each (2 or 4); S - 1 slices are in flight while one is multiplied.
-template <int BM, int BN, int S>
-__global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(ConvArgs a, int tiles_n, int tiles_total) {
+// SPREAD: row m is stored at the pixel (s p, s q) of its image and the rest of that pixel's s x s block as zeros (ConvArgs::spread).
+template <int BM, int BN, int S, bool SPREAD>
+__global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(ConvArgs a, int tiles_n, int tiles_total, Divisor dpq, Divisor dq) {
     static_assert(S >= 2 && S <= 4, "two to four slice buffers");
     constexpr int kBM = BM, kBN = BN, kWM = BM / 64, kWN = BN / 64, kWaves = kWM * kWN;
     constexpr int kXBytes = kBM * kBK * 2;                  // x rows of one buffer
@@ -228,8 +229,8 @@ __global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(Con
     // ---- epilogue.  acc[i][j]: lane holds pixel (x row) l32 of tile i and channels 8*rb + 4*half + e of tile j
     unsigned char *stg = smem + (size_t)wv * (32 * kStgPitch);
     unsigned char *yg = static_cast<unsigned char *>(a.y);
-    const unsigned char *rg = static_cast<const unsigned char *>(a.res);
-    const unsigned char *mg = static_cast<const unsigned char *>(a.mask);
+    const unsigned char *rg = SPREAD ? nullptr : static_cast<const unsigned char *>(a.res);
+    const unsigned char *mg = SPREAD ? nullptr : static_cast<const unsigned char *>(a.mask);
     const int prow = lane >> 3, cseg = lane & 7;
     const int chan = n0 + wn * 64 + cseg * 8;
     // scale / shift of this lane's 8 channels in the row-major phase (the same for every row)
@@ -283,7 +284,15 @@ __global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(Con
             float v[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = v[e] * sc[e] + sh[e];
-            const size_t off = ((size_t)m * N + chan) * 2;
+            size_t off = ((size_t)m * N + chan) * 2;
+            if constexpr (SPREAD) {
+                const int n = divide(m, dpq), pq = m - n * (a.P * a.Q), p = divide(pq, dq), h = p * a.oy_s, w = (pq - p * a.Q) * a.oy_s;
+                off = (((size_t)n * a.OH + h) * a.OW + w) * N * 2 + (size_t)chan * 2;
+                const int rows = a.OH - h < a.oy_s ? a.OH - h : a.oy_s, cols = a.OW - w < a.oy_s ? a.OW - w : a.oy_s;
+                for (int dy = 0; dy < rows; ++dy)
+                    for (int dx = dy == 0; dx < cols; ++dx)
+                        *reinterpret_cast<u32x4 *>(yg + off + ((size_t)dy * a.OW + dx) * N * 2) = u32x4{0u, 0u, 0u, 0u};
+            }
             if (rg) {
                 const u32x4 rv = rres[kAhead ? (i & 1) : 0][t];
                 v[0] += lo16(rv.x); v[1] += hi16(rv.x); v[2] += lo16(rv.y); v[3] += hi16(rv.y);
@@ -362,12 +371,15 @@ const Tile *choose_tile(const ConvArgs &a) {
         if (tiles > 0x3FFFFFF0LL) return nullptr;
         if (tiles >= (a.Cout <= 128 ? 512 : 128)) return &t;
     }
-    if (a.Cin >= 512 && tiles_of(a, kTiles[3]) <= 512) return &kTiles[3];
+    // The spread form stores four times the rows it computes: two workgroups to a CU overlap that, the deeper ring does not.  Gradient of a strided
+    // layer alone, us, four buffers | two: 1024 -> 2048 at 128 x 14 x 14 48 | 38, at 100 x 13 x 11 47 | 34, 512 -> 1024 at 64 x 28 x 28 32 | 24.  (From 128
+    // tiles of 256 x 256 on those: 256 -> 512 at 128 x 56 x 56 66, two launches 92, 128 x 128 tiles 79; 512 -> 1024 at 128 x 28 x 28 39 | 50 | 45.)
+    if (a.Cin >= 512 && tiles_of(a, kTiles[3]) <= 512) return &kTiles[a.spread ? 2 : 3];
     return nullptr;
 }
 
-template <int BM, int BN, int S>
-hipError_t launch_tile(const ConvArgs &a, hipStream_t stream) {
+template <int BM, int BN, int S, bool SPREAD>
+hipError_t launch_as(const ConvArgs &a, hipStream_t stream) {
     constexpr size_t pipe = (size_t)S * ((size_t)BM * gemm::kBK * 2 + (size_t)BN * gemm::kBK * 2);
     constexpr size_t stage_out = (size_t)(BM / 64) * (BN / 64) * 32 * gemm::kStgPitch;
     constexpr size_t lds = pipe > stage_out ? pipe : stage_out;
@@ -378,13 +390,19 @@ hipError_t launch_tile(const ConvArgs &a, hipStream_t stream) {
     const long long blocks = (total + 7) / 8 * 8;
     static bool raised = false;
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm::gemm_nt_kernel<BM, BN, S>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm::gemm_nt_kernel<BM, BN, S, SPREAD>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    gemm::gemm_nt_kernel<BM, BN, S><<<dim3((unsigned)blocks), dim3(threads), lds, stream>>>(a, tiles_n, (int)total);
+    gemm::gemm_nt_kernel<BM, BN, S, SPREAD><<<dim3((unsigned)blocks), dim3(threads), lds, stream>>>(
+        a, tiles_n, (int)total, make_divisor(SPREAD ? a.P * a.Q : 1), make_divisor(SPREAD ? a.Q : 1));
     return hipGetLastError();
+}
+
+template <int BM, int BN, int S>
+hipError_t launch_tile(const ConvArgs &a, hipStream_t stream) {
+    return a.spread ? launch_as<BM, BN, S, true>(a, stream) : launch_as<BM, BN, S, false>(a, stream);
 }
 
 }  // namespace
@@ -405,7 +423,7 @@ const char *gemm_nt_kernel_name(const ConvArgs &a) {
 }
 
 hipError_t launch_gemm_nt(const ConvArgs &a, hipStream_t stream) {
-    const Tile *t = conv_check(a) ? nullptr : choose_tile(a);
+    const Tile *t = (a.spread ? conv_scatter_check(a) : conv_check(a)) || (a.oy_s && !a.spread) ? nullptr : choose_tile(a);
     if (!t) return hipErrorInvalidValue;
     if (t->bm == 256) return t->bn == 256 ? launch_tile<256, 256, 2>(a, stream) : launch_tile<256, 192, 2>(a, stream);
     if (t->bn == 256) return launch_tile<128, 256, 3>(a, stream);

@@ -24,6 +24,9 @@ struct ConvArgs {
     // taps (w_r0 + r * w_step, w_s0 + s * w_step) of a weight tensor [Cout, wR, wS, Cin].
     int oy_s = 0, oy_a = 0, oy_b = 0, OH = 0, OW = 0;
     int wR = 0, wS = 0, w_r0 = 0, w_s0 = 0, w_step = 1;
+    // With the scattered form of a 1x1 layer: the pixels of the oy_s x oy_s block that starts at an output pixel, inside the image and not
+    // written themselves, are stored as zeros (launch_conv_spread: a strided 1x1 layer's data gradient in one pass).
+    int spread = 0;
 };
 
 // Division by a launch constant as a multiplication, exact for 0 <= n < 2^31: with 2^(s-1) < d <= 2^s and mul = ceil(2^(31+s) / d),
@@ -89,6 +92,10 @@ hipError_t launch_conv(const ConvArgs &a, hipStream_t stream);
 const char *conv_scatter_check(const ConvArgs &a);
 const char *conv_scatter_kernel_name(const ConvArgs &a);
 hipError_t launch_conv_scatter(const ConvArgs &a, hipStream_t stream);
+// A stride-1 1x1 layer stored at the pixels (stride p, stride q) of an [N, OH, OW, Cout] tensor, zeros between (no residual, no mask)
+bool conv_spread_applies(const ConvArgs &a, int stride, int OH, int OW);
+void as_spread(ConvArgs &a, int stride, int OH, int OW);
+hipError_t launch_conv_spread(const ConvArgs &a, hipStream_t stream);
 bool dgrad_s2_applies(const ConvArgs &a);
 hipError_t launch_dgrad_s2(const ConvArgs &a, hipStream_t stream);
 // conv_splitk.hip: layers with too little output to fill the chip, the reduction split over a workgroup's wavefronts

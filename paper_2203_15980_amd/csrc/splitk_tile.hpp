@@ -84,6 +84,7 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int tiles_m, int ti
     const int em = m0 + (tid >> 3), ec = n0 + 4 * (tid & 7);
     const bool finishes = tid < 256 && em < a.M && ec < a.Cout;
     size_t eoff = 0;
+    int erows = 1, ecols = 1;          // spread form: rows and columns of the pixel's block
     u32x4 eres = {0u, 0u, 0u, 0u}, emask = {0u, 0u, 0u, 0u};
     if (finishes) {
         size_t pixel = (size_t)em;
@@ -91,6 +92,10 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int tiles_m, int ti
             const int n = divide(em, inv.pq), pq = em - n * PQ;
             const int p = divide(pq, inv.q), q = pq - p * a.Q;
             pixel = ((size_t)n * a.OH + (p * a.oy_s + a.oy_a)) * a.OW + (q * a.oy_s + a.oy_b);
+            if (a.spread) {
+                erows = a.OH - p * a.oy_s < a.oy_s ? a.OH - p * a.oy_s : a.oy_s;
+                ecols = a.OW - q * a.oy_s < a.oy_s ? a.OW - q * a.oy_s : a.oy_s;
+            }
         }
         eoff = (pixel * a.Cout + ec) * ES;
         auto read4 = [&](const void *p) {
@@ -213,6 +218,13 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int tiles_m, int ti
         for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
     }
     unsigned char *y = static_cast<unsigned char *>(a.y) + eoff;
+    if (a.spread)
+        for (int at = 1; at < erows * ecols; ++at) {
+            const int dy = at / ecols, dx = at - dy * ecols;
+            unsigned char *z = y + ((size_t)dy * a.OW + dx) * a.Cout * ES;
+            if constexpr (BF16) *reinterpret_cast<u32x2 *>(z) = u32x2{0u, 0u};
+            else *reinterpret_cast<u32x4 *>(z) = u32x4{0u, 0u, 0u, 0u};
+        }
     if constexpr (BF16) {
         u32x2 o = {pack2(v[0], v[1]), pack2(v[2], v[3])};
         if (a.mask) o = u32x2{keep_where_positive_bf16(o.x, emask[0]), keep_where_positive_bf16(o.y, emask[1])};
