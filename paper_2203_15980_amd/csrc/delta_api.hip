@@ -1464,6 +1464,10 @@ bool spreads_in_place(const delta_bwd_desc &D, const delta::ConvArgs &da) {
     const delta_layer_desc &L = D.fwd;
     return strided_1x1(L) && D.gx != DELTA_NO_TENSOR && D.gx_add == DELTA_NO_TENSOR && !D.mask_gx && delta::conv_spread_applies(da, L.stride, L.H, L.W);
 }
+// Whether that launch also makes gpre = gy * [y > 0] of a layer that has a mask of its own.
+bool masks_on_the_way(const delta_bwd_desc &D, const delta::ConvArgs &fa, const delta::ConvArgs &da, OneLaunch one) {
+    return one == OL_JOINT && D.fwd.relu && !D.gy_masked && D.gx_add == DELTA_NO_TENSOR && delta::joint1x1_masks(da, fa);
+}
 // `fa` after as_stride_1
 uint64_t backward_workspace_bytes(const delta_layer_desc &L, const delta::ConvArgs &fa) {
     uint64_t need = partials_bytes(fa) + staging_bytes(L, fa);
@@ -1781,6 +1785,9 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
         delta::ConvArgs fo = fa;                             // the forward layer's own geometry (fa is its stride-1 view)
         fo.stride = L.stride; fo.P = outP; fo.Q = outQ; fo.M = L.N * outP * outQ;
         const bool no_spread = D.gpre == D.gy && class_only(D, fo);
+        const OneLaunch one = one_launch(D, fo, fa, da);
+        const bool masks = masks_on_the_way(D, fa, da, one);     // the gradients' own launch makes gpre
+        const unsigned char *masked_by = nullptr;
         if (own_mask || (L.stride > 1 && !direct && !no_spread)) {
             Tensor &tgp = c->tensors[D.gpre];
             const unsigned char *yp = nullptr;
@@ -1790,7 +1797,9 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
                 yp = c->arena + ty.offset;
             }
             if ((r = compute_writes(c, tgp)) != DELTA_OK) return r;
-            if (L.stride == 1 || direct)
+            if (masks)
+                masked_by = yp;
+            else if (L.stride == 1 || direct)
                 HIP_TRY(c, delta::launch_relu_mask(yp, c->arena + tgy.offset, c->arena + tgp.offset, tgp.bytes,
                                                    fa.bf16, s));
             else
@@ -1799,7 +1808,6 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
         }
         const unsigned char *gp = c->arena + c->tensors[D.gpre].offset;
         Ev ready;
-        const OneLaunch one = one_launch(D, fo, fa, da);
         const bool aside = D.gw && one == OL_NONE && wgrad_aside(L, fa);
         if (D.gw) {
             if ((r = compute_uses(c, c->tensors[L.x])) != DELTA_OK) return r;
@@ -1844,7 +1852,9 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
                 const uint64_t need = delta::joint1x1_workspace_bytes(fa);
                 unsigned char *sums = static_cast<unsigned char *>(D.workspace) + ((D.workspace_bytes - need) & ~(uint64_t)255);
                 if (aux_holds(c, sums, need) && (r = join_aux(c)) != DELTA_OK) return r;
-                HIP_TRY(c, delta::launch_joint1x1(da, fa, gp, static_cast<float *>(D.gw), sums, need, s));
+                unsigned char *gpre = masks ? c->arena + c->tensors[D.gpre].offset : nullptr;
+                if (masks) da.x = c->arena + tgy.offset;
+                HIP_TRY(c, delta::launch_joint1x1(da, fa, da.x, masked_by, gpre, static_cast<float *>(D.gw), sums, need, s));
             } else if (one == OL_LAYER) {
                 HIP_TRY(c, delta::launch_small_backward(&da, fa, gp, static_cast<float *>(D.gw), s));
             } else if (in_place) {

@@ -17,11 +17,15 @@
 //  * LDS rows: the 64-byte groups of a row are permuted by the row's low bits, the 16-byte pieces of a group by the next two, so that the four
 //    rows a transposing read touches and the sixteen a gx read touches spread over the banks; the direct load fixes where a lane's
 //    16 bytes land, so the permutation is applied to the address each lane fetches;
-//  * rows past the last pixel are fetched from the last pixel and overwritten with zeros in LDS before they are read.
+//  * rows past the last pixel are fetched from the last pixel and overwritten with zeros in LDS before they are read;
+//  * OWN: a layer with a ReLU of its own brings gy and y, whose rows have one buffer: gpre = gy * [y > 0] replaces gy in LDS and leaves for memory on
+//    the way, instead of in a launch before this one that reads both and whose result is read again.
 // Backward of three conv2_x bottlenecks on 32 x 56 x 56 440 -> 346 us, of conv3_x's first on 128 x 56 x 56 610 -> 551, of its others on 128 x 28 x 28 322 -> 278.
 // joint1x1_applies says where the line lies and what both sides measured.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -41,27 +45,33 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 struct Args {
     const unsigned char *g, *x, *add, *wt;       // [M,K], [M,C], [M,C] (ADD), [C,K]
     unsigned char *gx;                           // [M,C]
+    const unsigned char *y;                      // OWN: g is gy, and gpre = gy * [y > 0] is made here
+    unsigned char *gpre;                         // [M,K] both
     float *partial;                              // [workers][slices][KT CT][4 tiles][4][64 lanes] f32x4
     int M, C, nchunks, workers, slices, mask;
 };
 
-template <int KT, int CT, bool ADD> struct Shape {
-    static constexpr int kPixels = KT + 2 * CT <= 6 ? 64 : 32;                    // of a chunk
+template <int KT, int CT, bool ADD, bool OWN> struct Shape {
+    static constexpr int kPixels = KT + 2 * CT <= 6 && !OWN ? 64 : 32;            // of a chunk
     static constexpr int kG = kPixels * KT * 128, kX = kPixels * CT * 128;        // bytes
     static constexpr int kSlice = kG + kX * (ADD ? 2 : 1), kOut = ADD ? 0 : kX;   // of a chunk; of the separate output tile
-    static constexpr int kFit = (160 * 1024 - kOut) / kSlice, kStages = kFit < 4 ? kFit : 4;
+    static constexpr int kY = OWN ? kG : 0;                                       // y's rows, one buffer of them
+    static constexpr int kFit = (160 * 1024 - kOut - kY) / kSlice, kStages = kFit < 4 ? kFit : 4;
     static constexpr int kBlocks = kSlice / 1024, kLoads = (kBlocks + 7) / 8;     // 1 KB loads of a chunk; per wavefront
-    static constexpr int kStores = (kX + 8191) / 8192;                           // 16-byte stores per thread that has any
+    static constexpr int kStores = (kX + 8191) / 8192;                           // 16-byte stores of gx per thread that has any
+    static constexpr int kMasks = kY / 8192;                                     // 16-byte pieces of gpre (and of y) per thread
     // 32 x 32 tiles of gw: NK x NC, on WK x WC wavefronts (QS of them on each, sharing a chunk's pixels)
     static constexpr int NK = 2 * KT, NC = 2 * CT;
     static constexpr int WC = NC >= 8 ? 8 : NK >= 8 && NC == 2 ? 1 : NK == 2 && NC == 4 ? 4 : 2;
     static constexpr int WK = NC >= 8 ? 1 : NK >= 8 && NC == 2 ? 8 : NK == 2 ? 2 : 4;
     static constexpr int QS = 8 / (WK * WC), TK = NK / WK, TC = NC / WC;
     // gx: slabs of 16 channels, SW to a wavefront, PG wavefronts share a slab's pixels
-    static constexpr int kSlabs = 4 * CT, SW = kSlabs > 8 ? kSlabs / 8 : 1, PG = kSlabs < 8 ? 8 / kSlabs : 1, kPT = kPixels / 16 / PG;
+    static constexpr int kSlabs = 4 * CT, SW = kSlabs > 8 ? kSlabs / 8 : 1, kGroups = kSlabs < 8 ? kSlabs : 8;
+    static constexpr int PG = 8 / kGroups, kPT = kPixels / 16 / PG;
     static constexpr int kSums = QS > 1 ? (QS - 1) * WK * WC * TK * TC * 4096 : 0;
-    static constexpr int kLds = kStages * kSlice + kOut > kSums ? kStages * kSlice + kOut : kSums;
-    static_assert(kStages >= 3 && kLds <= 160 * 1024 && kSlice % 1024 == 0 && (kStages - 2) * kLoads + (kStages - 1) * kStores <= 63, "LDS, vmcnt");
+    static constexpr int kRing = kStages * kSlice + kOut + kY, kLds = kRing > kSums ? kRing : kSums;
+    static_assert(kStages >= 3 && kLds <= 160 * 1024 && kSlice % 1024 == 0 && (kStages - 2) * kLoads + (kStages - 1) * (kStores + kMasks) <= 63, "LDS, vmcnt");
+    static_assert(!OWN || (!ADD && kY % 8192 == 0), "a whole number of pieces to a thread");
 };
 
 // How the 64-byte groups of a row of T * 128 bytes are permuted, and the 16-byte pieces of a group.
@@ -84,9 +94,9 @@ __device__ __forceinline__ void meet() {
     asm volatile("" ::: "memory");
 }
 
-template <int KT, int CT, bool ADD>
+template <int KT, int CT, bool ADD, bool OWN>
 __global__ __launch_bounds__(512) void joint1x1_kernel(Args a) {
-    using T = Shape<KT, CT, ADD>;
+    using T = Shape<KT, CT, ADD, OWN>;
     constexpr int S = T::kStages, P = T::kPixels, XP = CT * 128, L = T::kLoads;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
@@ -129,14 +139,43 @@ __global__ __launch_bounds__(512) void joint1x1_kernel(Args a) {
             load_lds_b128(base[i], (uint32_t)(m0 + r) * pitch[i] + seg[i], lds0 + (uint32_t)(buf * T::kSlice) + dst[i]);
         }
     };
+    // OWN: y's rows of a chunk, laid out as gpre's, a thread's pieces 512 apart; they have one buffer, free as soon as the chunk before is masked
+    unsigned char *ybuf = smem + S * T::kSlice + T::kOut;
+    auto fetch_y = [&](int chunk) {
+        if constexpr (OWN) {
+            const int m0 = chunk * P, last = a.M - 1 - m0;
+#pragma unroll
+            for (int i = 0; i < T::kMasks; ++i) {
+                const int at = (tid + 512 * i) * 16, r = at / (KT * 128), slot = at % (KT * 128) >> 4;
+                const uint32_t where = (uint32_t)((((slot >> 2) ^ group_flip<KT>(r)) << 6) + (((slot & 3) ^ piece_flip(r)) << 4));
+                load_lds_b128(a.y, (uint32_t)(m0 + (r < last ? r : last)) * krow + where,
+                              lds0 + (uint32_t)(S * T::kSlice + T::kOut + wv * 1024 + i * 8192));
+            }
+        }
+    };
     // Loads and stores complete in order: a chunk has landed when at most the later chunks' loads and the stores issued since are under way.
-    const bool stores = wv * 1024 < T::kX;                       // this wavefront stores rows (kStores times a chunk)
-    auto wait_chunk = [&](int later, int stored) {
+    const bool stores = wv * 1024 < T::kX;                       // this wavefront stores rows of gx (kStores times a chunk)
+    const bool masks = OWN && slice == 0;                        // the first slice stores gpre (kMasks times a chunk)
+    auto wait_for = [&](int later, int stored, auto each) {
 #pragma unroll
         for (int r = 0; r <= S - 2; ++r)
 #pragma unroll
             for (int s = 0; s <= S - 1; ++s)
-                if (later == r && stored == s) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(r * L + s * T::kStores) : "memory");
+                if (later == r && stored == s) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(r * L + s * decltype(each)::value) : "memory");
+    };
+    auto wait_chunk = [&](int t, int mine) {
+        if constexpr (OWN) {
+            // y of chunk t was the first thing asked for after chunk t - 1 was masked; behind it came chunk t + S - 2 and that chunk's stores
+            const bool steady = t + S - 2 < mine;
+            if (t == 0) wait_for(steady ? S - 2 : 0, 0, std::integral_constant<int, 0>());
+            else if (masks && stores) wait_for(steady, steady, std::integral_constant<int, T::kStores + T::kMasks>());
+            else if (masks) wait_for(steady, steady, std::integral_constant<int, T::kMasks>());
+            else if (stores) wait_for(steady, steady, std::integral_constant<int, T::kStores>());
+            else wait_for(steady, 0, std::integral_constant<int, 0>());
+        } else {
+            const int later = mine - 1 - t < S - 2 ? mine - 1 - t : S - 2;
+            wait_for(later, !stores ? 0 : t < S - 1 ? t : S - 1, std::integral_constant<int, T::kStores>());
+        }
     };
 
     // ---- gw: transposing reads.  A lane supplies row 8 (lane / 32) + (lane % 16) / 4 (+ 4) of a 16-pixel step and channels
@@ -167,7 +206,7 @@ __global__ __launch_bounds__(512) void joint1x1_kernel(Args a) {
 
     // ---- this wavefront's rows of wt, for the whole launch, behind the first chunk: slab s, 32 channels of k per step, lane: c l16, k 8 quad .. + 7
     constexpr int kSteps = KT * 2;
-    const int sg = wv % (8 / T::PG), pg = wv / (8 / T::PG);
+    const int sg = wv % T::kGroups, pg = wv / T::kGroups;
     u32x4 wt[T::SW][kSteps];
 #pragma unroll
     for (int s = 0; s < T::SW; ++s)
@@ -180,14 +219,17 @@ __global__ __launch_bounds__(512) void joint1x1_kernel(Args a) {
 #pragma unroll
         for (int q = 0; q < kSteps; ++q) asm volatile("" : "+v"(wt[s][q]));
 
+    if constexpr (OWN) fetch_y(chunk_of(0));
 #pragma unroll
     for (int t = 1; t < S - 1; ++t)
         if (t < mine) fetch(chunk_of(t), t);
     for (int t = 0, buf = 0; t < mine; ++t) {
-        const int later = mine - 1 - t < S - 2 ? mine - 1 - t : S - 2;
-        wait_chunk(later, stores ? (t < S - 1 ? t : S - 1) : 0); // this wavefront's part of chunk t has landed
+        wait_chunk(t, mine);                                     // this wavefront's part of chunk t has landed
         meet();                                                  // everyone's has; the buffer of chunk t - 1 is free
-        if (t + S - 1 < mine) fetch(chunk_of(t + S - 1), buf == 0 ? S - 1 : buf - 1);
+        auto ahead = [&] {
+            if (t + S - 1 < mine) fetch(chunk_of(t + S - 1), buf == 0 ? S - 1 : buf - 1);
+        };
+        if constexpr (!OWN) ahead();
         unsigned char *sl = smem + buf * T::kSlice;
         const int m0 = chunk_of(t) * P, valid = a.M - m0;
         if (valid < P) {                                         // the last chunk of all: rows past the last pixel
@@ -196,6 +238,28 @@ __global__ __launch_bounds__(512) void joint1x1_kernel(Args a) {
                 if (r >= valid) *reinterpret_cast<u32x4 *>(sl + i * 16) = u32x4{0u, 0u, 0u, 0u};
             }
             meet();
+        }
+        if constexpr (OWN) {                                     // gpre = gy * [y > 0], in place and to memory
+            u32x4 o[T::kMasks];
+#pragma unroll
+            for (int i = 0; i < T::kMasks; ++i) {
+                const int at = (tid + 512 * i) * 16;
+                const u32x4 gv = *reinterpret_cast<const u32x4 *>(sl + at), yv = *reinterpret_cast<const u32x4 *>(ybuf + at);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[i][e] = keep_where_positive_bf16(gv[e], yv[e]);
+                *reinterpret_cast<u32x4 *>(sl + at) = o[i];
+            }
+            meet();
+            if (t + 1 < mine) fetch_y(chunk_of(t + 1));
+            ahead();
+            if (masks) {
+#pragma unroll
+                for (int i = 0; i < T::kMasks; ++i) {
+                    const int at = (tid + 512 * i) * 16, r = at / (KT * 128), slot = at % (KT * 128) >> 4;
+                    const uint32_t where = (uint32_t)((((slot >> 2) ^ group_flip<KT>(r)) << 6) + (((slot & 3) ^ piece_flip(r)) << 4));
+                    if (r < valid) *reinterpret_cast<u32x4 *>(a.gpre + (size_t)(m0 + r) * krow + where) = o[i];
+                }
+            }
         }
         // ---- gw
 #pragma unroll
@@ -311,17 +375,17 @@ bool plan_for(const ConvArgs &fa, Plan &p) {
     return true;
 }
 
-template <int KT, int CT, bool ADD>
+template <int KT, int CT, bool ADD, bool OWN>
 hipError_t launch(const Args &w, hipStream_t stream) {
-    using T = Shape<KT, CT, ADD>;
+    using T = Shape<KT, CT, ADD, OWN>;
     static bool raised = false;
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&joint1x1_kernel<KT, CT, ADD>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&joint1x1_kernel<KT, CT, ADD, OWN>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, T::kLds);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    joint1x1_kernel<KT, CT, ADD><<<dim3((unsigned)((w.workers + 7) / 8 * 8 * w.slices)), dim3(512), T::kLds, stream>>>(w);
+    joint1x1_kernel<KT, CT, ADD, OWN><<<dim3((unsigned)((w.workers + 7) / 8 * 8 * w.slices)), dim3(512), T::kLds, stream>>>(w);
     return hipGetLastError();
 }
 
@@ -351,24 +415,42 @@ size_t joint1x1_workspace_bytes(const ConvArgs &fa) {
     return joint1x1_applies(fa) && joint::plan_for(fa, p) ? (size_t)p.workers * p.slices * p.kt * p.ct * 16384 : 0;
 }
 
+// The widest gradient to the fewest input channels, where gpre is most of what a launch moves.  us with its reduction, the mask's launch before it | on the way:
+// 64 -> 256 on 401408 pixels 180 | 135, 100352 47 | 37, 34496 27 | 23, 6305 16.1 | 15.8; 128 -> 512 on 100352 108 | 91, 39200 51 | 43, 9025 27 | 26; 64 -> 512 on
+// 100352 91 | 78; 192 -> 256 (three slices, of which the first stores gpre) on 25088 27.3 | 27.2.  128 -> 512 keeps three chunks of gy and x and one of y in 144 KB: chunks
+// of 16 pixels in four buffers 113 us (half the work per barrier), of 32 with y in two 109.
+bool joint1x1_masks(const ConvArgs &da, const ConvArgs &fa) {
+    joint::Plan p;
+    return joint1x1_applies(fa) && joint::plan_for(fa, p) && (p.kt == 4 || p.kt == 8) && p.ct == 1 && !da.res;
+}
+
+// gpre, where it is not null: g is gy and gpre = gy * [y > 0] is made and stored here (joint1x1_masks).
 // da: the data gradient's convolution, complete (its mask, where there is one, is x); fa: the layer, with x and scale; g = gpre; gw fp32
 // [Cout][Cin]; workspace of joint1x1_workspace_bytes(fa), 16-byte aligned.
-hipError_t launch_joint1x1(const ConvArgs &da, const ConvArgs &fa, const void *g, float *gw, void *workspace, size_t workspace_bytes,
-                           hipStream_t stream) {
+hipError_t launch_joint1x1(const ConvArgs &da, const ConvArgs &fa, const void *g, const void *y, void *gpre, float *gw, void *workspace,
+                           size_t workspace_bytes, hipStream_t stream) {
     joint::Plan p;
     if (!joint1x1_applies(fa) || !joint::plan_for(fa, p) || !g || !gw || !workspace || !fa.x || !fa.scale || !da.w || !da.y ||
         (da.mask && da.mask != fa.x) || da.x != g || da.M != fa.M || da.Cin != fa.Cout || da.Cout != fa.Cin || da.oy_s || da.relu ||
-        workspace_bytes < joint1x1_workspace_bytes(fa) ||
-        (((uintptr_t)g | (uintptr_t)fa.x | (uintptr_t)da.w | (uintptr_t)da.y | (uintptr_t)da.res | (uintptr_t)workspace) & 15))
+        workspace_bytes < joint1x1_workspace_bytes(fa) || !y != !gpre || (gpre && (!joint1x1_masks(da, fa) || gpre == g || gpre == y)) ||
+        (((uintptr_t)g | (uintptr_t)fa.x | (uintptr_t)da.w | (uintptr_t)da.y | (uintptr_t)da.res | (uintptr_t)workspace |
+          (uintptr_t)y | (uintptr_t)gpre) & 15))
         return hipErrorInvalidValue;
     joint::Args w;
     w.g = static_cast<const unsigned char *>(g); w.x = static_cast<const unsigned char *>(fa.x); w.add = static_cast<const unsigned char *>(da.res);
     w.wt = static_cast<const unsigned char *>(da.w); w.gx = static_cast<unsigned char *>(da.y); w.partial = static_cast<float *>(workspace);
     w.M = fa.M; w.C = fa.Cin; w.nchunks = p.nchunks; w.workers = p.workers; w.slices = p.slices; w.mask = da.mask != nullptr;
+    w.y = static_cast<const unsigned char *>(y); w.gpre = static_cast<unsigned char *>(gpre);
     hipError_t e;
+    if (gpre) {                                                  // chunks of 32 pixels, as many workers or fewer
+        const int chunks = (fa.M + 31) / 32, each = (chunks + p.workers - 1) / p.workers;
+        w.nchunks = chunks;
+        w.workers = p.workers = (chunks + each - 1) / each;
+        e = p.kt == 4 ? joint::launch<4, 1, false, true>(w, stream) : joint::launch<8, 1, false, true>(w, stream);
+    } else
     switch (p.kt * 10 + p.ct) {
 #define DELTA_JOINT(KT, CT) \
-    case KT * 10 + CT: e = da.res ? joint::launch<KT, CT, true>(w, stream) : joint::launch<KT, CT, false>(w, stream); break;
+    case KT * 10 + CT: e = da.res ? joint::launch<KT, CT, true, false>(w, stream) : joint::launch<KT, CT, false, false>(w, stream); break;
     DELTA_JOINT(1, 1) DELTA_JOINT(1, 2) DELTA_JOINT(1, 4) DELTA_JOINT(2, 1) DELTA_JOINT(2, 2) DELTA_JOINT(2, 4)
     DELTA_JOINT(4, 1) DELTA_JOINT(4, 2) DELTA_JOINT(8, 1)
 #undef DELTA_JOINT

@@ -218,8 +218,9 @@ hipError_t launch_wgrad3x3(const ConvArgs &a, const void *g, float *gw, void *wo
 // joint1x1.hip: both gradients of a 1x1 stride-1 bf16 layer in one pass over its tensors (da: the data gradient's convolution, fa: the layer)
 bool joint1x1_applies(const ConvArgs &fa);
 size_t joint1x1_workspace_bytes(const ConvArgs &fa);
-hipError_t launch_joint1x1(const ConvArgs &da, const ConvArgs &fa, const void *g, float *gw, void *workspace, size_t workspace_bytes,
-                           hipStream_t stream);
+bool joint1x1_masks(const ConvArgs &da, const ConvArgs &fa);     // whether it can make gpre = gy * [y > 0] on the way
+hipError_t launch_joint1x1(const ConvArgs &da, const ConvArgs &fa, const void *g, const void *y, void *gpre, float *gw, void *workspace,
+                           size_t workspace_bytes, hipStream_t stream);
 // small_backward.hip: both gradients of a layer that cannot fill the chip in one launch (da: the data gradient's convolution
 // or null for the weight gradient alone, fa: the layer as
 // launch_wgrad or launch_wgrad_s2 takes it)

@@ -136,3 +136,49 @@ def test_infinities_in_the_last_pixel(torch_mod, Cin, Cout, H, W, add):  # noqa:
         assert torch.equal(got[inf], ref[inf])
         assert float((got[~inf] - ref[~inf]).abs().max() / ref[~inf].abs().max()) <= most
     d.close()
+
+
+@pytest.mark.parametrize("Cin,Cout,H,W,add", [(64, 256, 131, 193, False), (64, 256, 97, 89, False), (64, 256, 1, 12545, False), (128, 512, 131, 193, False),
+                                              (64, 512, 95, 95, False), (128, 512, 9001, 1, False), (64, 256, 131, 193, True), (128, 256, 131, 193, False)])
+def test_own_mask_on_the_way(torch_mod, Cin, Cout, H, W, add):  # noqa: F811
+    """A layer with a ReLU of its own: gpre and gx carry the bits of the mask's own launch followed by the masked layer, gw its sums in another order
+    (bound as in the helper above).  Chunks of 32 and 16 pixels, ragged ends, slices; the last two run the mask's launch."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    M = H * W
+    nbytes = [M * Cin * 2, M * Cout * 2, M * Cout * 2, M * Cin * 2, M * Cin * 2, M * Cout * 2, M * Cin * 2]    # x, y, gy, gx, gx_add, gpre, gx apart
+    d = make_delta(torch, sum(nbytes) + (2 << 20))
+    d.bind(nbytes)
+    gen = torch.Generator(device="cuda:0").manual_seed(43)
+    view = lambda t, C: d.arena[d.tensor_ptr(t) - d.arena.data_ptr():][:nbytes[t]].view(torch.int16).reshape(M, C)      # noqa: E731
+    for t, C in ((0, Cin), (1, Cout), (2, Cout), (4, Cin)):
+        d.alloc(t)
+        view(t, C).view(torch.bfloat16).normal_(generator=gen)
+    y = view(1, Cout)
+    y[0, :8] = torch.tensor([0, -32768, 1, 0x7F80, 0x7F81, -128, -1, 0x3F80], dtype=torch.int16, device="cuda:0")      # zeros, infinities, NaN
+    wt = torch.randn(Cin, Cout, device="cuda:0", generator=gen).to(torch.bfloat16)
+    scale = torch.rand(Cout, device="cuda:0", generator=gen) + 0.5
+    fwd = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=wt.data_ptr(), scale=scale.data_ptr(), shift=scale.data_ptr(), N=1, H=H, W=W,
+                       Cin=Cin, Cout=Cout, R=1, S=1, stride=1, pad=0, relu=1)
+    ws = torch.full((d.backward_workspace(fwd),), 255, dtype=torch.uint8, device="cuda:0")
+    gw = [torch.full((Cout, Cin), float("nan"), device="cuda:0") for _ in range(3)]
+    b = lambda gy, gpre, gx, masked, i: dl.BwdDesc(fwd=fwd, gy=gy, gpre=gpre, gx=gx, gx_add=4 if add else dl.NO_TENSOR, mask_gx=1, gy_masked=masked,  # noqa: E731
+                                                   wt=wt.data_ptr(), gw=gw[i].data_ptr(), workspace=ws.data_ptr(), workspace_bytes=ws.numel())
+    own = b(2, 5, 3, 0, 0)
+    assert d.backward_kernel(own).endswith(JOINT)
+    torch.cuda.synchronize()
+    d.backward_segment([own])
+    d.sync()
+    gpre, gx = view(5, Cout).clone(), view(3, Cin).clone()
+    want = torch.where((y > 0) & (y < 0x7F81), view(2, Cout), torch.zeros_like(y))
+    assert torch.equal(gpre, want)
+    view(5, Cout).fill_(0x7FC1)
+    torch.cuda.synchronize()
+    d.backward_segment([b(2, 5, 3, 0, 1), b(5, 5, 6, 1, 2)])     # again; and on the gradient as it left it
+    d.sync()
+    assert torch.equal(view(5, Cout), want) and torch.equal(view(3, Cin), gx) and torch.equal(view(6, Cin), gx)
+    assert torch.equal(gw[0], gw[1])
+    ref = (gpre.view(torch.bfloat16).double().t().contiguous() @ view(0, Cin).view(torch.bfloat16).double()) * scale.double()[:, None]
+    for g in gw:
+        assert float((g.double() - ref).abs().max() / ref.abs().max()) <= 1e-5
+    d.close()
