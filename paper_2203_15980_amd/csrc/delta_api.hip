@@ -1464,6 +1464,7 @@ bool spreads_in_place(const delta_bwd_desc &D, const delta::ConvArgs &da) {
     const delta_layer_desc &L = D.fwd;
     return strided_1x1(L) && D.gx != DELTA_NO_TENSOR && D.gx_add == DELTA_NO_TENSOR && !D.mask_gx && delta::conv_spread_applies(da, L.stride, L.H, L.W);
 }
+bool same_pixels(const delta_layer_desc &a, const delta_layer_desc &b) { return a.N == b.N && a.H == b.H && a.W == b.W && a.Cin == b.Cin; }
 // Whether that launch also makes gpre = gy * [y > 0] of a layer that has a mask of its own.
 bool masks_on_the_way(const delta_bwd_desc &D, const delta::ConvArgs &fa, const delta::ConvArgs &da, OneLaunch one) {
     return one == OL_JOINT && D.fwd.relu && !D.gy_masked && D.gx_add == DELTA_NO_TENSOR && delta::joint1x1_masks(da, fa);
@@ -1671,10 +1672,14 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
     }
     if ((r = need_identity_factors(c)) != DELTA_OK) return r;
     hipStream_t s = c->stream[S_COMPUTE];
+    // The descriptor of this call whose gx a stride-2 1x1 layer has stored with zeros between its pixels and nothing has written since: whoever adds
+    // that tensor need not read the zeros.
+    const delta_bwd_desc *even = nullptr;
     for (uint32_t i = 0; i < n; ++i) {
         const delta_bwd_desc &D = descs[i];
         const delta_layer_desc &L = D.fwd;
         const BwdKind kind = bwd_kind(L);
+        if (kind != BK_CONV || (even && (D.gx == even->gx || D.gpre == even->gx))) even = nullptr;
         if (kind == BK_STEM) {
             if ((r = prepare_backward_stem(c, D, i, fa)) != DELTA_OK) return r;
             Tensor &tgy = c->tensors[D.gy];
@@ -1854,11 +1859,13 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
                 if (aux_holds(c, sums, need) && (r = join_aux(c)) != DELTA_OK) return r;
                 unsigned char *gpre = masks ? c->arena + c->tensors[D.gpre].offset : nullptr;
                 if (masks) da.x = c->arena + tgy.offset;
-                HIP_TRY(c, delta::launch_joint1x1(da, fa, da.x, masked_by, gpre, static_cast<float *>(D.gw), sums, need, s));
+                HIP_TRY(c, delta::launch_joint1x1(da, fa, da.x, masked_by, gpre, static_cast<float *>(D.gw), sums, need,
+                                                     even && D.gx_add == even->gx && same_pixels(even->fwd, L), s));
             } else if (one == OL_LAYER) {
                 HIP_TRY(c, delta::launch_small_backward(&da, fa, gp, static_cast<float *>(D.gw), s));
             } else if (in_place) {
                 HIP_TRY(c, delta::launch_conv_spread(da, s));
+                if (L.stride == 2) even = &D;
             } else {
                 HIP_TRY(c, delta::launch_conv(da, s));
             }

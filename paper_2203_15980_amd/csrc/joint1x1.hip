@@ -17,6 +17,8 @@
 //  * LDS rows: the 64-byte groups of a row are permuted by the row's low bits, the 16-byte pieces of a group by the next two, so that the four
 //    rows a transposing read touches and the sixteen a gx read touches spread over the banks; the direct load fixes where a lane's
 //    16 bytes land, so the permutation is applied to the address each lane fetches;
+//  * EVEN: gx_add has values at pixels of even row and column only (a stride-2 layer's data gradient, just stored): the loads of the others go to a few
+//    zero pixels of the tensor, other ones in every workgroup, which the caches hold, so that a quarter of the tensor is read;
 //  * rows past the last pixel are fetched from the last pixel and overwritten with zeros in LDS before they are read;
 //  * OWN: a layer with a ReLU of its own brings gy and y, whose rows have one buffer: gpre = gy * [y > 0] replaces gy in LDS and leaves for memory on
 //    the way, instead of in a launch before this one that reads both and whose result is read again.
@@ -49,9 +51,14 @@ struct Args {
     unsigned char *gpre;                         // [M,K] both
     float *partial;                              // [workers][slices][KT CT][4 tiles][4][64 lanes] f32x4
     int M, C, nchunks, workers, slices, mask;
+    int N, H, W, zeros;                          // EVEN: images, their rows and columns; how many zero pixels stand for all, less one (1, 2, .. 16 less one)
+    Divisor dw, dh;
 };
 
-template <int KT, int CT, bool ADD, bool OWN> struct Shape {
+// What is added to gx: nothing; a tensor; a tensor whose pixels of odd row or column are known to be zeros.
+enum Add { NONE, ALL, EVEN };
+
+template <int KT, int CT, int ADD, bool OWN> struct Shape {
     static constexpr int kPixels = KT + 2 * CT <= 6 && !OWN ? 64 : 32;            // of a chunk
     static constexpr int kG = kPixels * KT * 128, kX = kPixels * CT * 128;        // bytes
     static constexpr int kSlice = kG + kX * (ADD ? 2 : 1), kOut = ADD ? 0 : kX;   // of a chunk; of the separate output tile
@@ -94,7 +101,7 @@ __device__ __forceinline__ void meet() {
     asm volatile("" ::: "memory");
 }
 
-template <int KT, int CT, bool ADD, bool OWN>
+template <int KT, int CT, int ADD, bool OWN>
 __global__ __launch_bounds__(512) void joint1x1_kernel(Args a) {
     using T = Shape<KT, CT, ADD, OWN>;
     constexpr int S = T::kStages, P = T::kPixels, XP = CT * 128, L = T::kLoads;
@@ -109,10 +116,12 @@ __global__ __launch_bounds__(512) void joint1x1_kernel(Args a) {
     const unsigned char *base[L];
     int row[L];
     uint32_t seg[L], pitch[L], dst[L];
+    bool even[L];
 #pragma unroll
     for (int i = 0; i < L; ++i) {
         const int n = wv * L + i < T::kBlocks ? wv * L + i : T::kBlocks - 1, b = n * 1024 + lane * 16;
         dst[i] = (uint32_t)n * 1024u;
+        even[i] = ADD == EVEN && n * 1024 >= T::kG + T::kX;
         if (n * 1024 < T::kG) {
             row[i] = b / (KT * 128);
             const int slot = b % (KT * 128) >> 4;
@@ -131,12 +140,17 @@ __global__ __launch_bounds__(512) void joint1x1_kernel(Args a) {
     }
     typedef __attribute__((address_space(3))) unsigned char *lptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
+    const int zero0 = ADD == EVEN ? worker % a.N * a.H * a.W + 1 : 0;   // pixel 1 of some image: every workgroup has lines of its own
     auto fetch = [&](int chunk, int buf) {
         const int m0 = chunk * P, last = a.M - 1 - m0;           // rows past the last pixel: that pixel
 #pragma unroll
         for (int i = 0; i < L; ++i) {
-            const int r = row[i] < last ? row[i] : last;
-            load_lds_b128(base[i], (uint32_t)(m0 + r) * pitch[i] + seg[i], lds0 + (uint32_t)(buf * T::kSlice) + dst[i]);
+            int m = m0 + (row[i] < last ? row[i] : last);
+            if (ADD == EVEN && even[i]) {
+                const int t = divide(m, a.dw), w = m - t * a.W, h = t - divide(t, a.dh) * a.H;
+                if ((h | w) & 1) m = zero0 + 2 * (row[i] & a.zeros);
+            }
+            load_lds_b128(base[i], (uint32_t)m * pitch[i] + seg[i], lds0 + (uint32_t)(buf * T::kSlice) + dst[i]);
         }
     };
     // OWN: y's rows of a chunk, laid out as gpre's, a thread's pieces 512 apart; they have one buffer, free as soon as the chunk before is masked
@@ -375,7 +389,7 @@ bool plan_for(const ConvArgs &fa, Plan &p) {
     return true;
 }
 
-template <int KT, int CT, bool ADD, bool OWN>
+template <int KT, int CT, int ADD, bool OWN>
 hipError_t launch(const Args &w, hipStream_t stream) {
     using T = Shape<KT, CT, ADD, OWN>;
     static bool raised = false;
@@ -424,11 +438,17 @@ bool joint1x1_masks(const ConvArgs &da, const ConvArgs &fa) {
     return joint1x1_applies(fa) && joint::plan_for(fa, p) && (p.kt == 4 || p.kt == 8) && p.ct == 1 && !da.res;
 }
 
+// From here on a gx_add that is zeros but for its pixels of even row and column is read at those pixels only; the loads of the others take zeros that
+// the caches hold.  Block of a strided layer, 256 channels to 128, us, all of gx_add read | this: on 128 x 56 x 56 475 | 455, 96 376 | 365, 64 280 | 274, but
+// 40 209.5 | 211.2 and 24 155 | 156, where the caches still hold the tensor.  In several slices it never pays: 512 to 256 on 128 x 28 x 28 372 | 377, on
+// 64 x 56 x 56 650 | 660.
+constexpr size_t kEvenBytes = (size_t)96 << 20;
+
 // gpre, where it is not null: g is gy and gpre = gy * [y > 0] is made and stored here (joint1x1_masks).
 // da: the data gradient's convolution, complete (its mask, where there is one, is x); fa: the layer, with x and scale; g = gpre; gw fp32
 // [Cout][Cin]; workspace of joint1x1_workspace_bytes(fa), 16-byte aligned.
 hipError_t launch_joint1x1(const ConvArgs &da, const ConvArgs &fa, const void *g, const void *y, void *gpre, float *gw, void *workspace,
-                           size_t workspace_bytes, hipStream_t stream) {
+                           size_t workspace_bytes, bool add_even, hipStream_t stream) {
     joint::Plan p;
     if (!joint1x1_applies(fa) || !joint::plan_for(fa, p) || !g || !gw || !workspace || !fa.x || !fa.scale || !da.w || !da.y ||
         (da.mask && da.mask != fa.x) || da.x != g || da.M != fa.M || da.Cin != fa.Cout || da.Cout != fa.Cin || da.oy_s || da.relu ||
@@ -440,17 +460,22 @@ hipError_t launch_joint1x1(const ConvArgs &da, const ConvArgs &fa, const void *g
     w.g = static_cast<const unsigned char *>(g); w.x = static_cast<const unsigned char *>(fa.x); w.add = static_cast<const unsigned char *>(da.res);
     w.wt = static_cast<const unsigned char *>(da.w); w.gx = static_cast<unsigned char *>(da.y); w.partial = static_cast<float *>(workspace);
     w.M = fa.M; w.C = fa.Cin; w.nchunks = p.nchunks; w.workers = p.workers; w.slices = p.slices; w.mask = da.mask != nullptr;
+    w.N = fa.N; w.H = fa.H; w.W = fa.W; w.dw = make_divisor((uint32_t)fa.W); w.dh = make_divisor((uint32_t)fa.H);
+    w.zeros = 0;                                                 // pixels 1, 3, .. of the first row (of the first column, if there is one column)
+    while (w.zeros < 15 && 1 + 2 * (2 * w.zeros + 1) < fa.W) w.zeros = 2 * w.zeros + 1;
     w.y = static_cast<const unsigned char *>(y); w.gpre = static_cast<unsigned char *>(gpre);
     hipError_t e;
     if (gpre) {                                                  // chunks of 32 pixels, as many workers or fewer
         const int chunks = (fa.M + 31) / 32, each = (chunks + p.workers - 1) / p.workers;
         w.nchunks = chunks;
         w.workers = p.workers = (chunks + each - 1) / each;
-        e = p.kt == 4 ? joint::launch<4, 1, false, true>(w, stream) : joint::launch<8, 1, false, true>(w, stream);
+        e = p.kt == 4 ? joint::launch<4, 1, joint::NONE, true>(w, stream) : joint::launch<8, 1, joint::NONE, true>(w, stream);
+    } else if (add_even && da.res && p.ct == 4 && p.slices == 1 && (size_t)fa.M * fa.Cin * 2 >= kEvenBytes) {
+        e = p.kt == 1 ? joint::launch<1, 4, joint::EVEN, false>(w, stream) : joint::launch<2, 4, joint::EVEN, false>(w, stream);
     } else
     switch (p.kt * 10 + p.ct) {
 #define DELTA_JOINT(KT, CT) \
-    case KT * 10 + CT: e = da.res ? joint::launch<KT, CT, true, false>(w, stream) : joint::launch<KT, CT, false, false>(w, stream); break;
+    case KT * 10 + CT: e = da.res ? joint::launch<KT, CT, joint::ALL, false>(w, stream) : joint::launch<KT, CT, joint::NONE, false>(w, stream); break;
     DELTA_JOINT(1, 1) DELTA_JOINT(1, 2) DELTA_JOINT(1, 4) DELTA_JOINT(2, 1) DELTA_JOINT(2, 2) DELTA_JOINT(2, 4)
     DELTA_JOINT(4, 1) DELTA_JOINT(4, 2) DELTA_JOINT(8, 1)
 #undef DELTA_JOINT

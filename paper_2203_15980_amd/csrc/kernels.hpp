@@ -215,12 +215,13 @@ const char *wgrad3x3_check(const ConvArgs &a);
 size_t wgrad3x3_workspace_bytes(const ConvArgs &a);
 hipError_t launch_wgrad3x3(const ConvArgs &a, const void *g, float *gw, void *workspace, size_t workspace_bytes, hipStream_t stream);
 
-// joint1x1.hip: both gradients of a 1x1 stride-1 bf16 layer in one pass over its tensors (da: the data gradient's convolution, fa: the layer)
+// joint1x1.hip: both gradients of a 1x1 stride-1 bf16 layer in one pass over its tensors (da: the data gradient's convolution, fa: the layer;
+// add_even: da.res is known to hold zeros at every pixel of odd row or column)
 bool joint1x1_applies(const ConvArgs &fa);
 size_t joint1x1_workspace_bytes(const ConvArgs &fa);
 bool joint1x1_masks(const ConvArgs &da, const ConvArgs &fa);     // whether it can make gpre = gy * [y > 0] on the way
 hipError_t launch_joint1x1(const ConvArgs &da, const ConvArgs &fa, const void *g, const void *y, void *gpre, float *gw, void *workspace,
-                           size_t workspace_bytes, hipStream_t stream);
+                           size_t workspace_bytes, bool add_even, hipStream_t stream);
 // small_backward.hip: both gradients of a layer that cannot fill the chip in one launch (da: the data gradient's convolution
 // or null for the weight gradient alone, fa: the layer as
 // launch_wgrad or launch_wgrad_s2 takes it)

@@ -66,3 +66,49 @@ def test_spread_gradient_carries_the_bits_of_the_layer_at_stride_1(torch_mod, ca
     d.close()
     assert np.array_equal(got, want)
     assert want.any()
+
+
+@pytest.mark.parametrize("case", [(61, 57, 58, 0), (25, 8001, 1, 0), (98305, 1, 2, 0), (62, 57, 57, 1), (60, 56, 55, 0)], ids=lambda c: "%dx%dx%d_%d" % c)
+def test_a_gradient_with_known_zeros_is_added_as_if_all_of_it_were_read(torch_mod, case):  # noqa: F811
+    """The strided layer's gx added by the layer that runs next (256 -> 128 channels, both gradients in one pass): in one call, where its zeros are
+    known, the bits of one call per layer.  The last flag: a third layer overwrites the tensor in between.  (60 x 56 x 55 lies below the line.)"""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    N, H, W, between = case
+    print("case", case, flush=True)
+    P, Q, rng = (H - 1) // 2 + 1, (W - 1) // 2 + 1, np.random.default_rng(7)
+    bits = lambda *shape: ((rng.integers(0, 1 << 16, shape, np.uint16) & 0x80FF) | 0x3F00).astype(np.uint16)     # noqa: E731  # +-[0.5, 2)
+    x, g512, g128 = bits(N, H, W, 256), bits(N, P, Q, 512), bits(N, H, W, 128)
+    dev = lambda *shape: _dev(torch, bits(*shape).view(np.uint8).reshape(-1))                                    # noqa: E731
+    d, put, get = _small_ctx(torch, [x.nbytes, g512.nbytes, g128.nbytes, x.nbytes, x.nbytes, g512.nbytes, g128.nbytes],
+                             mb=4 + (3 * x.nbytes + 2 * g512.nbytes + 2 * g128.nbytes >> 20))
+    put(0, x), put(1, g512), put(2, g128)
+    put(3, np.full_like(x, 12345))
+    one, keep = torch.ones(512, device="cuda:0"), []
+
+    def desc(gy, y, gx, add, cout, stride, gw):
+        w, wt, out = torch.zeros(cout * 256, dtype=torch.bfloat16, device="cuda:0"), dev(256, cout), torch.zeros(cout, 256, device="cuda:0")
+        fwd = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=y, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=one.data_ptr(), shift=one.data_ptr(), N=N, H=H, W=W,
+                           Cin=256, Cout=cout, R=1, S=1, stride=stride, pad=0, relu=0)
+        work = torch.empty(max(256, d.backward_workspace(fwd)), dtype=torch.uint8, device="cuda:0")
+        keep.extend([w, wt, out, work])
+        return dl.BwdDesc(fwd=fwd, gy=gy, gpre=gy, gx=gx, gx_add=add, mask_gx=int(add != dl.NO_TENSOR), wt=wt.data_ptr(), gw=out.data_ptr() if gw else None,
+                          workspace=work.data_ptr(), workspace_bytes=work.numel())
+
+    chain = [desc(1, 5, 3, dl.NO_TENSOR, 512, 2, False)]
+    if between:
+        chain.append(desc(2, 6, 3, dl.NO_TENSOR, 128, 1, False))
+    chain.append(desc(2, 6, 4, 3, 128, 1, True))
+    assert ", spread" in d.backward_kernel(chain[0]) and "joint1x1" in d.backward_kernel(chain[-1]), [d.backward_kernel(k) for k in chain]
+    outs = []
+    for calls in ([chain], [[k] for k in chain]):
+        for call in calls:
+            d.backward_segment(call)
+        d.backward_join()
+        d.sync()
+        outs.append((get(4, x.shape, np.uint16).copy(), keep[-2].cpu().numpy().copy()))
+        d.release(4, dl.EV_FREE)
+        put(4, np.zeros_like(x))
+    d.close()
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+    assert outs[0][0].any()
