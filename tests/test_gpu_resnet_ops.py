@@ -62,6 +62,16 @@ def test_maxpool_is_bit_exact(torch_mod, dtype, N, H, W, C, R, stride, pad):
     assert got.tobytes() == ref.tobytes()          # a maximum of stored values needs no rounding
 
 
+# windows of 3 x 3 that hang over the image on every side: images smaller than the window, padding of two, strides past it
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("N,H,W,stride,pad", [(3, 1, 1, 1, 1), (2, 1, 6, 1, 2), (2, 5, 2, 2, 2), (1, 3, 3, 1, 0), (2, 7, 11, 4, 2), (5, 112, 111, 2, 1)])
+def test_maxpool_windows_over_the_edge_are_bit_exact(torch_mod, dtype, N, H, W, stride, pad):
+    print("maxpool", dtype, N, H, W, stride, pad, flush=True)
+    l = synth.LayerSpec("mp", "maxpool", "x0", None, "mp", N, H, W, 16, 16, 3, 3, stride, pad, False)
+    got, ref = run_one(torch_mod, l, dtype)
+    assert got.tobytes() == ref.tobytes()
+
+
 @pytest.mark.parametrize("dtype,tol", [("bf16", 2e-2), ("f32", 1e-4)])
 def test_avgpool_matches_oracle(torch_mod, dtype, tol):
     l = synth.LayerSpec("ap", "avgpool", "x0", None, "ap", 3, 7, 5, 72, 72, 7, 5, 1, 0, False)
