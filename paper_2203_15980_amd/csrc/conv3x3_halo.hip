@@ -24,8 +24,11 @@
 // first pieces of the next step are read under the last MFMAs of this one.  Taps outside the image are redirected to a row of zeros in LDS, so no
 // operand needs masking.  The step order is fixed, so the first forward and every recomputation
 // add in the same order and a recomputed tensor is bit-identical to the original.
+// A last round of few tiles goes out in runs of 128, 64 or 32 pixels (SPLIT, launch_one): ResNet-50 forward at batch 128 2260 -> 2230 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -54,8 +57,9 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int BM, int BN, int HL>
-__global__ __launch_bounds__((BM / 32) * (BN / 64) * 64, BM == 256 ? 4 : 1) void conv3x3_halo_kernel(ConvArgs a, int HR) {
+// SPLIT: the tiles from `whole` on go out in `pieces` runs of pixels each.
+template <int BM, int BN, int HL, bool SPLIT>
+__global__ __launch_bounds__((BM / 32) * (BN / 64) * 64, BM == 256 ? 4 : 1) void conv3x3_halo_kernel(ConvArgs a, int HR, int whole, int pieces) {
     constexpr int TP = 1;                         // 32-pixel tiles per wavefront (and 2 channel tiles)
     constexpr int KB = 128;                       // bytes of input channels per step (64 bf16)
     constexpr int WM = BM / (32 * TP), WN = BN / 64, NW = WM * WN, NT = NW * 64;
@@ -71,18 +75,27 @@ __global__ __launch_bounds__((BM / 32) * (BN / 64) * 64, BM == 256 ? 4 : 1) void
     unsigned char *hs = smem + 2 * WBUF;          // HR halo rows, then one row of zeros
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
+    const int lane = tid & 63, wv = SPLIT ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int wm = wv % WM, wn = wv / WM;
     const int l32 = lane & 31, half = lane >> 5;
 
+    // Tiles up to `whole`, then the others in `pieces` runs of pixels to a workgroup each: all its wavefronts load, the first of them multiply
     unsigned logical;
-    {
-        const unsigned nb = gridDim.x, per = nb >> 3, rem = nb & 7u;
+    int piece = 0, active = WM;
+    if (SPLIT && (int)blockIdx.x >= whole) {
+        const int at = (int)blockIdx.x - whole;
+        logical = (unsigned)(whole + at / pieces);
+        piece = at % pieces;
+        active = WM / pieces;
+    } else {
+        const unsigned nb = SPLIT ? (unsigned)whole : gridDim.x, per = nb >> 3, rem = nb & 7u;
         const unsigned xcd = blockIdx.x & 7u, idx = blockIdx.x >> 3;
         logical = xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
     }
     const int tiles_n = a.Cout / BN;
-    const int m0 = (int)(logical / tiles_n) * BM;
+    const int m0 = (int)(logical / tiles_n) * BM + piece * active * (32 * TP);
+    if (SPLIT && m0 >= a.M) return;                                       // a piece past the last pixel: the whole workgroup
+    const int rows = SPLIT ? active * (32 * TP) + 2 * a.W + 2 : HR;           // of the halo
     const int n0 = (int)(logical % tiles_n) * BN;
 
     const unsigned char *xg = static_cast<const unsigned char *>(a.x);
@@ -98,7 +111,7 @@ __global__ __launch_bounds__((BM / 32) * (BN / 64) * 64, BM == 256 ? 4 : 1) void
     for (int c = 0; c < HL; ++c) {
         const int idx = tid + c * NT, row = idx / SEGS, seg = idx % SEGS;
         const long long q = (long long)m0 - (W + 1) + row;
-        hoff[c] = (row < HR && q >= 0 && q < a.M) ? (uint32_t)q * cin_bytes + seg * 16u : 0xFFFFFFFFu;
+        hoff[c] = (row < rows && q >= 0 && q < a.M) ? (uint32_t)q * cin_bytes + seg * 16u : 0xFFFFFFFFu;
     }
     // ---- weight rows of this thread
     uint32_t woff[WL];
@@ -217,53 +230,65 @@ __global__ __launch_bounds__((BM / 32) * (BN / 64) * 64, BM == 256 ? 4 : 1) void
     for (int i = 2; i < D + 2; ++i)
         if (i < T) load_w(i, rw[i % D]);
     __syncthreads();
-    point(wbuf0, 0);
-    read_pieces(0, 0);
 
     // Step t multiplies out of buffer t % 2.  Its barrier stands before its last 16-wide step, when every
     // wavefront holds that step's pieces in registers: from there on buffer t % 2 takes the weights of
     // step t + 2, and the first pieces of step t + 1 (stored a step earlier) are read under the last MFMAs.
-    int tap = 0, cb = 0;
-    for (int t0 = 0; t0 < T; t0 += D) {
+    auto steps = [&](auto multiplies) {
+        constexpr bool kOn = decltype(multiplies)::value;
+        if constexpr (kOn) {
+            point(wbuf0, 0);
+            read_pieces(0, 0);
+        }
+        int tap = 0, cb = 0;
+        for (int t0 = 0; t0 < T; t0 += D) {
 #pragma unroll
-        for (int i = 0; i < D; ++i) {
-            const int t = t0 + i;
-            if (t < T) {
-                unsigned char *cur = (i & 1) ? wbuf1 : wbuf0;   // D is even: t % 2 == i % 2
-                unsigned char *nxt = (i & 1) ? wbuf0 : wbuf1;
-                const bool more = cb + 1 < CB;
-                if (tap == HALO_TAP && more) load_halo(cb + 1);
-                read_pieces(1, 1);
-                mfmas(0);
-                interleave();
-                read_pieces(2, 0);
-                mfmas(1);
-                interleave();
-                read_pieces(3, 1);
-                mfmas(0);
-                interleave();
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __syncthreads();
-                if (t + 2 < T) store_w(cur, rw[(i + 2) % D]);
-                if (t + 2 + D < T) load_w(t + 2 + D, rw[(i + 2) % D]);
-                if (tap == 8) {
-                    if (more) {
-                        store_halo();
-                        __syncthreads();
+            for (int i = 0; i < D; ++i) {
+                const int t = t0 + i;
+                if (t < T) {
+                    unsigned char *cur = (i & 1) ? wbuf1 : wbuf0;   // D is even: t % 2 == i % 2
+                    unsigned char *nxt = (i & 1) ? wbuf0 : wbuf1;
+                    const bool more = cb + 1 < CB;
+                    if (tap == HALO_TAP && more) load_halo(cb + 1);
+                    if constexpr (kOn) {
+                        read_pieces(1, 1);
+                        mfmas(0);
+                        interleave();
+                        read_pieces(2, 0);
+                        mfmas(1);
+                        interleave();
+                        read_pieces(3, 1);
+                        mfmas(0);
+                        interleave();
                     }
-                    tap = 0;
-                    ++cb;
-                } else {
-                    ++tap;
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    __syncthreads();
+                    if (t + 2 < T) store_w(cur, rw[(i + 2) % D]);
+                    if (t + 2 + D < T) load_w(t + 2 + D, rw[(i + 2) % D]);
+                    if (tap == 8) {
+                        if (more) {
+                            store_halo();
+                            __syncthreads();
+                        }
+                        tap = 0;
+                        ++cb;
+                    } else {
+                        ++tap;
+                    }
+                    if constexpr (kOn) {
+                        if (t + 1 < T) {
+                            point(nxt, tap);
+                            read_pieces(0, 0);
+                        }
+                        mfmas(1);
+                    }
                 }
-                if (t + 1 < T) {
-                    point(nxt, tap);
-                    read_pieces(0, 0);
-                }
-                mfmas(1);
             }
         }
-    }
+    };
+    // Wavefronts of a piece that have no pixels load and meet the others at every barrier
+    if (!SPLIT || wm < active) steps(std::true_type());
+    else steps(std::false_type());
 
     // ---- epilogue: row-major through a wavefront-private fp32 tile, scale/shift, residual + ReLU
     // (+ mask), one rounding, 128 contiguous bytes per pixel.  The residual and mask rows are
@@ -291,6 +316,7 @@ __global__ __launch_bounds__((BM / 32) * (BN / 64) * 64, BM == 256 ? 4 : 1) void
         sh[0] = h0.x; sh[1] = h0.y; sh[2] = h0.z; sh[3] = h0.w; sh[4] = h1.x; sh[5] = h1.y; sh[6] = h1.z; sh[7] = h1.w;
     }
     __syncthreads();
+    if (SPLIT && wm >= active) return;
     unsigned char *stg = smem + wv * (32 * kStgPitch);
 #pragma unroll
     for (int i = 0; i < TP; ++i) {
@@ -368,14 +394,33 @@ static hipError_t launch_one(const ConvArgs &a, hipStream_t stream) {
     const size_t smem = smem_bytes(BM, HR);
     static bool raised = false;                   // per instantiation
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv3x3_halo_kernel<BM, kBN, HL>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv3x3_halo_kernel<BM, kBN, HL, false>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
+        if constexpr (BM == 256)
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv3x3_halo_kernel<BM, kBN, HL, true>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
         if (e != hipSuccess) return e;
         raised = true;
     }
     const long long blocks = (((long long)a.M + BM - 1) / BM) * (a.Cout / kBN);
     if (blocks <= 0 || blocks > 0x7FFFFFFFLL || smem > kMaxLds || HR * 8 > HL * NT) return hipErrorInvalidValue;
-    conv3x3_halo_kernel<BM, kBN, HL><<<dim3((unsigned)blocks), dim3(NT), smem, stream>>>(a, HR);
+    if constexpr (BM == 256) {
+        // Tiles past the last whole round of the 256 CUs: each in as many pieces as leave a CU at most one, beside the tile it has.  A few whole tiles would
+        // have some CUs take one more than the others, two at a time, for half a round.  The block's forward, us, whole tiles | this, 14 x 14 x 256: 84 images
+        // (rest 4) 134 | 121, 100 (52) 136 | 127, 118 (108) 144 | 138; 28 x 28 x 128: 128 (16) 178 | 173, 100 (102) 149 | 147, but with more pieces than
+        // CUs, two to a tile, 105 (132) 159 | 165, 128 x 14 x 14 (136) 153 | 181.  Data gradients with their mask share the chip with the weight gradients
+        // of another stream, which fill such a round: 265 | 267 at 128 x 28 x 28.  Tiles of 128 pixels have no registers for it.
+        const int rest = (int)(blocks % 256);
+        int pieces = BM / 32;
+        while (rest * pieces > 256) pieces /= 2;
+        if (blocks > 256 && rest && pieces > 1 && !a.mask) {
+            const int whole = (int)blocks - rest;
+            conv3x3_halo_kernel<BM, kBN, HL, true><<<dim3((unsigned)(whole + rest * pieces)), dim3(NT), smem, stream>>>(a, HR, whole, pieces);
+            return hipGetLastError();
+        }
+    }
+    conv3x3_halo_kernel<BM, kBN, HL, false><<<dim3((unsigned)blocks), dim3(NT), smem, stream>>>(a, HR, 0, 1);
     return hipGetLastError();
 }
 

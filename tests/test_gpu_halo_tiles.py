@@ -16,6 +16,12 @@ CASES = [
     ("past_128_w31",      1, 83,  31,  64, 256, 3, 1, True, True, LOW),       # 21 x 4 workgroups of 128 pixels
     ("past_128_w32",      9, 9,   32, 128, 256, 3, 1, True, False, LOW),
     ("past_128_w63",      1, 41,  63,  64, 256, 3, 1, False, False, LOW),
+    # past a whole round of the chip the last tiles go out in pieces of 32, 64 and 128 pixels
+    ("pieces_32_w31",     1, 273, 31,  64, 512, 3, 1, True, True, HIGH),      # 34 x 8 workgroups: 16 tiles, half of them with 15 pixels
+    ("pieces_32_w62",     1, 146, 62, 128, 512, 3, 1, False, False, HIGH),    # 36 x 8: 32 tiles in eight pieces, the most
+    ("pieces_64_w63",     1, 159, 63,  64, 512, 3, 1, True, False, HIGH),     # 40 x 8: 64 tiles in four
+    ("pieces_128_w33",    2, 184, 33,  64, 512, 3, 1, True, True, HIGH),      # 48 x 8: 128 tiles in two
+    ("whole_again_w33",   1, 373, 33,  64, 512, 3, 1, True, False, HIGH),     # 49 x 8: 136 tiles, whole
     ("past_wide_w64",     1, 65,  64,  64, 512, 3, 1, True, False, LOW),      # enough pixels for 256, rows too long for it
     ("past_wide_w127",    1, 33, 127,  64, 512, 3, 1, True, True, LOW),       # the longest halo
 ]
