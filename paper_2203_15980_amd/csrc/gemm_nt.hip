@@ -348,11 +348,12 @@ long long tiles_of(const ConvArgs &a, const Tile &t) {
 
 // Width of the w tile: the one whose number of rounds over the 256 CUs (one workgroup per CU) times
 // its cost per tile is smaller; e.g. 768 output channels are 3 tiles of 256 (192 workgroups at
-// batch 32 x 512: a quarter of the chip idle) but 4 tiles of 192 (256 workgroups, one full round).
+// batch 32 x 512: a quarter of the chip idle) but 4 tiles of 192 (256 workgroups, one full round).  A round also costs its first loads and its
+// stores, as much as 96 columns of four slices: strided 256 -> 512 on 128 x 56 x 56 (four rounds of 256 or five of 192, inside the forward pass) 68 -> 59 us.
 const Tile &pick_tile(const ConvArgs &a) {
     if (a.Cout <= 128) return kTiles[2];
     if (a.Cout <= 256 && tiles_of(a, kTiles[0]) < 192) return kTiles[4];
-    const long long c256 = ((tiles_of(a, kTiles[0]) + 255) / 256) * 256, c192 = ((tiles_of(a, kTiles[1]) + 255) / 256) * 192;
+    const long long start = 24576 / a.Cin, c256 = ((tiles_of(a, kTiles[0]) + 255) / 256) * (256 + start), c192 = ((tiles_of(a, kTiles[1]) + 255) / 256) * (192 + start);
     return c192 < c256 ? kTiles[1] : kTiles[0];
 }
 
