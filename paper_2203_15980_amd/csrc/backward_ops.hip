@@ -432,13 +432,15 @@ __global__ __launch_bounds__(256) void softmax_ce_bwd_kernel(const uint16_t *log
 // ---------------------------------------------------------------- classifier z = x w^T + bias
 //   gx[n][c] = sum_k gy[n][k] * scale_k * w[k][c]          gw[k][c] = scale_k * sum_n gy[n][k] * x[n][c], then sum_n gy[n][k]
 // Both are small products (0.5 GFLOP for 128 images, 2048 -> 1000) whose operands all sit in the L2; neither reads the other, and one launch
-// runs the tiles of both side by side.  Eight wavefronts to a tile split its reduction, and their sums meet in LDS in a fixed tree; operands
-// whose reduction index is the row in memory go through LDS that only their wavefront uses and come back transposed (ds_read_b64_tr_b16).
-//  * gw: 64 x 64 of (k, c), bf16 MFMAs (exact products, fp32 sums); the tiles of c = 0 also add gy up, in order, for the bias.
+// runs the tiles of both side by side.  Eight wavefronts to a tile of gx split its reduction, and their sums meet in LDS in a fixed tree; operands
+// whose reduction index is the row in memory go through LDS and come back transposed (ds_read_b64_tr_b16).
+//  * gw: 64 x 128 of (k, c), bf16 MFMAs (exact products, fp32 sums): 128 images of both operands in LDS, and a wavefront owns 32 x 32, so that no sums
+//    meet and nothing but the operands goes through LDS; the tiles of c = 0 also add gy up, in order, for the bias.  (64 x 64, the eight wavefronts with 16
+//    images each and their sums in LDS: 512 workgroups beside gx's 256 where the chip holds 512; the launch 14.0 -> 12.0 us at 128 images.)
 //  * gx: 32 images x 32 channels.  gy * scale keeps its 32 bits: it is split into three bf16 parts (8 + 8 + 8 bits, exact), each of
 //    which multiplies w.
 // What bounds it is the chain of launch, two round trips and a combine.  On the fp32 MFMA, which takes neither splitting nor transposing, the
-// 128 images took 18.8 us (two launches of 12 before that), a third of it MFMA issue: now 13.3 (head of 128 images 46.6 -> 41.2).
+// 128 images took 18.8 us (two launches of 12 before that), a third of it MFMA issue: now 12.0 (head of 128 images 46.6 -> 40.2).
 static constexpr int kDensePitch = 128;                          // bytes of a staged row of 64 channels
 __device__ __forceinline__ int dense_flip(int row) { return (row >> 1) & 1; }    // which way a row's two 64-byte halves lie (see wgrad1x1.hip)
 
@@ -458,93 +460,74 @@ __device__ __forceinline__ void dense_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// smem: 64 KB.
+// smem: 50 KB.
 __device__ __forceinline__ void dense_bwd_weight(const uint16_t *gy, const uint16_t *x, const float *scale, float *gw, int N, int Cin, int Cout,
                                                  unsigned block, unsigned char *smem) {
+    constexpr int kImages = 128, kBlock = kImages * kDensePitch; // images in LDS at once; bytes of a block: 64 channels of them
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cblocks = (Cin + 63) / 64, k0 = (int)(block / cblocks) * 64, c0 = (int)(block % cblocks) * 64;
-    // a step is 16 images; a lane fetches 16 bytes of rows lane / 8 and 8 + lane / 8 of both operands (channel counts are multiples of 8)
-    const int row = lane >> 3, seg = lane & 7;
-    const bool kin = k0 + seg * 8 < Cout, cin = c0 + seg * 8 < Cin;
-    unsigned char *stg = smem + wv * 8192;                       // 16 rows of gy, then of x; later this wavefront's sums, two tiles at a time
-    unsigned char *put = stg + row * kDensePitch + (((seg >> 2) ^ dense_flip(row)) << 6) + (seg & 3) * 16;     // row + 8: the same flip
-    const int srow = 8 * (lane >> 5) + ((lane & 15) >> 2), scol = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
-    const unsigned char *get = stg + srow * kDensePitch + scol;
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    u32x4 gb[2], xb[2];
-    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const int cblocks = (Cin + 127) / 128, k0 = (int)(block / cblocks) * 64, c0 = (int)(block % cblocks) * 128;
+    // a thread fetches 16 bytes of rows tid / 8 and 64 + tid / 8 of three blocks: gy, then x twice (channel counts are multiples of 8)
+    const int row = tid >> 3, seg = tid & 7;
+    unsigned char *put = smem + row * kDensePitch + (((seg >> 2) ^ dense_flip(row)) << 6) + (seg & 3) * 16;    // row + 64: the same flip
+    u32x4 in[6];
     auto fetch = [&](int n0) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int n = n0 + 8 * u + row;
-            gb[u] = n < N && kin ? *reinterpret_cast<const u32x4 *>(gy + (size_t)n * Cout + k0 + seg * 8) : zero;
-            xb[u] = n < N && cin ? *reinterpret_cast<const u32x4 *>(x + (size_t)n * Cin + c0 + seg * 8) : zero;
+        for (int i = 0; i < 6; ++i) {
+            const int n = n0 + row + 64 * (i & 1), ch = (i < 2 ? k0 : c0 + 64 * (i / 2 - 1)) + seg * 8, C = i < 2 ? Cout : Cin;
+            in[i] = n < N && ch < C ? *reinterpret_cast<const u32x4 *>((i < 2 ? gy : x) + (size_t)n * C + ch) : u32x4{0u, 0u, 0u, 0u};
         }
     };
-    fetch(16 * wv);
-    for (int n0 = 16 * wv; n0 < N; n0 += 128) {
-        dense_fence();
+    fetch(0);
+    // this wavefront's 32 x 32: classes k0 + 32 kq .., channels c0 + 32 cq ..
+    const int kq = wv & 1, cq = wv >> 1, half = lane >> 5, l32 = lane & 31;
+    const int k = k0 + 32 * kq + 4 * half, c = c0 + 32 * cq + l32;
+    f32x4 sc[4];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            *reinterpret_cast<u32x4 *>(put + u * 8 * kDensePitch) = gb[u];
-            *reinterpret_cast<u32x4 *>(put + 2048 + u * 8 * kDensePitch) = xb[u];
-        }
-        fetch(n0 + 128);
-        dense_fence();
-        s16x8 gf[2], xf[2];
+    for (int e4 = 0; e4 < 4; ++e4) sc[e4] = k + 8 * e4 < Cout ? *reinterpret_cast<const f32x4 *>(scale + k + 8 * e4) : f32x4{0.f, 0.f, 0.f, 0.f};
+    const int srow = 8 * half + ((lane & 15) >> 2), scol = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    const unsigned char *gget = smem + srow * kDensePitch + ((kq ^ dense_flip(srow)) << 6) + scol;             // row + 4, row + 16: the same flip
+    const unsigned char *xget = smem + (1 + (cq >> 1)) * kBlock + srow * kDensePitch + (((cq & 1) ^ dense_flip(srow)) << 6) + scol;
+    f32x16 acc[4];                                               // steps of 16 images in turn: no sum is a longer chain than eight wavefronts' were
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int at = (h ^ dense_flip(srow)) << 6;
-            gf[h] = dense_tr_read(get + at, 4 * kDensePitch);    // row + 4: the same flip
-            xf[h] = dense_tr_read(get + 2048 + at, 4 * kDensePitch);
-        }
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int e = 0; e < 16; ++e) acc[u][e] = 0.f;
+    float bias = 0.f;                                            // of class k0 + tid % 64, images tid / 64, + 8, ..
+    for (int n0 = 0; n0 < N; n0 += kImages) {
+        const int here = N - n0 < kImages ? N - n0 : kImages;
+        if (n0) __syncthreads();                                 // the images before are read
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, gf[i]), __builtin_bit_cast(bf16x8, xf[j]), acc[i][j], 0, 0, 0);
+        for (int i = 0; i < 6; ++i) *reinterpret_cast<u32x4 *>(put + (i >> 1) * kBlock + (i & 1) * (64 * kDensePitch)) = in[i];
+        __syncthreads();
+        if (n0 + kImages < N) fetch(n0 + kImages);
+        for (int s = 0; 16 * s < here; s += 4)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {                        // rows past the last image are zeros of both
+                if (16 * (s + u) >= here) break;
+                const int at = 16 * (s + u) * kDensePitch;
+                acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, dense_tr_read(gget + at, 4 * kDensePitch)),
+                                                                 __builtin_bit_cast(bf16x8, dense_tr_read(xget + at, 4 * kDensePitch)), acc[u], 0, 0, 0);
+            }
+        if (c0 == 0)
+            for (int n = tid >> 6; n < here; n += 8)
+                bias += __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t *>(smem + n * kDensePitch + (((lane >> 5) ^ dense_flip(n)) << 6) + (lane & 31) * 2) << 16);
     }
     // lane: column (c) l % 32, rows (k) 8 e4 + 4 (l / 32) + e of a 32 x 32 tile in register 4 e4 + e
+    if (c < Cin) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        if (i) __syncthreads();                                  // the sums before are read
-        dense_fence();
+        for (int e4 = 0; e4 < 4; ++e4)
+            if (k + 8 * e4 < Cout)                               // four classes, inside or outside together
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4)
-                *reinterpret_cast<f32x4 *>(stg + j * 4096 + e4 * 1024 + lane * 16) =
-                    f32x4{acc[i][j][4 * e4], acc[i][j][4 * e4 + 1], acc[i][j][4 * e4 + 2], acc[i][j][4 * e4 + 3]};
-        __syncthreads();
-        f32x4 part[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) part[v] = *reinterpret_cast<const f32x4 *>(smem + v * 8192 + tid * 16);
-        const f32x4 sum = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
-        const int k = k0 + 32 * i + 8 * ((tid >> 6) & 3) + 4 * (lane >> 5), c = c0 + 32 * (tid >> 8) + (lane & 31);
-        if (k < Cout && c < Cin) {                               // four classes, inside or outside together
-            const f32x4 sc = *reinterpret_cast<const f32x4 *>(scale + k);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) gw[(size_t)(k + e) * Cin + c] = sum[e] * sc[e];
-        }
+                for (int e = 0; e < 4; ++e)
+                    gw[(size_t)(k + 8 * e4 + e) * Cin + c] = ((acc[0][4 * e4 + e] + acc[1][4 * e4 + e]) + (acc[2][4 * e4 + e] + acc[3][4 * e4 + e])) * sc[e4][e];
     }
-    if (c0 == 0) {                                               // the bias: eight threads to a class, every eighth image each
-        const int k = k0 + (tid & 63), g = tid >> 6;
-        float sum = 0.f;
-        if (k < Cout)
-            for (int n = g; n < N; n += 8) sum += __uint_as_float((uint32_t)gy[(size_t)n * Cout + k] << 16);
+    if (c0 == 0) {                                               // the bias: eight threads to a class
+        float *part = reinterpret_cast<float *>(smem + 3 * kBlock);
+        part[tid] = bias;
         __syncthreads();
-        float *part = reinterpret_cast<float *>(smem);
-        part[tid] = sum;
-        __syncthreads();
-        if (tid < 64 && k < Cout) {
-            for (int v = 1; v < 8; ++v) sum += part[v * 64 + tid];
-            gw[(size_t)Cout * Cin + k] = sum;
+        if (tid < 64 && k0 + tid < Cout) {
+            for (int v = 1; v < 8; ++v) bias += part[v * 64 + tid];
+            gw[(size_t)Cout * Cin + k0 + tid] = bias;
         }
     }
 }
@@ -719,7 +702,7 @@ hipError_t launch_dense_bwd(const void *x, const void *w, const float *scale, co
     const long long tiles = ((long long)N + 31) / 32 * ((Cin + 31) / 32);
     // wavefronts to a tile of gx: those that have a step of 32 classes; all eight where every tile finds its place at once (they share the store)
     const int kw = tiles <= 512 ? 8 : Cout <= 32 ? 1 : Cout <= 64 ? 2 : Cout <= 128 ? 4 : 8;
-    const long long data = gx ? (tiles + 8 / kw - 1) / (8 / kw) : 0, weight = gw ? ((long long)Cout + 63) / 64 * ((Cin + 63) / 64) : 0;
+    const long long data = gx ? (tiles + 8 / kw - 1) / (8 / kw) : 0, weight = gw ? ((long long)Cout + 63) / 64 * ((Cin + 127) / 128) : 0;
     if (tiles > 0x7FFFFFFFLL || data + weight > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     if (data + weight == 0) return hipSuccess;
     auto run = [&](auto kernel) {
