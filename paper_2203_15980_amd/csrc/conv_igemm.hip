@@ -531,7 +531,7 @@ bool conv_spread_applies(const ConvArgs &a, int stride, int OH, int OW) {
     as_spread(sa, stride, OH, OW);
     if (conv_check(a) || a.oy_s || a.R != 1 || a.S != 1 || a.stride != 1 || a.res || a.mask || conv_scatter_check(sa)) return false;
     if (splitk_before_stream(a)) return true;
-    return !conv1x1_stream_applies(a) && (conv_splitk_applies(a) || gemm_nt_applies(a));
+    return !conv1x1_stream_applies(a) && (conv_splitk_applies(a) || gemm_nt_applies(sa));
 }
 
 hipError_t launch_conv_spread(const ConvArgs &a, hipStream_t stream) {

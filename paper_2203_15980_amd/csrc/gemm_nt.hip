@@ -375,7 +375,13 @@ const Tile *choose_tile(const ConvArgs &a) {
     // The spread form stores four times the rows it computes: two workgroups to a CU overlap that, the deeper ring does not.  Gradient of a strided
     // layer alone, us, four buffers | two: 1024 -> 2048 at 128 x 14 x 14 48 | 38, at 100 x 13 x 11 47 | 34, 512 -> 1024 at 64 x 28 x 28 32 | 24.  (From 128
     // tiles of 256 x 256 on those: 256 -> 512 at 128 x 56 x 56 66, two launches 92, 128 x 128 tiles 79; 512 -> 1024 at 128 x 28 x 28 39 | 50 | 45.)
-    if (a.Cin >= 512 && tiles_of(a, kTiles[3]) <= 512) return &kTiles[a.spread ? 2 : 3];
+    // Half a chip of them is where the layer's weight gradient, one workgroup of all its LDS to a CU on the other stream, no longer finds the rest free, and
+    // waits the longer for this launch: there the shorter one with a second to spread its result.  Block's backward, us, two launches | this, with the number
+    // of tiles: 256 -> 512 [116] 119 | 116, [142] 123 | 127, [166] 122 | 130, [232] 141 | 145, [330] 167 | 167; 512 -> 1024 [88] 120 | 116,
+    // [108] 126 | 128, [136] 135 | 140, [172] 155 | 153, [248] 177 | 175; 1024 -> 2048 [96] 154 | 156, [184] 221 | 221.
+    const long long small = tiles_of(a, kTiles[3]);
+    if (a.spread && small >= 96 && small < 256) return nullptr;
+    if (a.Cin >= 512 && small <= 512) return &kTiles[a.spread ? 2 : 3];
     return nullptr;
 }
 

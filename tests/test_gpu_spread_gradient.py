@@ -15,7 +15,9 @@ CASES = [
     (2, 14, 15, 256, 512, 3, 0, "conv_splitk bf16 32x32"),     # blocks of 3 x 3, cut short below and at the right
     (3, 13, 17, 512, 1024, 2, 1, "small_backward bf16"),
     (1, 28, 28, 256, 512, 2, 1, "small_backward bf16"),
-    (11, 55, 56, 256, 512, 2, 0, "gemm_nt bf16 128x128 ("),
+    (11, 55, 56, 256, 512, 2, 0, "gemm_nt bf16 128x128, four", "+ spread_add"),   # half a chip of tiles: two launches
+    (6, 55, 56, 256, 512, 2, 0, "gemm_nt bf16 128x128 ("),
+    (46, 27, 28, 512, 1024, 2, 0, "gemm_nt bf16 128x128 ("),
     (47, 56, 55, 256, 512, 2, 0, "gemm_nt bf16 128x256"),      # 47 x 28 x 28 rows: the last tile ragged
     (21, 56, 56, 512, 256, 2, 0, "gemm_nt bf16 256x"),
     (31, 27, 29, 1536, 512, 2, 0, "gemm_nt bf16 256x"),
