@@ -28,8 +28,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
-
 #include "kernels.hpp"
 
 namespace delta {
@@ -234,61 +232,57 @@ __global__ __launch_bounds__((BM / 32) * (BN / 64) * 64, BM == 256 ? 4 : 1) void
     // Step t multiplies out of buffer t % 2.  Its barrier stands before its last 16-wide step, when every
     // wavefront holds that step's pieces in registers: from there on buffer t % 2 takes the weights of
     // step t + 2, and the first pieces of step t + 1 (stored a step earlier) are read under the last MFMAs.
-    auto steps = [&](auto multiplies) {
-        constexpr bool kOn = decltype(multiplies)::value;
-        if constexpr (kOn) {
-            point(wbuf0, 0);
-            read_pieces(0, 0);
-        }
-        int tap = 0, cb = 0;
-        for (int t0 = 0; t0 < T; t0 += D) {
+    // Wavefronts of a piece that have no pixels load and meet the others at every barrier
+    const bool on = !SPLIT || wm < active;
+    if (on) {
+        point(wbuf0, 0);
+        read_pieces(0, 0);
+    }
+    int tap = 0, cb = 0;
+    for (int t0 = 0; t0 < T; t0 += D) {
 #pragma unroll
-            for (int i = 0; i < D; ++i) {
-                const int t = t0 + i;
-                if (t < T) {
-                    unsigned char *cur = (i & 1) ? wbuf1 : wbuf0;   // D is even: t % 2 == i % 2
-                    unsigned char *nxt = (i & 1) ? wbuf0 : wbuf1;
-                    const bool more = cb + 1 < CB;
-                    if (tap == HALO_TAP && more) load_halo(cb + 1);
-                    if constexpr (kOn) {
-                        read_pieces(1, 1);
-                        mfmas(0);
-                        interleave();
-                        read_pieces(2, 0);
-                        mfmas(1);
-                        interleave();
-                        read_pieces(3, 1);
-                        mfmas(0);
-                        interleave();
+        for (int i = 0; i < D; ++i) {
+            const int t = t0 + i;
+            if (t < T) {
+                unsigned char *cur = (i & 1) ? wbuf1 : wbuf0;   // D is even: t % 2 == i % 2
+                unsigned char *nxt = (i & 1) ? wbuf0 : wbuf1;
+                const bool more = cb + 1 < CB;
+                if (tap == HALO_TAP && more) load_halo(cb + 1);
+                if (on) {
+                    read_pieces(1, 1);
+                    mfmas(0);
+                    interleave();
+                    read_pieces(2, 0);
+                    mfmas(1);
+                    interleave();
+                    read_pieces(3, 1);
+                    mfmas(0);
+                    interleave();
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (t + 2 < T) store_w(cur, rw[(i + 2) % D]);
+                if (t + 2 + D < T) load_w(t + 2 + D, rw[(i + 2) % D]);
+                if (tap == 8) {
+                    if (more) {
+                        store_halo();
+                        __syncthreads();
                     }
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    __syncthreads();
-                    if (t + 2 < T) store_w(cur, rw[(i + 2) % D]);
-                    if (t + 2 + D < T) load_w(t + 2 + D, rw[(i + 2) % D]);
-                    if (tap == 8) {
-                        if (more) {
-                            store_halo();
-                            __syncthreads();
-                        }
-                        tap = 0;
-                        ++cb;
-                    } else {
-                        ++tap;
+                    tap = 0;
+                    ++cb;
+                } else {
+                    ++tap;
+                }
+                if (on) {
+                    if (t + 1 < T) {
+                        point(nxt, tap);
+                        read_pieces(0, 0);
                     }
-                    if constexpr (kOn) {
-                        if (t + 1 < T) {
-                            point(nxt, tap);
-                            read_pieces(0, 0);
-                        }
-                        mfmas(1);
-                    }
+                    mfmas(1);
                 }
             }
         }
-    };
-    // Wavefronts of a piece that have no pixels load and meet the others at every barrier
-    if (!SPLIT || wm < active) steps(std::true_type());
-    else steps(std::false_type());
+    }
 
     // ---- epilogue: row-major through a wavefront-private fp32 tile, scale/shift, residual + ReLU
     // (+ mask), one rounding, 128 contiguous bytes per pixel.  The residual and mask rows are
