@@ -84,23 +84,34 @@ __device__ __forceinline__ void wave_lds_fence() {
 // per workgroup, 256, 192 or 128 (BN / 64 wavefront columns).
 // S: LDS buffers of one K slice each (2 or 4); S - 1 slices are in flight while one is multiplied.
 // SPREAD: row m is stored at the pixel (s p, s q) of its image and the rest of that pixel's s x s block as zeros (ConvArgs::spread).
-template <int BM, int BN, int S, bool SPREAD>
-__global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(ConvArgs a, int tiles_n, int tiles_total, Divisor dpq, Divisor dq) {
+// SPLIT: the tiles from `whole` on go out in `pieces` runs of rows each: all wavefronts of such a workgroup load, those that have rows multiply.
+template <int BM, int BN, int S, bool SPREAD, bool SPLIT>
+__global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(ConvArgs a, int tiles_n, int tiles_total, Divisor dpq, Divisor dq, int whole,
+                                                                             int pieces) {
     static_assert(S >= 2 && S <= 4, "two to four slice buffers");
     constexpr int kBM = BM, kBN = BN, kWM = BM / 64, kWN = BN / 64, kWaves = kWM * kWN;
     constexpr int kXBytes = kBM * kBK * 2;                  // x rows of one buffer
     constexpr int kStageBytes = kXBytes + BN * kBK * 2;
     constexpr int XI = (kBM / 8 + kWaves - 1) / kWaves, WI = (BN / 8 + kWaves - 1) / kWaves;   // direct loads per wavefront and slice
     extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = SPLIT ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
     const int wm = wv / kWN, wn = wv % kWN;
     const int M = a.M, N = a.Cout, K = a.Cin;
     // XCD-aware numbering: XCD x (= blockIdx % 8) takes logical tiles x * per .. (x + 1) * per
-    const int per = (tiles_total + 7) / 8;
-    const int logical = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    const int per = ((SPLIT ? whole : tiles_total) + 7) / 8;
+    int logical = (blockIdx.x & 7) * per + (blockIdx.x >> 3), piece = 0, active = kWM;
+    if (SPLIT && (int)blockIdx.x >= whole) {
+        const int at = (int)blockIdx.x - whole;
+        logical = whole + at / pieces;
+        piece = at % pieces;
+        active = kWM / pieces;
+    }
     if (logical >= tiles_total) return;
-    const int m0 = (logical / tiles_n) * kBM, n0 = (logical % tiles_n) * kBN;
+    const int m0 = (logical / tiles_n) * kBM + piece * active * 64, n0 = (logical % tiles_n) * kBN;
+    if (SPLIT && m0 >= M) return;                                       // a piece past the last row: the whole workgroup
+    const bool on = !SPLIT || wm < active;
+    const int mend = SPLIT && m0 + active * 64 < M ? m0 + active * 64 : M;
 
     // ---- direct loads: one instruction fills 8 tile rows (1 KB); per slice a wavefront issues XI for
     // x and WI for w (when the rows do not divide evenly the last wavefronts repeat a neighbour's rows)
@@ -116,7 +127,7 @@ __global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(Con
         const int r = 8 * g + (lane >> 3);                              // row of the tile this lane fills
         const int piece = (lane & 7) ^ ((r >> 1) & 7);                 // which 16 bytes of the row land in this lane's slot
         int xr = m0 + r;
-        xr = xr < M ? xr : M - 1;
+        xr = xr < mend ? xr : mend - 1;
         size_t xpix = (size_t)xr;
         if (a.stride != 1) {                                            // a strided 1x1 layer reads every stride-th pixel
             const int oq = xr % a.Q, t = xr / a.Q, op = t % a.P, n = t / a.P;
@@ -192,7 +203,7 @@ __global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(Con
     wait_slices((nslices - 1 < S - 2) ? nslices - 1 : S - 2);          // slice 0 has landed
     __syncthreads();
     if (S - 1 < nslices) fetch(S - 1, S - 1);
-    read_step(0, 0, 0);
+    if (on) read_step(0, 0, 0);
     for (int t = 0; t < nslices; ++t) {
         const int buf = t % S;
 #pragma unroll
@@ -208,23 +219,25 @@ __global__ __launch_bounds__((BM / 64) * (BN / 64) * 64) void gemm_nt_kernel(Con
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __syncthreads();                   // everyone's have
                 if (t + S < nslices) fetch(t + S, buf);
-                if (t + 1 < nslices) read_step((t + 1) % S, 0, 0);
-            } else {
-                read_step(buf, q + 1, (q + 1) & 1);
             }
+            if (on) {
+                if (q != 3) read_step(buf, q + 1, (q + 1) & 1);
+                else if (t + 1 < nslices) read_step((t + 1) % S, 0, 0);
 #pragma unroll
-            for (int i = 0; i < kTM; ++i)
+                for (int i = 0; i < kTM; ++i)
 #pragma unroll
-                for (int j = 0; j < kTN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[q & 1][j]),
-                                                                        __builtin_bit_cast(bf16x8, xf[q & 1][i]), acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < kTN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[q & 1][j]),
+                                                                            __builtin_bit_cast(bf16x8, xf[q & 1][i]), acc[i][j], 0, 0, 0);
 #pragma unroll
-            for (int k = 0; k < kTM + kTN; ++k) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, (kTM * kTN) / (kTM + kTN), 0);
+                for (int k = 0; k < kTM + kTN; ++k) {
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x008, (kTM * kTN) / (kTM + kTN), 0);
+                }
             }
         }
     }
+    if (SPLIT && !on) return;
 
     // ---- epilogue.  acc[i][j]: lane holds pixel (x row) l32 of tile i and channels 8*rb + 4*half + e of tile j
     unsigned char *stg = smem + (size_t)wv * (32 * kStgPitch);
@@ -385,8 +398,8 @@ const Tile *choose_tile(const ConvArgs &a) {
     return nullptr;
 }
 
-template <int BM, int BN, int S, bool SPREAD>
-hipError_t launch_as(const ConvArgs &a, hipStream_t stream) {
+template <int BM, int BN, int S, bool SPREAD, bool SPLIT = false>
+hipError_t launch_as(const ConvArgs &a, hipStream_t stream, int whole = 0, int pieces = 1) {
     constexpr size_t pipe = (size_t)S * ((size_t)BM * gemm::kBK * 2 + (size_t)BN * gemm::kBK * 2);
     constexpr size_t stage_out = (size_t)(BM / 64) * (BN / 64) * 32 * gemm::kStgPitch;
     constexpr size_t lds = pipe > stage_out ? pipe : stage_out;
@@ -394,21 +407,31 @@ hipError_t launch_as(const ConvArgs &a, hipStream_t stream) {
     constexpr int threads = (BM / 64) * (BN / 64) * 64;
     const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.Cout + BN - 1) / BN;
     const long long total = (long long)tiles_m * tiles_n;
-    const long long blocks = (total + 7) / 8 * 8;
+    const long long blocks = SPLIT ? whole + (total - whole) * pieces : (total + 7) / 8 * 8;
     static bool raised = false;
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm::gemm_nt_kernel<BM, BN, S, SPREAD>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm::gemm_nt_kernel<BM, BN, S, SPREAD, SPLIT>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    gemm::gemm_nt_kernel<BM, BN, S, SPREAD><<<dim3((unsigned)blocks), dim3(threads), lds, stream>>>(
-        a, tiles_n, (int)total, make_divisor(SPREAD ? a.P * a.Q : 1), make_divisor(SPREAD ? a.Q : 1));
+    gemm::gemm_nt_kernel<BM, BN, S, SPREAD, SPLIT><<<dim3((unsigned)blocks), dim3(threads), lds, stream>>>(
+        a, tiles_n, (int)total, make_divisor(SPREAD ? a.P * a.Q : 1), make_divisor(SPREAD ? a.Q : 1), whole, pieces);
     return hipGetLastError();
 }
 
 template <int BM, int BN, int S>
 hipError_t launch_tile(const ConvArgs &a, hipStream_t stream) {
+    if constexpr (BM == 256) {
+        // Tiles past the last whole round of the 256 CUs, in as many pieces as leave a CU at most one: shorter than a tile, whose workgroup has its CU to
+        // itself.  An encoder layer, us, whole tiles | this: 22 x 256 tokens (96 of 352 tiles of 768 -> 3072 left over) 178 | 174, 24 x 256 180 | 175,
+        // 30 x 256 196 | 194.  Masked data gradients share the chip with another stream's work, which fills such a round.
+        const long long total = tiles_of(a, Tile{BM, BN, S});
+        const int rest = (int)(total % 256);
+        int pieces = 4;
+        while (rest * pieces > 256) pieces /= 2;
+        if (total > 256 && rest && pieces > 1 && !a.spread && !a.mask) return launch_as<BM, BN, S, false, true>(a, stream, (int)(total - rest), pieces);
+    }
     return a.spread ? launch_as<BM, BN, S, true>(a, stream) : launch_as<BM, BN, S, false>(a, stream);
 }
 
