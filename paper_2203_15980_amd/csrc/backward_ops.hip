@@ -435,12 +435,16 @@ __global__ __launch_bounds__(256) void softmax_ce_bwd_kernel(const uint16_t *log
 // runs the tiles of both side by side.  Eight wavefronts to a tile of gx split its reduction, and their sums meet in LDS in a fixed tree; operands
 // whose reduction index is the row in memory go through LDS and come back transposed (ds_read_b64_tr_b16).
 //  * gw: 64 x 128 of (k, c), bf16 MFMAs (exact products, fp32 sums): 128 images of both operands in LDS, and a wavefront owns 32 x 32, so that no sums
-//    meet and nothing but the operands goes through LDS; the tiles of c = 0 also add gy up, in order, for the bias.  (64 x 64, the eight wavefronts with 16
-//    images each and their sums in LDS: 512 workgroups beside gx's 256 where the chip holds 512; the launch 14.0 -> 12.0 us at 128 images.)
+//    meet and nothing but the operands goes through LDS; the tiles of c = 0 also add gy up for the bias.  (64 x 64, the eight wavefronts with 16
+//    images each and their sums in LDS: 512 workgroups beside gx's 256 where the chip holds 512.)  The sums are the same eight in both, of every eighth
+//    step of 16 images, added as a tree.  Four sums of every fourth step are longer chains: distance from float64 over the norm 3.98e-8 | 3.97e-8
+//    (these) at 128 images, 6.07 | 5.65 at 512, 7.63 | 6.62 at 1024, 14.7 | 10.6 at 4096.
 //  * gx: 32 images x 32 channels.  gy * scale keeps its 32 bits: it is split into three bf16 parts (8 + 8 + 8 bits, exact), each of
 //    which multiplies w.
 // What bounds it is the chain of launch, two round trips and a combine.  On the fp32 MFMA, which takes neither splitting nor transposing, the
-// 128 images took 18.8 us (two launches of 12 before that), a third of it MFMA issue: now 12.0 (head of 128 images 46.6 -> 40.2).
+// 128 images took 18.8 us (two launches of 12 before that), a third of it MFMA issue.  2048 -> 1000, one launch after the other, us, 64 x 64 tiles | this:
+// 3 images 6.9 | 6.6, 64 8.9 | 7.2, 128 11.4 | 7.7, 256 16.8 | 14.9, 512 27 | 24, 1024 48 | 44, 4096 269 | 168.  (141 registers and more, one workgroup to a CU instead
+// of two: 6.4, 7.1, 9.5, 15.3, 27, 51, 201.)
 static constexpr int kDensePitch = 128;                          // bytes of a staged row of 64 channels
 __device__ __forceinline__ int dense_flip(int row) { return (row >> 1) & 1; }    // which way a row's two 64-byte halves lie (see wgrad1x1.hip)
 
@@ -460,7 +464,9 @@ __device__ __forceinline__ void dense_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// smem: 50 KB.
+// smem: 50 KB.  FEW: at most 128 images, a step to a sum.  Otherwise the images come in groups of 32, every fourth group in turn (0, 4, 8, .., then
+// 1, 5, ..), so that two of the eight sums at a time are in registers: 128 of those are what two workgroups to a CU leave.
+template <bool FEW>
 __device__ __forceinline__ void dense_bwd_weight(const uint16_t *gy, const uint16_t *x, const float *scale, float *gw, int N, int Cin, int Cout,
                                                  unsigned block, unsigned char *smem) {
     constexpr int kImages = 128, kBlock = kImages * kDensePitch; // images in LDS at once; bytes of a block: 64 channels of them
@@ -469,48 +475,91 @@ __device__ __forceinline__ void dense_bwd_weight(const uint16_t *gy, const uint1
     // a thread fetches 16 bytes of rows tid / 8 and 64 + tid / 8 of three blocks: gy, then x twice (channel counts are multiples of 8)
     const int row = tid >> 3, seg = tid & 7;
     unsigned char *put = smem + row * kDensePitch + (((seg >> 2) ^ dense_flip(row)) << 6) + (seg & 3) * 16;    // row + 64: the same flip
+    const int groups = (N + 31) / 32;
+    const int end0 = (groups + 3) / 4, end1 = end0 + (groups + 2) / 4, end2 = end1 + (groups + 1) / 4;       // places where three of the four classes end
+    auto class_of = [&](int place) { return place < end0 ? 0 : place < end1 ? 1 : place < end2 ? 2 : 3; };
+    auto group_at = [&](int place) {
+        if (FEW) return place;
+        const int q = class_of(place);
+        return 4 * (place - (q == 0 ? 0 : q == 1 ? end0 : q == 2 ? end1 : end2)) + q;
+    };
     u32x4 in[6];
-    auto fetch = [&](int n0) {
+    auto fetch = [&](int at) {                                   // the groups in places at .. at + 3
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
-            const int n = n0 + row + 64 * (i & 1), ch = (i < 2 ? k0 : c0 + 64 * (i / 2 - 1)) + seg * 8, C = i < 2 ? Cout : Cin;
-            in[i] = n < N && ch < C ? *reinterpret_cast<const u32x4 *>((i < 2 ? gy : x) + (size_t)n * C + ch) : u32x4{0u, 0u, 0u, 0u};
+            const int place = at + (wv >> 2) + 2 * (i & 1), n0 = place < groups ? 32 * group_at(place) : N;
+            const int ch = (i < 2 ? k0 : c0 + 64 * (i / 2 - 1)) + seg * 8, C = i < 2 ? Cout : Cin;
+            in[i] = n0 + (row & 31) < N && ch < C ? *reinterpret_cast<const u32x4 *>((i < 2 ? gy : x) + (size_t)n0 * C + (unsigned)((row & 31) * C + ch))
+                                                  : u32x4{0u, 0u, 0u, 0u};
         }
     };
     fetch(0);
     // this wavefront's 32 x 32: classes k0 + 32 kq .., channels c0 + 32 cq ..
     const int kq = wv & 1, cq = wv >> 1, half = lane >> 5, l32 = lane & 31;
     const int k = k0 + 32 * kq + 4 * half, c = c0 + 32 * cq + l32;
-    f32x4 sc[4];
-#pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) sc[e4] = k + 8 * e4 < Cout ? *reinterpret_cast<const f32x4 *>(scale + k + 8 * e4) : f32x4{0.f, 0.f, 0.f, 0.f};
     const int srow = 8 * half + ((lane & 15) >> 2), scol = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
     const unsigned char *gget = smem + srow * kDensePitch + ((kq ^ dense_flip(srow)) << 6) + scol;             // row + 4, row + 16: the same flip
     const unsigned char *xget = smem + (1 + (cq >> 1)) * kBlock + srow * kDensePitch + (((cq & 1) ^ dense_flip(srow)) << 6) + scol;
-    f32x16 acc[4];                                               // steps of 16 images in turn: no sum is a longer chain than eight wavefronts' were
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[u][e] = 0.f;
-    float bias = 0.f;                                            // of class k0 + tid % 64, images tid / 64, + 8, ..
-    for (int n0 = 0; n0 < N; n0 += kImages) {
-        const int here = N - n0 < kImages ? N - n0 : kImages;
-        if (n0) __syncthreads();                                 // the images before are read
+    auto multiply = [&](int step, f32x16 &acc) {                 // rows past the last image are zeros of both
+        const int at = 16 * step * kDensePitch;
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, dense_tr_read(gget + at, 4 * kDensePitch)),
+                                                      __builtin_bit_cast(bf16x8, dense_tr_read(xget + at, 4 * kDensePitch)), acc, 0, 0, 0);
+    };
+    auto store = [&] {
 #pragma unroll
         for (int i = 0; i < 6; ++i) *reinterpret_cast<u32x4 *>(put + (i >> 1) * kBlock + (i & 1) * (64 * kDensePitch)) = in[i];
         __syncthreads();
-        if (n0 + kImages < N) fetch(n0 + kImages);
-        for (int s = 0; 16 * s < here; s += 4)
+    };
+    f32x4 sc[4];
+    auto fetch_scale = [&] {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {                        // rows past the last image are zeros of both
-                if (16 * (s + u) >= here) break;
-                const int at = 16 * (s + u) * kDensePitch;
-                acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, dense_tr_read(gget + at, 4 * kDensePitch)),
-                                                                 __builtin_bit_cast(bf16x8, dense_tr_read(xget + at, 4 * kDensePitch)), acc[u], 0, 0, 0);
+        for (int e4 = 0; e4 < 4; ++e4) sc[e4] = k + 8 * e4 < Cout ? *reinterpret_cast<const f32x4 *>(scale + k + 8 * e4) : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    f32x16 sum[2];                                               // of the first four of the eight sums, of the others
+    const f32x16 none = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float bias = 0.f, biases = 0.f;                              // of class k0 + tid % 64, every eighth image; one sum to 128 images, then one to a class of groups
+    const unsigned char *bget = smem + wv * kDensePitch + (((lane >> 5) ^ dense_flip(wv)) << 6) + (lane & 31) * 2;     // row + 8: the same flip
+    auto add_bias = [&](int r) { bias += __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t *>(bget + r * kDensePitch) << 16); };
+    if constexpr (FEW) {
+        fetch_scale();
+        store();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            f32x16 acc[2] = {none, none};
+            if (32 * j < N) {
+                multiply(2 * j, acc[0]);
+                multiply(2 * j + 1, acc[1]);
             }
+            if (j & 1) sum[j >> 1] += acc[0] + acc[1];
+            else sum[j >> 1] = acc[0] + acc[1];
+        }
         if (c0 == 0)
-            for (int n = tid >> 6; n < here; n += 8)
-                bias += __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t *>(smem + n * kDensePitch + (((lane >> 5) ^ dense_flip(n)) << 6) + (lane & 31) * 2) << 16);
+            for (int r = 0; r < N; r += 8) add_bias(r);
+    } else {
+        f32x16 acc[2] = {none, none};
+        sum[0] = sum[1] = none;
+        for (int at = 0; at < groups; at += 4) {
+            if (at) __syncthreads();                             // the images before are read
+            store();
+            if (at + 4 < groups) fetch(at + 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int place = at + j, q = class_of(place);
+                if (place >= groups) break;
+                multiply(2 * j, acc[0]);
+                multiply(2 * j + 1, acc[1]);
+                if (c0 == 0)
+#pragma unroll
+                    for (int r = 32 * j; r < 32 * j + 32; r += 8) add_bias(r);
+                if (place + 1 == groups || class_of(place + 1) != q) {
+                    sum[q >> 1] += acc[0] + acc[1];
+                    acc[0] = acc[1] = none;
+                    biases += bias;
+                    bias = 0.f;
+                }
+            }
+        }
+        fetch_scale();
     }
     // lane: column (c) l % 32, rows (k) 8 e4 + 4 (l / 32) + e of a 32 x 32 tile in register 4 e4 + e
     if (c < Cin) {
@@ -518,12 +567,11 @@ __device__ __forceinline__ void dense_bwd_weight(const uint16_t *gy, const uint1
         for (int e4 = 0; e4 < 4; ++e4)
             if (k + 8 * e4 < Cout)                               // four classes, inside or outside together
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    gw[(size_t)(k + 8 * e4 + e) * Cin + c] = ((acc[0][4 * e4 + e] + acc[1][4 * e4 + e]) + (acc[2][4 * e4 + e] + acc[3][4 * e4 + e])) * sc[e4][e];
+                for (int e = 0; e < 4; ++e) gw[(size_t)(k + 8 * e4 + e) * Cin + c] = (sum[0][4 * e4 + e] + sum[1][4 * e4 + e]) * sc[e4][e];
     }
     if (c0 == 0) {                                               // the bias: eight threads to a class
         float *part = reinterpret_cast<float *>(smem + 3 * kBlock);
-        part[tid] = bias;
+        part[tid] = bias += biases;
         __syncthreads();
         if (tid < 64 && k0 + tid < Cout) {
             for (int v = 1; v < 8; ++v) bias += part[v * 64 + tid];
@@ -635,16 +683,16 @@ __device__ __forceinline__ void dense_bwd_data(const uint16_t *gy, const uint16_
 // The first `data_blocks` workgroups tiles of gx, whose reductions are longer, the others tiles of gw.  With few classes a tile of gx has steps for KW
 // of the eight wavefronts, and a workgroup takes 8 / KW tiles.  gx alone, us with eight to a tile | this: 4096 x 768, 8 classes 13.0 | 5.3,
 // 4096 x 2048, 40 classes 34 | 15; up to 512 tiles eight are better: 128 x 512, 32 classes 3.0 | 3.5, 512 x 768, 24 classes 3.4 | 3.7.
-template <int KW, bool WEIGHT>
+template <int KW, bool WEIGHT, bool FEW>
 __global__ __launch_bounds__(512) void dense_bwd_kernel(const uint16_t *gy, const uint16_t *w, const uint16_t *x, const float *scale,
                                                         uint16_t *gx, float *gw, int N, int Cin, int Cout, unsigned data_blocks) {
-    constexpr int kEach = WEIGHT ? 8192 : 32 * 144;
+    constexpr int kEach = WEIGHT ? 8192 : 32 * 144;          // gw's 50 KB or less: registers hold two workgroups to a CU, LDS too
     __shared__ __align__(16) unsigned char smem[8 * kEach];
     if (!WEIGHT || blockIdx.x < data_blocks) {
         const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / (KW * 64));
         dense_bwd_data<KW>(gy, w, scale, gx, N, Cin, Cout, blockIdx.x * (8 / KW) + group, threadIdx.x & (KW * 64 - 1), smem + group * KW * kEach, kEach);
     } else {
-        dense_bwd_weight(gy, x, scale, gw, N, Cin, Cout, blockIdx.x - data_blocks, smem);
+        dense_bwd_weight<FEW>(gy, x, scale, gw, N, Cin, Cout, blockIdx.x - data_blocks, smem);
     }
 }
 
@@ -710,10 +758,11 @@ hipError_t launch_dense_bwd(const void *x, const void *w, const float *scale, co
                                                                          static_cast<const uint16_t *>(x), scale, static_cast<uint16_t *>(gx), gw, N,
                                                                          Cin, Cout, (unsigned)data);
     };
-    if (gw) kw == 1 ? run(bops::dense_bwd_kernel<1, true>) : kw == 2 ? run(bops::dense_bwd_kernel<2, true>)
-          : kw == 4 ? run(bops::dense_bwd_kernel<4, true>) : run(bops::dense_bwd_kernel<8, true>);
-    else kw == 1 ? run(bops::dense_bwd_kernel<1, false>) : kw == 2 ? run(bops::dense_bwd_kernel<2, false>)
-       : kw == 4 ? run(bops::dense_bwd_kernel<4, false>) : run(bops::dense_bwd_kernel<8, false>);
+    const bool few = N <= 128;
+#define DELTA_DENSE(KW) \
+    (!gw ? run(bops::dense_bwd_kernel<KW, false, false>) : few ? run(bops::dense_bwd_kernel<KW, true, true>) : run(bops::dense_bwd_kernel<KW, true, false>))
+    kw == 1 ? DELTA_DENSE(1) : kw == 2 ? DELTA_DENSE(2) : kw == 4 ? DELTA_DENSE(4) : DELTA_DENSE(8);
+#undef DELTA_DENSE
     return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""The classifier's two gradients at the edges of their tiles (64 x 64 of gw, 32 x 32 of gx, steps of 16 images and 32 classes), each alone and
+"""The classifier's two gradients at the edges of their tiles (64 x 128 of gw, 32 x 32 of gx, steps of 16 images and 32 classes), each alone and
 both together, against float64 on the stored operands; scale of one, of 24 significant bits and of magnitudes far apart.
 
 dL/dx: bf16 storage, 2^-9 of the element (4e-3 of the maximum); gy * scale is rounded to 32 bits as an fp32 product is, its three parts are exact.
@@ -101,3 +101,32 @@ def test_an_infinite_scale_stays_with_its_class(torch_mod, N, Cin, Cout):  # noq
     wf, gf = on.to_f64(w, "bf16").reshape(Cout, Cin), on.to_f64(g, "bf16")
     assert np.array_equal(got, np.sign(gf[:, 2:3]) * np.sign(wf[2])[None] * np.inf)
     d.close()
+
+
+@pytest.mark.parametrize("N,Cin,Cout", [(128, 64, 8), (129, 64, 8), (192, 128, 72), (255, 320, 40), (520, 64, 56), (4096, 192, 24)])
+def test_weight_sums_of_every_eighth_step(torch_mod, N, Cin, Cout):  # noqa: F811
+    """Eight sums, of every eighth step of 16 images: 2^24 in one image and -2^24 eight steps on (the last step of its sum, where there is one), a
+    single one in each step of the other seven sums.  Exact, as no sum of the tree leaves 24 bits; 2^24 + 1 does, and the ones are lost where sums are
+    of every fourth step."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    n, k = np.arange(N)[:, None], np.arange(Cout)[None]
+    g = np.where((n // 16 % 8 != k % 8) & (n % 16 == k % 16), 1.0, 0.0).astype(np.float32)       # class k: 2^24 in sum k % 8
+    for c in range(Cout):
+        steps = range(16 * (c % 8), N, 128)
+        if len(steps) > 1:
+            g[steps[0], c], g[steps[-1], c] = 2.0 ** 24, -2.0 ** 24
+    x = np.full((N, 1, 1, Cin), 0x3F80, np.uint16)
+    g16 = synth.f32_to_bf16_bits(g).reshape(g.shape)
+    d, put, get = _small_ctx(torch, [x.nbytes, g16.nbytes, g16.nbytes, x.nbytes])
+    put(0, x)
+    put(2, g16)
+    w, one, gw = torch.zeros(Cout * Cin, dtype=torch.bfloat16, device="cuda:0"), torch.ones(Cout, device="cuda:0"), torch.zeros(Cout * Cin + Cout, device="cuda:0")
+    fc = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=one.data_ptr(), shift=one.data_ptr(), N=N, H=1, W=1,
+                      Cin=Cin, Cout=Cout, R=1, S=1, stride=1, pad=0, relu=0)
+    d.backward_segment([dl.BwdDesc(fwd=fc, gy=2, gpre=2, gx=dl.NO_TENSOR, gx_add=dl.NO_TENSOR, gw=gw.data_ptr())])
+    d.backward_join()
+    d.sync()
+    got = gw.cpu().numpy()[:Cout * Cin].reshape(Cout, Cin)
+    d.close()
+    assert np.array_equal(got, np.broadcast_to(g.astype(np.float64).sum(0)[:, None], got.shape)) and got.any()
