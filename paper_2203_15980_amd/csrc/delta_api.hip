@@ -1831,7 +1831,12 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
                 if ((r = compute_uses(c, c->tensors[L.x])) != DELTA_OK) return r;
                 maskp = c->arena + c->tensors[L.x].offset;
             }
-            if ((r = compute_writes(c, tgx)) != DELTA_OK) return r;
+            if ((r = compute_writes(c, tgx)) != DELTA_OK) {
+                // no room for gx: gpre is resident by now, so it is made as it would have been without it
+                if (masks)
+                    HIP_TRY(c, delta::launch_relu_mask(masked_by, c->arena + tgy.offset, c->arena + c->tensors[D.gpre].offset, tgy.bytes, fa.bf16, s));
+                return r;
+            }
             da.x = gp; da.w = D.wt; da.res = addp; da.mask = maskp; da.y = c->arena + tgx.offset;
             da.scale = c->ones; da.shift = c->zeros;
             if (in_place) delta::as_spread(da, L.stride, L.H, L.W);

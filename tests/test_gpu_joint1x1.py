@@ -182,3 +182,34 @@ def test_own_mask_on_the_way(torch_mod, Cin, Cout, H, W, add):  # noqa: F811
     for g in gw:
         assert float((g.double() - ref).abs().max() / ref.abs().max()) <= 1e-5
     d.close()
+
+
+def test_own_mask_without_room_for_gx(torch_mod):  # noqa: F811
+    """The arena holds gpre and not gx: the call says so, and gpre, resident from then on, is gy * [y > 0] and not what its memory held."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    H, W, Cin, Cout = 131, 193, 64, 256
+    M = H * W
+    nbytes = [M * Cin * 2, M * Cout * 2, M * Cout * 2, M * Cin * 2, M * Cout * 2]      # x, y, gy, gx, gpre
+    arena = torch.full((sum(nbytes) - nbytes[3] // 2,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    d = dl.Delta(arena, torch.cuda.current_stream().cuda_stream)
+    d.bind(nbytes)
+    gen = torch.Generator(device="cuda:0").manual_seed(47)
+    view = lambda t: d.arena[d.tensor_ptr(t) - d.arena.data_ptr():][:nbytes[t]].view(torch.int16).reshape(M, -1)      # noqa: E731
+    for t in (0, 1, 2):
+        d.alloc(t)
+        view(t).view(torch.bfloat16).normal_(generator=gen)
+    w, one, gw = torch.zeros(Cin, Cout, dtype=torch.bfloat16, device="cuda:0"), torch.ones(Cout, device="cuda:0"), torch.zeros(Cout, Cin, device="cuda:0")
+    fwd = dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=1, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=one.data_ptr(), shift=one.data_ptr(), N=1, H=H, W=W,
+                       Cin=Cin, Cout=Cout, R=1, S=1, stride=1, pad=0, relu=1)
+    ws = torch.zeros(d.backward_workspace(fwd), dtype=torch.uint8, device="cuda:0")
+    desc = dl.BwdDesc(fwd=fwd, gy=2, gpre=4, gx=3, gx_add=dl.NO_TENSOR, mask_gx=1, wt=w.data_ptr(), gw=gw.data_ptr(), workspace=ws.data_ptr(),
+                      workspace_bytes=ws.numel())
+    assert d.backward_kernel(desc).endswith(JOINT)
+    torch.cuda.synchronize()
+    with pytest.raises(dl.DeltaError) as e:
+        d.backward_segment([desc])
+    d.sync()
+    assert e.value.status == dl.ERR_OOM_ARENA
+    assert torch.equal(view(4), torch.where(view(1) > 0, view(2), torch.zeros_like(view(2))))
+    d.close()
