@@ -381,6 +381,10 @@ static int tile_pixels(const ConvArgs &a) {
     return a.W > 63 || (((long long)a.M + 255) / 256) * (a.Cout / kBN) < 128 ? 128 : 256;
 }
 
+static int pieces_of(const ConvArgs &a, int BM) {
+    return BM == 256 ? tail_pieces(a, (((long long)a.M + BM - 1) / BM) * (a.Cout / kBN), BM / 32) : 1;
+}
+
 template <int BM, int HL>
 static hipError_t launch_one(const ConvArgs &a, hipStream_t stream) {
     constexpr int NT = (BM / 32) * (kBN / 64) * 64;
@@ -405,10 +409,8 @@ static hipError_t launch_one(const ConvArgs &a, hipStream_t stream) {
         // (rest 4) 134 | 121, 100 (52) 136 | 127, 118 (108) 144 | 138; 28 x 28 x 128: 128 (16) 178 | 173, 100 (102) 149 | 147, but with more pieces than
         // CUs, two to a tile, 105 (132) 159 | 165, 128 x 14 x 14 (136) 153 | 181.  Data gradients with their mask share the chip with the weight gradients
         // of another stream, which fill such a round: 265 | 267 at 128 x 28 x 28.  Tiles of 128 pixels have no registers for it.
-        const int rest = (int)(blocks % 256);
-        int pieces = BM / 32;
-        while (rest * pieces > 256) pieces /= 2;
-        if (blocks > 256 && rest && pieces > 1 && !a.mask) {
+        const int rest = (int)(blocks % 256), pieces = pieces_of(a, BM);
+        if (pieces > 1) {
             const int whole = (int)blocks - rest;
             conv3x3_halo_kernel<BM, kBN, HL, true><<<dim3((unsigned)(whole + rest * pieces)), dim3(NT), smem, stream>>>(a, HR, whole, pieces);
             return hipGetLastError();
@@ -434,6 +436,8 @@ bool conv3x3_halo_applies(const ConvArgs &a) {
 const char *conv3x3_halo_kernel_name(const ConvArgs &a) {
     return halo::tile_pixels(a) == 128 ? "conv3x3_halo bf16 128x64 (4x1 waves)" : "conv3x3_halo bf16 256x64 (8x1 waves)";
 }
+
+int conv3x3_halo_pieces(const ConvArgs &a) { return halo::pieces_of(a, halo::tile_pixels(a)); }
 
 hipError_t launch_conv3x3_halo(const ConvArgs &a, hipStream_t stream) {
     if (conv_check(a) || !conv3x3_halo_applies(a)) return hipErrorInvalidValue;

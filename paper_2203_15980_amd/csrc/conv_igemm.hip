@@ -441,6 +441,11 @@ const char *conv_kernel_name(const ConvArgs &a) {
     return bn == 128 ? "conv_igemm f32 128x128 (2x2 waves)" : "conv_igemm f32 128x64 (4x1 waves)";
 }
 
+int conv_pieces(const ConvArgs &a) {
+    if (splitk_before_stream(a) || conv1x1_stream_applies(a) || conv3x3_c64_applies(a) || conv_splitk_applies(a)) return 1;
+    return conv3x3_halo_applies(a) ? conv3x3_halo_pieces(a) : gemm_nt_applies(a) ? gemm_nt_pieces(a) : 1;
+}
+
 // Host-side shape check; the kernel assumes exactly this.
 const char *conv_check(const ConvArgs &a) {
     const int kc = a.bf16 ? 64 : 32;

@@ -1925,6 +1925,11 @@ delta_status delta_backward_join(delta_ctx *c) {
     return join_aux(c);
 }
 
+static void pieces_text(char *out, size_t cap, const delta::ConvArgs &a) {
+    const int n = delta::conv_pieces(a);
+    if (n > 1) snprintf(out, cap, ", last tiles in %d pieces", n);
+}
+
 delta_status delta_layer_kernel(delta_ctx *c, const delta_layer_desc *layer, char *out, uint64_t cap) {
     delta_status r = need_gpu(c);
     if (r != DELTA_OK) return r;
@@ -1935,8 +1940,12 @@ delta_status delta_layer_kernel(delta_ctx *c, const delta_layer_desc *layer, cha
     r = prepare_layer(c, *layer, 0, a, pa, flops);
     if (r != DELTA_OK) return r;
     const char *name = "?";
+    char pieces[40] = "";
     switch (layer->op) {
-    case DELTA_OP_CONV: name = delta::stem_applies(a) ? "stem7x7 bf16" : delta::conv_kernel_name(a); break;
+    case DELTA_OP_CONV:
+        name = delta::stem_applies(a) ? "stem7x7 bf16" : delta::conv_kernel_name(a);
+        if (!delta::stem_applies(a)) pieces_text(pieces, sizeof pieces, a);
+        break;
     case DELTA_OP_MAXPOOL: name = "maxpool"; break;
     case DELTA_OP_AVGPOOL: name = "avgpool"; break;
     case DELTA_OP_SOFTMAX_CE: name = "softmax_ce"; break;
@@ -1952,7 +1961,7 @@ delta_status delta_layer_kernel(delta_ctx *c, const delta_layer_desc *layer, cha
     case DELTA_OP_ADD: name = "add bf16"; break;
     default: break;
     }
-    snprintf(out, (size_t)cap, "%s", name);
+    snprintf(out, (size_t)cap, "%s%s", name, pieces);
     return DELTA_OK;
 }
 
@@ -1978,7 +1987,7 @@ delta_status delta_backward_kernel(delta_ctx *c, const delta_bwd_desc *desc, cha
         return DELTA_OK;
     }
     if ((r = prepare_backward(c, D, 0, fa, da)) != DELTA_OK) return r;
-    char gx[160] = "", gw[80] = "";                       // a C entry: nothing here throws
+    char gx[160] = "", gw[80] = "", pieces[40] = "";      // a C entry: nothing here throws
     if (D.gx != DELTA_NO_TENSOR) {
         const char *name = nullptr, *before = "", *after = strided_1x1(L) ? " + spread_add" : "";
         if (class_dgrad(D)) {
@@ -1997,8 +2006,11 @@ delta_status delta_backward_kernel(delta_ctx *c, const delta_bwd_desc *desc, cha
                 delta::as_spread(da, L.stride, L.H, L.W);
             }
             name = delta::conv_kernel_name(da);
+            if (D.mask_gx && !strided_1x1(L)) da.mask = c->arena;        // that there is one (a staged gradient gets it when it is spread)
+            pieces_text(pieces, sizeof pieces, da);
+            da.mask = nullptr;
         }
-        snprintf(gx, sizeof gx, "gx: %s%s%s", before, name, after);
+        snprintf(gx, sizeof gx, "gx: %s%s%s%s", before, name, pieces, after);
     }
     if (D.gw) {
         delta::ConvArgs fo = fa;
@@ -2006,7 +2018,7 @@ delta_status delta_backward_kernel(delta_ctx *c, const delta_bwd_desc *desc, cha
         fo.M = L.N * fo.P * fo.Q;
         const OneLaunch one = one_launch(D, fo, fa, da);
         if (one == OL_LAYER) snprintf(gx, sizeof gx, "gx: %s%s", delta::small_backward_name(fa), da.spread ? ", spread" : strided_1x1(L) ? " + spread_add" : "");
-        if (one == OL_JOINT) snprintf(gx, sizeof gx, "gx: joint1x1 bf16");
+        if (one == OL_JOINT) snprintf(gx, sizeof gx, "%sgx: joint1x1 bf16", masks_on_the_way(D, fa, da, one) ? "gpre: joint1x1 bf16; " : "");
         if (one != OL_NONE)
             snprintf(gw, sizeof gw, "; gw: %s%s", one == OL_JOINT ? "joint1x1 bf16" : delta::small_backward_name(fa),
                      one == OL_LAYER || one == OL_JOINT ? ", the same launch" : one == OL_CLASS ? ", the launch of one class" : ", compute stream");

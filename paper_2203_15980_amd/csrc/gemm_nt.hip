@@ -420,17 +420,18 @@ hipError_t launch_as(const ConvArgs &a, hipStream_t stream, int whole = 0, int p
     return hipGetLastError();
 }
 
+int pieces_of(const ConvArgs &a, const Tile &t) { return t.bm == 256 ? tail_pieces(a, tiles_of(a, t), t.bm / 64) : 1; }
+
 template <int BM, int BN, int S>
 hipError_t launch_tile(const ConvArgs &a, hipStream_t stream) {
     if constexpr (BM == 256) {
         // Tiles past the last whole round of the 256 CUs, in as many pieces as leave a CU at most one: shorter than a tile, whose workgroup has its CU to
         // itself.  An encoder layer, us, whole tiles | this: 22 x 256 tokens (96 of 352 tiles of 768 -> 3072 left over) 178 | 174, 24 x 256 180 | 175,
         // 30 x 256 196 | 194.  Masked data gradients share the chip with another stream's work, which fills such a round.
-        const long long total = tiles_of(a, Tile{BM, BN, S});
-        const int rest = (int)(total % 256);
-        int pieces = 4;
-        while (rest * pieces > 256) pieces /= 2;
-        if (total > 256 && rest && pieces > 1 && !a.spread && !a.mask) return launch_as<BM, BN, S, false, true>(a, stream, (int)(total - rest), pieces);
+        const Tile t{BM, BN, S};
+        const long long total = tiles_of(a, t);
+        const int pieces = pieces_of(a, t);
+        if (pieces > 1) return launch_as<BM, BN, S, false, true>(a, stream, (int)(total - total % 256), pieces);
     }
     return a.spread ? launch_as<BM, BN, S, true>(a, stream) : launch_as<BM, BN, S, false>(a, stream);
 }
@@ -450,6 +451,11 @@ const char *gemm_nt_kernel_name(const ConvArgs &a) {
     if (t->bn == 256) return "gemm_nt bf16 128x256, three slice buffers (64x64 per wave, direct-to-LDS)";
     return t->stages == 4 ? "gemm_nt bf16 128x128, four slice buffers (64x64 per wave, direct-to-LDS)"
                           : "gemm_nt bf16 128x128 (64x64 per wave, direct-to-LDS)";
+}
+
+int gemm_nt_pieces(const ConvArgs &a) {
+    const Tile *t = choose_tile(a);
+    return t ? pieces_of(a, *t) : 1;
 }
 
 hipError_t launch_gemm_nt(const ConvArgs &a, hipStream_t stream) {

@@ -89,6 +89,17 @@ __device__ __forceinline__ float gelu_erf(float v) {
 const char *conv_check(const ConvArgs &a);
 const char *conv_kernel_name(const ConvArgs &a);
 hipError_t launch_conv(const ConvArgs &a, hipStream_t stream);
+// In how many pieces the tiles past the last whole round of the 256 CUs go out (1: whole), for a kernel that can cut a tile in up to `most`: as many as leave a
+// CU at most one.  conv_pieces: of the kernel that launch_conv takes.
+inline int tail_pieces(const ConvArgs &a, long long tiles, int most) {
+    const int rest = (int)(tiles % 256);
+    if (tiles <= 256 || !rest || a.spread || a.mask) return 1;
+    while (rest * most > 256) most /= 2;
+    return most;
+}
+int conv3x3_halo_pieces(const ConvArgs &a);
+int gemm_nt_pieces(const ConvArgs &a);
+int conv_pieces(const ConvArgs &a);
 const char *conv_scatter_check(const ConvArgs &a);
 const char *conv_scatter_kernel_name(const ConvArgs &a);
 hipError_t launch_conv_scatter(const ConvArgs &a, hipStream_t stream);

@@ -7,12 +7,13 @@ from test_gpu_parity import torch_mod  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
+GEMM = "gemm_nt bf16 256x%d (64x64 per wave, direct-to-LDS), last tiles in %d pieces"
 CASES = [
     # name           N  H    W   Cin Cout R st relu  res
-    ("pieces_64",    1, 257, 257, 256, 256,  1, 1, True, True, {"bf16": "gemm_nt bf16 256x256"}),      # 259 tiles: 3 in four pieces, the last with one row
-    ("pieces_128",   1, 149, 149, 256, 1024, 1, 1, True, False, {"bf16": "gemm_nt bf16 256x256"}),     # 87 x 4 tiles: 92 in two
-    ("pieces_192",   1, 273, 31,  256, 2048, 1, 1, False, True, {"bf16": "gemm_nt bf16 256x192"}),     # 34 x 11, the last columns ragged: 118 in two
-    ("strided",      2, 297, 223, 256, 1024, 1, 2, False, False, {"bf16": "gemm_nt bf16 256x256"}),    # 131 x 4 of 149 x 112 pixels twice: 12 in four
+    ("pieces_64",    1, 257, 257, 256, 256,  1, 1, True, True, {"bf16": GEMM % (256, 4)}),      # 259 tiles: 3 in four pieces, the last with one row
+    ("pieces_128",   1, 149, 149, 256, 1024, 1, 1, True, False, {"bf16": GEMM % (256, 2)}),     # 87 x 4 tiles: 92 in two
+    ("pieces_192",   1, 273, 31,  256, 2048, 1, 1, False, True, {"bf16": GEMM % (192, 2)}),     # 34 x 11, the last columns ragged: 118 in two
+    ("strided",      2, 297, 223, 256, 1024, 1, 2, False, False, {"bf16": GEMM % (256, 4)}),    # 131 x 4 of 149 x 112 pixels twice: 12 in four
 ]
 
 
