@@ -70,21 +70,23 @@ def test_spread_gradient_carries_the_bits_of_the_layer_at_stride_1(torch_mod, ca
     assert want.any()
 
 
-@pytest.mark.parametrize("case", [(61, 57, 58, 0), (25, 8001, 1, 0), (98305, 1, 2, 0), (62, 57, 57, 1), (60, 56, 55, 0)], ids=lambda c: "%dx%dx%d_%d" % c)
+@pytest.mark.parametrize("case", [(61, 57, 58, 128, 0, 1), (25, 8001, 1, 128, 0, 1), (98305, 1, 2, 128, 0, 1), (61, 57, 58, 64, 0, 1), (3, 257, 257, 64, 0, 1),
+                                  (62, 57, 57, 128, 1, 0), (60, 56, 55, 128, 0, 0), (60, 56, 55, 64, 0, 0)], ids=lambda c: "%dx%dx%d_%d_%d_%d" % c)
 def test_a_gradient_with_known_zeros_is_added_as_if_all_of_it_were_read(torch_mod, case):  # noqa: F811
-    """The strided layer's gx added by the layer that runs next (256 -> 128 channels, both gradients in one pass): in one call, where its zeros are
-    known, the bits of one call per layer.  The last flag: a third layer overwrites the tensor in between.  (60 x 56 x 55 lies below the line.)"""
+    """The strided layer's gx added by the layer that runs next (256 -> 128 or 64 channels, both gradients in one pass): in one call, where its zeros are
+    known (the last flag, by the kernel that ran), the bits of one call per layer.  The flag before: a third layer overwrites the tensor in between.
+    (60 x 56 x 55 lies below the line.)"""
     torch = torch_mod
     import paper_2203_15980_amd as dl
-    N, H, W, between = case
+    N, H, W, C, between, known = case
     print("case", case, flush=True)
     P, Q, rng = (H - 1) // 2 + 1, (W - 1) // 2 + 1, np.random.default_rng(7)
     bits = lambda *shape: ((rng.integers(0, 1 << 16, shape, np.uint16) & 0x80FF) | 0x3F00).astype(np.uint16)     # noqa: E731  # +-[0.5, 2)
-    x, g512, g128 = bits(N, H, W, 256), bits(N, P, Q, 512), bits(N, H, W, 128)
+    x, g512, gc = bits(N, H, W, 256), bits(N, P, Q, 512), bits(N, H, W, C)
     dev = lambda *shape: _dev(torch, bits(*shape).view(np.uint8).reshape(-1))                                    # noqa: E731
-    d, put, get = _small_ctx(torch, [x.nbytes, g512.nbytes, g128.nbytes, x.nbytes, x.nbytes, g512.nbytes, g128.nbytes],
-                             mb=4 + (3 * x.nbytes + 2 * g512.nbytes + 2 * g128.nbytes >> 20))
-    put(0, x), put(1, g512), put(2, g128)
+    d, put, get = _small_ctx(torch, [x.nbytes, g512.nbytes, gc.nbytes, x.nbytes, x.nbytes, g512.nbytes, gc.nbytes],
+                             mb=4 + (3 * x.nbytes + 2 * g512.nbytes + 2 * gc.nbytes >> 20))
+    put(0, x), put(1, g512), put(2, gc)
     put(3, np.full_like(x, 12345))
     one, keep = torch.ones(512, device="cuda:0"), []
 
@@ -99,18 +101,24 @@ def test_a_gradient_with_known_zeros_is_added_as_if_all_of_it_were_read(torch_mo
 
     chain = [desc(1, 5, 3, dl.NO_TENSOR, 512, 2, False)]
     if between:
-        chain.append(desc(2, 6, 3, dl.NO_TENSOR, 128, 1, False))
-    chain.append(desc(2, 6, 4, 3, 128, 1, True))
+        chain.append(desc(2, 6, 3, dl.NO_TENSOR, C, 1, False))
+    chain.append(desc(2, 6, 4, 3, C, 1, True))
     assert ", spread" in d.backward_kernel(chain[0]) and "joint1x1" in d.backward_kernel(chain[-1]), [d.backward_kernel(k) for k in chain]
-    outs = []
+    outs, even = [], []
     for calls in ([chain], [[k] for k in chain]):
-        for call in calls:
-            d.backward_segment(call)
-        d.backward_join()
-        d.sync()
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+            for call in calls:
+                d.backward_segment(call)
+            d.backward_join()
+            d.sync()
+        ran = [e.name for e in prof.events() if "joint1x1_kernel" in e.name]
+        even += [n.split("<")[1].split(">")[0].split(", ")[2] for n in ran]       # 0: nothing added, 1: a tensor, 2: one with known zeros
         outs.append((get(4, x.shape, np.uint16).copy(), keep[-2].cpu().numpy().copy()))
         d.release(4, dl.EV_FREE)
         put(4, np.zeros_like(x))
     d.close()
     assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
     assert outs[0][0].any()
+    if not even:
+        pytest.skip("the profiler saw no kernels here")
+    assert even == ["2" if known else "1", "1"], even
