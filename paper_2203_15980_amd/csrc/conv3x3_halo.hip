@@ -407,8 +407,10 @@ static hipError_t launch_one(const ConvArgs &a, hipStream_t stream) {
         // Tiles past the last whole round of the 256 CUs: each in as many pieces as leave a CU at most one, beside the tile it has.  A few whole tiles would
         // have some CUs take one more than the others, two at a time, for half a round.  The block's forward, us, whole tiles | this, 14 x 14 x 256: 84 images
         // (rest 4) 134 | 121, 100 (52) 136 | 127, 118 (108) 144 | 138; 28 x 28 x 128: 128 (16) 178 | 173, 100 (102) 149 | 147, but with more pieces than
-        // CUs, two to a tile, 105 (132) 159 | 165, 128 x 14 x 14 (136) 153 | 181.  Data gradients with their mask share the chip with the weight gradients
-        // of another stream, which fill such a round: 265 | 267 at 128 x 28 x 28.  Tiles of 128 pixels have no registers for it.
+        // CUs, two to a tile, 105 (132) 159 | 165, 128 x 14 x 14 (136) 153 | 181.  Beside a weight gradient on another stream, which fills such a round, pieces
+        // lose: convolutions of an identity block backward without masks, 28 x 28 x 128, 100 images 183 | 191, 14 x 14 x 256, 118 177 | 182, 84 151 | 152.5 (but
+        // 128 x 28 x 28 225 | 220); a weight gradient, then two forwards, 28 x 28 x 128, 100 images 94.8 | 99.7, 14 x 14 x 256, 118 105 | 108.5.
+        // Alone: 31.1 | 30.7, 33.9 | 31.9.  Tiles of 128 pixels have no registers for it.
         const int rest = (int)(blocks % 256), pieces = pieces_of(a, BM);
         if (pieces > 1) {
             const int whole = (int)blocks - rest;

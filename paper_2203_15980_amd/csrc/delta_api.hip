@@ -1075,6 +1075,7 @@ delta_status delta_recompute_segment(delta_ctx *c, const delta_layer_desc *layer
         switch (L.op) {
         case DELTA_OP_CONV:
             a.x = xp; a.y = yp; a.res = rp;
+            a.shared = c->aux_tail ? 1 : 0;
             if (delta::stem_applies(a)) HIP_TRY(c, delta::launch_stem(a, c->stream[S_COMPUTE]));
             else HIP_TRY(c, delta::launch_conv(a, c->stream[S_COMPUTE]));
             break;
@@ -1440,6 +1441,9 @@ bool wgrad_aside(const delta_layer_desc &L, const delta::ConvArgs &fa) {
     const uint64_t rows = L.stride == 2 && L.R == 3 ? (uint64_t)fa.M / 4 : (uint64_t)fa.M;
     return 2ull * rows * fa.R * fa.S * fa.Cin * fa.Cout >= kAsideFlops;
 }
+// Whether a data gradient's launch has company: its layer's weight gradient or an earlier one's on the other stream.  With a mask it is taken to have, as
+// inside a network, where the layers before have left theirs.
+int runs_beside(const delta_ctx *c, const delta_bwd_desc &D, bool aside) { return D.mask_gx || aside || c->aux_tail; }
 // How a layer that was asked for both gradients gets them where they are small (delta::launch_small_backward):
 // OL_LAYER - one launch for both; OL_CLASS - a strided 3x3 layer whose data gradient goes by parity class: the weight gradient in the
 // launch of class (1, 1); OL_WEIGHT - such a layer where one launch makes all four classes: the weight gradient in a launch of its own, without
@@ -1839,6 +1843,7 @@ delta_status delta_backward_segment(delta_ctx *c, const delta_bwd_desc *descs, u
             }
             da.x = gp; da.w = D.wt; da.res = addp; da.mask = maskp; da.y = c->arena + tgx.offset;
             da.scale = c->ones; da.shift = c->zeros;
+            da.shared = runs_beside(c, D, aside);
             if (in_place) delta::as_spread(da, L.stride, L.H, L.W);
             if (staged) { da.res = nullptr; da.mask = nullptr; da.y = staging; }
             if (class_dgrad(D)) {
@@ -1944,6 +1949,7 @@ delta_status delta_layer_kernel(delta_ctx *c, const delta_layer_desc *layer, cha
     switch (layer->op) {
     case DELTA_OP_CONV:
         name = delta::stem_applies(a) ? "stem7x7 bf16" : delta::conv_kernel_name(a);
+        a.shared = c->aux_tail ? 1 : 0;
         if (!delta::stem_applies(a)) pieces_text(pieces, sizeof pieces, a);
         break;
     case DELTA_OP_MAXPOOL: name = "maxpool"; break;
@@ -2006,9 +2012,8 @@ delta_status delta_backward_kernel(delta_ctx *c, const delta_bwd_desc *desc, cha
                 delta::as_spread(da, L.stride, L.H, L.W);
             }
             name = delta::conv_kernel_name(da);
-            if (D.mask_gx && !strided_1x1(L)) da.mask = c->arena;        // that there is one (a staged gradient gets it when it is spread)
+            da.shared = runs_beside(c, D, D.gw && wgrad_aside(L, fa));
             pieces_text(pieces, sizeof pieces, da);
-            da.mask = nullptr;
         }
         snprintf(gx, sizeof gx, "gx: %s%s%s%s", before, name, pieces, after);
     }

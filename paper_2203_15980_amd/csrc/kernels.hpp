@@ -27,6 +27,8 @@ struct ConvArgs {
     // With the scattered form of a 1x1 layer: the pixels of the oy_s x oy_s block that starts at an output pixel, inside the image and not
     // written themselves, are stored as zeros (launch_conv_spread: a strided 1x1 layer's data gradient in one pass).
     int spread = 0;
+    // Another stream's kernels run beside this launch (a weight gradient, most of them one workgroup to a CU): tail_pieces.
+    int shared = 0;
 };
 
 // Division by a launch constant as a multiplication, exact for 0 <= n < 2^31: with 2^(s-1) < d <= 2^s and mul = ceil(2^(31+s) / d),
@@ -90,10 +92,10 @@ const char *conv_check(const ConvArgs &a);
 const char *conv_kernel_name(const ConvArgs &a);
 hipError_t launch_conv(const ConvArgs &a, hipStream_t stream);
 // In how many pieces the tiles past the last whole round of the 256 CUs go out (1: whole), for a kernel that can cut a tile in up to `most`: as many as leave a
-// CU at most one.  conv_pieces: of the kernel that launch_conv takes.
+// CU at most one.  Whole where another stream's work fills such a round.  conv_pieces: of the kernel that launch_conv takes.
 inline int tail_pieces(const ConvArgs &a, long long tiles, int most) {
     const int rest = (int)(tiles % 256);
-    if (tiles <= 256 || !rest || a.spread || a.mask) return 1;
+    if (tiles <= 256 || !rest || a.spread || a.shared) return 1;
     while (rest * most > 256) most /= 2;
     return most;
 }

@@ -46,3 +46,45 @@ def test_pieces_are_named_where_tiles_are_cut(torch_mod, H, W, Cin, Cout, R, nam
                                       H=H, W=W, Cin=Cin, Cout=Cout, R=R, S=R, stride=1, pad=R // 2, relu=0))
     d.close()
     assert got == name
+
+
+def test_tiles_go_out_whole_beside_the_second_stream(torch_mod):  # noqa: F811
+    """A data gradient without a mask whose layer's weight gradient, or an earlier one, is on the second stream, and a forward launch beside one: whole
+    tiles.  Alone, and after the join: pieces.  The same bits all ways."""
+    torch = torch_mod
+    import paper_2203_15980_amd as dl
+    N, H, W, C = 2, 273, 33, 256                                 # 71 x 4 workgroups: 28 past a round
+    n = N * H * W * C * 2
+    d = make_delta(torch, 8 * n)
+    d.bind([n] * 6)                                              # x, y, gy, gx (beside its own), gx (alone), y of the forward launch
+    gen = torch.Generator(device="cuda:0").manual_seed(61)
+    view = lambda t: d.arena[d.tensor_ptr(t) - d.arena.data_ptr():][:n]                          # noqa: E731
+    for t in (0, 1, 2):
+        d.alloc(t)
+        view(t).view(torch.bfloat16).normal_(generator=gen)
+    w = torch.randn(C * 9 * C, device="cuda:0", generator=gen).to(torch.bfloat16)
+    one, gw = torch.ones(C, device="cuda:0"), torch.zeros(C * 9 * C, device="cuda:0")
+    lay = lambda y: dl.LayerDesc(x=0, res=dl.NO_TENSOR, y=y, dtype=dl.DTYPE_BF16, w=w.data_ptr(), scale=one.data_ptr(), shift=one.data_ptr(), N=N, H=H,   # noqa: E731
+                                 W=W, Cin=C, Cout=C, R=3, S=3, stride=1, pad=1, relu=0)
+    ws = torch.empty(d.backward_workspace(lay(1)), dtype=torch.uint8, device="cuda:0")
+    back = lambda gx, with_gw: dl.BwdDesc(fwd=lay(1), gy=2, gpre=2, gx=gx, gx_add=dl.NO_TENSOR, wt=w.data_ptr(), gw=gw.data_ptr() if with_gw else None,    # noqa: E731
+                                          workspace=ws.data_ptr(), workspace_bytes=ws.numel())
+    whole = "conv3x3_halo bf16 256x64 (8x1 waves)"
+    cut = whole + ", last tiles in 8 pieces"
+    torch.cuda.synchronize()
+    assert d.backward_kernel(back(3, True)).startswith("gx: %s; gw: " % whole) and "second stream" in d.backward_kernel(back(3, True))
+    assert d.backward_kernel(back(4, False)) == "gx: " + cut and d.layer_kernel(lay(5)) == cut
+    d.backward_segment([back(3, True)])
+    assert d.backward_kernel(back(4, False)) == "gx: " + whole and d.layer_kernel(lay(5)) == whole
+    d.recompute_segment([lay(5)])
+    d.backward_join()
+    assert d.backward_kernel(back(4, False)) == "gx: " + cut and d.layer_kernel(lay(5)) == cut
+    d.backward_segment([back(4, False)])
+    d.sync()
+    beside = view(5).clone()
+    assert torch.equal(view(3), view(4)) and view(3).any()
+    torch.cuda.synchronize()
+    d.recompute_segment([lay(5)])
+    d.sync()
+    assert torch.equal(view(5), beside)
+    d.close()
