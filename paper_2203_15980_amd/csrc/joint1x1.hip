@@ -431,11 +431,12 @@ size_t joint1x1_workspace_bytes(const ConvArgs &fa) {
 
 // The widest gradient to the fewest input channels, where gpre is most of what a launch moves.  us with its reduction, the mask's launch before it | on the way:
 // 64 -> 256 on 401408 pixels 180 | 135, 100352 47 | 37, 34496 27 | 23, 6305 16.1 | 15.8; 128 -> 512 on 100352 108 | 91, 39200 51 | 43, 9025 27 | 26; 64 -> 512 on
-// 100352 91 | 78; 192 -> 256 (three slices, of which the first stores gpre) on 25088 27.3 | 27.2.  128 -> 512 keeps three chunks of gy and x and one of y in 144 KB: chunks
+// 100352 91 | 78.  Every slice reads gy and y and masks them again, of which the first stores gpre: three (192 -> 256) on 25088 29.8 | 28.6, 100352 75 | 74, but
+// five (320 -> 256) 36.5 | 40.2, 96 | 113, seven (448 -> 256) 43 | 52, 122 | 161.  128 -> 512 keeps three chunks of gy and x and one of y in 144 KB: chunks
 // of 16 pixels in four buffers 113 us (half the work per barrier), of 32 with y in two 109.
 bool joint1x1_masks(const ConvArgs &da, const ConvArgs &fa) {
     joint::Plan p;
-    return joint1x1_applies(fa) && joint::plan_for(fa, p) && (p.kt == 4 || p.kt == 8) && p.ct == 1 && !da.res;
+    return joint1x1_applies(fa) && joint::plan_for(fa, p) && (p.kt == 4 || p.kt == 8) && p.ct == 1 && p.slices <= 3 && !da.res;
 }
 
 // From here on a gx_add that is zeros but for its pixels of even row and column is read at those pixels only; the loads of the others take zeros that
