@@ -430,13 +430,16 @@ size_t joint1x1_workspace_bytes(const ConvArgs &fa) {
 }
 
 // The widest gradient to the fewest input channels, where gpre is most of what a launch moves.  us with its reduction, the mask's launch before it | on the way:
-// 64 -> 256 on 401408 pixels 180 | 135, 100352 47 | 37, 34496 27 | 23, 6305 16.1 | 15.8; 128 -> 512 on 100352 108 | 91, 39200 51 | 43, 9025 27 | 26; 64 -> 512 on
-// 100352 91 | 78.  Every slice reads gy and y and masks them again, of which the first stores gpre: three (192 -> 256) on 25088 29.8 | 28.6, 100352 75 | 74, but
-// five (320 -> 256) 36.5 | 40.2, 96 | 113, seven (448 -> 256) 43 | 52, 122 | 161.  128 -> 512 keeps three chunks of gy and x and one of y in 144 KB: chunks
-// of 16 pixels in four buffers 113 us (half the work per barrier), of 32 with y in two 109.
+// 64 -> 256 on 401408 pixels 180 | 135, 100352 54 | 45, 34000 28.6 | 25.4, 14000 19.7 | 18.6, 9000 17.0 | 16.7, but 6000 15.7 | 15.8, 4100 14.3 | 14.6;
+// 128 -> 512 on 100352 112 | 91, 34000 52 | 44, 14000 33.6 | 29.8, 9050 27.1 | 26.7; 64 -> 512 on 34000 45 | 39, 14000 28.2 | 25.7, 11000 24.3 | 23.8, but 10500
+// 24.1 | 24.2, 9050 23.4 | 24.3.  Every slice reads gy and y and masks them again, of which the first stores gpre: with three (192 -> 256) 60000 pixels
+// 50.3 | 49.6 and 25088 29.7 | 28.6, but 18000 24.0 | 24.9, 16000 22.8 | 24.2, 11000 22.1 | 22.5; five (320 -> 256) on 25088 36.3 | 40.2, 100352 96 | 113,
+// seven (448 -> 256) 43 | 52, 122 | 161.  128 -> 512 keeps three chunks of gy and x and one of y in 144 KB: chunks of 16 pixels in four buffers 113 us (half the
+// work per barrier), of 32 with y in two 109.
 bool joint1x1_masks(const ConvArgs &da, const ConvArgs &fa) {
     joint::Plan p;
-    return joint1x1_applies(fa) && joint::plan_for(fa, p) && (p.kt == 4 || p.kt == 8) && p.ct == 1 && p.slices <= 3 && !da.res;
+    if (!joint1x1_applies(fa) || !joint::plan_for(fa, p) || p.ct != 1 || da.res) return false;
+    return p.kt == 4 ? p.slices == 1 && fa.M >= 7000 : p.kt == 8 && (p.slices == 2 || (p.slices == 1 && fa.M >= 11000));
 }
 
 // From here on a gx_add that is zeros but for its pixels of even row and column is read at those pixels only; the loads of the others take zeros that
