@@ -47,10 +47,10 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 struct Args {
     const unsigned char *g, *x, *add, *wt;       // [M,K], [M,C], [M,C] (ADD), [C,K]
     unsigned char *gx;                           // [M,C]
-    const unsigned char *y;                      // OWN: g is gy, and gpre = gy * [y > 0] is made here
-    unsigned char *gpre;                         // [M,K] both
     float *partial;                              // [workers][slices][KT CT][4 tiles][4][64 lanes] f32x4
     int M, C, nchunks, workers, slices, mask;
+    const unsigned char *y;                      // OWN: g is gy, and gpre = gy * [y > 0] is made here
+    unsigned char *gpre;                         // [M,K] both
     int N, H, W, zeros;                          // EVEN: images, their rows and columns; how many zero pixels stand for all, less one (1, 2, .. 16 less one)
     Divisor dw, dh;
 };
