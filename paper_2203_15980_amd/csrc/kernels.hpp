@@ -16,7 +16,13 @@ struct ConvArgs {
     const float *shift;   // [Cout]
     int N, H, W, Cin, Cout, R, S, stride, pad, P, Q, M;
     int relu;             // 0: none, 1: ReLU, 2: GELU (erf form; tiled kernel only)
-    int bf16;             // 1: bf16 storage, fp32 accumulate; 0: fp32
+    // (the next three share four bytes: kernels take this structure by value, and eight bytes more were 0.02 to 0.04 us of the smallest launches, 5 to 8 us)
+    short bf16;           // 1: bf16 storage, fp32 accumulate; 0: fp32
+    // With the scattered form of a 1x1 layer: the pixels of the oy_s x oy_s block that starts at an output pixel, inside the image and not
+    // written themselves, are stored as zeros (launch_conv_spread: a strided 1x1 layer's data gradient in one pass).
+    unsigned char spread = 0;
+    // Another stream's kernels run beside this launch (a weight gradient, most of them one workgroup to a CU): tail_pieces.
+    unsigned char shared = 0;
     // Scattered form (launch_conv_scatter only; the data gradient of a strided layer, one parity
     // class of input pixels at a time).  oy_s > 0: output pixel (n, p, q) is stored at pixel
     // (n, p * oy_s + oy_a, q * oy_s + oy_b) of an [N, OH, OW, Cout] tensor; res and mask are read
@@ -24,11 +30,6 @@ struct ConvArgs {
     // taps (w_r0 + r * w_step, w_s0 + s * w_step) of a weight tensor [Cout, wR, wS, Cin].
     int oy_s = 0, oy_a = 0, oy_b = 0, OH = 0, OW = 0;
     int wR = 0, wS = 0, w_r0 = 0, w_s0 = 0, w_step = 1;
-    // With the scattered form of a 1x1 layer: the pixels of the oy_s x oy_s block that starts at an output pixel, inside the image and not
-    // written themselves, are stored as zeros (launch_conv_spread: a strided 1x1 layer's data gradient in one pass).
-    int spread = 0;
-    // Another stream's kernels run beside this launch (a weight gradient, most of them one workgroup to a CU): tail_pieces.
-    int shared = 0;
 };
 
 // Division by a launch constant as a multiplication, exact for 0 <= n < 2^31: with 2^(s-1) < d <= 2^s and mul = ceil(2^(31+s) / d),
