@@ -317,7 +317,8 @@ delta_status delta_set_skip_copies(delta_ctx *ctx, int32_t skip);
  * (stride^2 times the arithmetic).  A 1x1 layer with stride > 1 only reads the input pixels
  * (stride*p, stride*q): gpre keeps the bytes of y, the weight gradient reads
  * just those, and the data gradient is computed at the output's resolution and stored to
- * those pixels, zeros between; with gx_add or mask_gx it goes into the workspace first, and gx_add is added in a second bf16 rounding.
+ * those pixels, zeros between, straight where the kernel that runs it can and nothing is added or masked; otherwise it goes into the workspace
+ * first (delta_backward_kernel says "spread_add"), and gx_add is added in a second bf16 rounding.
  * Other operators (bf16 only; gpre must be gy, gx_add unused):
  *   DELTA_OP_MAXPOOL   gx receives gy routed to the first maximal element of each window (scan order
  *                      r, then s); needs fwd.x resident.  With mask_gx, gx is also multiplied by [x > 0].

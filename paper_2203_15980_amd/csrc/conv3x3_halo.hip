@@ -24,7 +24,8 @@
 // first pieces of the next step are read under the last MFMAs of this one.  Taps outside the image are redirected to a row of zeros in LDS, so no
 // operand needs masking.  The step order is fixed, so the first forward and every recomputation
 // add in the same order and a recomputed tensor is bit-identical to the original.
-// A last round of few tiles goes out in runs of 128, 64 or 32 pixels (SPLIT, launch_one): ResNet-50 forward at batch 128 2260 -> 2230 us.
+// A last round of few tiles goes out in runs of 128, 64 or 32 pixels (SPLIT, launch_one): 128 x 28 x 28 x 128 39.9 -> 37.3 us, 5 of a ResNet-50 forward's 2250
+// at batch 128.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

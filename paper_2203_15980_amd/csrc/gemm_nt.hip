@@ -362,7 +362,11 @@ long long tiles_of(const ConvArgs &a, const Tile &t) {
 // Width of the w tile: the one whose number of rounds over the 256 CUs (one workgroup per CU) times
 // its cost per tile is smaller; e.g. 768 output channels are 3 tiles of 256 (192 workgroups at
 // batch 32 x 512: a quarter of the chip idle) but 4 tiles of 192 (256 workgroups, one full round).  A round also costs its first loads and its
-// stores, as much as 96 columns of four slices: strided 256 -> 512 on 128 x 56 x 56 (four rounds of 256 or five of 192, inside the forward pass) 68 -> 59 us.
+// stores, as much as 96 columns of four slices.  Rounds alone would take 192 columns where both have nearly the same (four rounds of 256, five of 192; seven and
+// nine; ..), at every such size the slower (us, 192 | 256, on as many rows): 256 -> 512 98560 66 | 57, 109056 69 | 59, strided on 128 x 56 x 56 71 | 59; 256 -> 1024
+// 49408 64 | 55, 54528 67 | 58; 512 -> 2048 49408 168 | 146, 77312 254 | 218; 1024 -> 2048 75000 390 | 342; 768 -> 3072 33024 220 | 183, 36864 232 | 205;
+// 768 -> 2304 43776 207 | 178; 768 -> 768 131328 221 | 185.  (Whole rounds: that few tiles of the last one go out in pieces is not counted, it makes the right side
+// 2 to 8 us better.)
 const Tile &pick_tile(const ConvArgs &a) {
     if (a.Cout <= 128) return kTiles[2];
     if (a.Cout <= 256 && tiles_of(a, kTiles[0]) < 192) return kTiles[4];
@@ -389,8 +393,10 @@ const Tile *choose_tile(const ConvArgs &a) {
     // layer alone, us, four buffers | two: 1024 -> 2048 at 128 x 14 x 14 48 | 38, at 100 x 13 x 11 47 | 34, 512 -> 1024 at 64 x 28 x 28 32 | 24.  (From 128
     // tiles of 256 x 256 on those: 256 -> 512 at 128 x 56 x 56 66, two launches 92, 128 x 128 tiles 79; 512 -> 1024 at 128 x 28 x 28 39 | 50 | 45.)
     // Half a chip of them is where the layer's weight gradient, one workgroup of all its LDS to a CU on the other stream, no longer finds the rest free, and
-    // waits the longer for this launch: there the shorter one with a second to spread its result.  Block's backward, us, two launches | this, with the number
-    // of tiles: 256 -> 512 [116] 119 | 116, [142] 123 | 127, [166] 122 | 130, [232] 141 | 145, [330] 167 | 167; 512 -> 1024 [88] 120 | 116,
+    // waits the longer for this launch: there the shorter one with a second to spread its result, 2 to 8 us better at most sizes below and 2 to 4 worse at the
+    // others.  The rule sees the launch alone: where no weight gradient is asked for one launch is the better there too (256 -> 512 [116] 16.0 | 13.3, [166]
+    // 17.7 | 13.7, [232] 20.7 | 16.0; 512 -> 1024 [136] 20.4 | 18.0, [248] 25.2 | 23.0; 1024 -> 2048 [96] 25.6 | 26.6, [184] 27.8 | 27.4).  Block's backward, us,
+    // two launches | this, with the number of tiles: 256 -> 512 [116] 119 | 116, [142] 123 | 127, [166] 122 | 130, [232] 141 | 145, [330] 167 | 167; 512 -> 1024 [88] 120 | 116,
     // [108] 126 | 128, [136] 135 | 140, [172] 155 | 153, [248] 177 | 175; 1024 -> 2048 [96] 154 | 156, [184] 221 | 221.
     const long long small = tiles_of(a, kTiles[3]);
     if (a.spread && small >= 96 && small < 256) return nullptr;

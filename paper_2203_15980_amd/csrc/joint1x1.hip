@@ -18,7 +18,7 @@
 //    rows a transposing read touches and the sixteen a gx read touches spread over the banks; the direct load fixes where a lane's
 //    16 bytes land, so the permutation is applied to the address each lane fetches;
 //  * EVEN: gx_add has values at pixels of even row and column only (a stride-2 layer's data gradient, just stored): the loads of the others go to a few
-//    zero pixels of the tensor, other ones in every workgroup, which the caches hold, so that a quarter of the tensor is read;
+//    zero pixels of the tensor, in an image by the worker's number, which the caches hold, so that a quarter of the tensor is read;
 //  * rows past the last pixel are fetched from the last pixel and overwritten with zeros in LDS before they are read;
 //  * OWN: a layer with a ReLU of its own brings gy and y, whose rows have one buffer: gpre = gy * [y > 0] replaces gy in LDS and leaves for memory on
 //    the way, instead of in a launch before this one that reads both and whose result is read again.
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(512) void joint1x1_kernel(Args a) {
     }
     typedef __attribute__((address_space(3))) unsigned char *lptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
-    const int zero0 = ADD == EVEN ? worker % a.N * a.H * a.W + 1 : 0;   // pixel 1 of some image: every workgroup has lines of its own
+    const int zero0 = ADD == EVEN ? worker % a.N * a.H * a.W + 1 : 0;   // pixel 1 of an image: as many sets of lines as images, spread over the workers
     auto fetch = [&](int chunk, int buf) {
         const int m0 = chunk * P, last = a.M - 1 - m0;           // rows past the last pixel: that pixel
 #pragma unroll
@@ -444,7 +444,7 @@ bool joint1x1_masks(const ConvArgs &da, const ConvArgs &fa) {
 
 // From here on a gx_add that is zeros but for its pixels of even row and column is read at those pixels only; the loads of the others take zeros that
 // the caches hold.  Block of a strided layer, 256 channels to 128, us, all of gx_add read | this: on 128 x 56 x 56 475 | 455, 96 376 | 365, 64 280 | 274, but
-// 40 209.5 | 211.2 and 24 155 | 156, where the caches still hold the tensor.  In several slices it never pays: 512 to 256 on 128 x 28 x 28 372 | 377, on
+// 40 209.5 | 211.2 and 24 155 | 156, where the caches still hold the tensor; 256 to 64 (strided 1x1, 3x3 and this layer) 353 | 333, 288 | 272, 64 197 | 197.  In several slices it never pays: 512 to 256 on 128 x 28 x 28 372 | 377, on
 // 64 x 56 x 56 650 | 660.
 constexpr size_t kEvenBytes = (size_t)96 << 20;
 
