@@ -30,19 +30,20 @@
 namespace delta {
 namespace splitk {
 
-template <bool BF16, int KW, int AHEAD>
+template <bool BF16, int KW, int AHEAD, bool SPREAD>
 __global__ __launch_bounds__(KW * 64) void conv_splitk_kernel(ConvArgs a, int tiles_m, int tiles_n, int pixels_first,
                                                               Divisors inv) {
     __shared__ __align__(16) unsigned char smem[KW * kWaveLds];
     __shared__ __align__(16) float factors[64];
-    conv_tile<BF16, KW, AHEAD>(a, tiles_m, tiles_n, pixels_first, inv, xcd_run(blockIdx.x, gridDim.x), threadIdx.x, smem, factors);
+    conv_tile<BF16, KW, AHEAD, SPREAD>(a, tiles_m, tiles_n, pixels_first, inv, xcd_run(blockIdx.x, gridDim.x), threadIdx.x, smem, factors);
 }
 
 template <bool BF16, int KW, int AHEAD>
 hipError_t launch(const ConvArgs &a, hipStream_t stream) {
     const int tiles_m = (a.M + kTile - 1) / kTile, tiles_n = (a.Cout + kTile - 1) / kTile;
-    conv_splitk_kernel<BF16, KW, AHEAD><<<dim3((unsigned)tiles_m * (unsigned)tiles_n), dim3(KW * 64), 0, stream>>>(
-        a, tiles_m, tiles_n, weights_larger(a), divisors_of(a));
+    const dim3 grid((unsigned)tiles_m * (unsigned)tiles_n), block(KW * 64);
+    if (a.spread) conv_splitk_kernel<BF16, KW, AHEAD, true><<<grid, block, 0, stream>>>(a, tiles_m, tiles_n, weights_larger(a), divisors_of(a));
+    else conv_splitk_kernel<BF16, KW, AHEAD, false><<<grid, block, 0, stream>>>(a, tiles_m, tiles_n, weights_larger(a), divisors_of(a));
     return hipGetLastError();
 }
 

@@ -188,7 +188,7 @@ __global__ __launch_bounds__(512) void small_backward_kernel(ConvArgs da, int ti
     constexpr int kGroups = 8 / KW;                              // tiles of gx to a workgroup
     const int group = __builtin_amdgcn_readfirstlane(tid / (KW * 64));
     const unsigned logical = splitk::xcd_run(blockIdx.x - w.blocks, gridDim.x - w.blocks) * kGroups + group;
-    splitk::conv_tile<BF16, KW, 2>(da, tiles_m, tiles_n, pixels_first, inv, logical, tid & (KW * 64 - 1), smem + group * KW * splitk::kWaveLds,
+    splitk::conv_tile<BF16, KW, 2, BF16 && !PLAIN>(da, tiles_m, tiles_n, pixels_first, inv, logical, tid & (KW * 64 - 1), smem + group * KW * splitk::kWaveLds,
                                    factors + group * 64);
 }
 

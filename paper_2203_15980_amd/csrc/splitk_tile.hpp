@@ -61,8 +61,8 @@ __device__ __forceinline__ unsigned xcd_run(unsigned block, unsigned blocks) {
 // past the last tile computes nothing.  The axis that walks fastest is the one whose operand is smaller, so that an XCD reads its share of the
 // larger one once.  One barrier, which the whole workgroup has to reach.
 // wR, wS, w_r0, w_s0, w_step of `a` are filled by the launcher for every form (see ConvArgs).
-// AHEAD: steps in flight per wavefront.
-template <bool BF16, int KW, int AHEAD>
+// AHEAD: steps in flight per wavefront.  SPREAD: `a` may ask for the spread form.
+template <bool BF16, int KW, int AHEAD, bool SPREAD>
 __device__ __forceinline__ void conv_tile(const ConvArgs &a, int tiles_m, int tiles_n, int pixels_first, const Divisors &inv,
                                           unsigned logical, int tid, unsigned char *smem, float *factors) {
     constexpr int ES = BF16 ? 2 : 4;
@@ -92,7 +92,7 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int tiles_m, int ti
             const int n = divide(em, inv.pq), pq = em - n * PQ;
             const int p = divide(pq, inv.q), q = pq - p * a.Q;
             pixel = ((size_t)n * a.OH + (p * a.oy_s + a.oy_a)) * a.OW + (q * a.oy_s + a.oy_b);
-            if (a.spread) {
+            if (SPREAD && a.spread) {
                 erows = a.OH - p * a.oy_s < a.oy_s ? a.OH - p * a.oy_s : a.oy_s;
                 ecols = a.OW - q * a.oy_s < a.oy_s ? a.OW - q * a.oy_s : a.oy_s;
             }
@@ -218,7 +218,7 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int tiles_m, int ti
         for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
     }
     unsigned char *y = static_cast<unsigned char *>(a.y) + eoff;
-    if (a.spread)
+    if (SPREAD && a.spread)
         for (int at = 1; at < erows * ecols; ++at) {
             const int dy = at / ecols, dx = at - dy * ecols;
             unsigned char *z = y + ((size_t)dy * a.OW + dx) * a.Cout * ES;
