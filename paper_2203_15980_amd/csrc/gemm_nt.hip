@@ -398,6 +398,8 @@ const Tile *choose_tile(const ConvArgs &a) {
     // 17.7 | 13.7, [232] 20.7 | 16.0; 512 -> 1024 [136] 20.4 | 18.0, [248] 25.2 | 23.0; 1024 -> 2048 [96] 25.6 | 26.6, [184] 27.8 | 27.4).  Block's backward, us,
     // two launches | this, with the number of tiles: 256 -> 512 [116] 119 | 116, [142] 123 | 127, [166] 122 | 130, [232] 141 | 145, [330] 167 | 167; 512 -> 1024 [88] 120 | 116,
     // [108] 126 | 128, [136] 135 | 140, [172] 155 | 153, [248] 177 | 175; 1024 -> 2048 [96] 154 | 156, [184] 221 | 221.
+    // From 256 tiles on: 512 -> 1024 at 28 x 28, images 42 193 | 182, 64 238 | 234, 96 320 | 314, 128 389 | 384; 1024 -> 2048 at 14 x 14, where it depends on what meets on
+    // the two streams, 84 282 | 266, 100 303 | 297, 112 318 | 323, 128 349 | 353, 144 387 | 379, 160 450 | 408, 224 554 | 566, 256 610 | 597.
     const long long small = tiles_of(a, kTiles[3]);
     if (a.spread && small >= 96 && small < 256) return nullptr;
     if (a.Cin >= 512 && small <= 512) return &kTiles[a.spread ? 2 : 3];
