@@ -409,7 +409,8 @@ delta_status delta_backward_join(delta_ctx *ctx);
 delta_status delta_layer_kernel(delta_ctx *ctx, const delta_layer_desc *layer, char *out, uint64_t cap);
 /* The same for the backward of a layer: "gx: <data gradient>; gw: <weight gradient>, <its stream>", as far as the
  * descriptor asks for them; "gpre: <data gradient>; " in front where that launch also applies the layer's own ReLU mask.  Here and above a
- * convolution whose last tiles are cut up says so (", last tiles in 4 pieces").  Validates as delta_backward_segment does, except for residency. */
+ * convolution whose last tiles are cut up says so (", last tiles in 4 pieces"; not beside a weight gradient on the second stream, the layer's own or one not
+ * joined yet).  Validates as delta_backward_segment does, except for residency. */
 delta_status delta_backward_kernel(delta_ctx *ctx, const delta_bwd_desc *desc, char *out, uint64_t cap);
 
 /* Measurement probes (rooflines the hot path is reported against). */
